@@ -192,15 +192,15 @@ def bwd_leg(B, w, sh, Qg, Kg, Vg, ws_att, mask, eff_flops, dense_flops, steps, t
     ws = B.alloc_workspace(sh, B.CALL_ATTN_BWD)
     B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dO, sel_mask=mask, workspace=ws)  # untimed first launch
     ms = timed(lambda: B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dO, sel_mask=mask, workspace=ws), max(2, steps // 2))
-    # five matrix products on the attended keys against the forward's two; the kernels execute eight on every
-    # preceding cube (S three times, dP twice, dV, dK, dQ), with the selection as a mask
+    # five matrix products on the attended keys against the forward's two; the kernels execute three (S, dP, dQ) on
+    # every preceding cube, with the selection as a mask, and four (S, dP, dV, dK) on the attended keys
     tf = 2.5 * eff_flops / (ms * 1e-3) / 1e12
     return {
         "ms": ms,
-        "roofline": {"kernel": "attn_bwd_dq_kernel + attn_bwd_dkv_kernel<dV> + attn_bwd_dkv_kernel<dK> (whole call)",
+        "roofline": {"kernel": "attn_bwd_dq_kernel + attn_bwd_dkv_kernel (whole call)",
                      "bound": "mfma", "achieved": tf, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": tf / PEAK_BF16_TFLOPS, "traffic": BWD_MEASURED_TRAFFIC_BYTES.get((w.name, top_p)),
-                     "executed_tflops": 4.0 * dense_flops / (ms * 1e-3) / 1e12},
+                     "executed_tflops": (1.5 * dense_flops + 2.0 * eff_flops) / (ms * 1e-3) / 1e12},
     }
 
 

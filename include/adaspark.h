@@ -286,7 +286,7 @@ int adaspark_dense_attn_packed(const adaspark_shape *shape, const void *Q, const
  *   sel_mask   in   u32  [tokens*q_heads][ceil(cubes/32)], or NULL for dense causal attention
  *   dQ         out  bf16 [tokens][q_heads][head_dim];  dK, dV  out  bf16 [tokens][kv_heads][head_dim]
  *   workspace       adaspark_workspace_bytes(ADASPARK_CALL_ATTN_BWD): packed copies of K, V (natural and
- *                   transposed), of Q and dO (natural and transposed, in cube order) and two floats per row
+ *                   transposed), two floats per row, the selection bits transposed, and partial sums of dK and dV
  * p is rebuilt from lse in fp32 from exact score products (bf16 x bf16 accumulated in fp32, the softmax scale applied
  * in fp32); p and dS are rounded to bf16 for the other MFMA products, sums are fp32, outputs are rounded to bf16
  * once.  Limits as for the forward, and tokens*q_heads*ceil(cubes/32) < 2^30; causal != 0 only.

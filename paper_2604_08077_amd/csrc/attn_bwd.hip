@@ -2,24 +2,25 @@
 //
 // For a row r with attended keys A_r, scale c = 1/sqrt(D):  p = softmax(c q.k),  delta = dO.O,
 //     dV_j += p_j dO,   dS_j = p_j (dO.v_j - delta),   dQ = c sum_j dS_j k_j,   dK_j += c dS_j q.
-// p is rebuilt from the forward's log-sum-exp, so nothing of the forward's size is stored.  Three MFMA kernels, none
+// p is rebuilt from the forward's log-sum-exp, so nothing of the forward's size is stored.  Two MFMA kernels, neither
 // of which needs a transposition in registers or an atomic:
 //   attn_bwd_dq_kernel   row-stationary (like the forward's masked walk): a wavefront keeps Q and dO of 32 rows as
 //                        MFMA B operands, walks the key tiles of every cube up to its own, and accumulates dQ^T.
-//                        S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T.
-//   attn_bwd_dkv_kernel  key-stationary: a wavefront keeps K (and V) of 32 keys as B operands, walks the 64-row
-//                        tiles of every later cube and its own, and accumulates dV^T (WHICH = 0: S = Q.K^T,
-//                        dV^T += dO^T.P) or dK^T (WHICH = 1: S, dP = dO.V^T, dK^T += Q^T.dS).  Two passes because the
-//                        two accumulators together with both operand sets do not fit the register file.
-// In both, a row's selection bit for the key cube acts as a mask (dense work, like the forward's masked walk).
-// Streamed tiles come from packed, pre-swizzled copies (kvtile.h layouts) straight into LDS: K natural / V natural
-// / K transposed per 64 keys (two runs of the forward's pack kernel), Q, dO natural and transposed per 64 rows in
-// (cube, rank, head of the group) order (bwd_pack_rows_kernel).
+//                        S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T.  A row's selection bit for the key cube acts
+//                        as a mask (dense work, like the forward's masked walk).
+//   attn_bwd_dkv_kernel  key-stationary: a wavefront keeps K and V of 32 keys as B operands and accumulates dV^T and
+//                        dK^T over the rows that selected the keys' cube -- only those: the rows' state is nothing but
+//                        Q, dO and two floats, so rows are gathered into tiles, and the work follows the selection.
+//                        S = Q.K^T, dP = dO.V^T, dV^T += dO^T.P, dK^T += Q^T.dS.
+// The streamed tiles of the first come from packed, pre-swizzled copies (kvtile.h layouts) straight into LDS: K
+// natural / V natural / K transposed per 64 keys (two runs of the forward's pack kernel).  The second gathers rows of
+// Q and dO as the caller holds them, and reads each tile in LDS both ways: rows as they are, and transposed
+// (ds_read_b64_tr_b16).
 // The score products take Q and K as they are (bf16 x bf16 -> fp32: exact products, so the rebuilt probabilities
 // carry nothing but their own rounding, whatever the size of the scores) and their accumulators start from
 // -lse * sqrt(D), -inf for a row that did not select the key cube: the accumulator times the softmax scale in base
 // 2 is then the exponent of the probability, and the selection costs no instruction per score.  The dP accumulators
-// start from minus delta.  bwd_pack_rows_kernel leaves both start values per packed row.
+// start from minus delta.  bwd_row_values_kernel leaves both start values per row.
 #include <algorithm>
 #include <type_traits>
 
@@ -31,14 +32,43 @@ constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
+// How attn_bwd_dkv_kernel's work is cut.  A workgroup takes 256 keys (one of nkb key blocks) of one (key cube j, KV
+// head) and the rows of `span` consecutive row cubes c * span .. that selected j (and cube j's own rows, if it is one
+// of them).  Parts of the same keys are summed by bwd_reduce_kernel in a fixed order.  Parts (c, j) exist for
+// c >= j / span; they are numbered span * c * (c + 1) / 2 + j, so the workgroups of one c, which gather the same rows
+// at the same time, follow each other.
+struct BwdParts {
+    int span, nc;     // row cubes per part; ranges c
+    int nkb;          // 256-key blocks per cube
+    long long parts;  // per (KV head, key block)
+};
+static BwdParts bwd_parts(const Geom &g)
+{
+    BwdParts p;
+    p.nkb = (g.Cmax + BWD_ROWS - 1) / BWD_ROWS;
+    // A part costs its two sums' trip through memory (256 keys x D x 8 bytes written and read: about what 450 gathered
+    // rows of head-dim 128 cost to compute), so it should see some thousands of rows; but there should be a few parts
+    // per CU to keep the chip even at the end, and more than about 8,000 of them only take up memory.
+    const long long lists = (long long)g.Hkv * p.nkb * g.N;
+    const long long want = (8192 + g.G * g.Cmax - 1) / (g.G * g.Cmax);
+    const long long lo = lists * g.N / (2 * 8192), hi = std::max(1LL, lists * g.N / (2 * 1024));
+    p.span = (int)std::min((long long)g.N, std::max(1LL, std::max(lo, std::min(hi, want))));
+    p.nc = (g.N + p.span - 1) / p.span;
+    p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
+    return p;
+}
+
 struct BwdWorkspace {
     void *packA;             // launch_kv_pack(K, V): natural K first (its V^T half is not used here)
     void *packB;             // launch_kv_pack(V, K): natural V, then K transposed
-    uint16_t *Qn, *Qt, *dOn, *dOt;  // [Hkv][N][tpcr][64 * D]
-    // -lse * sqrt(D) and -delta per packed row (what the score and dP products start from)
-    float *lse2, *delta;     // [Hkv][N][tpcr * 64]; padding rows: -inf, 0
-    unsigned long long *colmask;  // [Hkv][N (key cube j)][N (row cube i)][tpcr]: bit k = row 64 t + k of cube i selects j
-    int tpcr;                // 64-row tiles per cube = ceil(Cmax * G / 64)
+    // -lse * sqrt(D) and -delta per row (what the score and dP products start from); entry [rows] belongs to the rows
+    // that pad a tile: -inf, 0
+    float *lse2, *delta;     // [S * Hq + 1]
+    unsigned long long *colmask;  // [Hkv][N (key cube j)][N (row cube i)][tpcr]: bit k = row 64 t + k of cube i selects j (j < i)
+    uint32_t *rowtab;        // [N][tpcr * 64]: row ids of the row tiles, KV head 0
+    float *part;             // [Hkv][nkb][parts][2 (dV, dK)][256 keys x D], in MFMA output order
+    BwdParts cut;
+    int tpcr;                // 64-row words per cube = ceil(Cmax * G / 64)
     size_t bytes;
 };
 
@@ -48,17 +78,17 @@ BwdWorkspace bwd_workspace(const Geom &g, void *ws)
     BwdWorkspace w;
     unsigned char *p = static_cast<unsigned char *>(ws);
     w.tpcr = (g.Cmax * g.G + 63) / 64;
-    const size_t tile_elems = (size_t)g.Hkv * g.N * w.tpcr * 64 * g.D;
+    w.cut = bwd_parts(g);
+    const size_t rows = (size_t)g.S * g.Hq + 1;
     size_t off = 0;
     w.packA = p + off; off = up(off + attn_workspace_bytes(g));
     w.packB = p + off; off = up(off + attn_workspace_bytes(g));
-    w.Qn = reinterpret_cast<uint16_t *>(p + off); off = up(off + tile_elems * 2);
-    w.Qt = reinterpret_cast<uint16_t *>(p + off); off = up(off + tile_elems * 2);
-    w.dOn = reinterpret_cast<uint16_t *>(p + off); off = up(off + tile_elems * 2);
-    w.dOt = reinterpret_cast<uint16_t *>(p + off); off = up(off + tile_elems * 2);
-    w.lse2 = reinterpret_cast<float *>(p + off); off = up(off + (size_t)g.Hkv * g.N * w.tpcr * 64 * 4);
-    w.delta = reinterpret_cast<float *>(p + off); off = up(off + (size_t)g.Hkv * g.N * w.tpcr * 64 * 4);
+    w.lse2 = reinterpret_cast<float *>(p + off); off = up(off + rows * 4);
+    w.delta = reinterpret_cast<float *>(p + off); off = up(off + rows * 4);
     w.colmask = reinterpret_cast<unsigned long long *>(p + off); off = up(off + (size_t)g.Hkv * g.N * g.N * w.tpcr * 8);
+    w.rowtab = reinterpret_cast<uint32_t *>(p + off); off = up(off + (size_t)g.N * w.tpcr * 64 * 4);
+    w.part = reinterpret_cast<float *>(p + off);
+    if (w.cut.nc > 1) off = up(off + (size_t)g.Hkv * w.cut.nkb * w.cut.parts * 2 * BWD_ROWS * g.D * 4);
     w.bytes = off;
     return w;
 }
@@ -90,88 +120,61 @@ inline unsigned bwd_grid(int Hkv, int per_head)
     return (unsigned)per_head * (unsigned)Hkv;
 }
 
-// One wavefront copies 64 dwords from global memory straight into LDS: lane l moves the 4 bytes at sbase + voff to
-// lds_addr + 4*l.
-__device__ __forceinline__ void dma_dword_s(uint32_t lds_addr, const void *sbase, uint32_t voff)
+// Direct-to-LDS copies with an address per lane: lane l moves the 16 (4) bytes at src to lds_addr + 16 * l (4 * l).
+__device__ __forceinline__ void dma_lane16(uint32_t lds_addr, const void *src)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase)
-                 : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_lane4(uint32_t lds_addr, const void *src)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
 }
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-
-// Row r of cube c in the packed row order: rank r / G, head r % G of the group.
-// Q, dO natural and transposed per 64-row tile; deltap = -dO.O; lse2p = -lse * sqrt(D) (-inf for padding rows).
-template <int D>
-__global__ __launch_bounds__(256) void bwd_pack_rows_kernel(Geom g, const uint16_t *__restrict__ Q,
-                                                            const uint16_t *__restrict__ dO,
-                                                            const uint16_t *__restrict__ O, const float *__restrict__ lse,
-                                                            int tpcr, uint16_t *__restrict__ Qn, uint16_t *__restrict__ Qt,
-                                                            uint16_t *__restrict__ dOn, uint16_t *__restrict__ dOt,
-                                                            float *__restrict__ lse2p, float *__restrict__ deltap)
+__device__ __forceinline__ uint2 pack_bf16(f32x4 x)
 {
-    constexpr int CPR = D / 8;
-    __shared__ __attribute__((aligned(16))) uint16_t qs[64][D + 8];
-    __shared__ __attribute__((aligned(16))) uint16_t gs[64][D + 8];
-    const int t = blockIdx.x, c = blockIdx.y, kv = blockIdx.z;
-    const CubeBox box = cube_box(g, c);
-    const int mrows = box.size() * g.G;
-    const size_t tile = (((size_t)kv * g.N + c) * tpcr) + t;
-    const size_t tile_base = tile * (size_t)(64 * D);
-    for (int x = threadIdx.x; x < 64 * CPR; x += 256) {
-        const int k = x / CPR, col = x % CPR;
-        const int r = 64 * t + k;
-        uint4 qq = make_uint4(0, 0, 0, 0), gg = make_uint4(0, 0, 0, 0);
-        float part = 0.f, l2 = INFINITY;  // (padding rows: minus its log-sum-exp is -inf, its probabilities 0)
-        if (r < mrows) {
-            const int n = token_of(g, box, r / g.G);
-            const size_t rowid = (size_t)n * g.Hq + kv * g.G + r % g.G;
-            const size_t src = rowid * D + col * 8;
-            qq = *reinterpret_cast<const uint4 *>(Q + src);
-            gg = *reinterpret_cast<const uint4 *>(dO + src);
-            const uint4 oo = *reinterpret_cast<const uint4 *>(O + src);
-            const uint32_t gw[4] = {gg.x, gg.y, gg.z, gg.w}, ow[4] = {oo.x, oo.y, oo.z, oo.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                part = fmaf(__uint_as_float(gw[e] << 16), __uint_as_float(ow[e] << 16), part);
-                part = fmaf(__uint_as_float(gw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), part);
-            }
-            l2 = lse[rowid] * sqrtf((float)D);  // = (lse in base 2) / (softmax scale in base 2)
-        }
-#pragma unroll
-        for (int d = CPR / 2; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
-        if (col == 0) {  // both with the sign the MFMA accumulators of the key-stationary kernels start from
-            lse2p[tile * 64 + k] = -l2;
-            deltap[tile * 64 + k] = -part;
-        }
-        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(Qn + tile_base) + k_tile_off<D>(k, col)) = qq;
-        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(dOn + tile_base) + k_tile_off<D>(k, col)) = gg;
-        *reinterpret_cast<uint4 *>(&qs[k][col * 8]) = qq;
-        *reinterpret_cast<uint4 *>(&gs[k][col * 8]) = gg;
-    }
-    __syncthreads();
-    for (int x = threadIdx.x; x < D * 8; x += 256) {
-        const int d = x / 8, kc = x % 8;
-        uint32_t wq[4], wg[4];
+    const bf16x2 a = {(__bf16)x[0], (__bf16)x[1]}, b = {(__bf16)x[2], (__bf16)x[3]};
+    return make_uint2(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b));
+}
+
+// What a row's products start from: lse2 = -lse * sqrt(D), delta = -dO.O; entry [rows]: what padding rows start from.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_row_values_kernel(long long rows, const uint16_t *__restrict__ dO,
+                                                             const uint16_t *__restrict__ O, const float *__restrict__ lse,
+                                                             float *__restrict__ lse2, float *__restrict__ delta)
+{
+    constexpr int CPR = D / 8;  // lanes per row, 16 bytes each
+    const long long r = ((long long)blockIdx.x * 256 + threadIdx.x) / CPR;
+    const int col = threadIdx.x % CPR;
+    float part = 0.f;
+    if (r < rows) {
+        const uint4 gg = *reinterpret_cast<const uint4 *>(dO + r * D + col * 8);
+        const uint4 oo = *reinterpret_cast<const uint4 *>(O + r * D + col * 8);
+        const uint32_t gw[4] = {gg.x, gg.y, gg.z, gg.w}, ow[4] = {oo.x, oo.y, oo.z, oo.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            wq[e] = (uint32_t)qs[kc * 8 + 2 * e][d] | ((uint32_t)qs[kc * 8 + 2 * e + 1][d] << 16);
-            wg[e] = (uint32_t)gs[kc * 8 + 2 * e][d] | ((uint32_t)gs[kc * 8 + 2 * e + 1][d] << 16);
+            part = fmaf(__uint_as_float(gw[e] << 16), __uint_as_float(ow[e] << 16), part);
+            part = fmaf(__uint_as_float(gw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), part);
         }
-        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(Qt + tile_base) + vt_tile_off(d, kc)) =
-            make_uint4(wq[0], wq[1], wq[2], wq[3]);
-        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(dOt + tile_base) + vt_tile_off(d, kc)) =
-            make_uint4(wg[0], wg[1], wg[2], wg[3]);
+    }
+#pragma unroll
+    for (int d = CPR / 2; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
+    if (col == 0 && r <= rows) {
+        lse2[r] = r < rows ? -lse[r] * sqrtf((float)D) : -INFINITY;  // = -(lse in base 2) / (softmax scale in base 2)
+        delta[r] = -part;
     }
 }
 
-// The selection bits transposed for the key-stationary kernels: one wavefront per (KV head, row cube i, row tile t);
-// lane k holds row 64 t + k's mask words, a ballot per cube turns 64 rows' bits into one 64-bit word.
+// The selection bits transposed for the key-stationary kernel: one wavefront per (KV head, row cube i, row tile t);
+// lane k holds the mask words of row 64 t + k (rank-major: row r of a cube is head r % G of rank r / G), a ballot per
+// cube turns 64 rows' bits into one 64-bit word.  sel_mask == nullptr: every row selects every cube.  KV head 0 also
+// leaves the row ids of the row tiles (those of KV head kv are kv * G higher).
 __global__ __launch_bounds__(64) void bwd_colmask_kernel(Geom g, const uint32_t *__restrict__ sel_mask, int tpcr,
-                                                        unsigned long long *__restrict__ colmask)
+                                                        unsigned long long *__restrict__ colmask,
+                                                        uint32_t *__restrict__ rowtab)
 {
     const int t = blockIdx.x, i = blockIdx.y, kv = blockIdx.z;
     const int lane = threadIdx.x;
@@ -179,8 +182,9 @@ __global__ __launch_bounds__(64) void bwd_colmask_kernel(Geom g, const uint32_t 
     const int r = 64 * t + lane;
     const bool valid = r < box.size() * g.G;
     const size_t rowid = valid ? (size_t)token_of(g, box, r / g.G) * g.Hq + kv * g.G + r % g.G : 0;
-    for (int jw = 0; jw < g.words; ++jw) {
-        const uint32_t word = valid ? sel_mask[rowid * g.words + jw] : 0u;
+    if (kv == 0) rowtab[((size_t)i * tpcr + t) * 64 + lane] = (uint32_t)rowid;
+    for (int jw = 0; 32 * jw < i; ++jw) {
+        const uint32_t word = valid ? (sel_mask != nullptr ? sel_mask[rowid * g.words + jw] : ~0u) : 0u;
         unsigned long long mine = 0ull;
 #pragma unroll
         for (int b = 0; b < 32; ++b) {
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(64) void bwd_colmask_kernel(Geom g, const uint32_t 
             if (lane == b) mine = bal;
         }
         const int j = 32 * jw + lane;
-        if (lane < 32 && j < g.N) colmask[(((size_t)kv * g.N + j) * g.N + i) * tpcr + t] = mine;
+        if (lane < 32 && j < i) colmask[(((size_t)kv * g.N + j) * g.N + i) * tpcr + t] = mine;
     }
 }
 
@@ -211,23 +215,6 @@ __device__ __forceinline__ void nat_half_bias(const unsigned char *kt, int n16, 
             const OP af = *reinterpret_cast<const OP *>(kt + k_tile_off<D>(krow, 4 * c + q4));
 #pragma unroll
             for (int s = 0; s < NS; ++s) acc[s][k2] = mfma16(af, bf[s][c], c == 0 ? init[s] : acc[s][k2]);
-        }
-}
-
-// The same with the accumulators started from init[k2]: four values, one per tile row 32 H + 8 q4 + 4 k2 + v, shared by
-// the slabs (minus a tile row's log-sum-exp or delta: the products then come out with it subtracted).
-template <int D, int NS, int H, typename OP>
-__device__ __forceinline__ void nat_half_from(const unsigned char *kt, int n16, int q4, const OP (&bf)[NS][D / 32],
-                                              const f32x4 (&init)[2], f32x4 (&acc)[NS][2])
-{
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2) {
-            const int krow = 32 * H + 8 * (n16 >> 2) + 4 * k2 + (n16 & 3);
-            const OP af = *reinterpret_cast<const OP *>(kt + k_tile_off<D>(krow, 4 * c + q4));
-#pragma unroll
-            for (int s = 0; s < NS; ++s) acc[s][k2] = mfma16(af, bf[s][c], c == 0 ? init[k2] : acc[s][k2]);
         }
 }
 
@@ -259,7 +246,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
                                                                   const uint16_t *__restrict__ Kt,
                                                                   const int32_t *__restrict__ csize,
                                                                   float *__restrict__ lse2p,
-                                                                  const float *__restrict__ deltap, int tpcr,
+                                                                  const float *__restrict__ deltap,
                                                                   const uint32_t *__restrict__ sel_mask,
                                                                   uint16_t *__restrict__ dQ)
 {
@@ -288,7 +275,6 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     bool valid[NS];
     bf16x8 qf[NS][KSTEPS], gf[NS][KSTEPS];
     float lse2[NS], delta[NS], psum[NS];
-    size_t prow[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         psum[s] = 0.f;
@@ -302,9 +288,8 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
             qf[s][c] = *reinterpret_cast<const bf16x8 *>(Q + rowid[s] * D + 32 * c + 8 * q4);
             gf[s][c] = *reinterpret_cast<const bf16x8 *>(dO + rowid[s] * D + 32 * c + 8 * q4);
         }
-        prow[s] = ((size_t)kv * g.N + i) * tpcr * 64 + rr[s];
-        lse2[s] = lse2p[prow[s]];    // -lse * sqrt(D): what the score products start from
-        delta[s] = deltap[prow[s]];  // minus delta: what the dP products start from
+        lse2[s] = lse2p[rowid[s]];    // -lse * sqrt(D): what the score products start from
+        delta[s] = deltap[rowid[s]];  // minus delta: what the dP products start from
     }
 
     const float c2 = BWD_LOG2E / sqrtf((float)D);  // softmax scale in base 2
@@ -400,214 +385,379 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     }
     // The probabilities above were built from the caller's log-sum-exp, which the forward kernels give to about
     // 1e-3; their sum over the row says by how much it is off.  dQ is linear in them, so it is divided by the sum
-    // here, and the packed log-sum-exp is corrected for the dK / dV kernel that runs next.
+    // here, and the log-sum-exp is corrected for the dK / dV kernel that runs next.
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const float total = quad_sum(psum[s]);
         if (!valid[s]) continue;
-        if (q4 == 0) lse2p[prow[s]] = lse2[s] - log2f(total) / c2;
+        if (q4 == 0) lse2p[rowid[s]] = lse2[s] - log2f(total) / c2;
         const float scale = 1.0f / (sqrtf((float)D) * total);
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e) {
-            bf16x2 a, b;
-            a[0] = (__bf16)(acc[s][e][0] * scale); a[1] = (__bf16)(acc[s][e][1] * scale);
-            b[0] = (__bf16)(acc[s][e][2] * scale); b[1] = (__bf16)(acc[s][e][3] * scale);
-            uint2 o;
-            o.x = *reinterpret_cast<uint32_t *>(&a);
-            o.y = *reinterpret_cast<uint32_t *>(&b);
-            *reinterpret_cast<uint2 *>(dQ + rowid[s] * D + 16 * e + 4 * q4) = o;
-        }
+        for (int e = 0; e < D / 16; ++e)
+            *reinterpret_cast<uint2 *>(dQ + rowid[s] * D + 16 * e + 4 * q4) = pack_bf16(acc[s][e] * scale);
     }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// dV (WHICH = 0) / dK (WHICH = 1): workgroup = 256 keys of one (cube j, KV head); walks the row tiles of cube j
-// and of every later cube, from the last one down.  Early cubes (the long walks) first.
+// dV, dK: workgroup = 256 keys of one (key cube j, KV head) and one range of row cubes (BwdParts).
+//
+// The rows of the range that selected cube j are listed in LDS from the transposed selection bits, BWD_LIST_WORDS
+// 64-row words at a time, and gathered 64 at a time: natural Q and dO rows and their two start values, three LDS
+// stages, started two tiles ahead.  A 256-byte (128-byte) row is fetched whole by 16 (8) lanes; the 16-byte chunk that
+// lands in a slot is chosen by the lane that fetches it (row_swizzle), so that both kinds of operand read are free of
+// bank conflicts: 16 consecutive rows at one chunk (ds_read_b128, S and dP), and 4 x 16-element blocks read transposed
+// (ds_read_b64_tr_b16, the A operands of dV^T and dK^T).
+//
+// Bound by the matrix pipes and the operand reads that feed them (16 bytes of LDS per lane for every two MFMAs).  Both
+// accumulators and both operand sets of 32 keys are 192 of the 256 registers that two wavefronts per SIMD leave: scores
+// are therefore worked 16 rows at a time and the order of reads and MFMAs is fixed.  At 65,536 tokens, 28/4 heads of
+// 128, Top-p 0.9 (61 % selected): 31.0 ms and 0.45 ms of sums, 1.23 PFLOP/s over selected pairs; two kernels that
+// walked every row with the selection as a mask took 40.7 + 29.1 ms (and the transposed copies of Q and dO they
+// streamed 0.4 ms).  At 16,384 tokens, where cube 0's walk used to outlast everything: 2.2 + 0.1 against 8.5 ms.
 // ---------------------------------------------------------------------------------------------------------------
-template <int D, int WHICH, bool MASKED>
+constexpr int BWD_LIST_WORDS = 64;
+
+template <int D>
+struct Dkv {
+    static constexpr int TILE = 64 * D * 2;
+    static constexpr int OFF_LSE = 2 * TILE;  // Q, dO, then 64 floats lse2, 64 floats delta
+    static constexpr int STAGE = 2 * TILE + 512;
+    static constexpr int NST = 3;
+    static constexpr int OFF_ROWS = NST * STAGE;  // row ids of the list
+    static constexpr int OFF_WORDS = OFF_ROWS + 64 * BWD_LIST_WORDS * 4;
+    static constexpr int OFF_BASE = OFF_WORDS + BWD_LIST_WORDS * 8;
+    static constexpr int BYTES = OFF_BASE + (BWD_LIST_WORDS + 1) * 4 + 12;
+    static_assert(BYTES <= 160 * 1024, "LDS of one CU");
+};
+
+// Slot of 16-byte chunk c of tile row r.  An LDS line is 16 slots: one row of head-dim 128, two of 64.  A ds_read_b128 of 64 lanes is served
+// 16 lanes at a time, lanes 0-3, 12-15, 20-27 first: with the chunk index equal in 0-15 and one higher in 16-31, the
+// lines' swizzle values must be distinct and those of rows 4..11 closed under ^ 1.  A transposing read is served 32
+// lanes at a time, 8 rows at two neighbouring chunks: their values must differ above bit 0 (measured: 241 bytes per
+// clock for both kinds; a plain row number gives 227 and 122).
+template <int D>
+__device__ __forceinline__ int row_swizzle(int r)
+{
+    if (D == 128) return (((r & 7) ^ (((r >> 3) & 1) << 2)) << 1) | ((r >> 3) & 1);
+    const int line = r >> 1;
+    return (((line & 3) ^ (((line >> 2) & 1) << 1)) << 1) | ((line >> 2) & 1);
+}
+template <int D>
+__device__ __forceinline__ int row_tile_off(int r, int c)
+{
+    if (D == 128) return r * 256 + ((c ^ row_swizzle<D>(r)) << 4);
+    return (r >> 1) * 256 + (((((r & 1) << 3) | c) ^ row_swizzle<D>(r)) << 4);
+}
+
+// LDS reads by address.
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t addr)
+{
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(addr);
+}
+// Two transposing reads, `step` bytes apart.  In each, lane (n16, q4) gets the elements at column n16 of the four
+// 16-element row pieces that lanes 16 q4 .. 16 q4 + 15 point to (lane 4 k + m of them: 8 bytes, elements 4 m .. 4 m + 3 of
+// row k).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ bf16x8 lds_read_tr2(uint32_t addr, int step)
+{
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4 *>(addr));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4 *>(addr + step));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int D>
 __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const uint16_t *__restrict__ K,
                                                                    const uint16_t *__restrict__ V,
-                                                                   const uint16_t *__restrict__ Qn,
-                                                                   const uint16_t *__restrict__ Qt,
-                                                                   const uint16_t *__restrict__ dOn,
-                                                                   const uint16_t *__restrict__ dOt,
-                                                                   const float *__restrict__ lse2p,
-                                                                   const float *__restrict__ deltap, int tpcr,
-                                                                   const int32_t *__restrict__ csize,
+                                                                   const uint16_t *__restrict__ Q,
+                                                                   const uint16_t *__restrict__ dO,
+                                                                   const float *__restrict__ lse2,
+                                                                   const float *__restrict__ delta, int tpcr,
                                                                    const unsigned long long *__restrict__ colmask,
-                                                                   uint16_t *__restrict__ dOut)
+                                                                   const uint32_t *__restrict__ rowtab, BwdParts cut, float *__restrict__ part,
+                                                                   uint16_t *__restrict__ dK, uint16_t *__restrict__ dV)
 {
-    constexpr int NS = 2, KSTEPS = D / 32;
-    constexpr int TILE = 64 * D * 2;
-    constexpr int NT = WHICH == 0 ? 2 : 3;   // dV: Q natural, dO transposed; dK: Q natural, dO natural, Q transposed
-    constexpr int VEC = NT * TILE;           // per row tile: then 64 floats lse2, 64 floats delta
-    constexpr int SLOT = VEC + 2 * 256;
-    constexpr int TPS = WHICH == 0 ? 2 : 1;  // row tiles per step (per barrier): as many as two stages of them fit
-    constexpr int STAGE = TPS * SLOT;
-    constexpr int PIECES = TILE / 1024;
+    using C = Dkv<D>;
+    constexpr int NS = 2, KSTEPS = D / 32, DT = D / 16;
+    constexpr int CPR = D / 8;               // 16-byte chunks per row
+    constexpr int RPI = 64 / CPR;            // rows per direct-to-LDS instruction
+    constexpr int PER = 64 / RPI / 8;        // such instructions per wavefront, tile and operand
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+    uint32_t *rows = reinterpret_cast<uint32_t *>(smem + C::OFF_ROWS);
+    unsigned long long *words = reinterpret_cast<unsigned long long *>(smem + C::OFF_WORDS);
+    int *base = reinterpret_cast<int *>(smem + C::OFF_BASE);
 
-    const int nkb = (g.Cmax + BWD_ROWS - 1) / BWD_ROWS;
     int kv, slot;
-    if (!bwd_head_slot(blockIdx.x, g.Hkv, g.N * nkb, kv, slot)) return;
-    const int kb = slot % nkb;
-    const int j = slot / nkb;
+    if (!bwd_head_slot(blockIdx.x, g.Hkv, (int)(cut.nkb * cut.parts), kv, slot)) return;
+    const int kb = slot % cut.nkb;
+    const int pidx = (int)cut.parts - 1 - slot / cut.nkb;  // the later ranges, which have the most parts, first
+    int c = (int)((sqrtf(1.0f + 8.0f * (float)pidx / (float)cut.span) - 1.0f) * 0.5f);
+    while (c > 0 && (long long)cut.span * c * (c + 1) / 2 > pidx) --c;
+    while (c + 1 < cut.nc && (long long)cut.span * (c + 1) * (c + 2) / 2 <= pidx) ++c;
+    const int j = pidx - (int)((long long)cut.span * c * (c + 1) / 2);
     const CubeBox box = cube_box(g, j);
     const int size_j = box.size();
     if (kb * BWD_ROWS >= size_j) return;
+    const bool single = cut.nc - j / cut.span == 1;  // these keys have no other part
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n16 = lane & 15, q4 = lane >> 4;
 
     // the wavefront's keys (B operands)
-    int key[NS];
-    bool valid[NS];
-    size_t krow[NS];
+    const int key0 = kb * BWD_ROWS + wave * 32;
+    const bool busy = key0 < size_j;  // (a wavefront without keys only helps with the loads)
     bf16x8 kf[NS][KSTEPS], vf[NS][KSTEPS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        key[s] = kb * BWD_ROWS + wave * 32 + s * 16 + n16;
-        valid[s] = key[s] < size_j;
-        krow[s] = ((size_t)token_of(g, box, valid[s] ? key[s] : size_j - 1) * g.Hkv + kv) * D;
+        const int key = min(key0 + s * 16 + n16, size_j - 1);
+        const size_t krow = ((size_t)token_of(g, box, key) * g.Hkv + kv) * D;
 #pragma unroll
-        for (int c = 0; c < KSTEPS; ++c) {
-            kf[s][c] = *reinterpret_cast<const bf16x8 *>(K + krow[s] + 32 * c + 8 * q4);
-            if (WHICH == 1) vf[s][c] = *reinterpret_cast<const bf16x8 *>(V + krow[s] + 32 * c + 8 * q4);
+        for (int k = 0; k < KSTEPS; ++k) {
+            kf[s][k] = *reinterpret_cast<const bf16x8 *>(K + krow + 32 * k + 8 * q4);
+            vf[s][k] = *reinterpret_cast<const bf16x8 *>(V + krow + 32 * k + 8 * q4);
         }
     }
     const float c2 = BWD_LOG2E / sqrtf((float)D);  // softmax scale in base 2
+    const uint32_t nrows_all = (uint32_t)(g.S * g.Hq);
 
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
-    const size_t head_tiles = (size_t)kv * g.N * tpcr;
-    const size_t cm_base = ((size_t)kv * g.N + j) * g.N;
-    // row tile t of cube i into slot `slot` of `stage`: the tiles by all wavefronts, the two per-row vectors by
-    // wavefront 0
-    auto issue_tile = [&](int stage, int slot, int i, int t) __attribute__((always_inline)) {
-        const size_t tile = head_tiles + (size_t)i * tpcr + t;
-        stage = stage * TPS + slot;  // in units of SLOT
-#pragma unroll
-        for (int which = 0; which < NT; ++which)
-#pragma unroll
-            for (int u = 0; u < PIECES / 8; ++u) {
-                const int sub = wave * (PIECES / 8) + u;
-                const uint16_t *base = WHICH == 0 ? (which == 0 ? Qn : dOt) : (which == 0 ? Qn : which == 1 ? dOn : Qt);
-                const unsigned char *src = reinterpret_cast<const unsigned char *>(base) + tile * (size_t)TILE + sub * 1024;
-                dma_1k_s(__builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(stage * SLOT + which * TILE + sub * 1024)),
-                         uniform_ptr(src), (uint32_t)(lane * 16));
-            }
-        if (wave == 0) {
-            const uint32_t vec = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(stage * SLOT + VEC));
-            dma_dword_s(vec, uniform_ptr(lse2p + tile * 64), (uint32_t)(lane * 4));
-            dma_dword_s(vec + 256, uniform_ptr(deltap + tile * 64), (uint32_t)(lane * 4));
-        }
-    };
-    auto tiles_of = [&](int i) { return (csize[i] * g.G + 63) >> 6; };
-    // the TPS tiles t .. t + TPS - 1 of cube i, as far as the cube has them (nt tiles)
-    auto issue = [&](int stage, int i, int t, int nt) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < TPS; ++u)
-            if (t + u < nt) issue_tile(stage, u, i, t + u);
-    };
-
-    f32x4 acc[NS][D / 16];
+    f32x4 accV[NS][DT], accK[NS][DT];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e) acc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < DT; ++e) accV[s][e] = accK[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Row cubes from the last one down to the own cube: workgroups that start together then stream the same tiles at
-    // the same time, whatever their key cube, and one copy in L2 serves them all.
-    int ii = g.N - 1, it = 0, int_ = tiles_of(g.N - 1);
-    issue(0, ii, 0, int_);
-    if ((it += TPS) >= int_) { --ii; it = 0; int_ = ii >= j ? tiles_of(ii) : 0; }
-    int stage = 0;
-    for (int i = g.N - 1; i >= j; --i) {
-        const int nt = tiles_of(i);
-        for (int tb = 0; tb < nt; tb += TPS) {
-            tile_barrier();
-            if (ii >= j) {
-                issue(stage ^ 1, ii, it, int_);
-                if ((it += TPS) >= int_) { --ii; it = 0; int_ = ii >= j ? tiles_of(ii) : 0; }
-            }
-            auto tile_work = [&](int slot) __attribute__((always_inline)) {
-            const int t = tb + slot;
-            const unsigned char *t0 = smem + stage * STAGE + slot * SLOT;
-            const float *lv = reinterpret_cast<const float *>(t0 + VEC);
-            const float *dv = lv + 64;
-            // bit k: row k of the tile selected cube j (rows of the own cube attend it by rule)
-            unsigned long long cm = ~0ull;
-            if (MASKED && i > j) cm = colmask[(cm_base + i) * tpcr + t];
-            // S[row, key]: the streamed rows take the place the keys have in the forward (qk_tile's row order)
-            bf16x8 pf[NS][2];
-            auto half = [&](auto hc) __attribute__((always_inline)) {
-                constexpr int H = decltype(hc)::value;
-                f32x4 sacc[NS][2], pacc[NS][2];
-                const int rb = 32 * H + 8 * q4;  // the lane's eight rows of this half: rb .. rb + 7
-                const uint32_t bits = (uint32_t)(cm >> rb);  // their selection bits
-                // What the products start from: -lse * sqrt(D) of the row (times the softmax scale in base 2 the
-                // accumulator is then the exponent of the probability), -inf for a row that did not select this key
-                // cube (probabilities 0); and minus the row's delta for dP.
-                f32x4 sinit[2], pinit[2];
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    // The lane's part in a tile's loads: piece u of this wavefront is RPI rows of the tile, one 16-byte slot per lane.
+    // (Computed anew for every tile, here and below, by hiding where `lane` comes from: registers are short.)
+    auto fresh_lane = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto issue = [&](int stage, int first) __attribute__((always_inline)) {
+        const uint32_t dst = lds0 + (uint32_t)(stage * C::STAGE);
+        const int l = fresh_lane();
 #pragma unroll
-                for (int k2 = 0; k2 < 2; ++k2) {
-                    sinit[k2] = *reinterpret_cast<const f32x4 *>(lv + rb + 4 * k2);
-                    if (MASKED) {
+        for (int u = 0; u < PER; ++u) {
+            const int r = (wave * PER + u) * RPI + l / CPR;
+            const uint32_t rid = min(rows[first + r], nrows_all - 1);
+            const int chunk = ((l & 15) ^ row_swizzle<D>(r)) & (CPR - 1);
+            const size_t off = (size_t)rid * D + chunk * 8;
+            const uint32_t piece = dst + (uint32_t)((wave * PER + u) * 1024);
+            dma_lane16(__builtin_amdgcn_readfirstlane(piece), Q + off);
+            dma_lane16(__builtin_amdgcn_readfirstlane(piece + C::TILE), dO + off);
+        }
+        if (wave < 2) {  // the start values: wavefront 0 lse2, wavefront 1 delta
+            const float *vals = wave == 0 ? lse2 : delta;
+            dma_lane4(__builtin_amdgcn_readfirstlane(dst + C::OFF_LSE + 256 * wave), vals + rows[first + l]);
+        }
+    };
+    // Opens a tile: this wavefront's loads of it have landed (those of the next tile may stay in flight), then everybody's.
+    auto open_tile = [&](bool more) __attribute__((always_inline)) {
+        if (!more) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else if (wave < 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * PER + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * PER) : "memory");
+    };
+
+    // Operand reads: the lane's place in a tile for both kinds, without the 16-row block (an immediate offset) and the
+    // chunk's high bits (flipped per read: a table of the addresses would not fit the register file).
+    const uint32_t nat0 = (uint32_t)row_tile_off<D>(n16, q4);
+    const uint32_t tr0 = (uint32_t)(row_tile_off<D>(4 * q4 + (n16 >> 2), (n16 & 3) >> 1) + 8 * (n16 & 1));
+    constexpr int BLK = 16 * D * 2;  // bytes of 16 tile rows
+
+    // One 64-row tile, in two halves of 32 rows.  OWN: the rows are cube j's own, from row r0 of its (rank, head) order.
+    // The order written here is the order executed (operands one step ahead of their MFMAs): left to itself the
+    // compiler starts more loads than there are registers for.
+    auto tile_work = [&](int stage, auto own_tag, int r0) __attribute__((always_inline)) {
+        constexpr bool OWN = decltype(own_tag)::value;
+        const uint32_t st = lds0 + (uint32_t)(stage * C::STAGE);
+        const uint32_t nat = st + nat0, tr = st + tr0;
+        auto rows_at = [&](int blk, int k, bf16x8 (&o)[2]) __attribute__((always_inline)) {  // Q, dO
+            uint32_t at;
+            asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "n"(k << 6), "v"(nat));
+            o[0] = lds_read<bf16x8>(at + (uint32_t)(blk * BLK));
+            o[1] = lds_read<bf16x8>(at + (uint32_t)(blk * BLK + C::TILE));
+        };
+        auto cols_at = [&](int H, int e, bf16x8 (&o)[2]) __attribute__((always_inline)) {  // Q^T, dO^T
+            uint32_t at;
+            asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "n"(e << 5), "v"(tr));
+            o[0] = lds_read_tr2(at + (uint32_t)(2 * H * BLK), BLK);
+            o[1] = lds_read_tr2(at + (uint32_t)(2 * H * BLK + C::TILE), BLK);
+        };
+        bf16x8 op[2][2];
+        rows_at(0, 0, op[0]);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (!((bits >> (4 * k2 + v)) & 1u)) sinit[k2][v] = -INFINITY;
+        for (int H = 0; H < 2; ++H) {
+            bf16x8 pp[NS], ds[NS];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {  // 16 rows: scores and dP
+                const uint32_t vec = st + (uint32_t)(C::OFF_LSE + 16 * (2 * H + x) * 4) + (uint32_t)(16 * q4);
+                const f32x4 li = lds_read<f32x4>(vec), di = lds_read<f32x4>(vec + 256);
+                f32x4 sa[NS], pa[NS];
+#pragma unroll
+                for (int k = 0; k < KSTEPS; ++k) {
+                    if (k + 1 < KSTEPS) rows_at(2 * H + x, k + 1, op[(k + 1) & 1]);
+                    else if (x == 0) rows_at(2 * H + 1, 0, op[(k + 1) & 1]);
+                    else cols_at(H, 0, op[(k + 1) & 1]);
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        sa[s] = mfma16(op[k & 1][0], kf[s][k], k == 0 ? li : sa[s]);
+                        pa[s] = mfma16(op[k & 1][1], vf[s][k], k == 0 ? di : pa[s]);
                     }
-                    if (WHICH == 1) pinit[k2] = *reinterpret_cast<const f32x4 *>(dv + rb + 4 * k2);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                nat_half_from<D, NS, H>(t0, n16, q4, kf, sinit, sacc);
-                if (WHICH == 1) nat_half_from<D, NS, H>(t0 + TILE, n16, q4, vf, pinit, pacc);
-                if (i == j) {  // causal edge inside the own cube: a row attends keys up to its own rank
-                    int r0 = 64 * t + rb;
-                    asm volatile("" : "+v"(r0));
+                if (OWN) {  // causal edge: a row attends keys up to its own rank
 #pragma unroll
-                    for (int k2 = 0; k2 < 2; ++k2)
+                    for (int v = 0; v < 4; ++v) {
+                        const int rank = (r0 + 16 * (2 * H + x) + 4 * q4 + v) / g.G;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int rrank = (r0 + 4 * k2 + v) / g.G;
-#pragma unroll
-                            for (int s = 0; s < NS; ++s)
-                                if (key[s] > rrank) sacc[s][k2][v] = -INFINITY;
-                        }
+                        for (int s = 0; s < NS; ++s)
+                            if (key0 + 16 * s + n16 > rank) sa[s][v] = -INFINITY;
+                    }
                 }
 #pragma unroll
-                for (int k2 = 0; k2 < 2; ++k2)
+                for (int s = 0; s < NS; ++s)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
+                    for (int v = 0; v < 4; ++v) {
+                        const float p = __builtin_amdgcn_exp2f(sa[s][v] * c2);
+                        pp[s][4 * x + v] = (__bf16)p;
+                        ds[s][4 * x + v] = (__bf16)(p * pa[s][v]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // dV^T += dO^T.P, dK^T += Q^T.dS over the half's 32 rows (k index 8 q4 + 4 x + v: row 16 x + 4 q4 + v)
 #pragma unroll
-                        for (int s = 0; s < NS; ++s) {
-                            const float p = __builtin_amdgcn_exp2f(sacc[s][k2][v] * c2);
-                            pf[s][H][4 * k2 + v] = (__bf16)(WHICH == 1 ? p * pacc[s][k2][v] : p);
-                        }
-            };
-            half(std::integral_constant<int, 0>{});
-            half(std::integral_constant<int, 1>{});
-            tn_tile<D, NS>(t0 + (WHICH == 0 ? TILE : 2 * TILE), n16, q4, pf, acc);
-            };
-            tile_work(0);
-            if (TPS > 1 && tb + 1 < nt) tile_work(1);
-            stage ^= 1;
+            for (int e = 0; e < DT; ++e) {
+                if (e + 1 < DT) cols_at(H, e + 1, op[(e + 1) & 1]);
+                else if (H == 0) rows_at(2, 0, op[(e + 1) & 1]);
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    accK[s][e] = mfma16(op[e & 1][0], ds[s], accK[s][e]);
+                    accV[s][e] = mfma16(op[e & 1][1], pp[s], accV[s][e]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // n listed rows through the tiles; OWN: they are rows f .. of cube j itself.
+    auto run_list = [&](int n, auto own_tag, int f) __attribute__((always_inline)) {
+        constexpr bool OWN = decltype(own_tag)::value;
+        const int nt = (n + 63) >> 6;
+        if (nt == 0) return;
+        issue(0, 0);
+        if (nt > 1) issue(1, 64);
+        int stage = 0;
+        for (int t = 0; t < nt; ++t) {
+            open_tile(t + 1 < nt);
+            const int s2 = stage == 0 ? 2 : stage - 1;  // (stage + 2) % 3: read last at tile t - 1
+            if (t + 2 < nt) issue(s2, 64 * (t + 2));
+            // (own cube: no row of the tile reaches the wavefront's keys if the last one does not)
+            if (busy && (!OWN || (f + 64 * t + 63) / g.G >= key0)) tile_work(stage, own_tag, f + 64 * t);
+            stage = stage == 2 ? 0 : stage + 1;
+        }
+    };
+
+    // ---- the rows: 64-row words w of the range's row cubes, BWD_LIST_WORDS at a time
+    const int i0 = max(c * cut.span, j + 1), i1 = min(g.N, (c + 1) * cut.span);
+    const int nwords = max(0, i1 - i0) * tpcr;
+    const unsigned long long *cm = colmask + (((size_t)kv * g.N + j) * g.N + i0) * tpcr;
+    const uint32_t *tab = rowtab + (size_t)i0 * tpcr * 64;
+    for (int w0 = 0; w0 < nwords; w0 += BWD_LIST_WORDS) {
+        __syncthreads();  // the list before is done with
+        const int l = fresh_lane();
+        if (wave == 0) {
+            const unsigned long long bits = w0 + l < nwords ? cm[w0 + l] : 0ull;
+            const int n = __popcll(bits);
+            int incl = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int up = __shfl_up(incl, d, 64);
+                if (l >= d) incl += up;
+            }
+            words[l] = bits;
+            base[l] = incl - n;
+            if (l == 63) base[BWD_LIST_WORDS] = incl;
+        }
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(base[BWD_LIST_WORDS]);
+        for (int x = wave; x < min(BWD_LIST_WORDS, nwords - w0); x += BWD_THREADS / 64) {
+            const unsigned long long bits = words[x];
+            if ((bits >> l) & 1ull)
+                rows[base[x] + __popcll(bits & ((1ull << l) - 1ull))] = tab[(size_t)(w0 + x) * 64 + l] + (uint32_t)(kv * g.G);
+        }
+        if (wave == 0 && n + l < ((n + 63) & ~63)) rows[n + l] = nrows_all;  // padding rows
+        __syncthreads();
+        run_list(n, std::integral_constant<bool, false>{}, 0);
+    }
+    // ---- cube j's own rows, in rank order
+    if (c == j / cut.span) {
+        const int own = size_j * g.G;
+        // (ranks below the block's first key attend none of its keys)
+        for (int f = kb * BWD_ROWS * g.G / 64 * 64; f < own; f += 64 * BWD_LIST_WORDS) {
+            const int n = min(own - f, 64 * BWD_LIST_WORDS);
+            __syncthreads();
+            for (int x = wave * 64 + fresh_lane(); x < ((n + 63) & ~63); x += BWD_THREADS)
+                rows[x] = x < n ? rowtab[(size_t)j * tpcr * 64 + f + x] + (uint32_t)(kv * g.G) : nrows_all;
+            __syncthreads();
+            run_list(n, std::integral_constant<bool, true>{}, f);
         }
     }
-    const float scale = WHICH == 1 ? 1.0f / sqrtf((float)D) : 1.0f;
+    if (!busy) return;
+
+    // ---- results: element (s, e, v) of lane (n16, q4) is key 16 s + n16, head-dim 16 e + 4 q4 + v
+    const float scale = 1.0f / sqrtf((float)D);
+    if (single) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        if (!valid[s]) continue;
+        for (int s = 0; s < NS; ++s) {
+            const int key = key0 + 16 * s + n16;
+            if (key >= size_j) continue;
+            const size_t o = ((size_t)token_of(g, box, key) * g.Hkv + kv) * D + 4 * q4;
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e) {
-            bf16x2 a, b;
-            a[0] = (__bf16)(acc[s][e][0] * scale); a[1] = (__bf16)(acc[s][e][1] * scale);
-            b[0] = (__bf16)(acc[s][e][2] * scale); b[1] = (__bf16)(acc[s][e][3] * scale);
-            uint2 o;
-            o.x = *reinterpret_cast<uint32_t *>(&a);
-            o.y = *reinterpret_cast<uint32_t *>(&b);
-            *reinterpret_cast<uint2 *>(dOut + krow[s] + 16 * e + 4 * q4) = o;
+            for (int e = 0; e < DT; ++e) {
+                *reinterpret_cast<uint2 *>(dV + o + 16 * e) = pack_bf16(accV[s][e]);
+                *reinterpret_cast<uint2 *>(dK + o + 16 * e) = pack_bf16(accK[s][e] * scale);
+            }
         }
+        return;
     }
+    float *out = part + (((size_t)kv * cut.nkb + kb) * cut.parts + pidx) * (2 * BWD_ROWS * D) + (size_t)wave * (32 * D) + lane * 4;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int e = 0; e < DT; ++e) {
+            *reinterpret_cast<f32x4 *>(out + (s * DT + e) * 256) = accV[s][e];
+            *reinterpret_cast<f32x4 *>(out + BWD_ROWS * D + (s * DT + e) * 256) = accK[s][e];
+        }
+}
+
+// Sums the parts of (KV head and key block, cube j) in range order; a thread owns four elements of dV and of dK.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, const float *__restrict__ part,
+                                                         uint16_t *__restrict__ dK, uint16_t *__restrict__ dV)
+{
+    constexpr int DT = D / 16;
+    const int j = blockIdx.y, kv = blockIdx.z / cut.nkb, kb = blockIdx.z % cut.nkb;
+    const int c0 = j / cut.span;
+    if (cut.nc - c0 == 1) return;
+    const CubeBox box = cube_box(g, j);
+    // position x of a part: wavefront, (s, e), lane
+    const int x = blockIdx.x * 256 + threadIdx.x;
+    const int lane = x & 63, e = (x >> 6) % DT, s = (x >> 6) / DT % 2, wave = (x >> 6) / (2 * DT);
+    const int key = kb * BWD_ROWS + wave * 32 + s * 16 + (lane & 15);
+    if (key >= box.size()) return;
+    const float *src = part + ((size_t)blockIdx.z * cut.parts + j) * (2 * BWD_ROWS * D) + (size_t)x * 4;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f}, k = v;
+    for (int c = c0; c < cut.nc; ++c) {
+        const float *p = src + ((size_t)cut.span * c * (c + 1) / 2) * (2 * BWD_ROWS * D);
+        v += *reinterpret_cast<const f32x4 *>(p);
+        k += *reinterpret_cast<const f32x4 *>(p + BWD_ROWS * D);
+    }
+    const size_t o = ((size_t)token_of(g, box, key) * g.Hkv + kv) * D + 16 * e + 4 * (lane >> 4);
+    *reinterpret_cast<uint2 *>(dV + o) = pack_bf16(v);
+    *reinterpret_cast<uint2 *>(dK + o) = pack_bf16(k * (1.0f / sqrtf((float)D)));
 }
 
 template <int D>
@@ -620,13 +770,12 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     if (e != hipSuccess) return e;
     e = launch_kv_pack(g, V, K, w.packB, false, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bwd_pack_rows_kernel<D>), dim3(w.tpcr, g.N, g.Hkv), dim3(256), 0, st, g, Q, dO, O, lse, w.tpcr,
-                       w.Qn, w.Qt, w.dOn, w.dOt, w.lse2, w.delta);
+    const long long rows = (long long)g.S * g.Hq;
+    hipLaunchKernelGGL((bwd_row_values_kernel<D>), dim3((unsigned)((rows + 1 + 256 / (D / 8) - 1) / (256 / (D / 8)))),
+                       dim3(256), 0, st, rows, dO, O, lse, w.lse2, w.delta);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (sel_mask != nullptr) {
-        hipLaunchKernelGGL(bwd_colmask_kernel, dim3(w.tpcr, g.N, g.Hkv), dim3(64), 0, st, g, sel_mask, w.tpcr, w.colmask);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    hipLaunchKernelGGL(bwd_colmask_kernel, dim3(w.tpcr, g.N, g.Hkv), dim3(64), 0, st, g, sel_mask, w.tpcr, w.colmask, w.rowtab);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
 
     const size_t half_elems = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * D;
     const uint16_t *Kn = reinterpret_cast<const uint16_t *>(w.packA);
@@ -638,30 +787,30 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     const int nblk = (g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS;
     const dim3 grid_q(bwd_grid(g.Hkv, g.N * nblk));
     const int lds_q = 2 * 3 * TILE;
-    const int nkb = (g.Cmax + BWD_ROWS - 1) / BWD_ROWS;
-    const dim3 grid_k(bwd_grid(g.Hkv, g.N * nkb));
-    const int lds_v = 2 * 2 * (2 * TILE + 512), lds_k = 2 * (3 * TILE + 512);
+    const BwdParts &cut = w.cut;
+    const dim3 grid_k(bwd_grid(g.Hkv, (int)(cut.nkb * cut.parts)));
+    constexpr int lds_k = Dkv<D>::BYTES;
 #define ADASPARK_BWD_LAUNCH(MASKED)                                                                                    \
     do {                                                                                                               \
-        static LdsOptIn opted_q, opted_v, opted_k;                                                                     \
+        static LdsOptIn opted_q;                                                                                       \
         e = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED>), lds_q);                     \
         if (e != hipSuccess) return e;                                                                                 \
         hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, Kn, Vn,    \
-                           Kt, csize, w.lse2, w.delta, w.tpcr, sel_mask, dQ);                                          \
-        e = opted_v.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D, 0, MASKED>), lds_v);                 \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, 0, MASKED>), grid_k, dim3(BWD_THREADS), lds_v, st, g, K, V, w.Qn,   \
-                           w.Qt, w.dOn, w.dOt, w.lse2, w.delta, w.tpcr, csize, w.colmask, dV);                                 \
-        e = opted_k.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D, 1, MASKED>), lds_k);                 \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, 1, MASKED>), grid_k, dim3(BWD_THREADS), lds_k, st, g, K, V, w.Qn,   \
-                           w.Qt, w.dOn, w.dOt, w.lse2, w.delta, w.tpcr, csize, w.colmask, dK);                                 \
+                           Kt, csize, w.lse2, w.delta, sel_mask, dQ);                                                  \
     } while (0)
     if (sel_mask != nullptr)
         ADASPARK_BWD_LAUNCH(true);
     else
         ADASPARK_BWD_LAUNCH(false);
 #undef ADASPARK_BWD_LAUNCH
+    static LdsOptIn opted_k;
+    e = opted_k.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D>), lds_k);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<D>), grid_k, dim3(BWD_THREADS), lds_k, st, g, K, V, Q, dO, w.lse2, w.delta, w.tpcr,
+                       w.colmask, w.rowtab, cut, w.part, dK, dV);
+    if (cut.nc > 1)
+        hipLaunchKernelGGL((bwd_reduce_kernel<D>), dim3(BWD_ROWS * D / 4 / 256, g.N, g.Hkv * cut.nkb), dim3(256), 0, st, g, cut,
+                           w.part, dK, dV);
     return hipGetLastError();
 }
 

@@ -87,6 +87,27 @@ def test_backward_matches_oracle(B, oracle, name, p):
     run_case(B, oracle, name, p)
 
 
+# What the dK/dV kernel cuts by: one cube (no part to sum), cubes of 65 rows per KV head (a second 64-row word with one row),
+# of 63 and 64 tokens, more than 64 words per cube (two lists) with four 256-key blocks, many cubes per part and a
+# last range with a single one, a text tail of one token.
+GATHER = [
+    ("one_cube", (2, 4, 4), (2, 4, 4), 2, 1, 64, 1.0, 0),
+    ("rows65", (3, 1, 26), (1, 1, 13), 5, 1, 128, 0.7, 0),
+    ("tokens63", (4, 7, 9), (1, 7, 9), 3, 1, 128, 0.6, 0),
+    ("tokens64", (5, 8, 8), (1, 8, 8), 2, 2, 64, 0.6, 1),
+    ("two_lists", (8, 16, 16), (4, 16, 16), 7, 1, 64, 1.0, 0),
+    ("parts", (65, 4, 4), (1, 4, 4), 1, 1, 128, 0.5, 1),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,p,text", GATHER, ids=[c[0] for c in GATHER])
+def test_backward_gathered_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, p, text):
+    w = synth.Workload(name, 40, *grid, *cube, hq, hkv, d, (p,), (1.0,) * hkv, text)
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
+    run_case(B, oracle, name, p)
+    run_case(B, oracle, name, 1.0, dense=True)
+
+
 @pytest.mark.parametrize("name,p", [("T_tiny", 0.8), ("T_ragged", 0.9), ("T_lead64", 0.8), ("M_bwd256", 0.8)])
 def test_backward_matches_the_exact_gradient(B, oracle, name, p):
     """Against the oracle's own gradient: delta = dO.o from the exact fp64 forward, not from the bf16 O the GPU
