@@ -15,7 +15,7 @@ CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libadaspark.so")
 OBJ_DIR = os.path.join(_HERE, "_build")
 
-SOURCES = ["api.hip", "pool.hip", "select.hip", "kvpack.hip", "attn_compact.hip", "attn_walk.hip", "attn_pairs.hip", "ffn.hip",
+SOURCES = ["api.hip", "pool.hip", "select.hip", "kvpack.hip", "attn_compact.hip", "attn_walk.hip", "attn_split.hip", "attn_pairs.hip", "ffn.hip",
            "ffn_gemm.hip", "attn_bwd.hip", "probe.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -1,6 +1,6 @@
 // Dense causal attention, and sparse attention (Eq. 3 + own-cube rule, Sec. 3.2) with the selection applied as a
 // mask: every row walks every preceding cube.  Also the entry that chooses between this kernel and the
-// compacting one (attn_compact.hip).
+// others (attn_split.hip, attn_compact.hip, attn_pairs.hip).
 //
 // Fixed-row walk with two wavefront sets in counter-phase.
 //
@@ -20,6 +20,9 @@
 // the barrier that opens it nobody reads K(t-1) or V(t-2) any more, and the direct-to-LDS loads of K(t+2) and
 // V(t+1) go into their stages; they are waited for two barriers later (the loads started one tile ago may stay in
 // flight).
+#include <algorithm>
+#include <cmath>
+
 #include "attn_tile.h"
 
 namespace adaspark {
@@ -563,6 +566,28 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     return hipGetLastError();
 }
 
+// Whether the kernel for short sequences (attn_split.hip) beats this one, from what each of them took on an MI355X (us;
+// the figures below reproduce 80 measured shapes of 1,024 to 16,384 tokens, heads 4/4 .. 32/8 of 64 and 128, cubes of
+// 32 to 256 tokens within about 15 %):
+//   walk   a slot (64 keys past 256 rows) takes 1.2 at head-dim 64 and 1.7 at 128, 0.6 more where cubes leave part of their
+//          tiles empty; the time is the longest walk's slots, or all slots over 256 CUs where that is more
+//   split  a step (32 keys past 32 rows) takes a CU 0.19 and 0.28 -- what its operands take from L2 -- and a workgroup
+//          4 to start and to combine its parts
+// Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 111 split, 161 walk; 16,384: 387, 336.
+// 2,048 tokens of 14/2 heads of 128 in cubes of 256: 60, 62; 4,096: 155, 110.
+static bool attn_split_pays(const Geom &g)
+{
+    if (!attn_split_fits(g)) return false;
+    const double groups = (double)g.N * g.Hkv, rows = (double)g.G * g.Cmax;  // (query cube, KV head) pairs; rows of one
+    const double share = g.causal ? 0.5 : 1.0;                               // of all cubes that the average walk visits
+    const double slots = (double)g.N * g.TPC, walks = groups * std::ceil(rows / 256);
+    const double slot = (g.D == 64 ? 1.2 : 1.7) + (g.Cmax % KEY_TILE != 0 ? 0.6 : 0.0);
+    const double walk = 8 + slot * std::max(slots, 1.1 * share * slots * walks / 256);
+    const double steps = (double)g.N * ((g.Cmax + 31) / 32), blocks = groups * std::ceil(rows / 32);
+    const double split = 10 + blocks / 256 * (4 + share * steps * (g.D == 64 ? 0.19 : 0.28));
+    return split < walk;
+}
+
 // Below this many candidate (row, cube) pairs the automatic choice is the masked walk outright (see launch_attn_d).
 constexpr unsigned long long AUTO_MIN_CANDIDATE_PAIRS = 2ull << 20;
 
@@ -575,6 +600,8 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
                                 int sparse_kernel, void *scratch, size_t scratch_bytes, uint16_t *O, float *lse,
                                 hipStream_t st)
 {
+    if ((sel_mask == nullptr || sparse_kernel == ADASPARK_SPARSE_AUTO) && attn_split_pays(g))
+        return launch_attn_split(g, Q, packed, sel_mask, O, lse, st);
     if (sel_mask == nullptr) return launch_walk<D, false>(g, Q, packed, nullptr, nullptr, 0, 0, O, lse, st);
     if (sparse_kernel == ADASPARK_SPARSE_COMPACT && g.causal)
         return launch_attn_compact(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);

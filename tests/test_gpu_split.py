@@ -1,0 +1,51 @@
+"""The attention kernel for short sequences at the sizes where its cutting can go wrong, against the fp64 oracle: row
+blocks of 31 / 32 / 33 rows, cubes of 31 / 32 / 33 keys and of one, a walk shorter than the eight wavefronts that share it,
+nothing selected, both causal modes, dense.  The entries choose it by shape: all of these are far on its side of the line
+(two dozen walks of a few steps)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_08077_amd import synth
+from test_gpu_parity import B, MAX_ABS, MEAN_ABS, lse_bound, oshape  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ("keys31", (3, 1, 31), (1, 1, 31), 1, 1, 64, 0),
+    ("keys32", (4, 4, 8), (1, 4, 8), 2, 1, 128, 0),
+    ("keys33", (5, 3, 11), (1, 3, 11), 1, 1, 128, 0),
+    ("rows33", (2, 1, 22), (1, 1, 11), 3, 1, 64, 0),
+    ("one_token_cubes", (2, 3, 7), (1, 1, 1), 4, 2, 64, 0),
+    ("one_cube", (2, 4, 9), (2, 4, 9), 7, 1, 128, 0),
+    ("text_tail", (3, 4, 8), (1, 4, 8), 6, 2, 128, 33),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text", SHAPES, ids=[s[0] for s in SHAPES])
+def test_short_sequences(B, oracle, name, grid, cube, hq, hkv, d, text):  # noqa: F811
+    w = synth.Workload(name, 41, *grid, *cube, hq, hkv, d, (0.6,), (1.0,) * hkv, text)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    Qg, Kg, Vg = Q.cuda(), K.cuda(), V.cuda()
+    kbar = oracle.cube_pool(osh, K)
+    rows = np.arange(w.S * w.Hq)
+
+    def check(what, got, want):
+        err = np.abs(got.reshape(-1, d).float().cpu().numpy().astype(np.float64) - want)
+        print(f"[{name} {what}] max-abs={err.max():.3e} mean-abs={err.mean():.3e}", flush=True)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+
+    for causal in (True, False):
+        for p in (0.0, 0.6):
+            mask = oracle.cube_select(osh, Q, kbar, p, causal=causal)[0]
+            print(f"[{name}] causal={causal} p={p}", flush=True)
+            O, lse = B.sparse_attn(sh, Qg, Kg, Vg, torch.from_numpy(mask.view(np.int32)).cuda(), causal=causal, return_lse=True)
+            torch.cuda.synchronize()
+            check(f"causal={causal} p={p}", O, oracle.sparse_attn(osh, Q, K, V, mask, causal=causal)[0])
+            if causal:
+                want, absdot = oracle.bwd.lse_rows(osh, Q.double().numpy(), K.double().numpy(), mask, rows)
+                assert (np.abs(lse.cpu().numpy().astype(np.float64) - want) <= lse_bound(absdot)).all()
+        O = B.dense_attn(sh, Qg, Kg, Vg, causal=causal)
+        torch.cuda.synchronize()
+        check(f"causal={causal} dense", O, oracle.dense_attn(osh, Q, K, V, causal=causal))
