@@ -3,13 +3,27 @@
 //   down :  F[r][n] = sum_k H[r][k] Wd[n][k]                                                    fp32 out
 // Both are C = A.B^T with A (activations) and B (weights) stored row-major with the reduction index contiguous.
 //
-// Workgroup = 256 activation rows x 256 weight rows, 64 reduction elements per step, 8 wavefronts (2 along the
-// activation rows x 4 along the weight rows, 128 x 64 each).  Tiles go from global memory straight into LDS
-// (global_load_lds_dwordx4), two stages, one workgroup barrier per step; the 16-byte chunks of a tile row are
+// Workgroup = 256 activation rows x 256 weight rows, 64 reduction elements per step, 8 wavefronts (2 along the activation
+// rows x 4 along the weight rows; a wavefront has 64 rows of either activation half and 32 of either weight half).  Tiles
+// go from global memory straight into LDS (global_load_lds_dwordx4), two stages; the 16-byte chunks of a tile row are
 // XOR-swizzled by the choice of which chunk a lane fetches, so that the MFMA operand reads are conflict-free.
 // mfma_f32_16x16x32_bf16 with the weights on the M side and the activations on the N side: a lane ends up with four
 // consecutive output features of one token, which is what a row-major store wants.  For the gated product a tile's
-// weight rows are 128 rows of W_gate and the same 128 rows of W_up, and every wavefront holds matching pairs.
+// weight halves are 128 rows of W_gate and the same 128 rows of W_up, so every wavefront holds matching pairs.
+//
+// A reduction step is two halves (the activation halves), a half is two slots -- operands into registers, 32 MFMAs --
+// with a workgroup barrier between slots, and the two wavefronts of a SIMD are one slot apart: while one multiplies, the
+// other reads its operands and starts loads.  A half's place in LDS is free as soon as both sets have read it, so loads run
+// a step and a half ahead in two stages.  In slots (set P: wavefronts 0-3, set Q: 4-7, one later), step k is
+//   P  4k: read A0 W0 W1, load A1(k+1)   4k+1: multiply   4k+2: read A1, load A0 W0 W1(k+2)   4k+3: multiply
+// Q's last read of A0 W0 W1(k) is in slot 4k+1 and of A1(k) in 4k+3, before their loads of step k+2 (same stage) start
+// in 4k+2 and 4k+4; those have to have landed (vmcnt, then the barrier) before P's reads in slots 4k+8 and 4k+10.
+//
+// Bound by power: with random operands the chip clocks 1.75 GHz under this kernel (2.0 without the loads and LDS reads),
+// where the matrix pipes then are 73 % busy.  65,536 tokens, 3584/18944, Top-p 0.7: 6.4 + 3.05 ms, 1.3 PFLOP/s; one barrier per
+// step, both wavefronts of a SIMD in phase and loads one step ahead: 7.0 + 3.3 ms.  Tried: both in phase with operands
+// prefetched across two barriers a step (6.7 + 3.2, loads spread between the MFMAs: 6.5 + 3.1), the barrier ahead of a
+// slot's last MFMAs (slower: it holds the other set's reads back).
 #include "attn_tile.h"
 #include "ffn.h"
 
@@ -19,8 +33,18 @@ constexpr int GT = FFN_ROW_TILE;            // rows of a tile, both operands
 constexpr int GK = 64;                      // reduction elements per step: 128 bytes per row
 constexpr int GEMM_THREADS = 512;
 constexpr int TILE_BYTES = GT * GK * 2;     // 32 KB
+constexpr int HALF_BYTES = TILE_BYTES / 2;
 constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // activations, weights
 constexpr int GEMM_LDS = 2 * STAGE_BYTES;   // 128 KB
+
+// Ends a slot: everything this wavefront has loaded but the newest KEEP loads (63: whatever is on the way) has landed and
+// its LDS reads are done, then the workgroup barrier.
+template <int KEEP>
+__device__ __forceinline__ void open_slot()
+{
+    if (KEEP == 63) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(KEEP) : "memory");
+}
 
 template <bool GATED>
 __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *__restrict__ A,
@@ -42,45 +66,57 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
     const int tn = (logical >> 2) % n_tiles;
     if (tm >= m_tiles || tm * GT >= *n_rows_ptr) return;
 
+    const int k_first = 0, nk = K / GK;
+
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n16 = lane & 15, q4 = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
 
-    // Tile loads: wavefront w fills the 4 KB [4w, 4w+4) KB of either tile: rows 32w .. 32w+31.  Physical 16-byte slot
-    // x of a tile holds chunk `chunk` of row `row` (vt_tile_coords); a lane's four sources stay fixed over the loop.
-    uint32_t voffA[4], voffW[4];
+    // Tile loads: of either half of either tile wavefront w fills rows 16 w .. 16 w + 15, two loads.  Physical 16-byte slot
+    // x of a tile holds chunk `chunk` of row `row` (vt_tile_coords); a lane's sources stay fixed over the loop.
+    uint32_t voffA[2][2], voffW[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 2; ++i) {
         int row, chunk;
-        vt_tile_coords((wave * 4 + i) * 64 + lane, row, chunk);
-        const long long arow = gather ? (long long)gather[tm * GT + row] : (long long)row;
-        voffA[i] = (uint32_t)(arow * K * 2 + chunk * 16);
-        voffW[i] = (uint32_t)((GATED ? (row & 127) : row) * K * 2 + chunk * 16);
-    }
-    const unsigned char *baseA = reinterpret_cast<const unsigned char *>(A) + (gather ? 0 : (size_t)tm * GT * K * 2);
-    const unsigned char *baseW =
-        GATED ? reinterpret_cast<const unsigned char *>(wave < 4 ? W0 : W1) + (size_t)tn * 128 * K * 2
-              : reinterpret_cast<const unsigned char *>(W0) + (size_t)tn * GT * K * 2;
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + (uint32_t)(wave * 4096));
-    auto issue = [&](int stage, int kstep) __attribute__((always_inline)) {
-        const void *sa = uniform_ptr(baseA + (size_t)kstep * (GK * 2));
-        const void *sw = uniform_ptr(baseW + (size_t)kstep * (GK * 2));
+        vt_tile_coords((wave * 2 + i) * 64 + lane, row, chunk);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            dma_1k_s(lds0 + (uint32_t)(stage * STAGE_BYTES + i * 1024), sa, voffA[i]);
-            dma_1k_s(lds0 + (uint32_t)(stage * STAGE_BYTES + TILE_BYTES + i * 1024), sw, voffW[i]);
+        for (int h = 0; h < 2; ++h) {
+            const long long arow = gather ? (long long)gather[tm * GT + h * 128 + row] : (long long)(h * 128 + row);
+            voffA[h][i] = (uint32_t)(arow * K * 2 + chunk * 16);
         }
+        voffW[i] = (uint32_t)(row * K * 2 + chunk * 16);
+    }
+    const unsigned char *baseA =
+        reinterpret_cast<const unsigned char *>(A) + (gather ? 0 : (size_t)tm * GT * K * 2) + (size_t)k_first * (GK * 2);
+    const unsigned char *baseW[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        baseW[h] = (GATED ? reinterpret_cast<const unsigned char *>(h == 0 ? W0 : W1) + (size_t)tn * 128 * K * 2
+                          : reinterpret_cast<const unsigned char *>(W0) + ((size_t)tn * GT + h * 128) * K * 2) +
+                   (size_t)k_first * (GK * 2);
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + (uint32_t)(wave * 2048));
+    auto issue_a = [&](int h, int k) __attribute__((always_inline)) {
+        const void *src = uniform_ptr(baseA + (size_t)k * (GK * 2));
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            dma_1k_s(lds0 + (uint32_t)((k & 1) * STAGE_BYTES + h * HALF_BYTES + i * 1024), src, voffA[h][i]);
+    };
+    auto issue_w = [&](int h, int k) __attribute__((always_inline)) {
+        const void *src = uniform_ptr(baseW[h] + (size_t)k * (GK * 2));
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            dma_1k_s(lds0 + (uint32_t)((k & 1) * STAGE_BYTES + TILE_BYTES + h * HALF_BYTES + i * 1024), src, voffW[i]);
     };
 
     // Operand reads: row rb + n16 (rb a multiple of 16), chunk 4c + q4 -> rb * 128 + lo[c]
-    uint32_t lo[2];
+    uint32_t ra[2], rw[2];  // of stage 0: + the stage
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-        lo[c] = (uint32_t)((n16 >> 1) * 256 + (((((n16 & 1) << 3) | (4 * c + q4)) ^ ((n16 >> 1) & 7)) << 4));
-    int wrow[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) wrow[g] = GATED ? (g >> 1) * 128 + wn * 32 + (g & 1) * 16 : wn * 64 + g * 16;
+    for (int c = 0; c < 2; ++c) {
+        const uint32_t lo = (uint32_t)((n16 >> 1) * 256 + (((((n16 & 1) << 3) | (4 * c + q4)) ^ ((n16 >> 1) & 7)) << 4));
+        ra[c] = lo + (uint32_t)(wm * 64 * 128);
+        rw[c] = lo + (uint32_t)(TILE_BYTES + wn * 32 * 128);
+    }
 
     f32x4 acc[8][4];
 #pragma unroll
@@ -88,52 +124,85 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[s][g] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // One reduction step: 16 groups of four MFMAs (half c of the step, slab s), each needing one activation operand
-    // and the half's four weight operands.  Operand loads run three groups ahead of their use through a ring of
-    // four registers, the second half's weights arrive under the first half's MFMAs, and the written order is kept.
-    auto compute = [&](int stage) __attribute__((always_inline)) {
-        const unsigned char *ta = smem + stage * STAGE_BYTES + wm * (128 * 128);
-        const unsigned char *tw = smem + stage * STAGE_BYTES + TILE_BYTES;
-        auto load_a = [&](int i) __attribute__((always_inline)) {
-            return *reinterpret_cast<const bf16x8 *>(ta + (i & 7) * 2048 + lo[i >> 3]);
-        };
-        auto load_w = [&](int c, int g) __attribute__((always_inline)) {
-            return *reinterpret_cast<const bf16x8 *>(tw + wrow[g] * 128 + lo[c]);
-        };
-        bf16x8 wf[2][4], ring[4];
+    bf16x8 a[8], w[2][4];  // operands: [c * 4 + slab] of one activation half, [weight half][c * 2 + group]
+    auto read_a = [&](int h, uint32_t st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            a[x] = *reinterpret_cast<const bf16x8 *>(smem + st + ra[x >> 2] + h * HALF_BYTES + (x & 3) * 2048);
+    };
+    auto read_w = [&](uint32_t st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                w[h][x] = *reinterpret_cast<const bf16x8 *>(smem + st + rw[x >> 1] + h * HALF_BYTES + (x & 1) * 2048);
+    };
+    // 32 MFMAs: activation half h times both weight halves
+    auto multiply = [&](int h) __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) wf[0][g] = load_w(0, g);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) ring[i] = load_a(i);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int c = i >> 3, sl = i & 7;
+        for (int x = 0; x < 8; ++x)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                acc[sl][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c][g], ring[i & 3], acc[sl][g], 0, 0, 0);
-            if (i + 3 < 16) ring[(i + 3) & 3] = load_a(i + 3);
-            if (i >= 1 && i <= 4) wf[1][i - 1] = load_w(1, i - 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+                acc[4 * h + (x & 3)][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[g >> 1][2 * (x >> 2) + (g & 1)], a[x],
+                                                                                 acc[4 * h + (x & 3)][g], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto issue_first = [&](int k) __attribute__((always_inline)) {  // all of a step but the second activation half
+        issue_a(0, k);
+        issue_w(0, k);
+        issue_w(1, k);
+    };
+    // the barrier before the slot that reads the second activation half of step k; before the one that reads step k's rest
+    auto open_second = [&](int k) __attribute__((always_inline)) {
+        if (k + 1 < nk) open_slot<8>();
+        else open_slot<0>();
+    };
+    auto open_first = [&](int k) __attribute__((always_inline)) {
+        if (k + 1 < nk) open_slot<8>();
+        else open_slot<2>();
     };
 
-    const int nk = K / GK;
-    issue(0, 0);
-    for (int k = 0; k < nk; k += 2) {
-        tile_barrier();  // step k has landed in stage 0; every wavefront is done reading stage 1
-        if (k + 1 < nk) issue(1, k + 1);
-        compute(0);
-        if (k + 1 < nk) {
-            tile_barrier();
-            if (k + 2 < nk) issue(0, k + 2);
-            compute(1);
+    issue_first(0);
+    issue_a(1, 0);
+    if (nk > 1) issue_first(1);
+    open_first(0);
+    if (wave < 4) {
+        for (int k = 0; k < nk; ++k) {
+            const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
+            read_a(0, st);
+            read_w(st);
+            if (k + 1 < nk) issue_a(1, k + 1);
+            open_slot<63>();
+            multiply(0);
+            open_second(k);
+            read_a(1, st);
+            if (k + 2 < nk) issue_first(k + 2);
+            open_slot<63>();
+            multiply(1);
+            open_first(k + 1);
+        }
+        open_slot<63>();
+    } else {
+        open_slot<63>();
+        for (int k = 0; k < nk; ++k) {
+            const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
+            read_a(0, st);
+            read_w(st);
+            if (k + 1 < nk) issue_a(1, k + 1);
+            open_second(k);
+            multiply(0);
+            open_slot<63>();
+            read_a(1, st);
+            if (k + 2 < nk) issue_first(k + 2);
+            open_first(k + 1);
+            multiply(1);
+            open_slot<63>();
         }
     }
 
     // Results: a lane holds output features 4*q4 .. 4*q4+3 of weight group g for the token of row n16 of slab s.
-    const size_t row0 = (size_t)tm * GT + wm * 128 + n16;
+    const size_t row0 = (size_t)tm * GT + wm * 64 + n16;  // slab s: + 128 (s / 4) + 16 (s % 4)
     if (GATED) {
         uint16_t *H = static_cast<uint16_t *>(out);
 #pragma unroll
@@ -151,7 +220,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
                 uint2 o;
                 o.x = *reinterpret_cast<uint32_t *>(&p0);
                 o.y = *reinterpret_cast<uint32_t *>(&p1);
-                *reinterpret_cast<uint2 *>(H + (row0 + s * 16) * ldo + tn * 128 + wn * 32 + g * 16 + 4 * q4) = o;
+                *reinterpret_cast<uint2 *>(H + (row0 + (s >> 2) * 128 + (s & 3) * 16) * ldo + tn * 128 + wn * 32 + g * 16 + 4 * q4) = o;
             }
     } else {
         float *F = static_cast<float *>(out);
@@ -159,7 +228,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
         for (int s = 0; s < 8; ++s)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f32x4 *>(F + (row0 + s * 16) * ldo + tn * GT + wn * 64 + g * 16 + 4 * q4) = acc[s][g];
+                *reinterpret_cast<f32x4 *>(F + (row0 + (s >> 2) * 128 + (s & 3) * 16) * ldo + tn * GT + (g >> 1) * 128 + wn * 32 +
+                                           (g & 1) * 16 + 4 * q4) = acc[s][g];
     }
 }
 
