@@ -24,6 +24,8 @@
 // step, both wavefronts of a SIMD in phase and loads one step ahead: 7.0 + 3.3 ms.  Tried: both in phase with operands
 // prefetched across two barriers a step (6.7 + 3.2, loads spread between the MFMAs: 6.5 + 3.1), the barrier ahead of a
 // slot's last MFMAs (slower: it holds the other set's reads back).
+#include <algorithm>
+
 #include "attn_tile.h"
 #include "ffn.h"
 
@@ -51,22 +53,28 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
                                                                 const int32_t *__restrict__ gather,
                                                                 const uint16_t *__restrict__ W0,
                                                                 const uint16_t *__restrict__ W1, int K, int n_tiles,
-                                                                int m_tiles, const int32_t *__restrict__ n_rows_ptr,
+                                                                const int32_t *__restrict__ n_rows_ptr,
                                                                 void *__restrict__ out, int ldo)
 {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+    const int m_tiles = (*n_rows_ptr + GT - 1) / GT;  // row tiles that hold activated tokens
+    if (m_tiles == 0) return;
+    const int splits = GATED ? 1 : ffn_down_splits(m_tiles, n_tiles, K);
     // Workgroup -> tile.  Consecutive workgroups go to different XCDs (each with its own L2), so the 32 tiles of a
     // 4 x 8 block -- four row tiles that share their weights with eight weight tiles that share their rows -- are
     // given to one XCD: block k of 32 goes to XCD k % 8.
     const int total = (m_tiles + 3) / 4 * 4 * n_tiles;
     const int idx = blockIdx.x >> 3;
-    const int logical = (((idx >> 5) * 8 + (blockIdx.x & 7)) << 5) + (idx & 31);
-    if (logical >= total) return;
+    const int block = (idx >> 5) * 8 + (blockIdx.x & 7), blocks = (total + 31) >> 5;  // (a split: that many blocks)
+    const int split = block / blocks;
+    const int logical = ((block - split * blocks) << 5) + (idx & 31);
+    if (split >= splits || logical >= total) return;
     const int tm = logical / (4 * n_tiles) * 4 + (logical & 3);
     const int tn = (logical >> 2) % n_tiles;
-    if (tm >= m_tiles || tm * GT >= *n_rows_ptr) return;
-
-    const int k_first = 0, nk = K / GK;
+    if (tm >= m_tiles) return;
+    // this split's reduction steps (at least one: K / GK >= splits)
+    const int k_first = (int)((long long)split * (K / GK) / splits);
+    const int nk = (int)((long long)(split + 1) * (K / GK) / splits) - k_first;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -223,7 +231,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
                 *reinterpret_cast<uint2 *>(H + (row0 + (s >> 2) * 128 + (s & 3) * 16) * ldo + tn * 128 + wn * 32 + g * 16 + 4 * q4) = o;
             }
     } else {
-        float *F = static_cast<float *>(out);
+        float *F = static_cast<float *>(out) + (size_t)split * m_tiles * GT * ldo;
 #pragma unroll
         for (int s = 0; s < 8; ++s)
 #pragma unroll
@@ -235,28 +243,38 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
 
 template <bool GATED>
 hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, const uint16_t *W0, const uint16_t *W1, int K,
-                       int n_tiles, int m_tiles, const int32_t *n_rows, void *out, int ldo, hipStream_t st)
+                       int n_tiles, long long blocks, const int32_t *n_rows, void *out, int ldo, hipStream_t st)
 {
     static LdsOptIn opted;  // one per instantiation
     const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&ffn_gemm_kernel<GATED>), GEMM_LDS);
     if (e != hipSuccess) return e;
-    const long long total = (long long)((m_tiles + 3) / 4 * 4) * n_tiles;
-    const long long blocks32 = ((total + 31) / 32 + 7) / 8 * 8;  // whole rounds over the eight XCDs
-    hipLaunchKernelGGL((ffn_gemm_kernel<GATED>), dim3((unsigned)(blocks32 * 32)), dim3(GEMM_THREADS), GEMM_LDS, st, A,
-                       gather, W0, W1, K, n_tiles, m_tiles, n_rows, out, ldo);
+    const long long grid = (blocks + 7) / 8 * 8 * 32;  // whole rounds over the eight XCDs
+    hipLaunchKernelGGL((ffn_gemm_kernel<GATED>), dim3((unsigned)grid), dim3(GEMM_THREADS), GEMM_LDS, st, A, gather, W0, W1, K,
+                       n_tiles, n_rows, out, ldo);
     return hipGetLastError();
 }
+
+// Blocks of 32 tiles for m_tiles row tiles (a multiple of four of them: a block is four row tiles high).
+static long long tile_blocks(long long m_tiles, int n_tiles) { return ((m_tiles + 3) / 4 * 4 * n_tiles + 31) / 32; }
 
 hipError_t launch_ffn_gemm_gated(const uint16_t *X, const int32_t *active, const uint16_t *Wg, const uint16_t *Wu,
                                  int d_model, int d_ff, int m_tiles, const int32_t *n_rows, uint16_t *H, hipStream_t st)
 {
-    return launch_gemm<true>(X, active, Wg, Wu, d_model, d_ff / 128, m_tiles, n_rows, H, d_ff, st);
+    return launch_gemm<true>(X, active, Wg, Wu, d_model, d_ff / 128, tile_blocks(m_tiles, d_ff / 128), n_rows, H, d_ff, st);
 }
 
 hipError_t launch_ffn_gemm_down(const uint16_t *H, const uint16_t *Wd, int d_ff, int d_model, int m_tiles,
                                 const int32_t *n_rows, float *F, hipStream_t st)
 {
-    return launch_gemm<false>(H, nullptr, Wd, nullptr, d_ff, d_model / GT, m_tiles, n_rows, F, d_model, st);
+    // How many tiles there are, and so how they are split, is known on the device: a grid for the worst case.  (A split
+    // has 32 or more blocks' worth of tiles only if it is the only one, and no more than FFN_SPLIT_TILES + 3 padding rows of
+    // tiles each otherwise.)
+    const int n_tiles = d_model / GT;
+    long long blocks = 0;
+    for (int m = 1; m <= m_tiles && (m - 1) * n_tiles < FFN_SPLIT_TILES; ++m)
+        blocks = std::max(blocks, ffn_down_splits(m, n_tiles, d_ff) * tile_blocks(m, n_tiles));
+    blocks = std::max(blocks, tile_blocks(m_tiles, n_tiles));
+    return launch_gemm<false>(H, nullptr, Wd, nullptr, d_ff, n_tiles, blocks, n_rows, F, d_model, st);
 }
 
 }  // namespace adaspark

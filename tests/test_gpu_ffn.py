@@ -109,6 +109,14 @@ def test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, p):
     check_outputs(f"{name} dense", f64(Y.cpu()), oracle.ffn.ffn_dense(x64, g64, u64, d64), x64)
 
 
+# Reductions that the W_down product splits unevenly (22 and 34 steps), over one and over several row tiles; columns
+# that end inside the residual kernel's blocks of 512; a reduction too short to split much
+@pytest.mark.parametrize("name,d_model,d_ff,p", [("T_ragged", 256, 1408, 0.6), ("T_gqa128", 768, 2176, 0.9), ("T_tiny", 1280, 2176, 0.7),
+                                                 ("T_tiny", 256, 256, 0.7)])
+def test_ffn_split_reduction(B, oracle, name, d_model, d_ff, p):
+    test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, p)
+
+
 def test_ffn_degenerate_masks(B, oracle):
     """No token activated: the input comes back bit for bit.  One activated token per cube: every other token of
     the cube moves by that token's FFN value.  Stale workspace contents must not matter."""
