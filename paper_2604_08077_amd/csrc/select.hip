@@ -17,17 +17,25 @@
 // holds all candidates of its rows), later ones by cube_select_wide_kernel (four or eight wavefronts share the
 // rows and split the candidates).
 #include <algorithm>
+#include <type_traits>
 
 #include "geom.h"
 
 namespace adaspark {
 
 constexpr int SELM_THREADS = 256;
-constexpr int SELM_SLABS = 2;                                      // 16-row slabs per wavefront
-constexpr int SELM_ROWS = (SELM_THREADS / 64) * SELM_SLABS * 16;  // rows per workgroup
+constexpr int SELM_WAVES = SELM_THREADS / 64;
 constexpr int SELM_MAX_CUBES = 256;
 constexpr int SELM_SWITCH_BIT = 21;  // Top-p threshold search: bits down to this one on all candidates, the rest on a short list
 constexpr int SELM_SHORT = 16;       // entries of a lane's short list
+// With no more 16-row slabs than the chip holds wavefronts (four per SIMD) a wavefront takes one: its time is a chain of
+// dependent steps per slab.  2,048 tokens of 4/4 heads of 64 in cubes of 32: 12.5 us, 18.7 with two; 1,080 tokens of 6/2 heads of
+// 128: 9.2, 13.6.  With more, two share the mean-key operands.
+constexpr int SELM_FEW_SLABS = 4096;
+// The registers (and so the wavefronts per SIMD: four, three, two) and the loops that are not cut short go by the most
+// candidates a launch can have, 64, 128 or 256: earlier query cubes get launches of their own if those have two rounds of
+// workgroups or more.  30,000 tokens of 32/8 heads, 150 cubes: 370 us, 445 in one launch; 65,536 of 28/4, 256 cubes: 695, 760.
+constexpr int SELM_SPLIT_BLOCKS = 1024;
 
 typedef __bf16 sel_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sel_f32x4 __attribute__((ext_vector_type(4)));
@@ -162,36 +170,37 @@ __device__ __forceinline__ float selm_quad_max(float x)
 // TOPK: fixed Top-K selection (the ablation baseline of "Effect of Top-P Adaptive Selection") instead of Top-p: the
 // top_k most relevant preceding cubes, ties by lower index.  The values ranked are then the logits themselves
 // (as order-preserving integer keys: no softmax, nothing can underflow) and the "mass" is a count.
-template <int D, int MAXG, bool TOPK>
-__global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
+template <int D, int MAXG, int SLABS, bool TOPK>
+__global__ __launch_bounds__(SELM_THREADS, MAXG == 8 ? 3 : 2) void cube_select_mfma_kernel(
     Geom g, int NG, int i_end, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ ksplit, float top_p,
     int top_k, uint32_t *__restrict__ sel_mask, int32_t *__restrict__ sel_count)
 {
     constexpr int KS = D / 32;
+    constexpr int ROWS = SELM_WAVES * SLABS * 16;  // per workgroup
     // the threshold search's short lists (see below): SELM_SHORT entries and a dump slot per lane
     __shared__ uint32_t shortlist[SELM_THREADS / 64][SELM_SHORT + 1][64];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n16 = lane & 15, q4 = lane >> 4;
     // workgroup -> (query cube, KV head, block of rows); late cubes (most candidates) first
-    const int nblk_max = (g.G * g.Cmax + SELM_ROWS - 1) / SELM_ROWS;
+    const int nblk_max = (g.G * g.Cmax + ROWS - 1) / ROWS;
     const int blk = blockIdx.x % nblk_max;
     const int kv = (blockIdx.x / nblk_max) % g.Hkv;
     const int i = i_end - 1 - blockIdx.x / (nblk_max * g.Hkv);  // this launch covers query cubes [.., i_end)
     const CubeBox qbox = cube_box(g, i);
     const int P = g.G * qbox.size();  // rows of this (cube, KV head): rho = rank * G + head-in-group
-    if (blk * SELM_ROWS >= P) return;
+    if (blk * ROWS + wave * SLABS * 16 >= P) return;  // (no barriers below)
     // Candidates are the video cubes before the own cube: cubes [Np, cend).  A query after the video scores every
     // video cube; the text cubes before a row's own are always attended: those bits are set whatever the rule
     // selects.
     const SelRange cr = sel_range(g, i);
     const int cend = cr.cend, ncand = cr.ncand, nforced = cr.nforced;
 
-    int rowg[SELM_SLABS];  // global row id of this lane's column, -1: past the end
-    int rowq[SELM_SLABS];  // row whose Q is loaded (a valid one also for padding columns)
+    int rowg[SLABS];  // global row id of this lane's column, -1: past the end
+    int rowq[SLABS];  // row whose Q is loaded (a valid one also for padding columns)
 #pragma unroll
-    for (int s = 0; s < SELM_SLABS; ++s) {
-        const int rho = blk * SELM_ROWS + (wave * SELM_SLABS + s) * 16 + n16;
+    for (int s = 0; s < SLABS; ++s) {
+        const int rho = blk * ROWS + (wave * SLABS + s) * 16 + n16;
         const int rc = min(rho, P - 1);
         const int rid = token_of(g, qbox, rc / g.G) * g.Hq + kv * g.G + rc % g.G;
         rowg[s] = rho < P ? rid : -1;
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
         // p >= 1 (or k >= number of candidates): every candidate; p = 0 (k = 0): none
         const int keep = (TOPK ? top_k >= ncand : top_p >= 1.f) ? ncand : 0;
 #pragma unroll
-        for (int s = 0; s < SELM_SLABS; ++s) {
+        for (int s = 0; s < SLABS; ++s) {
             if (rowg[s] < 0) continue;
             for (int w = q4; w < g.words; w += 4)
                 sel_mask[(size_t)rowg[s] * g.words + w] = sel_all_candidates(g, w, cr, keep != 0) | sel_forced_bits(g, w, i);
@@ -211,18 +220,18 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
         return;
     }
 
-    sel_bf16x8 qf[SELM_SLABS][KS];
+    sel_bf16x8 qf[SLABS][KS];
 #pragma unroll
-    for (int s = 0; s < SELM_SLABS; ++s)
+    for (int s = 0; s < SLABS; ++s)
 #pragma unroll
         for (int c = 0; c < KS; ++c)
             qf[s][c] = *reinterpret_cast<const sel_bf16x8 *>(Q + (size_t)rowq[s] * D + 32 * c + 8 * q4);
 
     // ---- logits: acc[s][cg][v] = q(row n16 of slab s) . kbar(cube 16cg + 4q4 + v)
     const int ng = (cend + 15) >> 4;  // cube groups up to the last candidate (the same for every row here)
-    sel_f32x4 acc[SELM_SLABS][MAXG];
+    sel_f32x4 acc[SLABS][MAXG];
 #pragma unroll
-    for (int s = 0; s < SELM_SLABS; ++s)
+    for (int s = 0; s < SLABS; ++s)
 #pragma unroll
         for (int cg = 0; cg < MAXG; ++cg) acc[s][cg] = sel_f32x4{0.f, 0.f, 0.f, 0.f};
     // The mean-key operands go from global memory (they stay in L2: a few MB per call) straight into registers,
@@ -241,7 +250,7 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
 #pragma unroll
             for (int o = 0; o < HALF; ++o)
 #pragma unroll
-                for (int s = 0; s < SELM_SLABS; ++s)
+                for (int s = 0; s < SLABS; ++s)
                     acc[s][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf0[o], qf[s][o / 3], acc[s][cg], 0, 0, 0);
             if (cg + 1 < ng) {
 #pragma unroll
@@ -250,7 +259,7 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
 #pragma unroll
             for (int o = 0; o < HALF; ++o)
 #pragma unroll
-                for (int s = 0; s < SELM_SLABS; ++s)
+                for (int s = 0; s < SLABS; ++s)
                     acc[s][cg] =
                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf1[o], qf[s][KSH + o / 3], acc[s][cg], 0, 0, 0);
         }
@@ -259,7 +268,7 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
     const float scale = 1.44269504088896340736f / sqrtf((float)D);
     const int ng4 = (ng + 3) >> 2;  // groups are processed four at a time below
 #pragma unroll
-    for (int s = 0; s < SELM_SLABS; ++s) {
+    for (int s = 0; s < SLABS; ++s) {
         // ---- softmax numerators e = exp2(logit*log2(e)/sqrt(D) - max), 0 for non-candidates; kept in acc
         // (a cube group whose 16 cubes are all candidates -- most are -- needs no test per value: the group-level
         // conditions are the same in every lane and become scalar branches)
@@ -303,14 +312,18 @@ __global__ __launch_bounds__(SELM_THREADS, 2) void cube_select_mfma_kernel(
         } else {
             float part = 0.f;
 #pragma unroll
-            for (int cg = 0; cg < MAXG; ++cg)
+            for (int k4 = 0; k4 < (MAXG + 3) / 4; ++k4) {
+                const bool any = k4 < ng4;  // (past the last candidate: no exponentials)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    // (non-candidates hold -inf and the maximum is finite -- there is a candidate: exp2 gives 0)
-                    const float e = __builtin_amdgcn_exp2f(acc[s][cg][v] - mx);
-                    acc[s][cg][v] = e;
-                    part += e;
-                }
+                for (int cg = 4 * k4; cg < 4 * k4 + 4 && cg < MAXG; ++cg)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        // (non-candidates hold -inf and the maximum is finite -- there is a candidate: exp2 gives 0)
+                        const float e = any ? __builtin_amdgcn_exp2f(acc[s][cg][v] - mx) : 0.f;
+                        acc[s][cg][v] = e;
+                        part += e;
+                    }
+            }
             target = top_p * selm_quad_sum(part);
         }
 
@@ -1241,6 +1254,35 @@ size_t select_workspace_bytes(const Geom &g)
     return select_status_offset(g) + 256;  // and the status word (in a block of its own)
 }
 
+// Query cubes [0, end) with cube_select_mfma_kernel.  by_range: cubes [0, 64), [64, 128) and the rest in launches of
+// their own, each with registers for as many candidates as its cubes have.
+template <int D, int SLABS, bool TOPK>
+static void launch_select_narrow(const Geom &g, int NG, int end, bool by_range, const uint16_t *Q, const uint16_t *ksplit,
+                                 float top_p, int top_k, uint32_t *sel_mask, int32_t *sel_count, hipStream_t st)
+{
+    const int rows = SELM_WAVES * SLABS * 16, nblk = (g.G * g.Cmax + rows - 1) / rows;
+    auto launch = [&](auto maxg, int lo, int hi) {
+        constexpr int MAXG = decltype(maxg)::value;
+        hipLaunchKernelGGL((cube_select_mfma_kernel<D, MAXG, SLABS, TOPK>), dim3((unsigned)((size_t)(hi - lo) * g.Hkv * nblk)),
+                           dim3(SELM_THREADS), 0, st, g, NG, hi, Q, ksplit, top_p, top_k, sel_mask, sel_count);
+    };
+    // (non-causal: every query cube has all candidates)
+    auto split_at = [&](int lo) {
+        return by_range && g.causal && (long long)lo * g.Hkv * nblk >= SELM_SPLIT_BLOCKS ? lo : 0;
+    };
+    if (end > 128) {
+        const int lo = split_at(128);
+        launch(std::integral_constant<int, 16>{}, lo, end);
+        end = lo;
+    }
+    if (end > 64) {
+        const int lo = split_at(64);
+        launch(std::integral_constant<int, 8>{}, lo, end);
+        end = lo;
+    }
+    if (end > 0) launch(std::integral_constant<int, 4>{}, 0, end);
+}
+
 template <int D, bool TOPK>
 static void launch_select_d(const Geom &g, int NG, const uint16_t *Q, const uint16_t *ksplit, float top_p, int top_k,
                             uint32_t *sel_mask, int32_t *sel_count, hipStream_t st)
@@ -1249,14 +1291,10 @@ static void launch_select_d(const Geom &g, int NG, const uint16_t *Q, const uint
     // (in non-causal mode every query cube has all video cubes as candidates)
     const int i_narrow = g.N <= SELM_MAX_CUBES ? g.N : (g.causal ? SELM_MAX_CUBES : 0);
     if (i_narrow > 0) {
-        const int nblk_max = (g.G * g.Cmax + SELM_ROWS - 1) / SELM_ROWS;
-        const dim3 grid((unsigned)((size_t)i_narrow * g.Hkv * nblk_max)), block(SELM_THREADS);
-        if (i_narrow <= 64)
-            hipLaunchKernelGGL((cube_select_mfma_kernel<D, 4, TOPK>), grid, block, 0, st, g, NG, i_narrow, Q, ksplit,
-                               top_p, top_k, sel_mask, sel_count);
+        if ((long long)i_narrow * g.Hkv * ((g.G * g.Cmax + 15) / 16) <= SELM_FEW_SLABS)
+            launch_select_narrow<D, 1, TOPK>(g, NG, i_narrow, false, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
         else
-            hipLaunchKernelGGL((cube_select_mfma_kernel<D, 16, TOPK>), grid, block, 0, st, g, NG, i_narrow, Q, ksplit,
-                               top_p, top_k, sel_mask, sel_count);
+            launch_select_narrow<D, 2, TOPK>(g, NG, i_narrow, true, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
     }
     if (g.N > i_narrow) {  // the later query cubes: a row's candidates are spread over 4 or 8 wavefronts
         const int nblk_max = (g.G * g.Cmax + SELW_ROWS - 1) / SELW_ROWS;

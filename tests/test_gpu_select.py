@@ -1,0 +1,36 @@
+"""Cube selection where the kernel for up to 256 candidates changes its launch: one or two 16-row slabs per wavefront (few or
+many rows), and in the second case launches of their own for the query cubes below 64, below 128 and the rest.  Sets against the
+fp64 oracle, as in the parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_08077_amd import synth
+from test_gpu_parity import B, check_selection, oshape, to_u32  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # cubes, tokens of a cube, query heads, KV heads, head_dim
+    ("few_64", 64, 5, 3, 1, 64),
+    ("few_65", 65, 16, 1, 1, 128),
+    ("few_129", 129, 17, 2, 2, 64),
+    ("few_256", 256, 4, 4, 1, 128),
+    ("many_64", 64, 64, 32, 8, 64),
+    ("many_65", 65, 64, 32, 8, 64),
+    ("many_128", 128, 64, 32, 8, 64),
+    ("many_129", 129, 64, 32, 8, 64),
+    ("many_205", 205, 33, 32, 16, 128),
+]
+
+
+@pytest.mark.parametrize("name,cubes,tokens,hq,hkv,d", SHAPES, ids=[s[0] for s in SHAPES])
+def test_selection_launches(B, oracle, name, cubes, tokens, hq, hkv, d):  # noqa: F811
+    w = synth.Workload(name, 43, cubes, 1, tokens, 1, 1, tokens, hq, hkv, d, (0.8,), (1.0,) * hkv)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, _ = synth.generate(w)
+    kbar = oracle.cube_pool(osh, K).astype(np.float32)
+    print(f"[{name}] {w.S * hq} rows", flush=True)
+    mask, count, _, _ = B.cube_select(sh, Q.cuda(), torch.from_numpy(kbar).cuda(), 0.8)
+    torch.cuda.synchronize()
+    ref_mask, ref_count, near = oracle.cube_select(osh, Q, kbar, 0.8)
+    check_selection(name, to_u32(mask), count.cpu().numpy(), ref_mask, ref_count, near)
