@@ -30,6 +30,7 @@ namespace adaspark {
 
 constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
+constexpr int DQ_SHARED_BLOCKS = 384;  // dq_keys
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
 // How attn_bwd_dkv_kernel's work is cut.  A workgroup takes 256 keys (one of nkb key blocks) of one (key cube j, KV
@@ -51,7 +52,11 @@ static BwdParts bwd_parts(const Geom &g)
     // per CU to keep the chip even at the end, and more than about 8,000 of them only take up memory.
     const long long lists = (long long)g.Hkv * p.nkb * g.N;
     const long long want = (8192 + g.G * g.Cmax - 1) / (g.G * g.Cmax);
-    const long long lo = lists * g.N / (2 * 8192), hi = std::max(1LL, lists * g.N / (2 * 1024));
+    const long long lo = lists * g.N / (2 * 8192);
+    long long hi = std::max(1LL, lists * g.N / (2 * 1024));
+    // (up to two parts per CU: one round of workgroups with twice the rows instead, which leaves half the sums.  TBD)
+    const long long most = lists * (g.N + 1) / 2;
+    if (most <= 512) hi = (most + 255) / 256;
     p.span = (int)std::min((long long)g.N, std::max(1LL, std::max(lo, std::min(hi, want))));
     p.nc = (g.N + p.span - 1) / p.span;
     p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
@@ -218,27 +223,29 @@ __device__ __forceinline__ void nat_half_bias(const unsigned char *kt, int n16, 
         }
 }
 
-// acc^T[d, n] += T[d, 0..63] . B[0..63, n] for slabs 0..NS-1: T a transposed tile in LDS (rows = head-dim), B in
-// registers in the operand order qk_tile's outputs pack into (bf[s][half] = entities 32*half + 8*q4 + 0..7).
-template <int D, int NS>
-__device__ __forceinline__ void tn_tile(const unsigned char *tt, int n16, int q4, const bf16x8 (&bf)[NS][2],
+// acc^T[d, n] += T[d, k] . B[k, n] over the entities k = 32 H .. 32 H + 31 of a tile, slabs 0..NS-1: T a transposed tile in
+// LDS (rows = head-dim), B in registers in the operand order qk_tile's outputs pack into (bf[s][H] = entities
+// 32 H + 8 q4 + 0..7).
+template <int D, int NS, int H>
+__device__ __forceinline__ void tn_half(const unsigned char *tt, int n16, int q4, const bf16x8 (&bf)[NS][2],
                                         f32x4 (&acc)[NS][D / 16])
 {
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl)
+    for (int e = 0; e < D / 16; ++e) {
+        const bf16x8 af = *reinterpret_cast<const bf16x8 *>(tt + vt_tile_off(16 * e + n16, 4 * H + q4));
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e) {
-            const bf16x8 af = *reinterpret_cast<const bf16x8 *>(tt + vt_tile_off(16 * e + n16, 4 * sl + q4));
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                acc[s][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[s][sl], acc[s][e], 0, 0, 0);
-        }
+        for (int s = 0; s < NS; ++s)
+            acc[s][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[s][H], acc[s][e], 0, 0, 0);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// dQ: workgroup = 256 rows (packed row order) of one (cube i, KV head); late cubes (the long walks) first.
+// dQ: workgroup = 256 / KEYS rows (packed row order) of one (cube i, KV head); late cubes (the long walks) first.
+// KEYS = 1: a wavefront per 32 rows.  KEYS = 2: two, wavefronts w and w + 4, each with half of every tile's keys; their
+// sums are added through LDS at the end.  A tile takes a workgroup 1.5 us at head-dim 128 (its MFMAs and exponentials), and
+// with few workgroups the longest walk is the kernel's time: half as long, over twice as many workgroups (dq_keys).
 // ---------------------------------------------------------------------------------------------------------------
-template <int D, bool MASKED>
+template <int D, bool MASKED, int KEYS>
 __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const uint16_t *__restrict__ Q,
                                                                   const uint16_t *__restrict__ dO,
                                                                   const uint16_t *__restrict__ Kn,
@@ -250,24 +257,26 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
                                                                   const uint32_t *__restrict__ sel_mask,
                                                                   uint16_t *__restrict__ dQ)
 {
-    constexpr int NS = 2, KSTEPS = D / 32;
+    constexpr int NS = 2, KSTEPS = D / 32, DT = D / 16;
+    constexpr int ROWS = BWD_ROWS / KEYS;
     constexpr int TILE = 64 * D * 2;       // bytes of one tile
     constexpr int STAGE = 3 * TILE;        // K natural, V natural, K transposed
     constexpr int PIECES = TILE / 1024;    // 1 KB pieces per tile
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
 
-    const int nblk = (g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS;
+    const int nblk = (g.Cmax * g.G + ROWS - 1) / ROWS;
     int kv, slot;
     if (!bwd_head_slot(blockIdx.x, g.Hkv, g.N * nblk, kv, slot)) return;
     const int blk = slot % nblk;
     const int i = g.N - 1 - slot / nblk;
     const CubeBox box = cube_box(g, i);
     const int mrows = box.size() * g.G;
-    if (blk * BWD_ROWS >= mrows) return;
+    if (blk * ROWS >= mrows) return;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n16 = lane & 15, q4 = lane >> 4;
+    const int rgroup = wave & (8 / KEYS - 1), khalf = wave / (8 / KEYS);  // 32 rows of the workgroup; half of a tile's keys
 
     // the wavefront's rows
     int rr[NS], rank[NS];
@@ -278,7 +287,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         psum[s] = 0.f;
-        const int r = blk * BWD_ROWS + wave * 32 + s * 16 + n16;
+        const int r = blk * ROWS + rgroup * 32 + s * 16 + n16;
         valid[s] = r < mrows;
         rr[s] = valid[s] ? r : mrows - 1;
         rank[s] = rr[s] / g.G;
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e) acc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < DT; ++e) acc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     int ij = 0, it = 0, int_ = tiles_of(0);  // next tile to issue
     issue(0, 0, 0);
@@ -377,10 +386,41 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
                             ds[s][H][4 * k2 + v] = (__bf16)(p * pacc[s][k2][v]);
                         }
             };
-            half(std::integral_constant<int, 0>{});
-            half(std::integral_constant<int, 1>{});
-            tn_tile<D, NS>(ktt, n16, q4, ds, acc);
+            if (KEYS == 1) {
+                half(std::integral_constant<int, 0>{});
+                half(std::integral_constant<int, 1>{});
+                tn_half<D, NS, 0>(ktt, n16, q4, ds, acc);
+                tn_half<D, NS, 1>(ktt, n16, q4, ds, acc);
+            } else if (khalf == 0) {
+                half(std::integral_constant<int, 0>{});
+                tn_half<D, NS, 0>(ktt, n16, q4, ds, acc);
+            } else {
+                half(std::integral_constant<int, 1>{});
+                tn_half<D, NS, 1>(ktt, n16, q4, ds, acc);
+            }
             stage ^= 1;
+        }
+    }
+    if (KEYS == 2) {  // (no load is in flight: the last tile's were waited for)
+        static_assert(KEYS == 1 || 4 * 64 * (NS * DT * 16 + NS * 4) <= 2 * STAGE, "the second half's sums fit the tiles' place");
+        f32x4 *sums = reinterpret_cast<f32x4 *>(smem);              // [4][NS * DT][64]
+        float *psums = reinterpret_cast<float *>(sums + 4 * NS * DT * 64);  // [4][NS][64]
+        __syncthreads();
+        if (khalf == 1) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+#pragma unroll
+                for (int e = 0; e < DT; ++e) sums[((size_t)rgroup * (NS * DT) + s * DT + e) * 64 + lane] = acc[s][e];
+                psums[(rgroup * NS + s) * 64 + lane] = psum[s];
+            }
+        }
+        __syncthreads();
+        if (khalf == 1) return;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma unroll
+            for (int e = 0; e < DT; ++e) acc[s][e] += sums[((size_t)rgroup * (NS * DT) + s * DT + e) * 64 + lane];
+            psum[s] += psums[(rgroup * NS + s) * 64 + lane];
         }
     }
     // The probabilities above were built from the caller's log-sum-exp, which the forward kernels give to about
@@ -393,7 +433,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
         if (q4 == 0) lse2p[rowid[s]] = lse2[s] - log2f(total) / c2;
         const float scale = 1.0f / (sqrtf((float)D) * total);
 #pragma unroll
-        for (int e = 0; e < D / 16; ++e)
+        for (int e = 0; e < DT; ++e)
             *reinterpret_cast<uint2 *>(dQ + rowid[s] * D + 16 * e + 4 * q4) = pack_bf16(acc[s][e] * scale);
     }
 }
@@ -750,6 +790,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
     if (key >= box.size()) return;
     const float *src = part + ((size_t)blockIdx.z * cut.parts + j) * (2 * BWD_ROWS * D) + (size_t)x * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f}, k = v;
+#pragma unroll 4
     for (int c = c0; c < cut.nc; ++c) {
         const float *p = src + ((size_t)cut.span * c * (c + 1) / 2) * (2 * BWD_ROWS * D);
         v += *reinterpret_cast<const f32x4 *>(p);
@@ -758,6 +799,15 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
     const size_t o = ((size_t)token_of(g, box, key) * g.Hkv + kv) * D + 16 * e + 4 * (lane >> 4);
     *reinterpret_cast<uint2 *>(dV + o) = pack_bf16(v);
     *reinterpret_cast<uint2 *>(dK + o) = pack_bf16(k * (1.0f / sqrtf((float)D)));
+}
+
+// Whether two wavefronts share 32 rows in the dQ kernel.  With W workgroups of 256 rows the kernel takes the longest walk or
+// W / 256 average ones (half as long), whichever is more; shared, a little over half the longest or W / 256 such halves.
+// TBD
+static int dq_keys(const Geom &g)
+{
+    const long long blocks = (long long)g.N * g.Hkv * ((g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS);
+    return blocks <= DQ_SHARED_BLOCKS ? 2 : 1;
 }
 
 template <int D>
@@ -784,25 +834,29 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     const int32_t *csize = reinterpret_cast<const int32_t *>(Kt + half_elems);
     constexpr int TILE = 64 * D * 2;
 
-    const int nblk = (g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS;
-    const dim3 grid_q(bwd_grid(g.Hkv, g.N * nblk));
+    const int keys = dq_keys(g), rows_q = BWD_ROWS / keys;
+    const dim3 grid_q(bwd_grid(g.Hkv, g.N * ((g.Cmax * g.G + rows_q - 1) / rows_q)));
     const int lds_q = 2 * 3 * TILE;
     const BwdParts &cut = w.cut;
     const dim3 grid_k(bwd_grid(g.Hkv, (int)(cut.nkb * cut.parts)));
     constexpr int lds_k = Dkv<D>::BYTES;
-#define ADASPARK_BWD_LAUNCH(MASKED)                                                                                    \
-    do {                                                                                                               \
-        static LdsOptIn opted_q;                                                                                       \
-        e = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED>), lds_q);                     \
-        if (e != hipSuccess) return e;                                                                                 \
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, Kn, Vn,    \
-                           Kt, csize, w.lse2, w.delta, sel_mask, dQ);                                                  \
-    } while (0)
+    auto launch_dq = [&](auto masked, auto keys_c) -> hipError_t {
+        constexpr bool MASKED = decltype(masked)::value;
+        constexpr int KEYS = decltype(keys_c)::value;
+        static LdsOptIn opted_q;  // one per kernel instantiation
+        const hipError_t err = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED, KEYS>), lds_q);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED, KEYS>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, Kn, Vn,
+                           Kt, csize, w.lse2, w.delta, sel_mask, dQ);
+        return hipGetLastError();
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
     if (sel_mask != nullptr)
-        ADASPARK_BWD_LAUNCH(true);
+        e = keys == 2 ? launch_dq(std::true_type{}, two) : launch_dq(std::true_type{}, one);
     else
-        ADASPARK_BWD_LAUNCH(false);
-#undef ADASPARK_BWD_LAUNCH
+        e = keys == 2 ? launch_dq(std::false_type{}, two) : launch_dq(std::false_type{}, one);
+    if (e != hipSuccess) return e;
     static LdsOptIn opted_k;
     e = opted_k.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D>), lds_k);
     if (e != hipSuccess) return e;

@@ -108,6 +108,26 @@ def test_backward_gathered_rows(B, oracle, monkeypatch, name, grid, cube, hq, hk
     run_case(B, oracle, name, 1.0, dense=True)
 
 
+# The dQ kernel with two wavefronts per 32 rows, up to 384 workgroups' worth of 256 rows, and with one: both sides of the line;
+# cubes whose keys leave the second half of a tile empty, or with one key; row blocks of 128 and a remainder.
+DQ = [
+    ("blocks384", (48, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
+    ("blocks392", (49, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
+    ("keys31_rows124", (4, 1, 31), (1, 1, 31), 4, 1, 128, 0.7, 0),
+    ("keys33_rows132", (4, 3, 11), (1, 3, 11), 4, 1, 128, 0.7, 5),
+    ("keys97_rows291", (3, 1, 97), (1, 1, 97), 3, 1, 64, 0.7, 0),
+    ("keys33_blocks390", (130, 3, 11), (1, 3, 11), 3, 3, 128, 0.6, 0),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,p,text", DQ, ids=[c[0] for c in DQ])
+def test_backward_shared_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, p, text):
+    w = synth.Workload(name, 42, *grid, *cube, hq, hkv, d, (p,), (1.0,) * hkv, text)
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
+    run_case(B, oracle, name, p)
+    run_case(B, oracle, name, 1.0, dense=True)
+
+
 @pytest.mark.parametrize("name,p", [("T_tiny", 0.8), ("T_ragged", 0.9), ("T_lead64", 0.8), ("M_bwd256", 0.8)])
 def test_backward_matches_the_exact_gradient(B, oracle, name, p):
     """Against the oracle's own gradient: delta = dO.o from the exact fp64 forward, not from the bf16 O the GPU
