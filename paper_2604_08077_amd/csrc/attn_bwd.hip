@@ -30,7 +30,7 @@ namespace adaspark {
 
 constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
-constexpr int DQ_SHARED_BLOCKS = 384;  // dq_keys
+constexpr int DQ_SHARED_BLOCKS = 304;  // dq_keys
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
 // How attn_bwd_dkv_kernel's work is cut.  A workgroup takes 256 keys (one of nkb key blocks) of one (key cube j, KV
@@ -54,9 +54,12 @@ static BwdParts bwd_parts(const Geom &g)
     const long long want = (8192 + g.G * g.Cmax - 1) / (g.G * g.Cmax);
     const long long lo = lists * g.N / (2 * 8192);
     long long hi = std::max(1LL, lists * g.N / (2 * 1024));
-    // (up to two parts per CU: one round of workgroups with twice the rows instead, which leaves half the sums.  TBD)
+    // Up to two parts per CU, and row cubes of few rows: one round of workgroups with twice the rows instead, which leaves
+    // half the sums (a backward pass, us: 384 rows a cube, 1,080 tokens of 6/2 heads of 128: 93 against 96; 768 rows, 4,096
+    // tokens: 207, 211).  With more rows the longest part is what counts (1,024 rows, 8/2 heads of 64: 161, 158; 1,792
+    // rows, 14/2 heads of 128: 314, 300; 28/4 heads, 2,560 tokens: 315, 274).
     const long long most = lists * (g.N + 1) / 2;
-    if (most <= 512) hi = (most + 255) / 256;
+    if (most <= 512 && g.G * g.Cmax <= 768) hi = (most + 255) / 256;
     p.span = (int)std::min((long long)g.N, std::max(1LL, std::max(lo, std::min(hi, want))));
     p.nc = (g.N + p.span - 1) / p.span;
     p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
@@ -801,9 +804,11 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
     *reinterpret_cast<uint2 *>(dK + o) = pack_bf16(k * (1.0f / sqrtf((float)D)));
 }
 
-// Whether two wavefronts share 32 rows in the dQ kernel.  With W workgroups of 256 rows the kernel takes the longest walk or
-// W / 256 average ones (half as long), whichever is more; shared, a little over half the longest or W / 256 such halves.
-// TBD
+// Whether two wavefronts share 32 rows in the dQ kernel.  While the workgroups of 256 rows find a CU each the kernel takes what
+// the longest walk takes; shared, a little over half of that.  With more, every CU is busy most of the time and sharing only adds
+// its own cost.  A backward pass, us, shared and not: 72 workgroups of 256 rows 93, 108; 192 (6/2 heads of 128) 445, 528;
+// 256 (28/4 heads of 128) 197, 212; 256 (4/4 heads of 64) 532, 626; 288 (6/2, 128) 779, 819; 320 (8/2, 64) 479, 476;
+// 336 (6/2, 128) 1,015, 1,002; 336 (28/4, 128) 315, 304; 384 (8/2, 64) 619, 571; 448 (28/4, 128) 487, 439.
 static int dq_keys(const Geom &g)
 {
     const long long blocks = (long long)g.N * g.Hkv * ((g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS);

@@ -108,11 +108,11 @@ def test_backward_gathered_rows(B, oracle, monkeypatch, name, grid, cube, hq, hk
     run_case(B, oracle, name, 1.0, dense=True)
 
 
-# The dQ kernel with two wavefronts per 32 rows, up to 384 workgroups' worth of 256 rows, and with one: both sides of the line;
+# The dQ kernel with two wavefronts per 32 rows, up to 304 workgroups' worth of 256 rows, and with one: both sides of the line;
 # cubes whose keys leave the second half of a tile empty, or with one key; row blocks of 128 and a remainder.
 DQ = [
-    ("blocks384", (48, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
-    ("blocks392", (49, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
+    ("blocks304", (38, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
+    ("blocks312", (39, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
     ("keys31_rows124", (4, 1, 31), (1, 1, 31), 4, 1, 128, 0.7, 0),
     ("keys33_rows132", (4, 3, 11), (1, 3, 11), 4, 1, 128, 0.7, 5),
     ("keys97_rows291", (3, 1, 97), (1, 1, 97), 3, 1, 64, 0.7, 0),
