@@ -52,6 +52,12 @@ int check_ptrs(std::initializer_list<const void *> ps)
     return ADASPARK_OK;
 }
 
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + nb && y < x + na;
+}
+
 }  // namespace
 
 // Scratch memory of adaspark_cube_select_noalloc: the selection kernels' workspace (the three-term bf16 split of the
@@ -383,10 +389,14 @@ int adaspark_sparse_attn_bwd(const adaspark_shape *shape, const void *Q, const v
     if ((long long)g.S * g.Hq * g.words >= (1ll << 30)) return ADASPARK_EUNSUPPORTED;
     if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < attn_bwd_workspace_bytes(g))
         return ADASPARK_EWORKSPACE;
+    const size_t nq = (size_t)g.S * g.Hq * g.D * 2, nk = (size_t)g.S * g.Hkv * g.D * 2;
+    bool in_place = false;  // a gradient over Q or dO
+    for (const void *in : {Q, dO})
+        in_place = in_place || overlap(dQ, nq, in, nq) || overlap(dK, nk, in, nq) || overlap(dV, nk, in, nq);
     const hipError_t e = launch_attn_bwd(g, static_cast<const uint16_t *>(Q), static_cast<const uint16_t *>(K),
                                          static_cast<const uint16_t *>(V), static_cast<const uint16_t *>(O), lse,
                                          static_cast<const uint16_t *>(dO), sel_mask, static_cast<uint16_t *>(dQ),
-                                         static_cast<uint16_t *>(dK), static_cast<uint16_t *>(dV), workspace,
+                                         static_cast<uint16_t *>(dK), static_cast<uint16_t *>(dV), in_place, workspace,
                                          static_cast<hipStream_t>(stream));
     return e == hipSuccess ? ADASPARK_OK : ADASPARK_EHIP;
 }
@@ -422,11 +432,9 @@ int adaspark_ffn_sparse(const adaspark_shape *shape, const adaspark_ffn_dims *di
     if ((rc = check_ptrs({X, W_gate, W_up, W_down, Y})) != ADASPARK_OK) return rc;
     if (keep != nullptr && !aligned16(keep)) return ADASPARK_EINVAL;
     const Geom g = make_geom(*shape);
-    {   // Y must not overlap X at all: the mean compensation reads X rows of other tokens while Y is written
-        const uintptr_t x0 = reinterpret_cast<uintptr_t>(X), y0 = reinterpret_cast<uintptr_t>(Y);
-        const uintptr_t n = (uintptr_t)g.S * (uintptr_t)dims->d_model * 2u;
-        if (x0 < y0 + n && y0 < x0 + n) return ADASPARK_EINVAL;
-    }
+    // Y must not overlap X at all: the mean compensation reads X rows of other tokens while Y is written
+    const size_t n = (size_t)g.S * (size_t)dims->d_model * 2u;
+    if (overlap(X, n, Y, n)) return ADASPARK_EINVAL;
     if (workspace == nullptr || !aligned16(workspace) ||
         workspace_bytes < ffn_workspace(g, dims->d_model, dims->d_ff, nullptr).bytes)
         return ADASPARK_EWORKSPACE;

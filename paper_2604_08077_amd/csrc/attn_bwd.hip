@@ -43,14 +43,21 @@ struct BwdParts {
     int nkb;          // 256-key blocks per cube
     long long parts;  // per (KV head, key block)
 };
-static BwdParts bwd_parts(const Geom &g)
+static BwdParts bwd_cut(const Geom &g, long long span)
 {
     BwdParts p;
     p.nkb = (g.Cmax + BWD_ROWS - 1) / BWD_ROWS;
+    p.span = (int)span;
+    p.nc = (g.N + p.span - 1) / p.span;
+    p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
+    return p;
+}
+static BwdParts bwd_parts(const Geom &g)
+{
     // A part costs its two sums' trip through memory (256 keys x D x 8 bytes written and read: about what 450 gathered
     // rows of head-dim 128 cost to compute), so it should see some thousands of rows; but there should be a few parts
     // per CU to keep the chip even at the end, and more than about 8,000 of them only take up memory.
-    const long long lists = (long long)g.Hkv * p.nkb * g.N;
+    const long long lists = (long long)g.Hkv * ((g.Cmax + BWD_ROWS - 1) / BWD_ROWS) * g.N;
     const long long want = (8192 + g.G * g.Cmax - 1) / (g.G * g.Cmax);
     const long long lo = lists * g.N / (2 * 8192);
     long long hi = std::max(1LL, lists * g.N / (2 * 1024));
@@ -60,10 +67,12 @@ static BwdParts bwd_parts(const Geom &g)
     // rows, 14/2 heads of 128: 314, 300; 28/4 heads, 2,560 tokens: 315, 274).
     const long long most = lists * (g.N + 1) / 2;
     if (most <= 512 && g.G * g.Cmax <= 768) hi = (most + 255) / 256;
-    p.span = (int)std::min((long long)g.N, std::max(1LL, std::max(lo, std::min(hi, want))));
-    p.nc = (g.N + p.span - 1) / p.span;
-    p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
-    return p;
+    return bwd_cut(g, std::min((long long)g.N, std::max(1LL, std::max(lo, std::min(hi, want)))));
+}
+// (keys that have a single part are written where they belong, so with a single range there are no sums to hold)
+static size_t bwd_part_bytes(const Geom &g, const BwdParts &p)
+{
+    return p.nc > 1 ? (size_t)g.Hkv * p.nkb * p.parts * 2 * BWD_ROWS * g.D * 4 : 0;
 }
 
 struct BwdWorkspace {
@@ -75,12 +84,16 @@ struct BwdWorkspace {
     unsigned long long *colmask;  // [Hkv][N (key cube j)][N (row cube i)][tpcr]: bit k = row 64 t + k of cube i selects j (j < i)
     uint32_t *rowtab;        // [N][tpcr * 64]: row ids of the row tiles, KV head 0
     float *part;             // [Hkv][nkb][parts][2 (dV, dK)][256 keys x D], in MFMA output order
+    uint16_t *Q, *dO;        // copies of the caller's, if a gradient is written over one of them
     BwdParts cut;
     int tpcr;                // 64-row words per cube = ceil(Cmax * G / 64)
     size_t bytes;
 };
 
-BwdWorkspace bwd_workspace(const Geom &g, void *ws)
+// in_place: dQ, dK or dV lies over Q or dO, which the dK/dV kernel gathers from while gradients are being written, so the
+// kernels read copies.  These take part of the sums' place (they fit there but for short sequences: the place is made
+// at least as large as they are), and the sums are those of wider ranges.
+BwdWorkspace bwd_workspace(const Geom &g, void *ws, bool in_place)
 {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     BwdWorkspace w;
@@ -95,13 +108,17 @@ BwdWorkspace bwd_workspace(const Geom &g, void *ws)
     w.delta = reinterpret_cast<float *>(p + off); off = up(off + rows * 4);
     w.colmask = reinterpret_cast<unsigned long long *>(p + off); off = up(off + (size_t)g.Hkv * g.N * g.N * w.tpcr * 8);
     w.rowtab = reinterpret_cast<uint32_t *>(p + off); off = up(off + (size_t)g.N * w.tpcr * 64 * 4);
-    w.part = reinterpret_cast<float *>(p + off);
-    if (w.cut.nc > 1) off = up(off + (size_t)g.Hkv * w.cut.nkb * w.cut.parts * 2 * BWD_ROWS * g.D * 4);
-    w.bytes = off;
+    const size_t copy = up((size_t)g.S * g.Hq * g.D * 2), place = up(std::max(bwd_part_bytes(g, w.cut), 2 * copy));
+    w.Q = reinterpret_cast<uint16_t *>(p + off);
+    w.dO = reinterpret_cast<uint16_t *>(p + off + copy);
+    w.part = reinterpret_cast<float *>(p + off + (in_place ? 2 * copy : 0));
+    if (in_place)
+        while (2 * copy + bwd_part_bytes(g, w.cut) > place) w.cut = bwd_cut(g, w.cut.span + 1);  // (a single range has no sums)
+    w.bytes = off + place;
     return w;
 }
 
-size_t attn_bwd_workspace_bytes(const Geom &g) { return bwd_workspace(g, nullptr).bytes; }
+size_t attn_bwd_workspace_bytes(const Geom &g) { return bwd_workspace(g, nullptr, false).bytes; }
 
 // Workgroup -> (KV head, slot among the head's workgroups).  Consecutive workgroups go to different XCDs, each with
 // its own L2; the workgroups of one KV head stream the same tiles, so where the head count allows a head's
@@ -146,6 +163,16 @@ __device__ __forceinline__ uint2 pack_bf16(f32x4 x)
 {
     const bf16x2 a = {(__bf16)x[0], (__bf16)x[1]}, b = {(__bf16)x[2], (__bf16)x[3]};
     return make_uint2(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b));
+}
+
+__global__ __launch_bounds__(256) void bwd_copy_rows_kernel(long long pieces, const uint4 *__restrict__ Q,
+                                                            const uint4 *__restrict__ dO, uint4 *__restrict__ Qc,
+                                                            uint4 *__restrict__ dOc)
+{
+    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (x >= pieces) return;
+    Qc[x] = Q[x];
+    dOc[x] = dO[x];
 }
 
 // What a row's products start from: lse2 = -lse * sqrt(D), delta = -dO.O; entry [rows]: what padding rows start from.
@@ -818,9 +845,19 @@ static int dq_keys(const Geom &g)
 template <int D>
 static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t *K, const uint16_t *V,
                                const uint16_t *O, const float *lse, const uint16_t *dO, const uint32_t *sel_mask,
-                               uint16_t *dQ, uint16_t *dK, uint16_t *dV, void *ws, hipStream_t st)
+                               uint16_t *dQ, uint16_t *dK, uint16_t *dV, bool in_place, void *ws, hipStream_t st)
 {
-    const BwdWorkspace w = bwd_workspace(g, ws);
+    const BwdWorkspace w = bwd_workspace(g, ws, in_place);
+    if (in_place) {
+        const long long pieces = (long long)g.S * g.Hq * (D / 8);
+        hipLaunchKernelGGL(bwd_copy_rows_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, pieces,
+                           reinterpret_cast<const uint4 *>(Q), reinterpret_cast<const uint4 *>(dO),
+                           reinterpret_cast<uint4 *>(w.Q), reinterpret_cast<uint4 *>(w.dO));
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        Q = w.Q;
+        dO = w.dO;
+    }
     hipError_t e = launch_kv_pack(g, K, V, w.packA, false, st);  // natural K as it is: exact score products
     if (e != hipSuccess) return e;
     e = launch_kv_pack(g, V, K, w.packB, false, st);
@@ -875,10 +912,10 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
 
 hipError_t launch_attn_bwd(const Geom &g, const uint16_t *Q, const uint16_t *K, const uint16_t *V, const uint16_t *O,
                            const float *lse, const uint16_t *dO, const uint32_t *sel_mask, uint16_t *dQ, uint16_t *dK,
-                           uint16_t *dV, void *ws, hipStream_t st)
+                           uint16_t *dV, bool in_place, void *ws, hipStream_t st)
 {
-    if (g.D == 64) return launch_bwd_d<64>(g, Q, K, V, O, lse, dO, sel_mask, dQ, dK, dV, ws, st);
-    return launch_bwd_d<128>(g, Q, K, V, O, lse, dO, sel_mask, dQ, dK, dV, ws, st);
+    if (g.D == 64) return launch_bwd_d<64>(g, Q, K, V, O, lse, dO, sel_mask, dQ, dK, dV, in_place, ws, st);
+    return launch_bwd_d<128>(g, Q, K, V, O, lse, dO, sel_mask, dQ, dK, dV, in_place, ws, st);
 }
 
 }  // namespace adaspark

@@ -52,7 +52,7 @@ def workload(name):
     return synth.TEST_WORKLOADS.get(name) or synth.SAMPLED_WORKLOADS.get(name) or synth.WORKLOADS[name]
 
 
-def run_case(B, oracle, name, p, dense=False):
+def run_case(B, oracle, name, p, dense=False, over={}):
     w = workload(name)
     sh, osh = B.Shape.of(w), oshape(oracle, w)
     Q, K, V = synth.generate(w)
@@ -69,12 +69,15 @@ def run_case(B, oracle, name, p, dense=False):
     else:
         O, lse = B.sparse_attn(sh, Qg, Kg, Vg, mg, return_lse=True)
     torch.cuda.synchronize()
-    print(f"[{name}] backward", flush=True)
-    dQ, dK, dV = B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dOg, sel_mask=None if dense else mg)
+    Oc = f64(O.cpu()).reshape(-1, w.D)
+    inputs = {"Q": Qg, "K": Kg, "V": Vg, "O": O, "dO": dOg}
+    print(f"[{name}] backward {over}", flush=True)
+    dQ, dK, dV = B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dOg, sel_mask=None if dense else mg,
+                                   **{out: inputs[i] for out, i in over.items()})
     torch.cuda.synchronize()
     T = {}
     rq, rk, rv, _ = oracle.bwd.sparse_attn_bwd(osh, f64(Q), f64(K), f64(V), mask, f64(dO).reshape(-1, w.D),
-                                               O=f64(O.cpu()).reshape(-1, w.D), scales=T)
+                                               O=Oc, scales=T)
     check_grad(f"{name} dV", f64(dV.cpu()), rv, T["dV"])
     check_grad(f"{name} dQ", f64(dQ.cpu()), rq, T["dQ"])
     check_grad(f"{name} dK", f64(dK.cpu()), rk, T["dK"])
@@ -126,6 +129,23 @@ def test_backward_shared_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv,
     monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
     run_case(B, oracle, name, p)
     run_case(B, oracle, name, 1.0, dense=True)
+
+
+# Gradients written over the inputs they belong to: which output lies over which input.  dK and dV over Q or dO need as
+# many KV heads as query heads.  "one_cube": keys with no parts to sum.
+IN_PLACE = [
+    ("T_ragged", {"dQ": "dO"}), ("T_ragged", {"dQ": "Q", "dK": "K", "dV": "V"}), ("M_bwd256", {"dQ": "dO"}),
+    ("T_ragged", {"dQ": "O", "dK": "V", "dV": "K"}), ("T_mha64", {"dQ": "dO", "dK": "Q"}), ("T_mha64", {"dK": "Q", "dV": "dO"}),
+    ("T_mha64", {"dQ": "Q", "dV": "O"}), ("one_cube", {"dQ": "dO"}), ("one_cube", {"dK": "Q", "dV": "dO"}),
+]
+
+
+@pytest.mark.parametrize("name,over", IN_PLACE, ids=[n + "_" + "_".join(o + "_" + i for o, i in ov.items()) for n, ov in IN_PLACE])
+def test_backward_in_place(B, oracle, monkeypatch, name, over):
+    w = synth.Workload(name, 44, 2, 8, 8, 2, 8, 8, 2, 2, 64, (0.8,), (1.0,) * 2)
+    if name == "one_cube":
+        monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
+    run_case(B, oracle, name, 0.8, over=over)
 
 
 @pytest.mark.parametrize("name,p", [("T_tiny", 0.8), ("T_ragged", 0.9), ("T_lead64", 0.8), ("M_bwd256", 0.8)])
