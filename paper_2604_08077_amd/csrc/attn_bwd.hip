@@ -607,13 +607,15 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         asm volatile("" : "+v"(l));
         return l;
     };
-    auto issue = [&](int stage, int first) __attribute__((always_inline)) {
+    // A tile past the list's end (n rows) is padded with the list's last row -- a row that has its place in this tile anyway,
+    // so that what is not finite in it reaches nobody new -- under start values that give it no part.
+    auto issue = [&](int stage, int first, int n) __attribute__((always_inline)) {
         const uint32_t dst = lds0 + (uint32_t)(stage * C::STAGE);
         const int l = fresh_lane();
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int r = (wave * PER + u) * RPI + l / CPR;
-            const uint32_t rid = min(rows[first + r], nrows_all - 1);
+            const uint32_t rid = rows[min(first + r, n - 1)];
             const int chunk = ((l & 15) ^ row_swizzle<D>(r)) & (CPR - 1);
             const size_t off = (size_t)rid * D + chunk * 8;
             const uint32_t piece = dst + (uint32_t)((wave * PER + u) * 1024);
@@ -622,7 +624,8 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         }
         if (wave < 2) {  // the start values: wavefront 0 lse2, wavefront 1 delta
             const float *vals = wave == 0 ? lse2 : delta;
-            dma_lane4(__builtin_amdgcn_readfirstlane(dst + C::OFF_LSE + 256 * wave), vals + rows[first + l]);
+            dma_lane4(__builtin_amdgcn_readfirstlane(dst + C::OFF_LSE + 256 * wave),
+                      vals + (first + l < n ? rows[min(first + l, n - 1)] : nrows_all));
         }
     };
     // Opens a tile: this wavefront's loads of it have landed (those of the next tile may stay in flight), then everybody's.
@@ -717,13 +720,13 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         constexpr bool OWN = decltype(own_tag)::value;
         const int nt = (n + 63) >> 6;
         if (nt == 0) return;
-        issue(0, 0);
-        if (nt > 1) issue(1, 64);
+        issue(0, 0, n);
+        if (nt > 1) issue(1, 64, n);
         int stage = 0;
         for (int t = 0; t < nt; ++t) {
             open_tile(t + 1 < nt);
             const int s2 = stage == 0 ? 2 : stage - 1;  // (stage + 2) % 3: read last at tile t - 1
-            if (t + 2 < nt) issue(s2, 64 * (t + 2));
+            if (t + 2 < nt) issue(s2, 64 * (t + 2), n);
             // (own cube: no row of the tile reaches the wavefront's keys if the last one does not)
             if (busy && (!OWN || (f + 64 * t + 63) / g.G >= key0)) tile_work(stage, own_tag, f + 64 * t);
             stage = stage == 2 ? 0 : stage + 1;
@@ -758,7 +761,6 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
             if ((bits >> l) & 1ull)
                 rows[base[x] + __popcll(bits & ((1ull << l) - 1ull))] = tab[(size_t)(w0 + x) * 64 + l] + (uint32_t)(kv * g.G);
         }
-        if (wave == 0 && n + l < ((n + 63) & ~63)) rows[n + l] = nrows_all;  // padding rows
         __syncthreads();
         run_list(n, std::integral_constant<bool, false>{}, 0);
     }
@@ -769,8 +771,8 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         for (int f = kb * BWD_ROWS * g.G / 64 * 64; f < own; f += 64 * BWD_LIST_WORDS) {
             const int n = min(own - f, 64 * BWD_LIST_WORDS);
             __syncthreads();
-            for (int x = wave * 64 + fresh_lane(); x < ((n + 63) & ~63); x += BWD_THREADS)
-                rows[x] = x < n ? rowtab[(size_t)j * tpcr * 64 + f + x] + (uint32_t)(kv * g.G) : nrows_all;
+            for (int x = wave * 64 + fresh_lane(); x < n; x += BWD_THREADS)
+                rows[x] = rowtab[(size_t)j * tpcr * 64 + f + x] + (uint32_t)(kv * g.G);
             __syncthreads();
             run_list(n, std::integral_constant<bool, true>{}, f);
         }

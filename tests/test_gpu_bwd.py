@@ -148,6 +148,34 @@ def test_backward_in_place(B, oracle, monkeypatch, name, over):
     run_case(B, oracle, name, 0.8, over=over)
 
 
+@pytest.mark.parametrize("name", ["T_ragged", "T_text64"])
+def test_a_row_that_is_not_finite_stays_in_its_kv_head(B, oracle, name):
+    """dO of the last token's last query head is infinite, then not a number: what other KV heads get is bit for bit
+    what they get with a finite one, whatever pads their tiles of rows."""
+    w = workload(name)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(synth.BASE_SEED + 31 * w.config_id)
+    dO = torch.randn((w.S, w.Hq, w.D), generator=g, dtype=torch.float32).to(torch.bfloat16)
+    mask = oracle.cube_select(osh, Q, oracle.cube_pool(osh, K), 0.8)[0]
+    Qg, Kg, Vg = Q.cuda(), K.cuda(), V.cuda()
+    mg = torch.from_numpy(mask.view(np.int32)).cuda()
+    O, lse = B.sparse_attn(sh, Qg, Kg, Vg, mg, return_lse=True)
+    for sel in (mg, None):
+        want = B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dO.cuda(), sel_mask=sel)
+        for bad in (float("inf"), float("nan")):
+            worse = dO.clone()
+            worse[-1, -1] = bad
+            got = B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, worse.cuda(), sel_mask=sel)
+            torch.cuda.synchronize()
+            G = w.Hq // w.Hkv
+            for nm, a, b, keep in zip(("dQ", "dK", "dV"), got, want, (w.Hq - G, w.Hkv - 1, w.Hkv - 1)):
+                a, b = a[:, :keep].cpu(), b[:, :keep].cpu()
+                print(f"[{name} dense={sel is None} {bad}] {nm}: not finite {int((~a.isfinite()).sum())}", flush=True)
+                assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("name,p", [("T_tiny", 0.8), ("T_ragged", 0.9), ("T_lead64", 0.8), ("M_bwd256", 0.8)])
 def test_backward_matches_the_exact_gradient(B, oracle, name, p):
     """Against the oracle's own gradient: delta = dO.o from the exact fp64 forward, not from the bf16 O the GPU
