@@ -289,6 +289,8 @@ int adaspark_dense_attn_packed(const adaspark_shape *shape, const void *Q, const
  *   dQ         out  bf16 [tokens][q_heads][head_dim];  dK, dV  out  bf16 [tokens][kv_heads][head_dim]
  *   workspace       adaspark_workspace_bytes(ADASPARK_CALL_ATTN_BWD): packed copies of K, V (natural and
  *                   transposed), two floats per row, the selection bits transposed, and partial sums of dK and dV
+ *                   (fp32, up to some 8,000 parts of min(cube, 256) keys: 2.3 of 2.6 GB at 65,536 tokens
+ *                   in cubes of 256, 28/4 heads of 128), or copies of Q and dO where these are larger
  * p is rebuilt from lse in fp32 from exact score products (bf16 x bf16 accumulated in fp32, the softmax scale applied
  * in fp32); p and dS are rounded to bf16 for the other MFMA products, sums are fp32, outputs are rounded to bf16
  * once.  Limits as for the forward, and tokens*q_heads*ceil(cubes/32) < 2^30; causal != 0 only.

@@ -33,20 +33,21 @@ constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per w
 constexpr int DQ_SHARED_BLOCKS = 304;  // dq_keys
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
-// How attn_bwd_dkv_kernel's work is cut.  A workgroup takes 256 keys (one of nkb key blocks) of one (key cube j, KV
+// How attn_bwd_dkv_kernel's work is cut.  A workgroup takes up to 256 keys (one of nkb key blocks) of one (key cube j, KV
 // head) and the rows of `span` consecutive row cubes c * span .. that selected j (and cube j's own rows, if it is one
 // of them).  Parts of the same keys are summed by bwd_reduce_kernel in a fixed order.  Parts (c, j) exist for
 // c >= j / span; they are numbered span * c * (c + 1) / 2 + j, so the workgroups of one c, which gather the same rows
 // at the same time, follow each other.
 struct BwdParts {
     int span, nc;     // row cubes per part; ranges c
-    int nkb;          // 256-key blocks per cube
+    int nkb, keys;    // key blocks per cube; keys of one, as the sums are held (a multiple of 32, 256 but for small cubes)
     long long parts;  // per (KV head, key block)
 };
 static BwdParts bwd_cut(const Geom &g, long long span)
 {
     BwdParts p;
     p.nkb = (g.Cmax + BWD_ROWS - 1) / BWD_ROWS;
+    p.keys = std::min(BWD_ROWS, (g.Cmax + 31) / 32 * 32);
     p.span = (int)span;
     p.nc = (g.N + p.span - 1) / p.span;
     p.parts = (long long)p.span * (p.nc - 1) * p.nc / 2 + g.N;
@@ -72,7 +73,7 @@ static BwdParts bwd_parts(const Geom &g)
 // (keys that have a single part are written where they belong, so with a single range there are no sums to hold)
 static size_t bwd_part_bytes(const Geom &g, const BwdParts &p)
 {
-    return p.nc > 1 ? (size_t)g.Hkv * p.nkb * p.parts * 2 * BWD_ROWS * g.D * 4 : 0;
+    return p.nc > 1 ? (size_t)g.Hkv * p.nkb * p.parts * 2 * p.keys * g.D * 4 : 0;
 }
 
 struct BwdWorkspace {
@@ -83,7 +84,7 @@ struct BwdWorkspace {
     float *lse2, *delta;     // [S * Hq + 1]
     unsigned long long *colmask;  // [Hkv][N (key cube j)][N (row cube i)][tpcr]: bit k = row 64 t + k of cube i selects j (j < i)
     uint32_t *rowtab;        // [N][tpcr * 64]: row ids of the row tiles, KV head 0
-    float *part;             // [Hkv][nkb][parts][2 (dV, dK)][256 keys x D], in MFMA output order
+    float *part;             // [Hkv][nkb][parts][2 (dV, dK)][cut.keys x D], in MFMA output order
     uint16_t *Q, *dO;        // copies of the caller's, if a gradient is written over one of them
     BwdParts cut;
     int tpcr;                // 64-row words per cube = ceil(Cmax * G / 64)
@@ -795,13 +796,13 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         }
         return;
     }
-    float *out = part + (((size_t)kv * cut.nkb + kb) * cut.parts + pidx) * (2 * BWD_ROWS * D) + (size_t)wave * (32 * D) + lane * 4;
+    float *out = part + (((size_t)kv * cut.nkb + kb) * cut.parts + pidx) * (2 * cut.keys * D) + (size_t)wave * (32 * D) + lane * 4;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int e = 0; e < DT; ++e) {
             *reinterpret_cast<f32x4 *>(out + (s * DT + e) * 256) = accV[s][e];
-            *reinterpret_cast<f32x4 *>(out + BWD_ROWS * D + (s * DT + e) * 256) = accK[s][e];
+            *reinterpret_cast<f32x4 *>(out + cut.keys * D + (s * DT + e) * 256) = accK[s][e];
         }
 }
 
@@ -811,22 +812,23 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
                                                          uint16_t *__restrict__ dK, uint16_t *__restrict__ dV)
 {
     constexpr int DT = D / 16;
-    const int j = blockIdx.y, kv = blockIdx.z / cut.nkb, kb = blockIdx.z % cut.nkb;
+    const int per = cut.keys * D / 4 / 256;  // workgroups per key block
+    const int j = blockIdx.y, kv = blockIdx.z, kb = blockIdx.x / per;
     const int c0 = j / cut.span;
     if (cut.nc - c0 == 1) return;
     const CubeBox box = cube_box(g, j);
     // position x of a part: wavefront, (s, e), lane
-    const int x = blockIdx.x * 256 + threadIdx.x;
+    const int x = blockIdx.x % per * 256 + threadIdx.x;
     const int lane = x & 63, e = (x >> 6) % DT, s = (x >> 6) / DT % 2, wave = (x >> 6) / (2 * DT);
     const int key = kb * BWD_ROWS + wave * 32 + s * 16 + (lane & 15);
     if (key >= box.size()) return;
-    const float *src = part + ((size_t)blockIdx.z * cut.parts + j) * (2 * BWD_ROWS * D) + (size_t)x * 4;
+    const float *src = part + (((size_t)kv * cut.nkb + kb) * cut.parts + j) * (2 * cut.keys * D) + (size_t)x * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f}, k = v;
 #pragma unroll 4
     for (int c = c0; c < cut.nc; ++c) {
-        const float *p = src + ((size_t)cut.span * c * (c + 1) / 2) * (2 * BWD_ROWS * D);
+        const float *p = src + ((size_t)cut.span * c * (c + 1) / 2) * (2 * cut.keys * D);
         v += *reinterpret_cast<const f32x4 *>(p);
-        k += *reinterpret_cast<const f32x4 *>(p + BWD_ROWS * D);
+        k += *reinterpret_cast<const f32x4 *>(p + cut.keys * D);
     }
     const size_t o = ((size_t)token_of(g, box, key) * g.Hkv + kv) * D + 16 * e + 4 * (lane >> 4);
     *reinterpret_cast<uint2 *>(dV + o) = pack_bf16(v);
@@ -907,8 +909,8 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     hipLaunchKernelGGL((attn_bwd_dkv_kernel<D>), grid_k, dim3(BWD_THREADS), lds_k, st, g, K, V, Q, dO, w.lse2, w.delta, w.tpcr,
                        w.colmask, w.rowtab, cut, w.part, dK, dV);
     if (cut.nc > 1)
-        hipLaunchKernelGGL((bwd_reduce_kernel<D>), dim3(BWD_ROWS * D / 4 / 256, g.N, g.Hkv * cut.nkb), dim3(256), 0, st, g, cut,
-                           w.part, dK, dV);
+        hipLaunchKernelGGL((bwd_reduce_kernel<D>), dim3(cut.nkb * (cut.keys * D / 4 / 256), g.N, g.Hkv), dim3(256), 0, st, g,
+                           cut, w.part, dK, dV);
     return hipGetLastError();
 }
 

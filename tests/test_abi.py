@@ -216,3 +216,11 @@ def test_compact_list_entries_validate_before_launch(lib):
     rows, words = 4 * 8 * 8 * 4, 1
     assert with_mask.value >= plain.value + rows * words * 4
     assert csr(ok_ptr, ok_ptr, ok_ptr, plain.value) == -3           # room for the K/V copy but not for the mask rows
+
+
+@pytest.mark.parametrize("sh,most", [((8, 16, 16, 2, 4, 4, 4, 4, 64), 32), ((32, 16, 16, 2, 4, 4, 28, 4, 128), 256),
+                                     ((32, 16, 16, 4, 4, 8, 28, 4, 128), 256), ((9, 10, 12, 4, 4, 8, 6, 2, 128), 32)])
+def test_backward_workspace_of_small_cubes(lib, sh, most):
+    """Partial sums of dK and dV take the room of the keys that a cube has (32 and 128 here), not of a whole key block
+    of 256: at most `most` MB in all, where whole blocks took 52 to 1,161."""
+    assert binding.workspace_bytes(binding.Shape(*sh), binding.CALL_ATTN_BWD) <= most << 20
