@@ -323,7 +323,8 @@ typedef struct {
 } adaspark_ffn_dims;
 
 /* Workspace of adaspark_ffn_sparse: tables of the activated tokens, their hidden activations (bf16, d_ff per
- * token) and the layer's output for them (fp32, d_model per token), sized for all tokens activated. */
+ * token) and the layer's output for them (fp32, d_model per token), sized for all tokens activated.  With few activated tokens the
+ * output is held in several parts: at least room for the most that a smaller number of them takes, never more than 256 MB. */
 int adaspark_ffn_workspace_bytes(const adaspark_shape *shape, const adaspark_ffn_dims *dims, size_t *bytes);
 
 /*

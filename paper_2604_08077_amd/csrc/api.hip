@@ -435,12 +435,11 @@ int adaspark_ffn_sparse(const adaspark_shape *shape, const adaspark_ffn_dims *di
     // Y must not overlap X at all: the mean compensation reads X rows of other tokens while Y is written
     const size_t n = (size_t)g.S * (size_t)dims->d_model * 2u;
     if (overlap(X, n, Y, n)) return ADASPARK_EINVAL;
-    if (workspace == nullptr || !aligned16(workspace) ||
-        workspace_bytes < ffn_workspace(g, dims->d_model, dims->d_ff, nullptr).bytes)
-        return ADASPARK_EWORKSPACE;
+    const FfnWorkspace w = ffn_workspace(g, dims->d_model, dims->d_ff, workspace);
+    if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < w.bytes) return ADASPARK_EWORKSPACE;
     const hipError_t e = launch_ffn_sparse(g, dims->d_model, dims->d_ff, static_cast<const uint16_t *>(X),
                                            static_cast<const uint16_t *>(W_gate), static_cast<const uint16_t *>(W_up),
-                                           static_cast<const uint16_t *>(W_down), keep, static_cast<uint16_t *>(Y), workspace,
+                                           static_cast<const uint16_t *>(W_down), keep, static_cast<uint16_t *>(Y), w,
                                            static_cast<hipStream_t>(stream));
     return e == hipSuccess ? ADASPARK_OK : ADASPARK_EHIP;
 }

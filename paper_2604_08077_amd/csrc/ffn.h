@@ -42,6 +42,7 @@ struct FfnWorkspace {
     float *F;           // [splits][rows up to the activated ones'][d_model]  fp32 FFN(x) of the activated tokens, in as
                         //          many parts as the W_down product was split into
     long long rows;     // S rounded up to a multiple of FFN_ROW_TILE
+    long long down_blocks;  // blocks of 32 tiles that the W_down product's grid has to cover, however many tokens are activated
     size_t bytes;
 };
 FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws);
@@ -49,15 +50,17 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws);
 hipError_t launch_ffn_select(const Geom &g, int d_model, const uint16_t *X, float top_p, float eps, uint8_t *keep,
                              float *score, int32_t *keep_count, hipStream_t st);
 hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_t *X, const uint16_t *Wg,
-                             const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y, void *ws,
-                             hipStream_t st);
+                             const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y,
+                             const FfnWorkspace &w, hipStream_t st);
 
 // H[r][:] = silu(W_gate . x) * (W_up . x) for x = X[active[r]], r < *n_rows (rows up to the next multiple of
 // FFN_ROW_TILE are computed too, from the padding of `active`).  m_tiles: upper bound of row tiles (grid size).
 hipError_t launch_ffn_gemm_gated(const uint16_t *X, const int32_t *active, const uint16_t *Wg, const uint16_t *Wu,
                                  int d_model, int d_ff, int m_tiles, const int32_t *n_rows, uint16_t *H, hipStream_t st);
-// F[split][r][:]: over the splits (ffn_down_splits) summing to W_down . H[r][:], in fp32.
-hipError_t launch_ffn_gemm_down(const uint16_t *H, const uint16_t *Wd, int d_ff, int d_model, int m_tiles,
+// F[split][r][:]: over the splits (ffn_down_splits) summing to W_down . H[r][:], in fp32.  blocks: FfnWorkspace::down_blocks.
+hipError_t launch_ffn_gemm_down(const uint16_t *H, const uint16_t *Wd, int d_ff, int d_model, long long blocks,
                                 const int32_t *n_rows, float *F, hipStream_t st);
+// Blocks of 32 tiles for m_tiles row tiles (a multiple of four of them: a block is four row tiles high).
+inline long long ffn_tile_blocks(long long m_tiles, int n_tiles) { return ((m_tiles + 3) / 4 * 4 * n_tiles + 31) / 32; }
 
 }  // namespace adaspark

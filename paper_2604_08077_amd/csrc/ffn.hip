@@ -322,9 +322,16 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws)
     w.active = reinterpret_cast<int32_t *>(p + off); off = up(off + rows * 4);
     w.bypass = reinterpret_cast<int32_t *>(p + off); off = up(off + (size_t)g.S * 4);
     w.H = reinterpret_cast<uint16_t *>(p + off); off = up(off + rows * (size_t)d_ff * 2);
-    // one part for all rows, or several for few of them (ffn_down_splits)
-    const size_t tiles = rows / FFN_ROW_TILE * (size_t)(d_model / FFN_ROW_TILE);
-    const size_t f_tiles = std::max(tiles, std::min((size_t)FFN_SPLIT_TILES, 16 * tiles));
+    // F: one part for all rows, or several for few of them (ffn_down_splits).  How many rows there are is known on the
+    // device: room, and a grid, for the row-tile count that takes most.
+    const int m_tiles = (int)(rows / FFN_ROW_TILE), n_tiles = d_model / FFN_ROW_TILE;
+    size_t f_tiles = (size_t)m_tiles * n_tiles;
+    w.down_blocks = ffn_tile_blocks(m_tiles, n_tiles);
+    for (int m = 1; m <= m_tiles && m * n_tiles <= FFN_SPLIT_TILES / 2; ++m) {  // (with more tiles there is one part)
+        const int splits = ffn_down_splits(m, n_tiles, d_ff);
+        f_tiles = std::max(f_tiles, (size_t)splits * m * n_tiles);
+        w.down_blocks = std::max(w.down_blocks, splits * ffn_tile_blocks(m, n_tiles));
+    }
     w.F = reinterpret_cast<float *>(p + off); off = up(off + f_tiles * FFN_ROW_TILE * FFN_ROW_TILE * 4);
     w.bytes = off;
     w.rows = (long long)rows;
@@ -332,10 +339,9 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws)
 }
 
 hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_t *X, const uint16_t *Wg,
-                             const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y, void *ws,
-                             hipStream_t st)
+                             const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y,
+                             const FfnWorkspace &w, hipStream_t st)
 {
-    const FfnWorkspace w = ffn_workspace(g, d_model, d_ff, ws);
     hipLaunchKernelGGL(ffn_count_kernel, dim3(g.N), dim3(TAB_THREADS), 0, st, g, keep, w.cnt);
     hipLaunchKernelGGL(ffn_fill_kernel, dim3(g.N), dim3(TAB_THREADS), 0, st, g, keep, w.cnt, w.cube_ptr, w.active,
                        w.bypass);
@@ -345,7 +351,7 @@ hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_
     // hidden activations of the activated tokens, then the layer's output for them
     e = launch_ffn_gemm_gated(X, w.active, Wg, Wu, d_model, d_ff, m_tiles, w.cube_ptr + g.N, w.H, st);
     if (e != hipSuccess) return e;
-    e = launch_ffn_gemm_down(w.H, Wd, d_ff, d_model, m_tiles, w.cube_ptr + g.N, w.F, st);
+    e = launch_ffn_gemm_down(w.H, Wd, d_ff, d_model, w.down_blocks, w.cube_ptr + g.N, w.F, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(ffn_finish_kernel, dim3(g.N, (d_model + 511) / 512), dim3(FIN_THREADS), 0, st, g, d_model, d_ff, X, w.F,
                        w.cube_ptr, w.active, w.bypass, Y);

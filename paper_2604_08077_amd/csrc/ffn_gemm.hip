@@ -24,8 +24,6 @@
 // step, both wavefronts of a SIMD in phase and loads one step ahead: 7.0 + 3.3 ms.  Tried: both in phase with operands
 // prefetched across two barriers a step (6.7 + 3.2, loads spread between the MFMAs: 6.5 + 3.1), the barrier ahead of a
 // slot's last MFMAs (slower: it holds the other set's reads back).
-#include <algorithm>
-
 #include "attn_tile.h"
 #include "ffn.h"
 
@@ -254,27 +252,16 @@ hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, const uint16_t 
     return hipGetLastError();
 }
 
-// Blocks of 32 tiles for m_tiles row tiles (a multiple of four of them: a block is four row tiles high).
-static long long tile_blocks(long long m_tiles, int n_tiles) { return ((m_tiles + 3) / 4 * 4 * n_tiles + 31) / 32; }
-
 hipError_t launch_ffn_gemm_gated(const uint16_t *X, const int32_t *active, const uint16_t *Wg, const uint16_t *Wu,
                                  int d_model, int d_ff, int m_tiles, const int32_t *n_rows, uint16_t *H, hipStream_t st)
 {
-    return launch_gemm<true>(X, active, Wg, Wu, d_model, d_ff / 128, tile_blocks(m_tiles, d_ff / 128), n_rows, H, d_ff, st);
+    return launch_gemm<true>(X, active, Wg, Wu, d_model, d_ff / 128, ffn_tile_blocks(m_tiles, d_ff / 128), n_rows, H, d_ff, st);
 }
 
-hipError_t launch_ffn_gemm_down(const uint16_t *H, const uint16_t *Wd, int d_ff, int d_model, int m_tiles,
+hipError_t launch_ffn_gemm_down(const uint16_t *H, const uint16_t *Wd, int d_ff, int d_model, long long blocks,
                                 const int32_t *n_rows, float *F, hipStream_t st)
 {
-    // How many tiles there are, and so how they are split, is known on the device: a grid for the worst case.  (A split
-    // has 32 or more blocks' worth of tiles only if it is the only one, and no more than FFN_SPLIT_TILES + 3 padding rows of
-    // tiles each otherwise.)
-    const int n_tiles = d_model / GT;
-    long long blocks = 0;
-    for (int m = 1; m <= m_tiles && (m - 1) * n_tiles < FFN_SPLIT_TILES; ++m)
-        blocks = std::max(blocks, ffn_down_splits(m, n_tiles, d_ff) * tile_blocks(m, n_tiles));
-    blocks = std::max(blocks, tile_blocks(m_tiles, n_tiles));
-    return launch_gemm<false>(H, nullptr, Wd, nullptr, d_ff, n_tiles, blocks, n_rows, F, d_model, st);
+    return launch_gemm<false>(H, nullptr, Wd, nullptr, d_ff, d_model / GT, blocks, n_rows, F, d_model, st);
 }
 
 }  // namespace adaspark

@@ -224,3 +224,11 @@ def test_backward_workspace_of_small_cubes(lib, sh, most):
     """Partial sums of dK and dV take the room of the keys that a cube has (32 and 128 here), not of a whole key block
     of 256: at most `most` MB in all, where whole blocks took 52 to 1,161."""
     assert binding.workspace_bytes(binding.Shape(*sh), binding.CALL_ATTN_BWD) <= most << 20
+
+
+@pytest.mark.parametrize("sh,d_model,d_ff,most", [((9, 10, 12, 4, 4, 8), 3584, 18944, 128), ((9, 10, 12, 4, 4, 8), 256, 1024, 16),
+                                                  ((8, 16, 16, 2, 4, 4), 1024, 4096, 64), ((256, 16, 16, 4, 8, 8), 256, 1024, 256)])
+def test_ffn_workspace_of_few_tokens(lib, sh, d_model, d_ff, most):
+    """The split W_down product's parts take the room that some number of activated tokens can need (at most `most` MB in
+    all), not sixteen parts whatever the rule: 317, 24, 151 and 403 MB."""
+    assert binding.ffn_workspace_bytes(binding.Shape(*sh, 1, 1, 64), d_model, d_ff) <= most << 20
