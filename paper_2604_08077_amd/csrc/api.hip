@@ -157,6 +157,17 @@ const char *adaspark_status_string(int status)
     }
 }
 
+// Which side of the rule between the masked-walk / dense kernel (0) and the one for short sequences (1) a shape lies on.  Not
+// declared in the header: for tests that have to know which kernel they compare with the oracle.
+int adaspark_internal_short_sequence(const adaspark_shape *shape, int causal)
+{
+    const int rc = check_shape(shape);
+    if (rc != ADASPARK_OK) return rc;
+    Geom g = make_geom(*shape);
+    g.causal = causal != 0;
+    return attn_split_pays(g) ? 1 : 0;
+}
+
 int adaspark_cube_pool(const adaspark_shape *shape, const void *K, float *kbar, void *stream)
 {
     int rc = check_shape(shape);

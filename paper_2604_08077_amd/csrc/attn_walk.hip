@@ -582,7 +582,7 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
 //          4 to start and to combine its parts
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 111 split, 161 walk; 16,384: 387, 336.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 60, 62; 4,096: 155, 110.
-static bool attn_split_pays(const Geom &g)
+bool attn_split_pays(const Geom &g)
 {
     if (!attn_split_fits(g)) return false;
     const double groups = (double)g.N * g.Hkv, rows = (double)g.G * g.Cmax;  // (query cube, KV head) pairs; rows of one

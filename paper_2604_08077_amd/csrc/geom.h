@@ -176,8 +176,10 @@ unsigned long long candidate_pairs(const Geom &g);
 // be null): memory for the key-stationary kernel's records.
 hipError_t launch_attn(const Geom &g, const uint16_t *Q, void *packed, const uint32_t *sel_mask, int sparse_kernel,
                        void *scratch, size_t scratch_bytes, uint16_t *O, float *lse, hipStream_t st);
-// The kernel for short sequences (attn_split.hip); sel_mask == nullptr: dense.  attn_split_fits: its list of steps does.
+// The kernel for short sequences (attn_split.hip); sel_mask == nullptr: dense.  attn_split_fits: its list of steps does;
+// attn_split_pays: launch_attn takes it, for dense attention and where the choice is automatic.
 bool attn_split_fits(const Geom &g);
+bool attn_split_pays(const Geom &g);
 hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, uint16_t *O,
                              float *lse, hipStream_t st);
 // The compacting sparse kernel alone (attn_compact.hip).  flags (device, may be null): the flag block above; a

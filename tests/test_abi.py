@@ -232,3 +232,12 @@ def test_ffn_workspace_of_few_tokens(lib, sh, d_model, d_ff, most):
     """The split W_down product's parts take the room that some number of activated tokens can need (at most `most` MB in
     all), not sixteen parts whatever the rule: 317, 24, 151 and 403 MB."""
     assert binding.ffn_workspace_bytes(binding.Shape(*sh, 1, 1, 64), d_model, d_ff) <= most << 20
+
+
+def test_which_shapes_are_short_sequences(lib):
+    """The rule between the kernel for short sequences (1) and the walk (0) at the shapes where both were measured."""
+    for sh, want in (((8, 16, 16, 2, 4, 4, 4, 4, 64), 1), ((9, 10, 12, 4, 4, 8, 6, 2, 128), 1),
+                     ((32, 16, 16, 4, 4, 8, 4, 4, 64), 1), ((64, 16, 16, 4, 4, 8, 4, 4, 64), 0),
+                     ((8, 16, 16, 4, 8, 8, 14, 2, 128), 1), ((16, 16, 16, 4, 8, 8, 14, 2, 128), 0)):
+        cs = binding.Shape(*sh)._c()
+        assert lib.adaspark_internal_short_sequence(ctypes.byref(cs), 1) == want, sh

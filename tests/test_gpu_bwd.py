@@ -91,8 +91,8 @@ def test_backward_matches_oracle(B, oracle, name, p):
 
 
 # What the dK/dV kernel cuts by: one cube (no part to sum), cubes of 65 rows per KV head (a second 64-row word with one row),
-# of 63 and 64 tokens, more than 64 words per cube (two lists) with four 256-key blocks, many cubes per part and a
-# last range with a single one, a text tail of one token.
+# of 63 and 64 tokens, more than 64 words per cube (two lists) with four 256-key blocks, two cubes per part (with a text tail
+# of one token, which fills the last range, and with a last range of a single cube), fourteen per part and a last range of four.
 GATHER = [
     ("one_cube", (2, 4, 4), (2, 4, 4), 2, 1, 64, 1.0, 0),
     ("rows65", (3, 1, 26), (1, 1, 13), 5, 1, 128, 0.7, 0),
@@ -100,6 +100,8 @@ GATHER = [
     ("tokens64", (5, 8, 8), (1, 8, 8), 2, 2, 64, 0.6, 1),
     ("two_lists", (8, 16, 16), (4, 16, 16), 7, 1, 64, 1.0, 0),
     ("parts", (65, 4, 4), (1, 4, 4), 1, 1, 128, 0.5, 1),
+    ("parts_last_single", (65, 4, 4), (1, 4, 4), 1, 1, 128, 0.5, 0),
+    ("parts_of_14", (60, 1, 4), (1, 1, 4), 8, 8, 64, 0.5, 0),
 ]
 
 

@@ -1,13 +1,15 @@
 """The attention kernel for short sequences at the sizes where its cutting can go wrong, against the fp64 oracle: row
 blocks of 31 / 32 / 33 rows, cubes of 31 / 32 / 33 keys and of one, a walk shorter than the eight wavefronts that share it,
-nothing selected, both causal modes, dense.  The entries choose it by shape: all of these are far on its side of the line
-(two dozen walks of a few steps)."""
+nothing selected, both causal modes, dense.  The entries choose it by shape; every test asserts which kernel its shape
+gets.  And the dense walk kernel at head-dim 64, which short shapes no longer reach, on shapes of its side of the line."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2604_08077_amd import synth
-from test_gpu_parity import B, MAX_ABS, MEAN_ABS, lse_bound, oshape  # noqa: F401
+from test_gpu_parity import B, MAX_ABS, MEAN_ABS, check_outputs, lse_bound, oshape, rows_of, stratified_rows  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +22,12 @@ SHAPES = [
     ("one_cube", (2, 4, 9), (2, 4, 9), 7, 1, 128, 0),
     ("text_tail", (3, 4, 8), (1, 4, 8), 6, 2, 128, 33),
 ]
+
+
+def short(B, sh, causal):  # noqa: F811
+    """1: the kernel for short sequences, 0: the walk."""
+    cs = sh._c()
+    return B.load().adaspark_internal_short_sequence(ctypes.byref(cs), int(causal))
 
 
 @pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text", SHAPES, ids=[s[0] for s in SHAPES])
@@ -37,6 +45,7 @@ def test_short_sequences(B, oracle, name, grid, cube, hq, hkv, d, text):  # noqa
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
 
     for causal in (True, False):
+        assert short(B, sh, causal) == 1
         for p in (0.0, 0.6):
             mask = oracle.cube_select(osh, Q, kbar, p, causal=causal)[0]
             print(f"[{name}] causal={causal} p={p}", flush=True)
@@ -49,3 +58,25 @@ def test_short_sequences(B, oracle, name, grid, cube, hq, hkv, d, text):  # noqa
         O = B.dense_attn(sh, Qg, Kg, Vg, causal=causal)
         torch.cuda.synchronize()
         check(f"causal={causal} dense", O, oracle.dense_attn(osh, Q, K, V, causal=causal))
+
+
+WALK64 = [  # grid, cube, query heads, KV heads, text after and before
+    ("cubes128", (64, 16, 16), (4, 4, 8), 4, 4, 0, 0),
+    ("cubes256", (32, 16, 16), (4, 8, 8), 8, 2, 0, 0),
+    ("clipped60_text", (16, 10, 15), (3, 4, 5), 48, 4, 70, 0),
+    ("clipped60_text_around", (24, 10, 15), (3, 4, 5), 32, 4, 70, 45),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,text,lead", WALK64, ids=[s[0] for s in WALK64])
+def test_dense_walk_of_64(B, oracle, name, grid, cube, hq, hkv, text, lead):  # noqa: F811
+    w = synth.Workload(name, 45, *grid, *cube, hq, hkv, 64, (0.6,), (1.0,) * hkv, text, lead)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    rows = stratified_rows(oracle, osh, w, 400)
+    for causal in (True, False):
+        assert short(B, sh, causal) == 0
+        print(f"[{name}] causal={causal}", flush=True)
+        O = B.dense_attn(sh, Q.cuda(), K.cuda(), V.cuda(), causal=causal)
+        torch.cuda.synchronize()
+        check_outputs(f"{name} causal={causal}", rows_of(O, rows, w), oracle.dense_attn(osh, Q, K, V, rows=rows, causal=causal))
