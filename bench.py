@@ -38,9 +38,9 @@ PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
 
 # HBM traffic of one sparse-attention launch (bytes), from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
-# scaled by a copy kernel of known size; keyed by (workload, top_p).  See profiles/.
+# scaled by a copy of known size; HBM traffic under profiles/, "forward 64k" and "top-p 0.5"; keyed by (workload, top_p).
 # (C3, 0.9): attn_walk_kernel<128, true>; (C3, 0.5): the key-stationary kernels together (pairs, own cubes, merge).
-MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 5.235e9, ("C3", 0.5): 3.767e10}
+MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 5.235e9, ("C3", 0.5): 3.776e10}
 
 
 def cube_tables(w):
@@ -143,8 +143,9 @@ def cpu_baseline(w, p, Q, K, V, budget_rows_sel=262144, budget_rows_attn=24576):
 # (28 heads x 128 = 3584 model width, 18944 hidden width).
 FFN_D_MODEL, FFN_D_FF, FFN_TOP_P = 3584, 18944, 0.7
 # Bytes the two matrix-product kernels of one adaspark_ffn_sparse call move between the L2 caches and the fabric
-# (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a copy of known size; see profiles/), keyed by workload.
-FFN_MEASURED_TRAFFIC_BYTES = {"C3": 2.237e10}
+# (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a copy of known size; HBM traffic under profiles/, "ffn 64k"), keyed
+# by workload.
+FFN_MEASURED_TRAFFIC_BYTES = {"C3": 2.297e10}
 
 
 def ffn_leg(B, w, steps, dense=True):
@@ -177,9 +178,10 @@ def ffn_leg(B, w, steps, dense=True):
     }
 
 
-# Bytes the three backward kernels of one call move between the L2 caches and the fabric (rocprofv3 --pmc FETCH_SIZE /
-# WRITE_SIZE, scaled by a copy of known size; see profiles/), keyed by (workload, top_p).
-BWD_MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 4.58e10}
+# Bytes all kernels of one backward call move between the L2 caches and the fabric (rocprofv3 --pmc FETCH_SIZE /
+# WRITE_SIZE, scaled by a copy of known size; HBM traffic under profiles/, "train 64k": packing, row values, column masks, dQ,
+# dK/dV and the sums), keyed by (workload, top_p).
+BWD_MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 4.57e10}
 
 
 def bwd_leg(B, w, sh, Qg, Kg, Vg, ws_att, mask, eff_flops, dense_flops, steps, top_p):

@@ -10,9 +10,9 @@
 // Cubes in which no row of the block takes part (selection) are left out of the walk.
 //
 // Bound by the latency of a step at the smallest sizes and by L2 above (every wavefront fetches 16 KB at head-dim 128
-// for 68 MFMAs: 15 TB/s over the chip), which is why the walk kernel takes over as soon as it fills the chip
-// (attn_split_pays).  2,048 tokens, 4/4 heads of 64, cubes of 32: 18.7 us, the walk kernel 126 us; 1,080 tokens, 6/2
-// heads of 128, clipped cubes of up to 128: 15 against 51 us.
+// for 34 MFMAs: 12 to 15 TB/s over the chip), which is why the walk kernel takes over as soon as it fills the chip
+// (attn_split_pays).  In a kernel trace: 2,048 tokens, 4/4 heads of 64, cubes of 32: 18.5 us, the walk kernel 127 us; 1,080
+// tokens, 6/2 heads of 128, clipped cubes of up to 128: 21.5 against 51 us.
 #include "attn_tile.h"
 
 namespace adaspark {

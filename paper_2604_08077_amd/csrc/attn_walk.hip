@@ -573,15 +573,17 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     return hipGetLastError();
 }
 
-// Whether the kernel for short sequences (attn_split.hip) beats this one, from what each of them took on an MI355X (us;
-// the figures below reproduce 80 measured shapes of 1,024 to 16,384 tokens, heads 4/4 .. 32/8 of 64 and 128, cubes of
-// 32 to 256 tokens within about 15 %):
+// Whether the kernel for short sequences (attn_split.hip) beats this one, from what each of them took on an MI355X (us).
+// Timed again on 101 shapes of 1,024 to 16,384 tokens, heads 4/4 .. 32/8 of 64 and 128, cubes of 32 to 256 tokens, the figures below
+// give the walk within 17 % on whole cubes and the split within 15 % or too high by up to 45 % (below 30 us); they pick the faster
+// kernel but for three shapes: 3 % and 12 % slower close to the line, and a walk of 126 against 84 on a clipped grid (4,200 tokens of
+// 8/2 heads of 64 in cubes of 4x4x8), where the walk is taken for faster than it is.
 //   walk   a slot (64 keys past 256 rows) takes 1.2 at head-dim 64 and 1.7 at 128, 0.6 more where cubes leave part of their
 //          tiles empty; the time is the longest walk's slots, or all slots over 256 CUs where that is more
 //   split  a step (32 keys past 32 rows) takes a CU 0.19 and 0.28 -- what its operands take from L2 -- and a workgroup
 //          4 to start and to combine its parts
-// Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 111 split, 161 walk; 16,384: 387, 336.
-// 2,048 tokens of 14/2 heads of 128 in cubes of 256: 60, 62; 4,096: 155, 110.
+// Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 109 split, 163 walk; 16,384: 388, 347.
+// 2,048 tokens of 14/2 heads of 128 in cubes of 256: 57, 60; 4,096: 148, 107.
 bool attn_split_pays(const Geom &g)
 {
     if (!attn_split_fits(g)) return false;

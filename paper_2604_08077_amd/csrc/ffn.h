@@ -14,7 +14,8 @@ constexpr int FFN_SPLIT_TILES = 1024;    // most (tile, split) pairs of a split 
 // long), each leaving an fp32 partial result.  One tile per CU and d_ff / 64 steps of 1.4 us each otherwise: few activated
 // tokens leave most of the chip idle.  The cost model: the rounds of workgroups over 256 CUs times the steps of one, and 0.1 us
 // of the chip's memory time per partial tile (512 KB written and read).  964 activated tokens, 3584/18944 (56 tiles):
-// 4 splits, 130 us; unsplit 414 us.  2,048 tokens (112 tiles): 4 splits, 250; 445 us.
+// 4 splits, 130 us; unsplit 381 to 444.  2,048 tokens (112 tiles): 2 splits, 251 us, and 18 to add the parts; 4 splits, 263
+// and 27; unsplit 425 and 13.
 __host__ __device__ inline int ffn_down_splits(int m_tiles, int n_tiles, int d_ff)
 {
     const int tiles = m_tiles * n_tiles, steps = d_ff / 64;

@@ -201,8 +201,8 @@ __global__ __launch_bounds__(TAB_THREADS) void ffn_fill_kernel(Geom g, const uin
 // Eqs. 6-7 for cube blockIdx.x and columns 512 blockIdx.y ..: F holds FFN(x) of the activated tokens (fp32, row = index in
 // the active list), in `splits` parts that are added in order.  A lane owns eight columns; the wavefronts take every
 // fourth activated token: y = x + F, and a sum of F, whose four parts are combined in order; then every fourth bypassed
-// token: x + mean.  Bound by memory (F, X and Y once each): 65,536 tokens of 3584, 47 % activated, 0.29 ms = 4.7 TB/s; 2,048
-// tokens with four parts, where one workgroup per cube and all columns took 33 us, 14 us.
+// token: x + mean.  Bound by memory (F, X and Y once each): 65,536 tokens of 3584, 47 % activated, 0.27 ms = 5.1 TB/s (0.35 with
+// one workgroup per cube and all columns); 2,048 tokens with four parts 21 us, where that took 33 with one.
 __global__ __launch_bounds__(FIN_THREADS) void ffn_finish_kernel(Geom g, int d_model, int d_ff, const uint16_t *__restrict__ X,
                                                                  const float *__restrict__ F,
                                                                  const int32_t *__restrict__ cube_ptr,
