@@ -296,7 +296,8 @@ int adaspark_dense_attn_packed(const adaspark_shape *shape, const void *Q, const
  * once.  Limits as for the forward, and tokens*q_heads*ceil(cubes/32) < 2^30; causal != 0 only.
  * Gradients may take the place of inputs of their size (same address): dQ that of Q, O or dO; dK and dV those of K
  * and V (with q_heads == kv_heads also those of Q, O and dO).  With a gradient over Q or dO the call works on copies of
- * these two in the workspace, at a little cost in time.  No other overlap of outputs with inputs or each other.
+ * these two in the workspace, which leaves less room for partial sums: a few percent slower, up to a third at a few thousand
+ * tokens.  No other overlap of outputs with inputs or each other.
  */
 int adaspark_sparse_attn_bwd(const adaspark_shape *shape, const void *Q, const void *K, const void *V, const void *O,
                              const float *lse, const void *dO, const uint32_t *sel_mask, int causal, void *dQ,

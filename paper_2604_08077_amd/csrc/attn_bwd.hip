@@ -63,8 +63,8 @@ static BwdParts bwd_parts(const Geom &g)
     const long long lo = lists * g.N / (2 * 8192);
     long long hi = std::max(1LL, lists * g.N / (2 * 1024));
     // Up to two parts per CU, and row cubes of few rows: one round of workgroups with twice the rows instead, which leaves
-    // half the sums (a backward pass, us: 384 rows a cube, 1,080 tokens of 6/2 heads of 128: 93 against 96; 768 rows, 4,096
-    // tokens: 207, 211).  With more rows the longest part is what counts (1,024 rows, 8/2 heads of 64: 161, 158; 1,792
+    // half the sums (a backward pass, us: 384 rows a cube, 1,080 tokens of 6/2 heads of 128: 92.0 against 94.5; 768 rows, 4,096
+    // tokens: 211.6, 216.1; runs of one side differ by 0.1).  With more rows the longest part is what counts (1,024 rows, 8/2 heads of 64: 161, 158; 1,792
     // rows, 14/2 heads of 128: 314, 300; 28/4 heads, 2,560 tokens: 315, 274).
     const long long most = lists * (g.N + 1) / 2;
     if (most <= 512 && g.G * g.Cmax <= 768) hi = (most + 255) / 256;
@@ -92,8 +92,8 @@ struct BwdWorkspace {
 };
 
 // in_place: dQ, dK or dV lies over Q or dO, which the dK/dV kernel gathers from while gradients are being written, so the
-// kernels read copies.  These take part of the sums' place (they fit there but for short sequences: the place is made
-// at least as large as they are), and the sums are those of wider ranges.
+// kernels read copies.  These take part of the sums' place (made at least as large as they are), and the sums are those of
+// wider ranges: a backward pass with dQ over dO, 1,080 tokens of 6/2 heads of 128, 108 us against 92; 4,096 tokens, 275 against 212.
 BwdWorkspace bwd_workspace(const Geom &g, void *ws, bool in_place)
 {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };

@@ -118,7 +118,7 @@ def test_backward_arguments_are_validated_before_launch(lib):
     fwd = ctypes.c_size_t(0)
     assert lib.adaspark_workspace_bytes(ctypes.byref(cs), binding.CALL_SPARSE_ATTN, ctypes.byref(fwd)) == 0
     rows, D = 4 * 8 * 8 * 4, 64
-    assert need.value >= 2 * fwd.value + 4 * rows * D * 2 + 2 * rows * 4      # two K/V packs, four row packs, two vectors
+    assert need.value >= 2 * fwd.value + 4 * rows * D * 2 + 2 * rows * 4      # two K/V packs, two vectors, sums of dK and dV (here more than four times Q)
     run = lambda q=ok_ptr, mask=ok_ptr, causal=1, ws=ok_ptr, nbytes=1 << 30, dq=ok_ptr: lib.adaspark_sparse_attn_bwd(
         ctypes.byref(cs), q, ok_ptr, ok_ptr, ok_ptr, ok_ptr, ok_ptr, mask, causal, dq, ok_ptr, ok_ptr, ws, nbytes, None)
     assert run(q=None) == -1 and run(dq=ctypes.c_void_p(4097)) == -1 and run(mask=ctypes.c_void_p(4100)) == -1
