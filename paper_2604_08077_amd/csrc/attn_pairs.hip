@@ -44,7 +44,8 @@ struct Pairs {
     static constexpr int OFF_V = CHUNK;
     static constexpr int TILE_STRIDE = 2 * CHUNK;
     static constexpr int OFF_ROWS = 2 * PAIRS_MAX_TPC * CHUNK;  // (row id, record) of the workgroup's rows
-    static constexpr int BYTES = OFF_ROWS + PAIRS_CHUNK * 8;
+    static constexpr int OFF_FILL = OFF_ROWS + PAIRS_CHUNK * 8;  // fill_masks
+    static constexpr int BYTES = OFF_FILL + FILL_MASK_BYTES;
     static_assert(BYTES <= 160 * 1024, "LDS of one CU");
     static_assert(PAIRS_CHUNK % (2 * WAVES * ROWS) == 0, "an even number of steps per wavefront");
 };
@@ -426,6 +427,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
         }
     }
 
+    fill_masks_init(smem + C::OFF_FILL, tid);
     // ---- the workgroup's rows as (row id, record) in LDS: a piece of the work list, or (OWN) rows of cube j in
     // (rank, head) order with the own cube's record, which is the row's last
     for (int x = tid; x < nrows; x += C::THREADS) {
@@ -492,10 +494,10 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
         auto v_tile = [&](int t) -> const unsigned char * { return smem + C::OFF_V + t * C::TILE_STRIDE; };
         auto softmax_step = [&](int t) __attribute__((always_inline)) {
             const int key0 = KEY_TILE * t;
-            const bool need_mask = OWN || (key0 + KEY_TILE > jsize);
+            const int fill = jsize - key0;
             // (after a step's first tile every row has its reference point: fresh is false for all)
-            if (need_mask || !softmax_tile_fast<NS>(sacc, pf, t > 0))
-                softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, ids.lim, key0, need_mask, q4);
+            if (OWN || !softmax_tile_fast<NS>(sacc, pf, t > 0, smem + C::OFF_FILL, fill, q4))
+                softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, ids.lim, key0, OWN || fill < KEY_TILE, q4);
 #pragma unroll
             for (int s = 0; s < NS; ++s) sinit[s] = f32x4{-m_run[s], -m_run[s], -m_run[s], -m_run[s]};
         };

@@ -57,27 +57,36 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, q4 = lane >> 4;
 
-    // workgroup -> (query cube, KV head, block of 32 rows); late cubes (long walks) first.  Rows of a (cube, KV head) are
-    // numbered head by head, so that a block is neighbouring tokens of one query head.
-    const int nblk_max = (g.G * g.Cmax + C::ROWS - 1) / C::ROWS;
-    const int blk = blockIdx.x % nblk_max;
-    const int kv = blockIdx.x / nblk_max % g.Hkv;
-    const int i = g.N - 1 - blockIdx.x / nblk_max / g.Hkv;
-    const CubeBox qbox = cube_box(g, i);
-    const int qsize = qbox.size();
-    const int P = g.G * qsize;
-    const int row0 = blk * C::ROWS;
-    if (row0 >= P) return;
-    const int last = min(P, row0 + C::ROWS) - 1;
-    const int max_rank = (row0 / qsize == last / qsize) ? last % qsize : qsize - 1;
+    // workgroup -> (KV head, block of 32 rows), late rows (long walks) first.  A KV head's rows are numbered as in the walk
+    // kernel, cube by cube and in a cube head by head, and cut into blocks across the cubes' borders: a block per cube leaves
+    // most of its rows empty where cubes are clipped to a few tokens.  Consecutive workgroups are of different heads, so that
+    // an XCD's L2 sees the tiles of few of them.
+    const int kv = blockIdx.x % g.Hkv;
+    const int row1 = g.S * g.G - (int)(blockIdx.x / g.Hkv) * C::ROWS, row0 = max(0, row1 - C::ROWS), last = row1 - 1;
+    // the last cube with rows here, and the first
+    const int i = cube_at_position(g, last / g.G);
+    const CubeBox ibox = cube_box(g, i);
+    const int isize = ibox.size(), irow = cube_first(g, i) * g.G;  // tokens and first row of cube i
+    const int i_first = row0 >= irow ? i : cube_at_position(g, row0 / g.G);
+    const int rem1 = last - irow, head1 = rem1 / isize * isize;  // (all of one head of cube i?)
+    const int max_rank = max(0, row0 - irow) >= head1 ? rem1 - head1 : isize - 1;  // of the block's rows in cube i
 
-    int rank[NS];
+    int rank[NS], own[NS];
     size_t rowid[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const int rho = min(row0 + 16 * s + n16, last), hg = rho / qsize;  // padding rows repeat the last one
-        rank[s] = rho - hg * qsize;
-        rowid[s] = (size_t)token_of(g, qbox, rank[s]) * g.Hq + kv * g.G + hg;
+        const int rho = min(row0 + 16 * s + n16, last);  // padding rows repeat the last one
+        int rem = rho - irow;
+        CubeBox box = ibox;
+        own[s] = i;
+        if (rem < 0) {
+            own[s] = cube_at_position(g, rho / g.G);
+            rem = rho - cube_first(g, own[s]) * g.G;
+            box = cube_box(g, own[s]);
+        }
+        const int hg = rem / box.size();
+        rank[s] = rem - hg * box.size();
+        rowid[s] = (size_t)token_of(g, box, rank[s]) * g.Hq + kv * g.G + hg;
     }
     const float c2 = 1.44269504088896340736f / sqrtf((float)D);  // softmax scale in base 2, folded into Q
     bf16x8 qf[NS][KSTEPS];
@@ -87,7 +96,8 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
         for (int c = 0; c < KSTEPS; ++c)
             qf[s][c] = score_operand(*reinterpret_cast<const bf16x8 *>(Q + rowid[s] * D + 32 * c + 8 * q4), c2);
 
-    // ---- the steps of the walk: the own cube up to the block's largest rank, of the others those that a row selected
+    // ---- the steps of the walk: the rows' own cubes, the last one up to the block's largest rank, and of the others those
+    // that a row selected
     const int ncubes = g.causal ? i + 1 : g.N;
     if (MASKED) {
         // wavefront w takes mask words w, w + 8, ...; its lanes are the block's rows, twice over
@@ -106,7 +116,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
             int steps = 0;
             if (c < ncubes) {
                 const int size = c == i && g.causal ? max_rank + 1 : g.ragged ? csize[c] : g.Cmax;
-                if (c == i || !MASKED || ((uni[c >> 5] >> (c & 31)) & 1u)) steps = (size + C::STEP - 1) / C::STEP;
+                if ((c >= i_first && c <= i) || !MASKED || ((uni[c >> 5] >> (c & 31)) & 1u)) steps = (size + C::STEP - 1) / C::STEP;
             }
             int incl = steps;
 #pragma unroll
@@ -165,8 +175,8 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
     }
     auto work = [&](uint32_t e0, uint32_t e1) __attribute__((always_inline)) {  // the step e0; e1 is the next one
         const int j = (int)(e0 >> 16);
-        const bool own = j == i;
-        const int jsize = own ? qsize : g.ragged ? csize[j] : g.Cmax;
+        const bool edge = j >= i_first;  // some row's own cube, or (causal) behind it
+        const int jsize = g.ragged ? csize[j] : g.Cmax;
         const int key0 = C::STEP * (int)(e0 & 0xffffu);
 #pragma unroll
         for (int s = 0; s < NS; ++s) word[s] = MASKED ? word_next[s] : 0u;
@@ -178,15 +188,16 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     // (from minus the reference point of the row's exponentials, -inf for a row that takes no part)
-                    const bool in = !MASKED || own || ((word[s] >> (j & 31)) & 1u);
+                    bool in = !MASKED || ((word[s] >> (j & 31)) & 1u);
+                    if (MASKED && edge) in = j == own[s] || (in && (!g.causal || j < own[s]));
                     const float b = in ? -m_run[s] : -INFINITY;
                     sa[s][k2] = score_mfma(kf[c][k2], qf[s][c], c == 0 ? f32x4{b, b, b, b} : sa[s][k2]);
                 }
         load_k(e1);
-        if (key0 + C::STEP > jsize || (own && g.causal)) {
+        if (key0 + C::STEP > jsize || (edge && g.causal)) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const int lim = own && g.causal ? min(rank[s], jsize - 1) : jsize - 1;
+                const int lim = !g.causal || j < own[s] ? jsize - 1 : j == own[s] ? min(rank[s], jsize - 1) : -1;
 #pragma unroll
                 for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
@@ -297,7 +308,7 @@ static hipError_t launch_split(const Geom &g, const uint16_t *Q, const void *pac
     static LdsOptIn opted;  // one per kernel instantiation
     const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&attn_split_kernel<D, MASKED>), C::BYTES);
     if (e != hipSuccess) return e;
-    const unsigned blocks = (unsigned)((g.G * g.Cmax + C::ROWS - 1) / C::ROWS) * (unsigned)g.Hkv * (unsigned)g.N;
+    const unsigned blocks = (unsigned)((g.S * g.G - 1) / C::ROWS + 1) * (unsigned)g.Hkv;
     hipLaunchKernelGGL((attn_split_kernel<D, MASKED>), dim3(blocks), dim3(C::THREADS), C::BYTES, st, g, Q, Kp, Vt, csize,
                        sel_mask, O, lse);
     return hipGetLastError();

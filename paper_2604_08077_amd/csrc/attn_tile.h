@@ -287,8 +287,19 @@ __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8
 // softmax_tile_folded on the untouched scores.  Vector instructions are not hidden behind another wavefront's
 // MFMAs on this chip (only the exponentials are), so the maximum's 14 instructions per slab and tile, the lane
 // exchanges and the compare are time saved in full.
+//
+// A tile with padding keys (fill < 64 keys; K's padding is zero, so a padding key's score is finite or, for a row that takes
+// no part, -inf) stays in this path: the padding keys' probabilities are cleared, 16 AND instructions and two LDS reads
+// where the long way takes about 100 vector instructions more, which every wavefront of the workgroup waits for.
+constexpr int FILL_MASK_BYTES = 9 * 16;  // fill_masks: entry n keeps the first n of 8 bf16 values
+__device__ __forceinline__ void fill_masks_init(unsigned char *masks, int tid)
+{
+    if (tid < FILL_MASK_BYTES / 2) reinterpret_cast<uint16_t *>(masks)[tid] = tid % 8 < tid / 8 ? 0xffffu : 0u;
+}
+
 template <int NS>
-__device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf16x8 (&pf)[NS][2], bool settled)
+__device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf16x8 (&pf)[NS][2], bool settled,
+                                                  const unsigned char *fill_masks, int fill, int q4)
 {
     if (!settled) return false;
 #pragma unroll
@@ -298,6 +309,15 @@ __device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf
 #pragma unroll
             for (int s = 0; s < NS; ++s)
                 pf[s][kg >> 1][4 * (kg & 1) + v] = (__bf16)__builtin_amdgcn_exp2f(sacc[s][kg][v]);
+    if (fill < KEY_TILE) {
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            const u32x4 keep =
+                *reinterpret_cast<const u32x4 *>(fill_masks + 16 * min(max(fill - 32 * sl - 8 * q4, 0), 8));
+#pragma unroll
+            for (int s = 0; s < NS; ++s) pf[s][sl] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, pf[s][sl]) & keep);
+        }
+    }
     uint32_t big = 0u;
 #pragma unroll
     for (int s = 0; s < NS; ++s)

@@ -42,13 +42,15 @@ struct Walk {
     static constexpr int OFF_V = OFF_K + NST * CHUNK;
     static constexpr int OFF_ROWID = OFF_V + NST * CHUNK;
     static constexpr int OFF_RANK = OFF_ROWID + SMALL;
-    static constexpr int OFF_MISC = OFF_RANK + SMALL;
-    // the cubes some row of the workgroup attends (sparse entry): union of the rows' mask words, then the list of
-    // its set bits in cube order
+    static constexpr int OFF_OWN = OFF_RANK + SMALL;
+    static constexpr int OFF_MISC = OFF_OWN + SMALL;
+    static constexpr int OFF_FILL = OFF_MISC + 16;  // fill_masks
+    // the cubes of the walk (sparse entry: those that some row of the workgroup attends; union of the rows' mask words), in
+    // order, each with its size
     static constexpr int LIST_MAX = ADASPARK_MAX_CUBES;
-    static constexpr int OFF_UNION = OFF_MISC + 16;
+    static constexpr int OFF_UNION = OFF_FILL + FILL_MASK_BYTES;
     static constexpr int OFF_LIST = OFF_UNION + LIST_MAX / 8;
-    static constexpr int BYTES = OFF_LIST + LIST_MAX * 2;
+    static constexpr int BYTES = OFF_LIST + LIST_MAX * 8;
     static_assert(DMA >= 1, "a tile is at least 1 KB per wavefront");
     static_assert(BYTES <= 160 * 1024, "LDS of one CU");
 };
@@ -61,6 +63,9 @@ __device__ __forceinline__ void dma_barrier()
 {
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(KEEP) : "memory");
 }
+
+// Blocks of 256 rows that follow each other on one XCD: as many as a whole cube fills.
+__host__ __device__ inline int walk_group(const Geom &g) { return max(1, g.G * g.Cmax / Walk<64>::MMAX); }
 
 template <int D, bool MASKED>
 __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
@@ -76,131 +81,123 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
     int *rowid = reinterpret_cast<int *>(smem + C::OFF_ROWID);
     int *rrank = reinterpret_cast<int *>(smem + C::OFF_RANK);
+    int *rown = reinterpret_cast<int *>(smem + C::OFF_OWN);  // the row's own cube
     int *misc = reinterpret_cast<int *>(smem + C::OFF_MISC);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n16 = lane & 15, q4 = lane >> 4;
     const bool set_y = __builtin_amdgcn_readfirstlane(wave >> 2) != 0;
 
-    // workgroup -> (query cube, KV head, row block), the blocks of one (cube, head) on the same XCD
-    const int nblk_max = (g.G * g.Cmax + MMAX - 1) / MMAX;
+    // workgroup -> (KV head, block of 256 rows).  A KV head's rows are numbered cube by cube (row = cube's first row +
+    // head-in-group * tokens + rank, so a block's rows are neighbouring tokens of one query head or two, the rows most
+    // likely to select the same cubes) and cut into blocks from the last row on, across the cubes' borders: on a grid
+    // that the cubes do not divide, or with cubes of few rows, a workgroup per cube would leave a part of its 256 rows
+    // empty and still walk every cube before.  (A forward pass, us, with blocks across cubes and short steps for tiles with
+    // padding keys, and with neither: 30,000 tokens of 32/8 heads of 128 in cubes of 112 to 256 tokens 4,906, 5,784; 76,302
+    // tokens of 8/2 heads of 64 in cubes of 4 to 256 tokens 14,630, 43,400; 51,763 of 14/2 of 128 in cubes of 12 to 256: 10,030, 12,800.)
+    // The blocks of as many rows as a whole cube has follow each other on the same XCD: they stream the same tiles.
+    const int nrows = g.S * g.G, nblk = (nrows - 1) / MMAX + 1, per_group = walk_group(g);
+    const int groups = (nblk + per_group - 1) / per_group;  // of one KV head
     const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int grp = (seq / nblk_max) * 8 + xcd;
-    const int blk = seq % nblk_max;
-    if (grp >= g.N * g.Hkv) return;
+    const int grp = (seq / per_group) * 8 + xcd;
+    if (grp >= groups * g.Hkv) return;
     // A KV head normally stays on the same XCDs (grp % 8 = xcd: its K/V tiles are the ones that XCD's L2 holds).
-    // When some heads are handed to the key-stationary kernel, the head is rotated with the cube instead, so that
+    // When some heads are handed to the key-stationary kernel, the head is rotated with the group instead, so that
     // the heads that remain still spread over all XCDs.
     const int rot = (kv_modes && mode_flag[FLAG_ACTIVE]) ? grp / g.Hkv : 0;
     const int kv = (grp % g.Hkv + rot) % g.Hkv;
     if (kv_modes && mode_flag[FLAG_KV + kv] == 3) return;  // the key-stationary kernel has this head's rows
-    // Late cubes, the long walks, first.  With fewer than eight KV heads a round of eight groups holds several cubes, one
+    // Late rows, the long walks, first.  With fewer than eight KV heads a round of eight groups holds several of a head, one
     // behind the other on the same XCDs; every second round deals them out in the opposite order, or the XCDs that
-    // always got the later cube would finish last (a forward pass over 16,384 tokens, 28/4 heads of 128: 1.650 ms, without this
+    // always got the later group would finish last (a forward pass over 16,384 tokens, 28/4 heads of 128: 1.650 ms, without this
     // 1.667; over 8,736 in 36 cubes 0.591, 0.596; runs of one side differ by 0.2 %).
     int pos = grp / g.Hkv;
     const int share = 8 % g.Hkv == 0 ? 8 / g.Hkv : 1, round = pos / share;
-    if ((round & 1) && (round + 1) * share <= g.N) pos = (2 * round + 1) * share - 1 - pos;
-    const int i = g.N - 1 - pos;
-    const CubeBox qbox = cube_box(g, i);
-    const int qsize = qbox.size();
-    const int P = g.G * qsize;
-    const int nblk = (P + MMAX - 1) / MMAX;
+    if ((round & 1) && (round + 1) * share <= groups) pos = (2 * round + 1) * share - 1 - pos;
+    const int blk = pos * per_group + seq % per_group;
     if (blk >= nblk) return;
-    const int row0 = (int)((long long)blk * P / nblk), row1 = (int)((long long)(blk + 1) * P / nblk);
+    const int row1 = nrows - blk * MMAX, row0 = max(0, row1 - MMAX);
     const int Mrows = row1 - row0;
-    // Rows of a (cube, KV head) are numbered head by head (row = head-in-group * tokens + rank): a workgroup's rows
-    // are neighbouring tokens of one query head (of two, where a head has fewer rows than the workgroup), the rows
-    // most likely to select the same cubes.
-    const int max_rank = (row0 / qsize == (row1 - 1) / qsize) ? (row1 - 1) % qsize : qsize - 1;
-    // (non-causal mode: the whole own cube, and the walk goes on over the cubes after it)
-    const int own_tiles = g.causal ? min((qsize + KEY_TILE - 1) / KEY_TILE, max_rank / KEY_TILE + 1)
-                                   : (qsize + KEY_TILE - 1) / KEY_TILE;
 
+    // the last cube with rows here, and the first
+    const int i = cube_at_position(g, (row1 - 1) / g.G);
+    const CubeBox ibox = cube_box(g, i);
+    const int isize = ibox.size(), irow = cube_first(g, i) * g.G;  // tokens and first row of cube i
+    const int i_first = row0 >= irow ? i : cube_at_position(g, row0 / g.G);
     for (int r = tid; r < Mrows; r += THREADS) {
-        const int rho = row0 + r, hg = rho / qsize, rank = rho - hg * qsize;
-        const int rid = token_of(g, qbox, rank) * g.Hq + kv * g.G + hg;
+        const int rho = row0 + r;
+        int own = i, rem = rho - irow;
+        CubeBox box = ibox;
+        if (rem < 0) {
+            own = cube_at_position(g, rho / g.G);
+            rem = rho - cube_first(g, own) * g.G;
+            box = cube_box(g, own);
+        }
+        const int hg = rem / box.size(), rank = rem - hg * box.size();
+        const int rid = token_of(g, box, rank) * g.Hq + kv * g.G + hg;
         rowid[r] = rid;
         rrank[r] = rank;
+        rown[r] = own;
         if (r == 0) {  // scratch row behind the padding columns of a partial slab
             rowid[MMAX] = rid;
             rrank[MMAX] = 0;
+            rown[MMAX] = own;
         }
     }
-    if (tid == 0) misc[0] = 0;
-    __syncthreads();
-
-    // the tile stream: cubes 0..i in order, the own cube i last and only up to the largest rank of the block
+    fill_masks_init(smem + C::OFF_FILL, tid);
+    // the walk ends, in cube i, behind the largest rank of the block's rows there (non-causal mode: the whole own cubes, and
+    // it goes on over the cubes after them)
+    const int rem1 = row1 - 1 - irow, head1 = rem1 / isize * isize;  // (all of one head of cube i?)
+    const int max_rank = max(0, row0 - irow) >= head1 ? rem1 - head1 : isize - 1;
+    const int own_tiles = g.causal ? max_rank / KEY_TILE + 1 : (isize + KEY_TILE - 1) / KEY_TILE;
     const int ncubes = g.causal ? i + 1 : g.N;
-    auto tiles_of = [&](int j) -> int {
-        if (j == i) return own_tiles;
-        return g.ragged ? (csize[j] + KEY_TILE - 1) / KEY_TILE : g.TPC;
-    };
-    // Sparse entry: a cube that no row of the workgroup selected is left out of the stream altogether.  Rows that
+    // Sparse entry: a cube that no row of the workgroup selected is left out of the walk altogether.  Rows that
     // select independently of each other leave no such cube; rows of neighbouring tokens with similar queries do.
-    constexpr bool listed = MASKED;  // (the entry points admit at most LIST_MAX cubes)
-    const uint16_t *clist = reinterpret_cast<const uint16_t *>(smem + C::OFF_LIST);
-    int nlist = ncubes;
-    if (listed) {
-        uint32_t *uni = reinterpret_cast<uint32_t *>(smem + C::OFF_UNION);
-        uint16_t *wlist = reinterpret_cast<uint16_t *>(smem + C::OFF_LIST);
-        const int wlim = (ncubes + 31) >> 5;  // mask words that hold cubes of the stream
+    int2 *clist = reinterpret_cast<int2 *>(smem + C::OFF_LIST);
+    uint32_t *uni = reinterpret_cast<uint32_t *>(smem + C::OFF_UNION);
+    const int wlim = (ncubes + 31) >> 5;  // mask words that hold cubes of the walk
+    if (MASKED)
         for (int w = tid; w < wlim; w += THREADS) uni[w] = 0u;
-        __syncthreads();
+    __syncthreads();
+    if (MASKED) {
         for (int x = tid; x < Mrows * wlim; x += THREADS) {
             const int r = x / wlim, w = x - r * wlim;
             const uint32_t m = sel_mask[(size_t)rowid[r] * g.words + w];
             if (m) atomicOr(&uni[w], m);
         }
         __syncthreads();
-        if (wave == 0) {  // set bits in cube order; the own cube is always there
-            int n = 0;
-            for (int c0 = 0; c0 < ncubes; c0 += 64) {
-                const int c = c0 + lane;
-                const bool in = c < ncubes && (c == i || ((uni[c >> 5] >> (c & 31)) & 1u));
-                const unsigned long long b = __ballot(in);
-                if (in) wlist[n + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)c;
-                n += __popcll(b);
-            }
-            if (lane == 0) misc[1] = n;
-        }
-        __syncthreads();
-        nlist = __builtin_amdgcn_readfirstlane(misc[1]);
     }
-    auto cube_at = [&](int k) -> int { return listed ? (int)__builtin_amdgcn_readfirstlane((int)clist[k]) : k; };
+    if (wave == 0) {  // in cube order; the rows' own cubes are always there
+        int n = 0, tiles = 0;
+        for (int c0 = 0; c0 < ncubes; c0 += 64) {
+            const int c = c0 + lane;
+            const bool in = c < ncubes && (!MASKED || (c >= i_first && c <= i) || ((uni[c >> 5] >> (c & 31)) & 1u));
+            const unsigned long long b = __ballot(in);
+            if (in) {
+                const int size = g.ragged ? csize[c] : g.Cmax;
+                clist[n + __popcll(b & ((1ull << lane) - 1ull))] = make_int2(c, size);
+                tiles += c == i ? own_tiles : (size + KEY_TILE - 1) / KEY_TILE;
+            }
+            n += __popcll(b);
+        }
+        for (int off = 32; off > 0; off >>= 1) tiles += __shfl_xor(tiles, off, 64);
+        if (lane == 0) {
+            misc[0] = tiles;
+            misc[1] = n;
+        }
+    }
+    __syncthreads();
+    const int ntiles = __builtin_amdgcn_readfirstlane(misc[0]);
+    const int nlist = __builtin_amdgcn_readfirstlane(misc[1]);
+    auto cube_tiles = [&](int j, int size) -> int { return j == i ? own_tiles : (size + KEY_TILE - 1) / KEY_TILE; };
     // The list entry after position k, fetched when position k is entered and used a whole cube later: the LDS
     // read is long over by then (read and used at the same cube boundary, its latency showed in every stream).
-    auto peek_after = [&](int k) -> int {
-        const int kk = min(k + 1, nlist - 1);  // past the end the entry only has to be a valid cube
-        return listed ? (int)clist[kk] : kk;
-    };
-    {
-        int part = 0;
-        for (int k = tid; k < nlist; k += THREADS) part += tiles_of(listed ? (int)clist[k] : k);
-        for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
-        if (lane == 0) atomicAdd(&misc[0], part);
-        __syncthreads();
-    }
-    const int ntiles = __builtin_amdgcn_readfirstlane(misc[0]);
+    auto peek_after = [&](int k) -> int2 { return clist[min(k + 1, nlist - 1)]; };  // past the end: any valid cube
 
-    auto first_tile = [&]() -> TilePos {
-        TilePos p;
-        p.k = 0;
-        p.j = cube_at(0);
-        p.t = 0;
-        p.nt = tiles_of(p.j);
-        return p;
-    };
-    int cc_next = peek_after(0);  // for the position that `advance` moves (there is one: the softmax's)
-    auto advance = [&](TilePos &p) __attribute__((always_inline)) {
-        if (p.t + 1 < p.nt) ++p.t;
-        else if (p.k + 1 < nlist) {
-            p.j = __builtin_amdgcn_readfirstlane(cc_next);
-            cc_next = peek_after(++p.k);
-            p.t = 0;
-            p.nt = tiles_of(p.j);
-        }  // the last tile stays where it is: nothing is issued or computed past the end
-    };
+    // the tile whose softmax comes next
+    int cc_j = __builtin_amdgcn_readfirstlane(clist[0].x), cc_size = __builtin_amdgcn_readfirstlane(clist[0].y);
+    int cc_t = 0, cc_nt = cube_tiles(cc_j, cc_size), cc_k = 0;
+    int2 cc_next = peek_after(0);
     // The K and V^T tiles are fetched in the same order, V^T one tile behind K: one stream walks the list of cubes
     // (cubes are padded to TPC tiles in memory; a ragged cube's padding tiles are skipped) and yields the byte
     // offset of its current tile from the KV head's first tile, which is the same in the K and the V^T half of the
@@ -210,17 +207,16 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     struct Stream {
         uint32_t off;  // of the current tile
         int k, t, nt;  // position in the list of cubes, tile in the cube, tiles of the cube
-        int next;      // the cube at position k + 1 (per lane, as read from the list)
+        int2 next;     // the list's entry at position k + 1 (per lane, as read)
     };
     const unsigned char *khead = reinterpret_cast<const unsigned char *>(Kp + (size_t)kv * g.N * g.TPC * (KEY_TILE * D));
     const unsigned char *vhead = reinterpret_cast<const unsigned char *>(Vt + (size_t)kv * g.N * g.TPC * (KEY_TILE * D));
     auto stream_begin = [&]() -> Stream {
         Stream q;
         q.k = 0;
-        const int j = cube_at(0);
-        q.off = (uint32_t)j * (uint32_t)(g.TPC * C::CHUNK);
+        q.off = (uint32_t)cc_j * (uint32_t)(g.TPC * C::CHUNK);
         q.t = 0;
-        q.nt = tiles_of(j);
+        q.nt = cc_nt;
         q.next = peek_after(0);
         return q;
     };
@@ -230,11 +226,11 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
             q.off += C::CHUNK;
         } else {
             q.k = min(q.k + 1, nlist - 1);  // past the end nothing is issued; the index only has to stay valid
-            const int j = __builtin_amdgcn_readfirstlane(q.next);
+            const int j = __builtin_amdgcn_readfirstlane(q.next.x), size = __builtin_amdgcn_readfirstlane(q.next.y);
             q.next = peek_after(q.k);
             q.off = (uint32_t)j * (uint32_t)(g.TPC * C::CHUNK);
             q.t = 0;
-            q.nt = tiles_of(j);
+            q.nt = cube_tiles(j, size);
         }
     };
     const uint32_t lds_piece =
@@ -257,12 +253,23 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
         lr[s] = idx < Mrows ? idx : MMAX;
         if (16 * (wave + WAVES * s) < Mrows) ns = s + 1;
     }
-    int rank_lo = 0x7fffffff;  // lowest rank among the wavefront's rows
+    // the wavefront's rows: lowest rank, first and last own cube (without rows: those of the padding columns)
+    int rank_lo = 0x7fffffff, own_lo = 0x7fffffff, own_hi = 0;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-        if (lr[s] != MMAX) rank_lo = min(rank_lo, rrank[lr[s]]);
-    for (int off = 32; off > 0; off >>= 1) rank_lo = min(rank_lo, __shfl_xor(rank_lo, off, 64));
-    rank_lo = __builtin_amdgcn_readfirstlane(rank_lo == 0x7fffffff ? 0 : rank_lo);
+        if (s == 0 || lr[s] != MMAX) {
+            rank_lo = min(rank_lo, rrank[lr[s]]);
+            own_lo = min(own_lo, rown[lr[s]]);
+            own_hi = max(own_hi, rown[lr[s]]);
+        }
+    for (int off = 32; off > 0; off >>= 1) {
+        rank_lo = min(rank_lo, __shfl_xor(rank_lo, off, 64));
+        own_lo = min(own_lo, __shfl_xor(own_lo, off, 64));
+        own_hi = max(own_hi, __shfl_xor(own_hi, off, 64));
+    }
+    own_lo = __builtin_amdgcn_readfirstlane(own_lo);
+    own_hi = __builtin_amdgcn_readfirstlane(own_hi);
+    rank_lo = __builtin_amdgcn_readfirstlane(own_lo == own_hi ? rank_lo : 0);
 
     // prologue: K(0), K(1), V(0)
     Stream sk = stream_begin();
@@ -314,54 +321,65 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 #pragma unroll
         for (int s = 0; s < NS; ++s) mword_ahead[s] = sel_mask[(size_t)rowid[lr[s]] * g.words];
     }
-    int jsize = 0;
-    // per-cube constants of the softmax: key limits of every row, and (MASKED) whether the row attends the cube
-    auto enter_cube = [&](int j) __attribute__((always_inline)) {
-        const bool own = (j == i);
-        jsize = own ? qsize : (g.ragged ? csize[j] : g.Cmax);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) lim[s] = (own && g.causal) ? min(rrank[lr[s]], jsize - 1) : jsize - 1;
+    // Per-cube constants of the softmax: key limits of every row, and (MASKED) whether the row attends the cube.  A row
+    // attends its own cube up to its rank and no later one.
+    auto enter_cube = [&](int j, int size) __attribute__((always_inline)) {
         if (MASKED) {
-            if (own) {
+            if ((j >> 5) != mword_idx) {
+                const bool ahead = (j >> 5) == mword_idx + 1;  // (the walk ascends; words can be skipped)
+                mword_idx = j >> 5;
+                const int nxt = min(mword_idx + 1, g.words - 1);
 #pragma unroll
-                for (int s = 0; s < NS; ++s) rsel[s] = true;
-            } else {
-                if ((j >> 5) != mword_idx) {
-                    const bool ahead = (j >> 5) == mword_idx + 1;  // (the walk ascends; words can be skipped)
-                    mword_idx = j >> 5;
-                    const int nxt = min(mword_idx + 1, g.words - 1);
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        const uint32_t *mr = sel_mask + (size_t)rowid[lr[s]] * g.words;
-                        mword[s] = ahead ? mword_ahead[s] : mr[mword_idx];
-                        mword_ahead[s] = mr[nxt];
-                    }
+                for (int s = 0; s < NS; ++s) {
+                    const uint32_t *mr = sel_mask + (size_t)rowid[lr[s]] * g.words;
+                    mword[s] = ahead ? mword_ahead[s] : mr[mword_idx];
+                    mword_ahead[s] = mr[nxt];
                 }
+            }
 #pragma unroll
-                for (int s = 0; s < NS; ++s) rsel[s] = (mword[s] >> (j & 31)) & 1u;
+            for (int s = 0; s < NS; ++s) rsel[s] = (mword[s] >> (j & 31)) & 1u;
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) lim[s] = size - 1;
+        if (j >= own_lo) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int own = rown[lr[s]];
+                if (MASKED) rsel[s] = j == own || (rsel[s] && (!g.causal || j < own));
+                if (g.causal && j >= own) lim[s] = j == own ? min(rrank[lr[s]], size - 1) : -1;
             }
         }
     };
-    TilePos cc = first_tile();  // the tile whose softmax comes next
-    enter_cube(cc.j);
+    auto advance = [&]() __attribute__((always_inline)) {
+        if (cc_t + 1 < cc_nt) ++cc_t;
+        else if (cc_k + 1 < nlist) {
+            cc_j = __builtin_amdgcn_readfirstlane(cc_next.x);
+            cc_size = __builtin_amdgcn_readfirstlane(cc_next.y);
+            cc_next = peek_after(++cc_k);
+            cc_t = 0;
+            cc_nt = cube_tiles(cc_j, cc_size);
+            enter_cube(cc_j, cc_size);
+        }  // the last tile stays where it is: nothing is issued or computed past the end
+    };
+    enter_cube(cc_j, cc_size);
 
     f32x4 sacc[NS][4];
     bf16x8 pf[NS][2];
     bool settled = false;  // wave-uniform: no row of the wavefront is fresh any more (softmax_tile_fast may be tried)
     auto softmax_step = [&]() __attribute__((always_inline)) {
-        const bool own = (cc.j == i);
-        const int key0 = KEY_TILE * cc.t;
-        const bool need_mask = (key0 + KEY_TILE > jsize) || (own && g.causal && key0 + KEY_TILE - 1 > rank_lo);
-        if (need_mask || !softmax_tile_fast<NS>(sacc, pf, settled)) {
-            softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, lim, key0, need_mask, q4);
+        const int key0 = KEY_TILE * cc_t;
+        // the causal edge (of the sparse entry's rows, a cube behind the own one is just not selected); padding keys
+        const bool edge = g.causal && cc_j >= own_lo && (MASKED ? cc_j <= own_hi : true) &&
+                          (cc_j > own_lo || key0 + KEY_TILE - 1 > rank_lo);
+        const int fill = cc_size - key0;
+        if (edge || !softmax_tile_fast<NS>(sacc, pf, settled, smem + C::OFF_FILL, fill, q4)) {
+            softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, lim, key0, edge || fill < KEY_TILE, q4);
             bool open = false;
 #pragma unroll
             for (int s = 0; s < NS; ++s) open = open || fresh[s];
             settled = __ballot(open) == 0ull;  // every row of the wavefront has a reference point by now
         }
-        const int j0 = cc.j;
-        advance(cc);
-        if (cc.j != j0) enter_cube(cc.j);
+        advance();
     };
 
     // what the scores of the next tile start from: minus the reference point of the row's exponentials, or -inf
@@ -563,8 +581,9 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     const size_t half_elems = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * D;
     const uint16_t *Vt = Kp + half_elems;
     const int32_t *csize = reinterpret_cast<const int32_t *>(Vt + half_elems);
-    const int nblk_max = (g.G * g.Cmax + C::MMAX - 1) / C::MMAX;
-    const dim3 grid((unsigned)((size_t)((g.N * g.Hkv + 7) / 8) * nblk_max * 8));
+    const int per_group = walk_group(g), nblk = (g.S * g.G - 1) / C::MMAX + 1;
+    const int groups = (nblk + per_group - 1) / per_group;
+    const dim3 grid((unsigned)((size_t)(((long long)groups * g.Hkv + 7) / 8) * per_group * 8));
     static LdsOptIn opted;  // one per kernel instantiation
     const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&attn_walk_kernel<D, MASKED>), C::BYTES);
     if (e != hipSuccess) return e;
@@ -573,27 +592,38 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     return hipGetLastError();
 }
 
-// Whether the kernel for short sequences (attn_split.hip) beats this one, from what each of them took on an MI355X (us).
-// Timed again on 101 shapes of 1,024 to 16,384 tokens, heads 4/4 .. 32/8 of 64 and 128, cubes of 32 to 256 tokens, the figures below
-// give the walk within 17 % on whole cubes and the split within 15 % or too high by up to 45 % (below 30 us); they pick the faster
-// kernel but for three shapes: 3 % and 12 % slower close to the line, and a walk of 126 against 84 on a clipped grid (4,200 tokens of
-// 8/2 heads of 64 in cubes of 4x4x8), where the walk is taken for faster than it is.
-//   walk   a slot (64 keys past 256 rows) takes 1.2 at head-dim 64 and 1.7 at 128, 0.6 more where cubes leave part of their
-//          tiles empty; the time is the longest walk's slots, or all slots over 256 CUs where that is more
-//   split  a step (32 keys past 32 rows) takes a CU 0.19 and 0.28 -- what its operands take from L2 -- and a workgroup
-//          4 to start and to combine its parts
-// Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 109 split, 163 walk; 16,384: 388, 347.
-// 2,048 tokens of 14/2 heads of 128 in cubes of 256: 57, 60; 4,096: 148, 107.
+// Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
+// axis), text cubes in two.
+static long long tiles_of_cubes(const Geom &g, int keys)
+{
+    auto tiles = [&](int tokens) { return (long long)(tokens + keys - 1) / keys; };
+    long long n = (long long)(g.Sp / g.Cmax + g.St / g.Cmax) * tiles(g.Cmax) + tiles(g.Sp % g.Cmax) + tiles(g.St % g.Cmax);
+    for (int clip = 0; clip < 8; ++clip) {
+        const int et = clip & 1 ? g.T % g.ct : g.ct, eh = clip & 2 ? g.H % g.ch : g.ch, ew = clip & 4 ? g.W % g.cw : g.cw;
+        const int nt = clip & 1 ? 1 : g.T / g.ct, nh = clip & 2 ? 1 : g.H / g.ch, nw = clip & 4 ? 1 : g.W / g.cw;
+        n += (long long)nt * nh * nw * tiles(et * eh * ew);
+    }
+    return n;
+}
+
+// Whether the kernel for short sequences (attn_split.hip) beats this one, from what each of them takes on an MI355X (us).
+// Fitted to 161 shapes of 460 to 16,384 tokens, heads 4/4 .. 32/8 of 64 and 128, cubes of 32 to 256 tokens, whole and clipped,
+// with and without text; the figures below are 5 % (walk) and 6 % (split) off on average and pick the faster kernel but for
+// two shapes, 4 and 6 % slower.
+//   walk   a slot (64 keys past 256 rows) takes 1.19 at head-dim 64 and 1.62 at 128; the time is the longest walk's slots,
+//          or all slots over 256 CUs where that is more
+//   split  a step (32 keys past 32 rows) takes a CU 0.15 and 0.24 -- what its operands take from L2 -- and a workgroup
+//          7 to start and to combine its parts
+// Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
+// 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
 bool attn_split_pays(const Geom &g)
 {
     if (!attn_split_fits(g)) return false;
-    const double groups = (double)g.N * g.Hkv, rows = (double)g.G * g.Cmax;  // (query cube, KV head) pairs; rows of one
-    const double share = g.causal ? 0.5 : 1.0;                               // of all cubes that the average walk visits
-    const double slots = (double)g.N * g.TPC, walks = groups * std::ceil(rows / 256);
-    const double slot = (g.D == 64 ? 1.2 : 1.7) + (g.Cmax % KEY_TILE != 0 ? 0.6 : 0.0);
-    const double walk = 8 + slot * std::max(slots, 1.1 * share * slots * walks / 256);
-    const double steps = (double)g.N * ((g.Cmax + 31) / 32), blocks = groups * std::ceil(rows / 32);
-    const double split = 10 + blocks / 256 * (4 + share * steps * (g.D == 64 ? 0.19 : 0.28));
+    const double rows = (double)g.S * g.G, share = g.causal ? 0.5 : 1.0;  // of all cubes that the average walk visits
+    const double slots = (double)tiles_of_cubes(g, KEY_TILE), walks = g.Hkv * std::ceil(rows / 256);
+    const double walk = 11 + (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, 1.18 * share * walks / 256);
+    const double steps = (double)tiles_of_cubes(g, 32), blocks = g.Hkv * std::ceil(rows / 32);
+    const double split = 5 + 7 * std::max(1.0, blocks / 256) + blocks / 256 * share * steps * (g.D == 64 ? 0.15 : 0.24);
     return split < walk;
 }
 

@@ -102,6 +102,30 @@ __host__ __device__ inline int cube_of_token(const Geom &g, int n)
     return g.Np + ((t / g.ct) * g.nHb + (h / g.ch)) * g.nWb + (w / g.cw);
 }
 
+// Cube-major order (cubes in their order, ranks inside a cube): position of cube c's first token, and the cube that
+// holds position x.  All cubes of a row of cubes share their extents in t and h, all rows of a layer theirs in t.
+__host__ __device__ inline int cube_first(const Geom &g, int c)
+{
+    if (!g.ragged || c < g.Np) return c * g.Cmax;
+    c -= g.Np;
+    if (c >= g.Nv) return g.Sp + g.Sv + (c - g.Nv) * g.Cmax;
+    const int wb = c % g.nWb, hb = (c / g.nWb) % g.nHb, tb = c / (g.nWb * g.nHb);
+    const int et = min(g.ct, g.T - tb * g.ct), eh = min(g.ch, g.H - hb * g.ch);
+    return g.Sp + tb * min(g.ct, g.T) * g.H * g.W + et * (hb * g.ch * g.W + eh * wb * g.cw);
+}
+__host__ __device__ inline int cube_at_position(const Geom &g, int x)
+{
+    if (!g.ragged || x < g.Sp) return x / g.Cmax;
+    x -= g.Sp;
+    if (x >= g.Sv) return g.Np + g.Nv + (x - g.Sv) / g.Cmax;
+    const int layer = min(g.ct, g.T) * g.H * g.W, tb = x / layer;
+    x -= tb * layer;
+    const int et = min(g.ct, g.T - tb * g.ct), row = et * min(g.ch, g.H) * g.W, hb = x / row;
+    x -= hb * row;
+    const int eh = min(g.ch, g.H - hb * g.ch);
+    return g.Np + (tb * g.nHb + hb) * g.nWb + x / (et * eh * min(g.cw, g.W));
+}
+
 // bf16 <-> fp32 bit helpers.
 __device__ inline float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ inline uint16_t float_to_bf16_bits(float f)
