@@ -165,7 +165,7 @@ int adaspark_internal_short_sequence(const adaspark_shape *shape, int causal)
     if (rc != ADASPARK_OK) return rc;
     Geom g = make_geom(*shape);
     g.causal = causal != 0;
-    return attn_split_pays(g) ? 1 : 0;
+    return attn_split_pays(g, false) ? 1 : 0;
 }
 
 int adaspark_cube_pool(const adaspark_shape *shape, const void *K, float *kbar, void *stream)

@@ -271,7 +271,7 @@ __device__ __forceinline__ void tn_half(const unsigned char *tt, int n16, int q4
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// dQ: workgroup = 256 / KEYS rows (packed row order) of one (cube i, KV head); late cubes (the long walks) first.
+// dQ: workgroup = 256 / KEYS rows of one KV head; late rows (the long walks) first.
 // KEYS = 1: a wavefront per 32 rows.  KEYS = 2: two, wavefronts w and w + 4, each with half of every tile's keys; their
 // sums are added through LDS at the end.  A tile takes a workgroup 1.5 us at head-dim 128 (its MFMAs and exponentials), and
 // with few workgroups the longest walk is the kernel's time: half as long, over twice as many workgroups (dq_keys).
@@ -295,43 +295,57 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     constexpr int PIECES = TILE / 1024;    // 1 KB pieces per tile
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
 
-    const int nblk = (g.Cmax * g.G + ROWS - 1) / ROWS;
-    int kv, slot;
-    if (!bwd_head_slot(blockIdx.x, g.Hkv, g.N * nblk, kv, slot)) return;
-    const int blk = slot % nblk;
-    const int i = g.N - 1 - slot / nblk;
-    const CubeBox box = cube_box(g, i);
-    const int mrows = box.size() * g.G;
-    if (blk * ROWS >= mrows) return;
+    int4 *place = reinterpret_cast<int4 *>(smem + 2 * STAGE);  // [BWD_ROWS] a row's own cube, its rank there, its id
+    uint32_t *uni = reinterpret_cast<uint32_t *>(place + BWD_ROWS);
+    uint16_t *clist = reinterpret_cast<uint16_t *>(uni + ADASPARK_MAX_CUBES / 32);  // the cubes of the walk
+    int *nlist_s = reinterpret_cast<int *>(clist + ADASPARK_MAX_CUBES);
 
+    // A KV head's rows are numbered cube by cube and in a cube head by head, and cut into blocks from the last row on, across
+    // the cubes' borders, as in the forward's walk, and the cubes that no row of the block selected are left out.  (A layer's
+    // training pass, us, with a workgroup's rows in one cube and all cubes before it walked, and so: 6,426 tokens of 32/8 heads
+    // in cubes of up to 128 of which half the heads select few 2,235, 1,796; 6,805 tokens of 28/4 heads, neighbours' queries
+    // alike, on a grid of 9 x 10 2,824, 2,178.)
+    const int nrows = g.S * g.G;
+    int kv, slot;
+    if (!bwd_head_slot(blockIdx.x, g.Hkv, (nrows - 1) / ROWS + 1, kv, slot)) return;
+    const int row1 = nrows - slot * ROWS, row0 = max(0, row1 - ROWS), last = row1 - 1;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n16 = lane & 15, q4 = lane >> 4;
     const int rgroup = wave & (8 / KEYS - 1), khalf = wave / (8 / KEYS);  // 32 rows of the workgroup; half of a tile's keys
 
-    // the wavefront's rows
-    int rr[NS], rank[NS];
-    size_t rowid[NS];
+    // the wavefront's rows: lane l works out row l % 32 (rows past the last one repeat it)
+    const RowAt at = row_at(g, kv, min(row0 + rgroup * 32 + (lane & 31), last));
+    if (lane < 32) place[rgroup * 32 + lane] = make_int4(at.cube, at.rank, at.id, 0);  // (KEYS == 2: the same twice)
     bool valid[NS];
+    int rid[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        valid[s] = row0 + rgroup * 32 + s * 16 + n16 <= last;
+        rid[s] = __shfl(at.id, 16 * s + n16, 64);
+    }
+    // The rows' first mask words (a row's words are shared out among the four lanes that hold it): asked for first, used
+    // last.
+    uint32_t mask0 = 0u;
+    if (MASKED) {
+        if (q4 < g.words) mask0 = sel_mask[(size_t)rid[0] * g.words + q4] | sel_mask[(size_t)rid[1] * g.words + q4];
+        for (int w = tid; w < g.words; w += BWD_THREADS) uni[w] = 0u;
+    }
     bf16x8 qf[NS][KSTEPS], gf[NS][KSTEPS];
     float lse2[NS], delta[NS], psum[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         psum[s] = 0.f;
-        const int r = blk * ROWS + rgroup * 32 + s * 16 + n16;
-        valid[s] = r < mrows;
-        rr[s] = valid[s] ? r : mrows - 1;
-        rank[s] = rr[s] / g.G;
-        rowid[s] = (size_t)token_of(g, box, rank[s]) * g.Hq + kv * g.G + rr[s] % g.G;
 #pragma unroll
         for (int c = 0; c < KSTEPS; ++c) {
-            qf[s][c] = *reinterpret_cast<const bf16x8 *>(Q + rowid[s] * D + 32 * c + 8 * q4);
-            gf[s][c] = *reinterpret_cast<const bf16x8 *>(dO + rowid[s] * D + 32 * c + 8 * q4);
+            qf[s][c] = *reinterpret_cast<const bf16x8 *>(Q + (size_t)rid[s] * D + 32 * c + 8 * q4);
+            gf[s][c] = *reinterpret_cast<const bf16x8 *>(dO + (size_t)rid[s] * D + 32 * c + 8 * q4);
         }
-        lse2[s] = lse2p[rowid[s]];    // -lse * sqrt(D): what the score products start from
-        delta[s] = deltap[rowid[s]];  // minus delta: what the dP products start from
+        lse2[s] = lse2p[rid[s]];    // -lse * sqrt(D): what the score products start from
+        delta[s] = deltap[rid[s]];  // minus delta: what the dP products start from
     }
 
+    auto row_place = [&](int s) -> int4 { return place[rgroup * 32 + s * 16 + n16]; };
     const float c2 = BWD_LOG2E / sqrtf((float)D);  // softmax scale in base 2
 
     // tile stream: cubes 0..i, the tiles of each that hold keys
@@ -352,6 +366,33 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
                          uniform_ptr(src), (uint32_t)(lane * 16));
             }
     };
+
+    // The walk: the rows' own cubes, and of those before them the ones that some row of the block selected.
+    __syncthreads();
+    // the last cube with rows here, and the first
+    const int i = __builtin_amdgcn_readfirstlane(place[last - row0].x), i_first = __builtin_amdgcn_readfirstlane(place[0].x);
+    if (MASKED) {
+        if (mask0) atomicOr(&uni[q4], mask0);
+        for (int w = q4 + 4; 32 * w <= i; w += 4) {
+            const uint32_t m = sel_mask[(size_t)rid[0] * g.words + w] | sel_mask[(size_t)rid[1] * g.words + w];
+            if (m) atomicOr(&uni[w], m);
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        int n = 0;
+        for (int c0 = 0; c0 <= i; c0 += 64) {
+            const int c = c0 + lane;
+            const bool in = c <= i && (!MASKED || c >= i_first || ((uni[c >> 5] >> (c & 31)) & 1u));
+            const unsigned long long b = __ballot(in);
+            if (in) clist[n + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)c;
+            n += __popcll(b);
+        }
+        if (lane == 0) *nlist_s = n;
+    }
+    __syncthreads();
+    const int nlist = __builtin_amdgcn_readfirstlane(*nlist_s);
+    auto entry = [&](int k) -> int { return clist[min(k, nlist - 1)]; };  // past the end: any valid cube
     auto tiles_of = [&](int j) { return (csize[j] + 63) >> 6; };
 
     f32x4 acc[NS][D / 16];
@@ -360,33 +401,56 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 #pragma unroll
         for (int e = 0; e < DT; ++e) acc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    int ij = 0, it = 0, int_ = tiles_of(0);  // next tile to issue
-    issue(0, 0, 0);
-    if (++it == int_) { ++ij; it = 0; int_ = ij <= i ? tiles_of(ij) : 0; }
+    // (a list entry is read when the cube before it is entered: the LDS read is long over when it is used)
+    int inext = entry(1);
+    int ik = 0, ij = __builtin_amdgcn_readfirstlane(entry(0)), it = 0, int_ = tiles_of(ij);  // next tile to issue
+    int issued = ij;  // cube of the tile issued last: where the walk goes on when it is through with its cube
+    auto issue_next = [&](int stage) __attribute__((always_inline)) {
+        if (ik >= nlist) return;
+        issued = ij;
+        issue(stage, ij, it);
+        if (++it == int_) {
+            ++ik;
+            ij = __builtin_amdgcn_readfirstlane(inext);
+            int_ = tiles_of(ij);
+            inext = entry(ik + 1);
+            it = 0;
+        }
+    };
+    issue_next(0);
     int stage = 0;
     uint32_t mw[NS] = {0u, 0u};
-    for (int j = 0; j <= i; ++j) {
-        const int nt = tiles_of(j);
-        const int size_j = csize[j];
+    int mw_idx = -1;
+    for (int k = 0; k < nlist; ++k) {
+        const int j = issued, size_j = csize[j], nt = tiles_of(j);
+        const bool late = j >= i_first;  // some rows' own cube, or behind it
         // What the score products start from: minus the row's log-sum-exp; -inf for a row that did not select cube
-        // j, which then takes no part (probabilities 0)
+        // j, which then takes no part (probabilities 0).  lim: the last key the row attends.
+        if (MASKED && (j >> 5) != mw_idx) {
+            mw_idx = j >> 5;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) mw[s] = sel_mask[(size_t)row_place(s).z * g.words + mw_idx];
+        }
         float le[NS];
+        int lim[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             le[s] = lse2[s];
-            if (MASKED && j < i) {
-                if ((j & 31) == 0) mw[s] = sel_mask[rowid[s] * g.words + (j >> 5)];
-                if (!((mw[s] >> (j & 31)) & 1u)) le[s] = -INFINITY;
+            lim[s] = size_j - 1;
+            if (MASKED && !((mw[s] >> (j & 31)) & 1u)) le[s] = -INFINITY;
+            if (late) {
+                const int4 at = row_place(s);
+                if (j >= at.x) {
+                    le[s] = j == at.x ? lse2[s] : -INFINITY;
+                    lim[s] = at.y;
+                }
             }
         }
         for (int t = 0; t < nt; ++t) {
             tile_barrier();
-            if (ij <= i) {
-                issue(stage ^ 1, ij, it);
-                if (++it == int_) { ++ij; it = 0; int_ = ij <= i ? tiles_of(ij) : 0; }
-            }
+            issue_next(stage ^ 1);
             const unsigned char *kt = smem + stage * STAGE, *vt = kt + TILE, *ktt = vt + TILE;
-            const bool edge = j == i || 64 * t + 64 > size_j;  // the own cube's causal edge, padding keys: few tiles
+            const bool edge = late || 64 * t + 64 > size_j;  // the own cubes' causal edge, padding keys: few tiles
             bf16x8 ds[NS][2];
             auto half = [&](auto hc) __attribute__((always_inline)) {
                 constexpr int H = decltype(hc)::value;
@@ -403,7 +467,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
                                 const int key = kb + 4 * k2 + v;
-                                if (key >= size_j || (j == i && key > rank[s])) sacc[s][k2][v] = -INFINITY;
+                                if (key > lim[s]) sacc[s][k2][v] = -INFINITY;
                             }
                 }
 #pragma unroll
@@ -461,11 +525,12 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     for (int s = 0; s < NS; ++s) {
         const float total = quad_sum(psum[s]);
         if (!valid[s]) continue;
-        if (q4 == 0) lse2p[rowid[s]] = lse2[s] - log2f(total) / c2;
+        const size_t rid = row_place(s).z;
+        if (q4 == 0) lse2p[rid] = lse2[s] - log2f(total) / c2;
         const float scale = 1.0f / (sqrtf((float)D) * total);
 #pragma unroll
         for (int e = 0; e < DT; ++e)
-            *reinterpret_cast<uint2 *>(dQ + rowid[s] * D + 16 * e + 4 * q4) = pack_bf16(acc[s][e] * scale);
+            *reinterpret_cast<uint2 *>(dQ + rid * D + 16 * e + 4 * q4) = pack_bf16(acc[s][e] * scale);
     }
 }
 
@@ -842,7 +907,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
 // 336 (6/2, 128) 1,015, 1,002; 336 (28/4, 128) 315, 304; 384 (8/2, 64) 619, 571; 448 (28/4, 128) 487, 439.
 static int dq_keys(const Geom &g)
 {
-    const long long blocks = (long long)g.N * g.Hkv * ((g.Cmax * g.G + BWD_ROWS - 1) / BWD_ROWS);
+    const long long blocks = (long long)g.Hkv * ((g.S * g.G - 1) / BWD_ROWS + 1);
     return blocks <= DQ_SHARED_BLOCKS ? 2 : 1;
 }
 
@@ -881,8 +946,8 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     constexpr int TILE = 64 * D * 2;
 
     const int keys = dq_keys(g), rows_q = BWD_ROWS / keys;
-    const dim3 grid_q(bwd_grid(g.Hkv, g.N * ((g.Cmax * g.G + rows_q - 1) / rows_q)));
-    const int lds_q = 2 * 3 * TILE;
+    const dim3 grid_q(bwd_grid(g.Hkv, (g.S * g.G - 1) / rows_q + 1));
+    const int lds_q = 2 * 3 * TILE + BWD_ROWS * 16 + ADASPARK_MAX_CUBES / 8 + ADASPARK_MAX_CUBES * 2 + 16;
     const BwdParts &cut = w.cut;
     const dim3 grid_k(bwd_grid(g.Hkv, (int)(cut.nkb * cut.parts)));
     constexpr int lds_k = Dkv<D>::BYTES;

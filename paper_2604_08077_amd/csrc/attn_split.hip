@@ -63,31 +63,19 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
     // an XCD's L2 sees the tiles of few of them.
     const int kv = blockIdx.x % g.Hkv;
     const int row1 = g.S * g.G - (int)(blockIdx.x / g.Hkv) * C::ROWS, row0 = max(0, row1 - C::ROWS), last = row1 - 1;
-    // the last cube with rows here, and the first
-    const int i = cube_at_position(g, last / g.G);
-    const CubeBox ibox = cube_box(g, i);
-    const int isize = ibox.size(), irow = cube_first(g, i) * g.G;  // tokens and first row of cube i
-    const int i_first = row0 >= irow ? i : cube_at_position(g, row0 / g.G);
-    const int rem1 = last - irow, head1 = rem1 / isize * isize;  // (all of one head of cube i?)
-    const int max_rank = max(0, row0 - irow) >= head1 ? rem1 - head1 : isize - 1;  // of the block's rows in cube i
-
+    // Lane l works out row l % 32 (rows past the last one repeat it), and the lanes that hold a row's column fetch its place.
+    const RowAt at = row_at(g, kv, min(row0 + (lane & 31), last));
     int rank[NS], own[NS];
     size_t rowid[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const int rho = min(row0 + 16 * s + n16, last);  // padding rows repeat the last one
-        int rem = rho - irow;
-        CubeBox box = ibox;
-        own[s] = i;
-        if (rem < 0) {
-            own[s] = cube_at_position(g, rho / g.G);
-            rem = rho - cube_first(g, own[s]) * g.G;
-            box = cube_box(g, own[s]);
-        }
-        const int hg = rem / box.size();
-        rank[s] = rem - hg * box.size();
-        rowid[s] = (size_t)token_of(g, box, rank[s]) * g.Hq + kv * g.G + hg;
+        rank[s] = __shfl(at.rank, 16 * s + n16, 64);
+        own[s] = __shfl(at.cube, 16 * s + n16, 64);
+        rowid[s] = (size_t)__shfl(at.id, 16 * s + n16, 64);
     }
+    // the last cube with rows here, and the first
+    const int i = __builtin_amdgcn_readlane(at.cube, 31), i_first = __builtin_amdgcn_readfirstlane(at.cube);
+    const int max_rank = __builtin_amdgcn_readlane(block_max_rank(at, row1 - row0), 31);  // of the block's rows in cube i
     const float c2 = 1.44269504088896340736f / sqrtf((float)D);  // softmax scale in base 2, folded into Q
     bf16x8 qf[NS][KSTEPS];
 #pragma unroll

@@ -119,46 +119,33 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     const int row1 = nrows - blk * MMAX, row0 = max(0, row1 - MMAX);
     const int Mrows = row1 - row0;
 
-    // the last cube with rows here, and the first
-    const int i = cube_at_position(g, (row1 - 1) / g.G);
-    const CubeBox ibox = cube_box(g, i);
-    const int isize = ibox.size(), irow = cube_first(g, i) * g.G;  // tokens and first row of cube i
-    const int i_first = row0 >= irow ? i : cube_at_position(g, row0 / g.G);
     for (int r = tid; r < Mrows; r += THREADS) {
-        const int rho = row0 + r;
-        int own = i, rem = rho - irow;
-        CubeBox box = ibox;
-        if (rem < 0) {
-            own = cube_at_position(g, rho / g.G);
-            rem = rho - cube_first(g, own) * g.G;
-            box = cube_box(g, own);
-        }
-        const int hg = rem / box.size(), rank = rem - hg * box.size();
-        const int rid = token_of(g, box, rank) * g.Hq + kv * g.G + hg;
-        rowid[r] = rid;
-        rrank[r] = rank;
-        rown[r] = own;
+        const RowAt at = row_at(g, kv, row0 + r);
+        rowid[r] = at.id;
+        rrank[r] = at.rank;
+        rown[r] = at.cube;
         if (r == 0) {  // scratch row behind the padding columns of a partial slab
-            rowid[MMAX] = rid;
+            rowid[MMAX] = at.id;
             rrank[MMAX] = 0;
-            rown[MMAX] = own;
+            rown[MMAX] = at.cube;
         }
+        if (r == Mrows - 1) misc[2] = block_max_rank(at, Mrows), misc[3] = at.size;
     }
     fill_masks_init(smem + C::OFF_FILL, tid);
-    // the walk ends, in cube i, behind the largest rank of the block's rows there (non-causal mode: the whole own cubes, and
-    // it goes on over the cubes after them)
-    const int rem1 = row1 - 1 - irow, head1 = rem1 / isize * isize;  // (all of one head of cube i?)
-    const int max_rank = max(0, row0 - irow) >= head1 ? rem1 - head1 : isize - 1;
-    const int own_tiles = g.causal ? max_rank / KEY_TILE + 1 : (isize + KEY_TILE - 1) / KEY_TILE;
-    const int ncubes = g.causal ? i + 1 : g.N;
     // Sparse entry: a cube that no row of the workgroup selected is left out of the walk altogether.  Rows that
     // select independently of each other leave no such cube; rows of neighbouring tokens with similar queries do.
     int2 *clist = reinterpret_cast<int2 *>(smem + C::OFF_LIST);
     uint32_t *uni = reinterpret_cast<uint32_t *>(smem + C::OFF_UNION);
-    const int wlim = (ncubes + 31) >> 5;  // mask words that hold cubes of the walk
     if (MASKED)
-        for (int w = tid; w < wlim; w += THREADS) uni[w] = 0u;
+        for (int w = tid; w < g.words; w += THREADS) uni[w] = 0u;
     __syncthreads();
+    // The last cube with rows here, and the first.  The walk ends, in cube i, behind the largest rank of the block's rows there
+    // (non-causal mode: the whole own cubes, and it goes on over the cubes after them).
+    const int i = __builtin_amdgcn_readfirstlane(rown[Mrows - 1]), i_first = __builtin_amdgcn_readfirstlane(rown[0]);
+    const int own_keys = __builtin_amdgcn_readfirstlane(g.causal ? misc[2] + 1 : misc[3]);
+    const int own_tiles = (own_keys + KEY_TILE - 1) / KEY_TILE;
+    const int ncubes = g.causal ? i + 1 : g.N;
+    const int wlim = (ncubes + 31) >> 5;  // mask words that hold cubes of the walk
     if (MASKED) {
         for (int x = tid; x < Mrows * wlim; x += THREADS) {
             const int r = x / wlim, w = x - r * wlim;
@@ -592,6 +579,9 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     return hipGetLastError();
 }
 
+// Below this many candidate (row, cube) pairs the automatic choice is the masked walk outright (see launch_attn_d).
+constexpr unsigned long long AUTO_MIN_CANDIDATE_PAIRS = 2ull << 20;
+
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
 // axis), text cubes in two.
 static long long tiles_of_cubes(const Geom &g, int keys)
@@ -616,19 +606,19 @@ static long long tiles_of_cubes(const Geom &g, int keys)
 //          7 to start and to combine its parts
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
-bool attn_split_pays(const Geom &g)
+//   choice  where this kernel would be one of those chosen from on the device, the dozen launches of that choice take 50
+//          (3,366 tokens of 28/4 heads of 128 in cubes of 32, half the heads selecting nearly nothing: 423 split; 538 in all where the
+//          choice was made, of which the walk 267)
+bool attn_split_pays(const Geom &g, bool choice)
 {
     if (!attn_split_fits(g)) return false;
     const double rows = (double)g.S * g.G, share = g.causal ? 0.5 : 1.0;  // of all cubes that the average walk visits
     const double slots = (double)tiles_of_cubes(g, KEY_TILE), walks = g.Hkv * std::ceil(rows / 256);
-    const double walk = 11 + (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, 1.18 * share * walks / 256);
+    const double walk = 11 + (choice && candidate_pairs(g) >= AUTO_MIN_CANDIDATE_PAIRS ? 50 : 0) + (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, 1.18 * share * walks / 256);
     const double steps = (double)tiles_of_cubes(g, 32), blocks = g.Hkv * std::ceil(rows / 32);
     const double split = 5 + 7 * std::max(1.0, blocks / 256) + blocks / 256 * share * steps * (g.D == 64 ? 0.15 : 0.24);
     return split < walk;
 }
-
-// Below this many candidate (row, cube) pairs the automatic choice is the masked walk outright (see launch_attn_d).
-constexpr unsigned long long AUTO_MIN_CANDIDATE_PAIRS = 2ull << 20;
 
 // Measured on MI355X (65,536 tokens, 28/4 heads, head_dim 128, rows selecting independently): the key-stationary
 // kernel is the faster one below this share of selected candidate cubes (break-even at 44 %).
@@ -639,7 +629,8 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
                                 int sparse_kernel, void *scratch, size_t scratch_bytes, uint16_t *O, float *lse,
                                 hipStream_t st)
 {
-    if ((sel_mask == nullptr || sparse_kernel == ADASPARK_SPARSE_AUTO) && attn_split_pays(g))
+    if ((sel_mask == nullptr || sparse_kernel == ADASPARK_SPARSE_AUTO) &&
+        attn_split_pays(g, sel_mask != nullptr && g.causal))
         return launch_attn_split(g, Q, packed, sel_mask, O, lse, st);
     if (sel_mask == nullptr) return launch_walk<D, false>(g, Q, packed, nullptr, nullptr, 0, 0, O, lse, st);
     if (sparse_kernel == ADASPARK_SPARSE_COMPACT && g.causal)

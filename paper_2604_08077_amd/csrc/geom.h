@@ -102,28 +102,55 @@ __host__ __device__ inline int cube_of_token(const Geom &g, int n)
     return g.Np + ((t / g.ct) * g.nHb + (h / g.ch)) * g.nWb + (w / g.cw);
 }
 
-// Cube-major order (cubes in their order, ranks inside a cube): position of cube c's first token, and the cube that
-// holds position x.  All cubes of a row of cubes share their extents in t and h, all rows of a layer theirs in t.
-__host__ __device__ inline int cube_first(const Geom &g, int c)
+// The cube that holds position x of the cube-major order (cubes in their order, ranks inside a cube), and the position of
+// its first token.  All cubes of a row of cubes share their extents in t and h, all rows of a layer theirs in t.
+struct CubeAt {
+    int c, first;
+    CubeBox box;
+};
+__host__ __device__ inline CubeAt cube_at(const Geom &g, int x)
 {
-    if (!g.ragged || c < g.Np) return c * g.Cmax;
-    c -= g.Np;
-    if (c >= g.Nv) return g.Sp + g.Sv + (c - g.Nv) * g.Cmax;
-    const int wb = c % g.nWb, hb = (c / g.nWb) % g.nHb, tb = c / (g.nWb * g.nHb);
-    const int et = min(g.ct, g.T - tb * g.ct), eh = min(g.ch, g.H - hb * g.ch);
-    return g.Sp + tb * min(g.ct, g.T) * g.H * g.W + et * (hb * g.ch * g.W + eh * wb * g.cw);
+    CubeAt r;
+    if (x < g.Sp || x >= g.Sp + g.Sv) {
+        const int start = x < g.Sp ? 0 : g.Sp + g.Sv, k = (x - start) / g.Cmax;
+        r.c = (x < g.Sp ? 0 : g.Np + g.Nv) + k;
+        r.first = start + k * g.Cmax;
+        r.box.t0 = -1; r.box.h0 = 0; r.box.w0 = r.first;
+        r.box.et = 1; r.box.eh = 1; r.box.ew = min(g.Cmax, (x < g.Sp ? g.Sp : g.S) - r.first);
+        return r;
+    }
+    const int v = x - g.Sp;
+    const int layer = min(g.ct, g.T) * g.H * g.W, tb = v / layer, in_layer = v - tb * layer;
+    const int et = min(g.ct, g.T - tb * g.ct), row = et * min(g.ch, g.H) * g.W, hb = in_layer / row, in_row = in_layer - hb * row;
+    const int eh = min(g.ch, g.H - hb * g.ch), whole = et * eh * min(g.cw, g.W), wb = in_row / whole;
+    r.c = g.Np + (tb * g.nHb + hb) * g.nWb + wb;
+    r.first = x - (in_row - wb * whole);
+    r.box.t0 = tb * g.ct; r.box.h0 = hb * g.ch; r.box.w0 = wb * g.cw;
+    r.box.et = et; r.box.eh = eh; r.box.ew = min(g.cw, g.W - r.box.w0);
+    return r;
 }
-__host__ __device__ inline int cube_at_position(const Geom &g, int x)
+
+// Row rho of KV head kv, rows numbered cube by cube in cube-major order and in a cube head by head: its cube, the cube's
+// tokens, the row's number there (head-in-group * tokens + rank), its rank and its id (token * Hq + query head).
+struct RowAt {
+    int cube, size, rem, rank, id;
+};
+__host__ __device__ inline RowAt row_at(const Geom &g, int kv, int rho)
 {
-    if (!g.ragged || x < g.Sp) return x / g.Cmax;
-    x -= g.Sp;
-    if (x >= g.Sv) return g.Np + g.Nv + (x - g.Sv) / g.Cmax;
-    const int layer = min(g.ct, g.T) * g.H * g.W, tb = x / layer;
-    x -= tb * layer;
-    const int et = min(g.ct, g.T - tb * g.ct), row = et * min(g.ch, g.H) * g.W, hb = x / row;
-    x -= hb * row;
-    const int eh = min(g.ch, g.H - hb * g.ch);
-    return g.Np + (tb * g.nHb + hb) * g.nWb + x / (et * eh * min(g.cw, g.W));
+    const CubeAt at = cube_at(g, rho / g.G);
+    RowAt r;
+    r.cube = at.c;
+    r.size = at.box.size();
+    r.rem = rho - at.first * g.G;
+    const int hg = r.rem / r.size;
+    r.rank = r.rem - hg * r.size;
+    r.id = token_of(g, at.box, r.rank) * g.Hq + kv * g.G + hg;
+    return r;
+}
+// The largest rank among a block's rows in the cube of its last row, of `rows` rows in all.
+__host__ __device__ inline int block_max_rank(const RowAt &last, int rows)
+{
+    return min(rows, last.rem + 1) <= last.rank + 1 ? last.rank : last.size - 1;  // (all of one head, or not)
 }
 
 // bf16 <-> fp32 bit helpers.
@@ -201,9 +228,10 @@ unsigned long long candidate_pairs(const Geom &g);
 hipError_t launch_attn(const Geom &g, const uint16_t *Q, void *packed, const uint32_t *sel_mask, int sparse_kernel,
                        void *scratch, size_t scratch_bytes, uint16_t *O, float *lse, hipStream_t st);
 // The kernel for short sequences (attn_split.hip); sel_mask == nullptr: dense.  attn_split_fits: its list of steps does;
-// attn_split_pays: launch_attn takes it, for dense attention and where the choice is automatic.
+// attn_split_pays: launch_attn takes it, for dense attention and where the choice is automatic (choice: and would otherwise
+// be made on the device).
 bool attn_split_fits(const Geom &g);
-bool attn_split_pays(const Geom &g);
+bool attn_split_pays(const Geom &g, bool choice);
 hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, uint16_t *O,
                              float *lse, hipStream_t st);
 // The compacting sparse kernel alone (attn_compact.hip).  flags (device, may be null): the flag block above; a
