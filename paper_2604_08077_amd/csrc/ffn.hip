@@ -11,8 +11,7 @@ namespace adaspark {
 
 constexpr int SEL_THREADS = 1024;
 constexpr int TAB_THREADS = 256;
-constexpr int FIN_WAVES = 4;
-constexpr int FIN_THREADS = 64 * FIN_WAVES;
+constexpr int FINISH_SMALL = 150;  // finish_small
 
 __device__ __forceinline__ float wave_sum(float x)
 {
@@ -38,7 +37,10 @@ __device__ float block_sum(const float *vals, int n, float *red)
     return tot;
 }
 
-// Eqs. 4-5 for cube blockIdx.x.
+// Eqs. 4-5 for cube blockIdx.x.  INFLIGHT: tokens of a wavefront whose loads are on the way together -- 4, whose sums then
+// stay in registers over a token's pieces; 16 where a token is a single piece per lane (d_model <= 512) and a cube has tokens
+// for it, so that 256 tokens are one trip to memory and not four.
+template <int INFLIGHT>
 __global__ __launch_bounds__(SEL_THREADS) void ffn_select_kernel(Geom g, int d_model, const uint16_t *__restrict__ X,
                                                                  float top_p, float eps, uint8_t *__restrict__ keep,
                                                                  float *__restrict__ score, int32_t *__restrict__ keep_count)
@@ -54,8 +56,8 @@ __global__ __launch_bounds__(SEL_THREADS) void ffn_select_kernel(Geom g, int d_m
     const int chunks = d_model / 8;  // 16-byte pieces of a token
     if (threadIdx.x == 0) *cnt = 0;
 
-    // token norms: a wavefront per token, four tokens in flight
-    constexpr int NW = SEL_THREADS / 64, INFLIGHT = 4;
+    // token norms: a wavefront per token, INFLIGHT tokens in flight
+    constexpr int NW = SEL_THREADS / 64;
     for (int r0 = wave; r0 < n; r0 += INFLIGHT * NW) {
         const uint16_t *x[INFLIGHT];
         float a[INFLIGHT];
@@ -99,11 +101,19 @@ __global__ __launch_bounds__(SEL_THREADS) void ffn_select_kernel(Geom g, int d_m
         const float sj = sc[j];
         bool k = true;
         if (!text && top_p < 1.0f) {
-            float before = 0.f;  // mass of the tokens ranked before j: larger score, or equal score and lower rank
-            for (int i = 0; i < n; ++i) {
+            // mass of the tokens ranked before j (larger score, or equal score and lower rank), added in rank order: those below
+            // the wavefront's tokens, these, those above
+            float before = 0.f;
+            const int w0 = __builtin_amdgcn_readfirstlane(j - lane), w1 = min(n, w0 + 64);
+#pragma unroll 8
+            for (int i = 0; i < w0; ++i) before += sc[i] >= sj ? sc[i] : 0.f;
+#pragma unroll 4
+            for (int i = w0; i < w1; ++i) {
                 const float si = sc[i];
-                if (si > sj || (si == sj && i < j)) before += si;
+                before += si > sj || (si == sj && i < j) ? si : 0.f;
             }
+#pragma unroll 8
+            for (int i = w1; i < n; ++i) before += sc[i] > sj ? sc[i] : 0.f;
             k = before < top_p;
         }
         const int tok = token_of(g, b, j);
@@ -198,38 +208,42 @@ __global__ __launch_bounds__(TAB_THREADS) void ffn_fill_kernel(Geom g, const uin
     }
 }
 
-// Eqs. 6-7 for cube blockIdx.x and columns 512 blockIdx.y ..: F holds FFN(x) of the activated tokens (fp32, row = index in
-// the active list), in `splits` parts that are added in order.  A lane owns eight columns; the wavefronts take every
-// fourth activated token: y = x + F, and a sum of F, whose four parts are combined in order; then every fourth bypassed
-// token: x + mean.  Bound by memory (F, X and Y once each): 65,536 tokens of 3584, 47 % activated, 0.27 ms = 5.1 TB/s (0.35 with
-// one workgroup per cube and all columns); 2,048 tokens with four parts 21 us, where that took 33 with one.
-__global__ __launch_bounds__(FIN_THREADS) void ffn_finish_kernel(Geom g, int d_model, int d_ff, const uint16_t *__restrict__ X,
-                                                                 const float *__restrict__ F,
-                                                                 const int32_t *__restrict__ cube_ptr,
-                                                                 const int32_t *__restrict__ active,
-                                                                 const int32_t *__restrict__ bypass, uint16_t *__restrict__ Y)
+// Eqs. 6-7 for cube blockIdx.x and columns COLS blockIdx.y ..: F holds FFN(x) of the activated tokens (fp32, row = index in
+// the active list), in `splits` parts that are added in order.  A lane owns eight columns of every (WAVES * 512 / COLS)-th
+// activated token: y = x + F, and a sum of F; the lanes' sums are combined in a fixed order; then of every so many-th
+// bypassed token: x + mean.  Bound by memory (F, X and Y once each) with WAVES = 4, COLS = 512: 65,536 tokens of 3584, 47 %
+// activated, 0.27 ms = 5.1 TB/s.  With few cubes by the trips to memory that a wavefront makes one after the other:
+// finish_small.
+template <int WAVES, int COLS>
+__global__ __launch_bounds__(64 * WAVES) void ffn_finish_kernel(Geom g, int d_model, int d_ff, const uint16_t *__restrict__ X,
+                                                                const float *__restrict__ F,
+                                                                const int32_t *__restrict__ cube_ptr,
+                                                                const int32_t *__restrict__ active,
+                                                                const int32_t *__restrict__ bypass, uint16_t *__restrict__ Y)
 {
-    __shared__ f32x4 sums[FIN_WAVES][2][64];
-    __shared__ int tpart[FIN_WAVES];
+    constexpr int THREADS = 64 * WAVES, LANES = COLS / 8, TOKENS = THREADS / LANES;  // lanes of a token, tokens at a time
+    __shared__ f32x4 sums[2][WAVES][LANES];
+    __shared__ int tpart[WAVES];
     const int c = blockIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int tid = threadIdx.x;
     // tokens of the cubes before this one: the start of its bypassed tokens (see ffn_fill_kernel)
     int tacc = 0;
-    for (int i = threadIdx.x; i < c; i += FIN_THREADS) tacc += cube_box(g, i).size();
+    for (int i = tid; i < c; i += THREADS) tacc += cube_box(g, i).size();
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) tacc += __shfl_xor(tacc, d, 64);
-    if (lane == 0) tpart[wave] = tacc;
+    if ((tid & 63) == 0) tpart[tid >> 6] = tacc;
     __syncthreads();
     int tbase = 0;
 #pragma unroll
-    for (int w = 0; w < FIN_WAVES; ++w) tbase += tpart[w];
+    for (int w = 0; w < WAVES; ++w) tbase += tpart[w];
     const int n = cube_box(g, c).size();
     const int first = cube_ptr[c], count = cube_ptr[c + 1] - first;
     const float inv = count > 0 ? 1.0f / (float)count : 0.f;
     const int m_tiles = (cube_ptr[g.N] + FFN_ROW_TILE - 1) / FFN_ROW_TILE;
     const int splits = count > 0 ? ffn_down_splits(m_tiles, d_model / FFN_ROW_TILE, d_ff) : 1;
     const size_t part = (size_t)m_tiles * FFN_ROW_TILE * d_model;
-    const int col = 512 * blockIdx.y + 8 * lane;
+    const int slot = LANES == 64 ? __builtin_amdgcn_readfirstlane(tid / 64) : tid / LANES;  // (scalar addresses)
+    const int col = COLS * blockIdx.y + 8 * (tid % LANES);
     const bool on = col < d_model;
 
     auto add_store = [&](int tok, const u32x4 &xv, const f32x4 &f0, const f32x4 &f1) __attribute__((always_inline)) {
@@ -242,62 +256,73 @@ __global__ __launch_bounds__(FIN_THREADS) void ffn_finish_kernel(Geom g, int d_m
         }
         *reinterpret_cast<u32x4 *>(Y + (size_t)tok * d_model + col) = o;
     };
-    constexpr int U = 4;  // tokens in flight
+    constexpr int U = WAVES == 4 ? 4 : 1, PARTS = 8 / U;  // tokens, and parts, in flight
     f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
     if (on) {
-        for (int r0 = wave; r0 < count; r0 += U * FIN_WAVES) {
+        for (int r0 = slot; r0 < count; r0 += U * TOKENS) {
             f32x4 v0[U], v1[U];
             u32x4 xv[U];
             int tok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int r = min(r0 + u * FIN_WAVES, count - 1);  // (past the end: loaded, not used)
+                const int r = min(r0 + u * TOKENS, count - 1);  // (past the end: loaded, not used)
                 const float *f = F + (size_t)(first + r) * d_model + col;
                 v0[u] = *reinterpret_cast<const f32x4 *>(f);
                 v1[u] = *reinterpret_cast<const f32x4 *>(f + 4);
                 tok[u] = active[first + r];
                 xv[u] = *reinterpret_cast<const u32x4 *>(X + (size_t)tok[u] * d_model + col);
             }
+#pragma unroll PARTS
             for (int p = 1; p < splits; ++p)
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const float *f = F + p * part + (size_t)(first + min(r0 + u * FIN_WAVES, count - 1)) * d_model + col;
+                    const float *f = F + p * part + (size_t)(first + min(r0 + u * TOKENS, count - 1)) * d_model + col;
                     v0[u] += *reinterpret_cast<const f32x4 *>(f);
                     v1[u] += *reinterpret_cast<const f32x4 *>(f + 4);
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (r0 + u * FIN_WAVES < count) {
+                if (r0 + u * TOKENS < count) {
                     acc0 += v0[u];
                     acc1 += v1[u];
                     add_store(tok[u], xv[u], v0[u], v1[u]);
                 }
         }
     }
-    sums[wave][0][lane] = acc0;
-    sums[wave][1][lane] = acc1;
-    __syncthreads();
-    f32x4 mean0 = sums[0][0][lane], mean1 = sums[0][1][lane];
+    // the tokens of a wavefront, then the wavefronts
 #pragma unroll
-    for (int w = 1; w < FIN_WAVES; ++w) {
-        mean0 += sums[w][0][lane];
-        mean1 += sums[w][1][lane];
+    for (int d = LANES; d < 64; d <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc0[e] += __shfl_xor(acc0[e], d, 64);
+            acc1[e] += __shfl_xor(acc1[e], d, 64);
+        }
+    if ((tid & 63) < LANES) {
+        sums[0][tid >> 6][tid % LANES] = acc0;
+        sums[1][tid >> 6][tid % LANES] = acc1;
+    }
+    __syncthreads();
+    f32x4 mean0 = sums[0][0][tid % LANES], mean1 = sums[1][0][tid % LANES];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+        mean0 += sums[0][w][tid % LANES];
+        mean1 += sums[1][w][tid % LANES];
     }
     mean0 *= inv;
     mean1 *= inv;
     if (!on) return;
     const int32_t *others = bypass + (tbase - first);
-    for (int r0 = wave; r0 < n - count; r0 += U * FIN_WAVES) {
+    for (int r0 = slot; r0 < n - count; r0 += U * TOKENS) {
         u32x4 xv[U];
         int tok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            tok[u] = others[min(r0 + u * FIN_WAVES, n - count - 1)];
+            tok[u] = others[min(r0 + u * TOKENS, n - count - 1)];
             xv[u] = *reinterpret_cast<const u32x4 *>(X + (size_t)tok[u] * d_model + col);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (r0 + u * FIN_WAVES < n - count) add_store(tok[u], xv[u], mean0, mean1);
+            if (r0 + u * TOKENS < n - count) add_store(tok[u], xv[u], mean0, mean1);
     }
 }
 
@@ -305,8 +330,12 @@ hipError_t launch_ffn_select(const Geom &g, int d_model, const uint16_t *X, floa
                              float *score, int32_t *keep_count, hipStream_t st)
 {
     const size_t lds = (size_t)(g.Cmax + SEL_THREADS / 64 + 4) * sizeof(float);
-    hipLaunchKernelGGL(ffn_select_kernel, dim3(g.N), dim3(SEL_THREADS), lds, st, g, d_model, X, top_p, eps, keep, score,
-                       keep_count);
+    if (d_model <= 512 && g.Cmax >= 128)
+        hipLaunchKernelGGL(ffn_select_kernel<16>, dim3(g.N), dim3(SEL_THREADS), lds, st, g, d_model, X, top_p, eps, keep,
+                           score, keep_count);
+    else
+        hipLaunchKernelGGL(ffn_select_kernel<4>, dim3(g.N), dim3(SEL_THREADS), lds, st, g, d_model, X, top_p, eps, keep,
+                           score, keep_count);
     return hipGetLastError();
 }
 
@@ -338,6 +367,15 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws)
     return w;
 }
 
+// Whether a cube's rows are shared out among sixteen wavefronts, 64 columns each, by the residual kernel: where the workgroups
+// of four wavefronts and 512 columns leave CUs idle, and a cube has rows for all.  A layer with its selection, us, so and with
+// four: 910 tokens of 256/1280 in 8 cubes 71, 104; 1,540 of 1536/8064 in 12 cubes 140, 168; 4,664 of 2048/10112 in 35 cubes 310, 316;
+// past the line, 4,131 of 2048/8448 in 42 cubes, 275, 267.
+static bool finish_small(const Geom &g, int d_model)
+{
+    return g.Cmax >= 128 && (long long)g.N * ((d_model + 511) / 512) <= FINISH_SMALL;
+}
+
 hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_t *X, const uint16_t *Wg,
                              const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y,
                              const FfnWorkspace &w, hipStream_t st)
@@ -353,8 +391,12 @@ hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_
     if (e != hipSuccess) return e;
     e = launch_ffn_gemm_down(w.H, Wd, d_ff, d_model, w.down_blocks, w.cube_ptr + g.N, w.F, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ffn_finish_kernel, dim3(g.N, (d_model + 511) / 512), dim3(FIN_THREADS), 0, st, g, d_model, d_ff, X, w.F,
-                       w.cube_ptr, w.active, w.bypass, Y);
+    if (finish_small(g, d_model))
+        hipLaunchKernelGGL((ffn_finish_kernel<16, 64>), dim3(g.N, d_model / 64), dim3(1024), 0, st, g, d_model, d_ff, X, w.F,
+                           w.cube_ptr, w.active, w.bypass, Y);
+    else
+        hipLaunchKernelGGL((ffn_finish_kernel<4, 512>), dim3(g.N, (d_model + 511) / 512), dim3(256), 0, st, g, d_model, d_ff, X,
+                           w.F, w.cube_ptr, w.active, w.bypass, Y);
     return hipGetLastError();
 }
 

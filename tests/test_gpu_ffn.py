@@ -117,6 +117,21 @@ def test_ffn_split_reduction(B, oracle, name, d_model, d_ff, p):
     test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, p)
 
 
+# The selection and residual kernels for few cubes, whose sixteen wavefronts take 128 tokens at a time: cubes of 127, 128, 129
+# and 300 tokens (clipped to 43, 86 and less), d_model on both sides of a single piece per lane, text of one token
+EDGES = {"tokens127": ((2, 1, 127), (1, 1, 127), 0), "tokens128": ((3, 4, 32), (1, 4, 32), 1), "tokens129": ((2, 3, 86), (1, 3, 43), 0),
+         "tokens300": ((3, 10, 17), (2, 10, 15), 0)}
+
+
+@pytest.mark.parametrize("name", EDGES)
+@pytest.mark.parametrize("d_model,d_ff", [(256, 640), (512, 256), (768, 1408)])
+def test_ffn_few_cubes(B, oracle, monkeypatch, name, d_model, d_ff):
+    grid, cube, text = EDGES[name]
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, synth.Workload(name, 48, *grid, *cube, 1, 1, 64, (0.6,), (1.0,), text))
+    test_ffn_select_matches_oracle(B, oracle, name, d_model, d_ff, 0.6)
+    test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, 0.6)
+
+
 def test_ffn_degenerate_masks(B, oracle):
     """No token activated: the input comes back bit for bit.  One activated token per cube: every other token of
     the cube moves by that token's FFN value.  Stale workspace contents must not matter."""
