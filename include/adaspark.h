@@ -90,7 +90,7 @@ typedef enum {
  *   PAIRS    key-stationary: a workgroup keeps one key cube on chip and runs the rows that selected it; every
  *            (row, selected cube) pair leaves a partial result of 2 * head_dim + 16 bytes in scratch memory (an
  *            fp16 vector scaled by its fp32 maximum) and a second kernel merges them per row.  Work follows the selection; the better choice when less than
- *            about 40 % of the cubes are selected.  Needs extra workspace (adaspark_pairs_workspace_bytes) and
+ *            about 40 % of the cubes are selected (cubes of 256 tokens; 15 % of cubes of up to 64).  Needs extra workspace (adaspark_pairs_workspace_bytes) and
  *            cubes of at most 256 tokens.  If the selection turns out to hold more pairs than the scratch
  *            memory was sized for, the call runs MASKED instead (decided on the device).
  *   AUTO     the choice is made on the device from the selected share (no host synchronisation).  PAIRS is

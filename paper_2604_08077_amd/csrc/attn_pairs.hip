@@ -27,7 +27,7 @@ namespace adaspark {
 constexpr int PAIRS_MAX_TPC = 4;          // a key cube of up to 256 tokens stays in LDS
 constexpr int PAIRS_MAX_SEGMENTS = 8192;  // (KV head, cube) work lists: two LDS histograms of that many counters
 constexpr int PAIRS_CHUNK = 3584;         // work-list entries per workgroup (staged in LDS: 28 KB); 14 steps per wavefront
-constexpr int PAIRS_HIST_ROWS = 256;      // rows per workgroup in the two transposition passes
+constexpr int PAIRS_TILE = 1024;          // rows per workgroup, a thread each, in the passes over the selection
 
 template <int D>
 struct Pairs {
@@ -57,13 +57,14 @@ bool pairs_supported(const Geom &g)
 
 // Scratch memory of the pair path, carved from `bytes` bytes at `base` (256-byte aligned):
 //   flags      i32 [4 + Hkv]  the kernel-choice flags (geom.h)
-//   kv_sel     u64 [Hkv]      selected (row, cube) pairs per KV head
+//   share      i32 [Hkv]      estimated share of selected candidate cubes per KV head, permille (behind the flags)
 //   qs         fp16 [R][D]    Q times the softmax scale in base 2 (rows of the heads this path takes): the operand of
 //                             the score MFMAs, see softmax_tile_folded
-//   cnt        i32 [R]        records per row = selected cubes + 1 (the own cube); 0 for rows of heads left to a
-//                             row-stationary kernel
-//   pair_ptr   i64 [R + 1]    exclusive scan of cnt: a row's records, in cube order, the own cube last
-//   tile_sum                  scratch of that scan
+//   cnt        i32 [R]        selected cubes per row
+//   pair_ptr   i64 [R + 1]    a row's records, in cube order, the own cube last: exclusive scan of cnt + 1 over the rows of
+//                             the heads this path takes
+//   tile_need  u32 [tiles][Hkv]  records that the rows of a tile (PAIRS_TILE rows) and KV head would need
+//   tile_off   i64 [tiles]    exclusive scan of the tiles' records
 //   seg_count  u32 [Hkv * N]  rows that selected cube j, per KV head
 //   seg_start  u32 [Hkv * N + 1]
 //   seg_cursor u32 [Hkv * N]
@@ -74,11 +75,11 @@ bool pairs_supported(const Geom &g)
 //                             MFMA output layout (head-dim 16 e + 4 q4 + v) sits at ((e / 2) * 4 + q4) * 8 + (e % 2) * 4 + v
 struct PairsScratch {
     int *flags;
-    unsigned long long *kv_sel;
     uint16_t *qs;
     int32_t *cnt;
     int64_t *pair_ptr;
-    long long *tile_sum;
+    uint32_t *tile_need;
+    long long *tile_off;
     uint32_t *seg_count, *seg_start, *seg_cursor, *seg_chunk;
     uint32_t *entries;
     float *ml;
@@ -88,11 +89,13 @@ struct PairsScratch {
 
 static size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
+static size_t pairs_tiles(const Geom &g) { return ((size_t)g.S * g.Hq + PAIRS_TILE - 1) / PAIRS_TILE; }
+
 static size_t pairs_table_bytes(const Geom &g)
 {
     const size_t R = (size_t)g.S * g.Hq, segs = (size_t)g.Hkv * g.N;
-    return FLAG_BLOCK_BYTES + 512 + up256(R * (size_t)g.D * 2) + up256(R * 4) + up256((R + 1) * 8) + up256(scan_tile_sum_bytes((long long)R)) +
-           4 * up256((segs + 1) * 4);
+    return FLAG_BLOCK_BYTES + 512 + up256(R * (size_t)g.D * 2) + up256(R * 4) + up256((R + 1) * 8) + up256(pairs_tiles(g) * g.Hkv * 4) +
+           up256(pairs_tiles(g) * 8) + 4 * up256((segs + 1) * 4);
 }
 
 static size_t pairs_record_bytes(const Geom &g, size_t records)
@@ -115,21 +118,21 @@ static PairsScratch pairs_layout(const Geom &g, void *base, size_t bytes)
         s.cap = 0;
         return s;
     }
-    static_assert((FLAG_KV + PAIRS_MAX_KV_HEADS) * 4 <= FLAG_BLOCK_BYTES && PAIRS_MAX_KV_HEADS * 8 <= 512,
-                  "flag block, head totals");
+    static_assert((FLAG_KV + PAIRS_MAX_KV_HEADS) * 4 <= FLAG_BLOCK_BYTES && PAIRS_MAX_KV_HEADS * 4 <= 512,
+                  "flag block, head shares");
     char *p = reinterpret_cast<char *>(base);
     s.flags = reinterpret_cast<int *>(p);
-    p += FLAG_BLOCK_BYTES;
-    s.kv_sel = reinterpret_cast<unsigned long long *>(p);  // right behind the flag block (geom.h)
-    p += 512;
+    p += FLAG_BLOCK_BYTES + 512;
     s.qs = reinterpret_cast<uint16_t *>(p);
     p += up256(R * (size_t)g.D * 2);
     s.cnt = reinterpret_cast<int32_t *>(p);
     p += up256(R * 4);
     s.pair_ptr = reinterpret_cast<int64_t *>(p);
     p += up256((R + 1) * 8);
-    s.tile_sum = reinterpret_cast<long long *>(p);
-    p += up256(scan_tile_sum_bytes((long long)R));
+    s.tile_need = reinterpret_cast<uint32_t *>(p);
+    p += up256(pairs_tiles(g) * g.Hkv * 4);
+    s.tile_off = reinterpret_cast<long long *>(p);
+    p += up256(pairs_tiles(g) * 8);
     s.seg_count = reinterpret_cast<uint32_t *>(p);
     p += up256((segs + 1) * 4);
     s.seg_start = reinterpret_cast<uint32_t *>(p);
@@ -176,194 +179,232 @@ __device__ __forceinline__ bool pairs_gate_closed(const int *flag, int force, in
     return !force && flag[FLAG_ESTIMATE] > below + below / 4;
 }
 
-__global__ __launch_bounds__(256) void pair_count_kernel(Geom g, long long R, const uint32_t *__restrict__ sel_mask,
-                                                         int32_t *__restrict__ cnt, uint32_t *__restrict__ seg_count,
-                                                         uint32_t *__restrict__ seg_cursor, int segs,
-                                                         unsigned long long *__restrict__ kv_sel,
-                                                         const int *__restrict__ flag, int force, int pairs_below_permille)
+// Whether the rows of KV head kv may become this path's: its estimated share is not well above the threshold.
+__device__ __forceinline__ bool pairs_head_open(const int *flag, int kv, int force, int pairs_below_permille)
+{
+    const int below = pairs_threshold(flag, pairs_below_permille);
+    return force || flag[FLAG_SHARE + kv] <= below + below / 4;
+}
+
+// The preparation is three passes, all of them over in a few microseconds where the path is not taken:
+//   pair_count_kernel   over the rows: selected cubes per row; records per (tile of rows, KV head); rows per (KV head, cube)
+//   pairs_plan_kernel   one workgroup: the heads this path takes; scans of the tiles' records, the lists' lengths and chunks
+//   pair_fill_kernel    over the rows: pair_ptr, the work lists, the scaled copy of Q
+// A row of a head that cannot be taken costs the first pass its counts only.  65,536 tokens of 28/4 heads, Top-p 0.5: 44 + 12 + 490 us (a
+// third of it the copy of Q); seven kernels with 256 rows a workgroup and 64-bit row numbers took 720.
+// (Ranges of 1,024 rows: a workgroup adds its counts to every list with one atomic, and its entries of a list lie together.)
+__device__ __forceinline__ void row_of(const Geom &g, uint32_t r, int &kv, int &i)
+{
+    const uint32_t n = r / (uint32_t)g.Hq;
+    kv = (int)((r - n * (uint32_t)g.Hq) / (uint32_t)g.G);
+    i = cube_of_token(g, (int)n);
+}
+
+template <typename F>
+__device__ __forceinline__ void for_selected(const uint32_t *mr, int i, F &&f)
+{
+    for (int w = 0; 32 * w < i; ++w) {
+        uint32_t bits = valid_bits(mr[w], w, i);
+        while (bits) {
+            const int b = __ffs(bits) - 1;
+            bits &= bits - 1;
+            f(32 * w + b);
+        }
+    }
+}
+
+__global__ __launch_bounds__(PAIRS_TILE) void pair_count_kernel(Geom g, uint32_t R, const uint32_t *__restrict__ sel_mask,
+                                                                int32_t *__restrict__ cnt, uint32_t *__restrict__ seg_count,
+                                                                uint32_t *__restrict__ tile_need, const int *__restrict__ flag,
+                                                                int force, int pairs_below_permille)
 {
     if (pairs_gate_closed(flag, force, pairs_below_permille)) return;
-    __shared__ unsigned int part[PAIRS_MAX_KV_HEADS];
-    if (threadIdx.x < PAIRS_MAX_KV_HEADS) part[threadIdx.x] = 0u;
+    extern __shared__ uint32_t hist[];  // [segs]
+    __shared__ uint32_t need[PAIRS_MAX_KV_HEADS];
+    const int segs = g.Hkv * g.N;
+    for (int x = threadIdx.x; x < segs; x += PAIRS_TILE) hist[x] = 0u;
+    if (threadIdx.x < PAIRS_MAX_KV_HEADS) need[threadIdx.x] = 0u;
     __syncthreads();
-    const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < segs) {  // cleared here for the passes that follow
-        seg_count[r] = 0u;
-        seg_cursor[r] = 0u;
-    }
+    const uint32_t r = blockIdx.x * PAIRS_TILE + threadIdx.x;
     if (r < R) {
+        int kv, i, c = 0;
+        row_of(g, r, kv, i);
         const uint32_t *mr = sel_mask + (size_t)r * g.words;
-        const int i = cube_of_token(g, (int)(r / g.Hq));
-        int c = 0;
-        for (int w = 0; 32 * w < i; ++w) c += __popc(valid_bits(mr[w], w, i));
-        cnt[r] = c + 1;  // and the own cube
-        atomicAdd(&part[(int)(r % g.Hq) / g.G], (unsigned int)c);
+        if (pairs_head_open(flag, kv, force, pairs_below_permille))
+            for_selected(mr, i, [&](int j) {
+                atomicAdd(&hist[kv * g.N + j], 1u);
+                ++c;
+            });
+        cnt[r] = c;
+        atomicAdd(&need[kv], (uint32_t)c + 1u);
     }
     __syncthreads();
-    if (threadIdx.x < g.Hkv && part[threadIdx.x]) atomicAdd(&kv_sel[threadIdx.x], (unsigned long long)part[threadIdx.x]);
+    for (int x = threadIdx.x; x < segs; x += PAIRS_TILE)
+        if (hist[x]) atomicAdd(&seg_count[x], hist[x]);
+    if (threadIdx.x < g.Hkv) tile_need[(size_t)blockIdx.x * g.Hkv + threadIdx.x] = need[threadIdx.x];
 }
 
-// Per KV head: the key-stationary kernel takes the head's rows (flags[FLAG_KV + kv] = 3) if its share of selected
-// candidate cubes is below the threshold (or force); if the records of the heads so chosen do not fit, none is
-// taken.  Then cnt is cleared for the rows of the other heads (run as a second kernel: pair_keep_kernel).
-__global__ __launch_bounds__(PAIRS_MAX_KV_HEADS) void pairs_mode_kernel(Geom g, long long cap,
-                                                                        unsigned long long candidates_per_head,
-                                                                        const unsigned long long *__restrict__ kv_sel,
-                                                                        int force, int pairs_below_permille,
-                                                                        int *__restrict__ flags)
+// Exclusive scan of one value per thread over the workgroup; all threads get the total.
+__device__ __forceinline__ unsigned long long block_scan(unsigned long long x, unsigned long long *lds,
+                                                         unsigned long long &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long incl = x;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long up = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += up;
+    }
+    __syncthreads();  // (lds: of the scan before)
+    if (lane == 63) lds[wave] = incl;
+    __syncthreads();
+    unsigned long long before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < PAIRS_TILE / 64; ++w) {
+        const unsigned long long t = lds[w];
+        if (w < wave) before += t;
+        total += t;
+    }
+    return before + incl - x;
+}
+
+// The key-stationary kernel takes a KV head's rows (flags[FLAG_KV + kv] = 3) if its share of selected candidate cubes is
+// below the threshold (or force); if the records of the heads so chosen do not fit, none is taken.
+__global__ __launch_bounds__(PAIRS_TILE) void pairs_plan_kernel(Geom g, long long cap, unsigned long long candidates_per_head,
+                                                                int tiles, const uint32_t *__restrict__ tile_need,
+                                                                const uint32_t *__restrict__ seg_count,
+                                                                long long *__restrict__ tile_off,
+                                                                uint32_t *__restrict__ seg_start,
+                                                                uint32_t *__restrict__ seg_chunk, int *__restrict__ flags,
+                                                                int force, int pairs_below_permille)
 {
     if (pairs_gate_closed(flags, force, pairs_below_permille)) return;
-    __shared__ unsigned long long need[PAIRS_MAX_KV_HEADS];
-    const int kv = threadIdx.x;
-    bool take = false;
-    if (kv < g.Hkv) {
-        take = force || kv_sel[kv] * 1000ull < candidates_per_head * (unsigned long long)pairs_threshold(flags, pairs_below_permille);
-        need[kv] = take ? kv_sel[kv] + (unsigned long long)g.S * g.G : 0ull;
+    __shared__ unsigned long long need[PAIRS_MAX_KV_HEADS], scan[PAIRS_TILE / 64];
+    __shared__ int take[PAIRS_MAX_KV_HEADS], active;
+    const int t = threadIdx.x;
+    if (t < PAIRS_MAX_KV_HEADS) need[t] = 0ull;
+    __syncthreads();
+    const int entries = tiles * g.Hkv;  // (tile, head): consecutive threads, consecutive entries
+    unsigned long long mine = 0;
+    const int step = PAIRS_TILE / g.Hkv * g.Hkv;  // a thread stays with one head
+    if (t < step)
+        for (int x = t; x < entries; x += step) mine += tile_need[x];
+    if (t < step && mine) atomicAdd(&need[t % g.Hkv], mine);
+    __syncthreads();
+    if (t == 0) {
+        unsigned long long total = 0;
+        const unsigned long long rows = (unsigned long long)g.S * g.G;
+        for (int kv = 0; kv < g.Hkv; ++kv) {
+            take[kv] = force || (pairs_head_open(flags, kv, force, pairs_below_permille) &&
+                                 (need[kv] - rows) * 1000ull <
+                                     candidates_per_head * (unsigned long long)pairs_threshold(flags, pairs_below_permille));
+            if (take[kv]) total += need[kv];
+        }
+        active = total > 0ull && total <= (unsigned long long)cap;
+        flags[FLAG_ACTIVE] = active;
     }
     __syncthreads();
-    unsigned long long total = 0;
-    for (int k = 0; k < g.Hkv; ++k) total += need[k];
-    const bool fits = total <= (unsigned long long)cap;
-    if (kv < g.Hkv) flags[FLAG_KV + kv] = (take && fits) ? 3 : 0;
-    if (kv == 0) flags[FLAG_ACTIVE] = (fits && total > 0ull) ? 1 : 0;
-}
-
-__global__ void pair_keep_kernel(Geom g, long long R, const int *__restrict__ flags, int32_t *__restrict__ cnt)
-{
-    if (!flags[FLAG_ACTIVE]) return;
-    const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < R && flags[FLAG_KV + (int)(r % g.Hq) / g.G] != 3) cnt[r] = 0;
-}
-
-// qs = fp16(Q * log2(e)/sqrt(D)) for the rows of the heads this path takes (the score operand: attn_tile.h); 8 elements
-// per thread.
-__global__ void pairs_scale_q_kernel(Geom g, long long chunks, float c2, const int *__restrict__ flags,
-                                     const uint16_t *__restrict__ Q, uint16_t *__restrict__ qs)
-{
-    if (!flags[FLAG_ACTIVE]) return;
-    // grid-stride: the grid is bounded, so that a launch that has nothing to do costs little
-    for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x < chunks; x += (long long)gridDim.x * blockDim.x) {
-        const long long row = x / (g.D / 8);
-        if (flags[FLAG_KV + (int)(row % g.Hq) / g.G] != 3) continue;
-        const bf16x8 q = *reinterpret_cast<const bf16x8 *>(Q + x * 8);
-        *reinterpret_cast<bf16x8 *>(qs + x * 8) = score_operand(q, c2);
+    if (t < g.Hkv) flags[FLAG_KV + t] = active && take[t] ? 3 : 0;
+    if (!active) return;
+    unsigned long long carry = 0, total;
+    for (int x0 = 0; x0 < tiles; x0 += PAIRS_TILE) {
+        const int x = x0 + t;
+        unsigned long long v = 0;
+        if (x < tiles)
+            for (int kv = 0; kv < g.Hkv; ++kv)
+                if (take[kv]) v += tile_need[(size_t)x * g.Hkv + kv];
+        const unsigned long long at = block_scan(v, scan, total);
+        if (x < tiles) tile_off[x] = (long long)(carry + at);
+        carry += total;
+    }
+    // lists: entries in the low half, chunks in the high one (fewer than 2^32 entries: record indices are 32-bit)
+    carry = 0;
+    const int segs = g.Hkv * g.N;
+    for (int x0 = 0; x0 < segs; x0 += PAIRS_TILE) {
+        const int x = x0 + t;
+        const unsigned long long n = x < segs && take[x / g.N] ? seg_count[x] : 0u;
+        const unsigned long long at = carry + block_scan(n | (n + PAIRS_CHUNK - 1) / PAIRS_CHUNK << 32, scan, total);
+        if (x < segs) {
+            seg_start[x] = (uint32_t)at;
+            seg_chunk[x] = (uint32_t)(at >> 32);
+        }
+        carry += total;
+    }
+    if (t == 0) {
+        seg_start[segs] = (uint32_t)carry;
+        seg_chunk[segs] = (uint32_t)(carry >> 32);
     }
 }
 
-// Transposition of the selection, two passes over the set bits of PAIRS_HIST_ROWS rows per workgroup.
-// FILL = false: seg_count[kv * N + j] += rows of this block that selected cube j.
-// FILL = true: the same count reserves a range of list (kv, j) with one global atomic, and every (row, cube) pair
-// is written into it as (row id, record index).
-template <bool FILL>
-__global__ __launch_bounds__(PAIRS_HIST_ROWS) void pair_transpose_kernel(
-    Geom g, long long R, const uint32_t *__restrict__ sel_mask, const int64_t *__restrict__ pair_ptr,
-    const int *__restrict__ mode_flag, uint32_t *__restrict__ seg_count, const uint32_t *__restrict__ seg_start, uint32_t *__restrict__ seg_cursor, uint32_t *__restrict__ entries)
+// Every (row, cube) pair of the heads taken is written into list (kv, j) as (row id, record index): the block's count of a
+// list reserves a range of it with one global atomic.  qs = fp16(Q * log2(e)/sqrt(D)) for the rows of these heads (the score
+// operand: attn_tile.h).
+__global__ __launch_bounds__(PAIRS_TILE) void pair_fill_kernel(Geom g, uint32_t R, float c2, const uint16_t *__restrict__ Q,
+                                                               const uint32_t *__restrict__ sel_mask,
+                                                               const int32_t *__restrict__ cnt,
+                                                               const long long *__restrict__ tile_off,
+                                                               const int *__restrict__ mode_flag,
+                                                               const uint32_t *__restrict__ seg_start,
+                                                               uint32_t *__restrict__ seg_cursor,
+                                                               int64_t *__restrict__ pair_ptr, uint32_t *__restrict__ entries,
+                                                               uint16_t *__restrict__ qs)
 {
     if (!mode_flag[FLAG_ACTIVE]) return;
-    extern __shared__ uint32_t hist[];  // [segs] counts, then (FILL) [segs] positions handed out
+    extern __shared__ uint32_t hist[];  // [segs] counts, then the ranges' first positions; [segs] positions handed out
+    __shared__ unsigned long long scan[PAIRS_TILE / 64];
     const int segs = g.Hkv * g.N;
     uint32_t *taken = hist + segs;
-    for (int x = threadIdx.x; x < (FILL ? 2 : 1) * segs; x += PAIRS_HIST_ROWS) hist[x] = 0u;
+    for (int x = threadIdx.x; x < 2 * segs; x += PAIRS_TILE) hist[x] = 0u;
     __syncthreads();
-    const long long r = (long long)blockIdx.x * PAIRS_HIST_ROWS + threadIdx.x;
-    int i = 0, kvN = 0;
-    const uint32_t *mr = nullptr;
+    const uint32_t r = blockIdx.x * PAIRS_TILE + threadIdx.x;
+    int i = 0, kv = 0;
     bool mine = false;  // rows of heads left to a row-stationary kernel take no part
+    const uint32_t *mr = sel_mask + (size_t)r * g.words;
     if (r < R) {
-        const int kv = (int)((r % g.Hq) / g.G);
+        row_of(g, r, kv, i);
         mine = mode_flag[FLAG_KV + kv] == 3;
-        i = mine ? cube_of_token(g, (int)(r / g.Hq)) : 0;
-        kvN = kv * g.N;
-        mr = sel_mask + (size_t)r * g.words;
-        for (int w = 0; 32 * w < i; ++w) {
-            uint32_t bits = valid_bits(mr[w], w, i);
-            while (bits) {
-                const int b = __ffs(bits) - 1;
-                bits &= bits - 1;
-                atomicAdd(&hist[kvN + 32 * w + b], 1u);
-            }
-        }
+        if (mine) for_selected(mr, i, [&](int j) { atomicAdd(&hist[kv * g.N + j], 1u); });
     }
-    __syncthreads();
-    if (!FILL) {
-        for (int x = threadIdx.x; x < segs; x += PAIRS_HIST_ROWS)
-            if (hist[x]) atomicAdd(&seg_count[x], hist[x]);
-        return;
-    }
-    // reserve this block's range in every list it adds to; hist[x] becomes the range's first position
-    for (int x = threadIdx.x; x < segs; x += PAIRS_HIST_ROWS)
+    unsigned long long total;
+    const unsigned long long slot0 =
+        (unsigned long long)tile_off[blockIdx.x] + block_scan(mine ? (unsigned long long)cnt[r] + 1ull : 0ull, scan, total);
+    if (r < R) pair_ptr[r] = (int64_t)slot0;
+    if (r == R - 1) pair_ptr[R] = (int64_t)(slot0 + (mine ? cnt[r] + 1 : 0));
+    // (the barriers of the scan: the counts are complete)
+    for (int x = threadIdx.x; x < segs; x += PAIRS_TILE)
         if (hist[x]) hist[x] = seg_start[x] + atomicAdd(&seg_cursor[x], hist[x]);
     __syncthreads();
-    if (r < R && mine) {
-        uint32_t slot = (uint32_t)pair_ptr[r];  // records of a row are numbered in cube order
-        for (int w = 0; 32 * w < i; ++w) {
-            uint32_t bits = valid_bits(mr[w], w, i);
-            while (bits) {
-                const int b = __ffs(bits) - 1;
-                bits &= bits - 1;
-                const int x = kvN + 32 * w + b;
-                const uint32_t pos = hist[x] + atomicAdd(&taken[x], 1u);
-                *reinterpret_cast<uint2 *>(entries + 2 * (size_t)pos) = make_uint2((uint32_t)r, slot);
-                ++slot;
-            }
-        }
+    if (mine) {
+        uint32_t slot = (uint32_t)slot0;  // records of a row are numbered in cube order
+        for_selected(mr, i, [&](int j) {
+            const int x = kv * g.N + j;
+            const uint32_t pos = hist[x] + atomicAdd(&taken[x], 1u);
+            *reinterpret_cast<uint2 *>(entries + 2 * (size_t)pos) = make_uint2(r, slot);
+            ++slot;
+        });
     }
-}
-
-// One workgroup: seg_start = exclusive scan of seg_count, seg_chunk = exclusive scan of the lists' chunk counts.
-constexpr int PLAN_THREADS = 1024;
-__global__ __launch_bounds__(PLAN_THREADS) void pairs_plan_kernel(int segs, const uint32_t *__restrict__ seg_count,
-                                                                  uint32_t *__restrict__ seg_start,
-                                                                  uint32_t *__restrict__ seg_chunk,
-                                                                  const int *__restrict__ flags)
-{
-    if (!flags[FLAG_ACTIVE]) return;
-    __shared__ uint32_t part[PLAN_THREADS], cpart[PLAN_THREADS];
-    const int t = threadIdx.x;
-    const int per = (segs + PLAN_THREADS - 1) / PLAN_THREADS;
-    uint32_t s = 0, cs = 0;
-    for (int k = 0; k < per; ++k)
-        if (t * per + k < segs) {
-            s += seg_count[t * per + k];
-            cs += (seg_count[t * per + k] + PAIRS_CHUNK - 1) / PAIRS_CHUNK;
-        }
-    part[t] = s;
-    cpart[t] = cs;
-    __syncthreads();
-    for (int off = 1; off < PLAN_THREADS; off <<= 1) {
-        const uint32_t v = t >= off ? part[t - off] : 0u, cv = t >= off ? cpart[t - off] : 0u;
-        __syncthreads();
-        part[t] += v;
-        cpart[t] += cv;
-        __syncthreads();
-    }
-    uint32_t run = part[t] - s, crun = cpart[t] - cs;
-    for (int k = 0; k < per; ++k)
-        if (t * per + k < segs) {
-            seg_start[t * per + k] = run;
-            seg_chunk[t * per + k] = crun;
-            run += seg_count[t * per + k];
-            crun += (seg_count[t * per + k] + PAIRS_CHUNK - 1) / PAIRS_CHUNK;
-        }
-    if (t == PLAN_THREADS - 1) {
-        seg_start[segs] = part[t];
-        seg_chunk[segs] = cpart[t];
+    const uint32_t per_row = (uint32_t)g.D / 8, first = blockIdx.x * PAIRS_TILE;
+    for (uint32_t x = threadIdx.x; x < PAIRS_TILE * per_row; x += PAIRS_TILE) {
+        const uint32_t row = first + x / per_row;
+        if (row >= R || mode_flag[FLAG_KV + (int)(row % (uint32_t)g.Hq) / g.G] != 3) continue;
+        const size_t at = (size_t)first * g.D + (size_t)x * 8;
+        *reinterpret_cast<bf16x8 *>(qs + at) = score_operand(*reinterpret_cast<const bf16x8 *>(Q + at), c2);
     }
 }
 
 // OWN = false: workgroup b runs chunk b of all lists' chunks: entries [c * PAIRS_CHUNK, ...) of the work list (kv, j)
 //              with seg_chunk[kv * N + j] <= b < seg_chunk[kv * N + j + 1], c = b - seg_chunk[kv * N + j].
-// OWN = true:  workgroup (kv, j, c) runs rows [c * PAIRS_CHUNK, ...) of cube j itself against it, causally (key rank
+// OWN = true:  workgroup b = (kv, j, c) runs rows [c * PAIRS_CHUNK, ...) of cube j itself against it, causally (key rank
 //              <= query rank); own_chunks workgroups per cube.
 template <int D, bool OWN>
-__global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
-    Geom g, int own_chunks, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ Kp,
+__device__ __forceinline__ void attn_pairs_work(
+    uint32_t block, const Geom &g, int own_chunks, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ Kp,
     const uint16_t *__restrict__ Vt, const int32_t *__restrict__ csize, const int64_t *__restrict__ pair_ptr, const uint32_t *__restrict__ seg_count,
     const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ seg_chunk,
     const uint32_t *__restrict__ entries, const int *__restrict__ mode_flag, uint16_t *__restrict__ rec,
     float *__restrict__ ml)
 {
-    if (!mode_flag[FLAG_ACTIVE]) return;
     using C = Pairs<D>;
     constexpr int NS = C::NS, WAVES = C::WAVES, PF = C::PF;
     constexpr int KSTEPS = D / 32, DT = D / 16;
@@ -374,11 +415,11 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
     const int n16 = lane & 15, q4 = lane >> 4;
 
     uint2 *rows = reinterpret_cast<uint2 *>(smem + C::OFF_ROWS);
-    int seg = (int)(blockIdx.x / own_chunks), c = (int)(blockIdx.x % own_chunks);
+    int seg = (int)(block / (uint32_t)own_chunks), c = (int)(block % (uint32_t)own_chunks);
     if (!OWN) {
-        // the list this chunk belongs to: the last seg with seg_chunk[seg] <= blockIdx.x (scalar binary search)
+        // the list this chunk belongs to: the last seg with seg_chunk[seg] <= block (scalar binary search)
         const int segs = g.Hkv * g.N;
-        const uint32_t b = blockIdx.x;
+        const uint32_t b = block;
         if (b >= seg_chunk[segs]) return;
         int lo = 0, hi = segs - 1;
         while (lo < hi) {
@@ -576,62 +617,85 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
     }
 }
 
-// D / 4 lanes per row: O = sum_k 2^(m_k - M) s_k h_k / sum_k 2^(m_k - M) l_k over the row's records (h = O / s in
-// fp16), in one pass with a running maximum.  A lane owns four adjacent head-dim elements: the four fp16 values at
-// byte 8 * lane of a record.
+// The own cubes' workgroups first, then the lists' (as many as could be; those past the last chunk return at once).
 template <int D>
-__global__ __launch_bounds__(256) void pairs_merge_kernel(long long R, const int64_t *__restrict__ pair_ptr,
+__global__ __launch_bounds__(FWD_MAX_THREADS) void attn_pairs_kernel(
+    Geom g, int own_chunks, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ Kp, const uint16_t *__restrict__ Vt,
+    const int32_t *__restrict__ csize, const int64_t *__restrict__ pair_ptr, const uint32_t *__restrict__ seg_count,
+    const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ seg_chunk, const uint32_t *__restrict__ entries,
+    const int *__restrict__ mode_flag, uint16_t *__restrict__ rec, float *__restrict__ ml)
+{
+    if (!mode_flag[FLAG_ACTIVE]) return;
+    const uint32_t own = (uint32_t)(g.Hkv * g.N) * (uint32_t)own_chunks;
+    if (blockIdx.x < own)
+        attn_pairs_work<D, true>(blockIdx.x, g, own_chunks, Q, Kp, Vt, csize, pair_ptr, seg_count, seg_start, seg_chunk, entries,
+                                 mode_flag, rec, ml);
+    else
+        attn_pairs_work<D, false>(blockIdx.x - own, g, 1, Q, Kp, Vt, csize, pair_ptr, seg_count, seg_start, seg_chunk, entries,
+                                  mode_flag, rec, ml);
+}
+
+// D / 8 lanes per row: O = sum_k 2^(m_k - M) s_k h_k / sum_k 2^(m_k - M) l_k over the row's records (h = O / s in
+// fp16), in one pass with a running maximum.  A lane owns the eight fp16 values at byte 16 * lane of a record: two blocks of
+// four adjacent head-dim elements.  Bound by memory (a record once, 272 bytes at head-dim 128): 65,536 tokens of
+// 28/4 heads, Top-p 0.5, 40.7 M records, 2.46 ms = 4.7 TB/s; four values and a 64-bit division per lane and row, 2.80.  30,000 tokens, half
+// the heads with two records a row, 0.21 ms and 0.45.
+template <int D>
+__global__ __launch_bounds__(256) void pairs_merge_kernel(uint32_t S, const int64_t *__restrict__ pair_ptr,
                                                           const uint16_t *__restrict__ rec, const float *__restrict__ ml,
                                                           const int *__restrict__ mode_flag, int Hq, int G,
                                                           uint16_t *__restrict__ O, float *__restrict__ lse)
 {
-    if (!mode_flag[FLAG_ACTIVE]) return;
-    constexpr int LPR = D / 4;  // lanes per row
-    typedef __fp16 h4 __attribute__((ext_vector_type(4)));
-    const int l = threadIdx.x % LPR;
-    // grid-stride over the rows: the grid is bounded, so that a launch that has nothing to do costs little
-    for (long long row = (long long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; row < R;
-         row += (long long)gridDim.x * (256 / LPR)) {
-    if (mode_flag[FLAG_KV + (int)(row % Hq) / G] != 3) continue;  // another kernel writes that row
-    const long long p0 = pair_ptr[row];
-    const int n = (int)(pair_ptr[row + 1] - p0);
-    const float *mlr = ml + (size_t)p0 * 4;
-    const uint16_t *recr = rec + (size_t)p0 * D + 4 * l;
-    float M = -INFINITY, L = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int U = 8;  // records in flight per lane
-    for (int k0 = 0; k0 < n; k0 += U) {
-        f32x4 x[U];
-        h4 h[U];
+    constexpr int LPR = D / 8;  // lanes per row
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    const int a = blockIdx.y, l = threadIdx.x % LPR;
+    if (!mode_flag[FLAG_ACTIVE] || mode_flag[FLAG_KV + a / G] != 3) return;  // (another kernel writes that head's rows)
+    // grid-stride over the tokens: the grid is bounded, so that a launch that has nothing to do costs little
+    for (uint32_t n = blockIdx.x * (256 / LPR) + threadIdx.x / LPR; n < S; n += gridDim.x * (256 / LPR)) {
+        const size_t row = (size_t)n * Hq + a;
+        const long long p0 = pair_ptr[row];
+        const int count = (int)(pair_ptr[row + 1] - p0);
+        const float *mlr = ml + (size_t)p0 * 4;
+        const uint16_t *recr = rec + (size_t)p0 * D + 8 * l;
+        float M = -INFINITY, L = 0.f;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        constexpr int U = 4;  // records in flight per lane
+        for (int k0 = 0; k0 < count; k0 += U) {
+            f32x4 x[U];
+            h8 h[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = min(k0 + u, n - 1);  // past the end: the last record again, with weight 0 below
-            x[u] = *reinterpret_cast<const f32x4 *>(mlr + (size_t)k * 4);  // m, l, s
-            h[u] = *reinterpret_cast<const h4 *>(recr + (size_t)k * D);
+            for (int u = 0; u < U; ++u) {
+                const int k = min(k0 + u, count - 1);  // past the end: the last record again, with weight 0 below
+                x[u] = *reinterpret_cast<const f32x4 *>(mlr + (size_t)k * 4);  // m, l, s
+                h[u] = *reinterpret_cast<const h8 *>(recr + (size_t)k * D);
+            }
+            float mx = M;
+#pragma unroll
+            for (int u = 0; u < U; ++u) mx = fmaxf(mx, x[u][0]);
+            const float scale = __builtin_amdgcn_exp2f(M - mx);  // 0 on the first trip (M = -inf)
+            M = mx;
+            L *= scale;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) acc[v] *= scale;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float w = (k0 + u < count) ? __builtin_amdgcn_exp2f(x[u][0] - M) : 0.f;
+                L = fmaf(w, x[u][1], L);
+                const float ws = w * x[u][2];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) acc[v] = fmaf(ws, (float)h[u][v], acc[v]);
+            }
         }
-        float mx = M;
+        const float inv = 1.0f / L;
+        // values 8 l .. 8 l + 7 of a record are elements 16 e + 4 q4 + 0..3 of e = 2 * (l / 4) and e + 1, q4 = l % 4
+        uint16_t *o = O + row * D + 32 * (l / 4) + 4 * (l % 4);
 #pragma unroll
-        for (int u = 0; u < U; ++u) mx = fmaxf(mx, x[u][0]);
-        const float scale = __builtin_amdgcn_exp2f(M - mx);  // 0 on the first trip (M = -inf)
-        M = mx;
-        L *= scale;
-        acc *= scale;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float w = (k0 + u < n) ? __builtin_amdgcn_exp2f(x[u][0] - M) : 0.f;
-            L = fmaf(w, x[u][1], L);
-            const float ws = w * x[u][2];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = fmaf(ws, (float)h[u][v], acc[v]);
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t w0 = (uint32_t)float_to_bf16_bits(acc[4 * e] * inv) | ((uint32_t)float_to_bf16_bits(acc[4 * e + 1] * inv) << 16);
+            const uint32_t w1 = (uint32_t)float_to_bf16_bits(acc[4 * e + 2] * inv) | ((uint32_t)float_to_bf16_bits(acc[4 * e + 3] * inv) << 16);
+            *reinterpret_cast<uint2 *>(o + 16 * e) = make_uint2(w0, w1);
         }
-    }
-    const float inv = 1.0f / L;
-    // position 4 l of a record is element (e, q4, v = 0) with e = 2 * (l / 8) + l % 2, q4 = (l % 8) / 2
-    const int d = 16 * (2 * (l / 8) + l % 2) + 4 * ((l % 8) / 2);
-    const uint32_t w0 = (uint32_t)float_to_bf16_bits(acc[0] * inv) | ((uint32_t)float_to_bf16_bits(acc[1] * inv) << 16);
-    const uint32_t w1 = (uint32_t)float_to_bf16_bits(acc[2] * inv) | ((uint32_t)float_to_bf16_bits(acc[3] * inv) << 16);
-    *reinterpret_cast<uint2 *>(O + (size_t)row * D + d) = make_uint2(w0, w1);
-    if (lse != nullptr && l == 0) lse[row] = (M + log2f(L)) * 0.69314718055994530942f;
+        if (lse != nullptr && l == 0) lse[row] = (M + log2f(L)) * 0.69314718055994530942f;
     }
 }
 
@@ -644,7 +708,7 @@ unsigned long long candidate_pairs(const Geom &g)
 }
 
 template <int D>
-static hipError_t launch_pairs_d(const Geom &g, const uint16_t *Q, const void *packed, const PairsScratch &sc,
+static hipError_t launch_pairs_d(const Geom &g, const void *packed, const PairsScratch &sc,
                                  const int *flag, uint16_t *O, float *lse, hipStream_t st)
 {
     using C = Pairs<D>;
@@ -652,11 +716,8 @@ static hipError_t launch_pairs_d(const Geom &g, const uint16_t *Q, const void *p
     const size_t half_elems = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * D;
     const uint16_t *Vt = Kp + half_elems;
     const int32_t *csize = reinterpret_cast<const int32_t *>(Vt + half_elems);
-    const long long R = (long long)g.S * g.Hq;
-    static LdsOptIn opted_lists, opted_own;  // one per kernel instantiation
-    hipError_t e = opted_lists.ensure(reinterpret_cast<const void *>(&attn_pairs_kernel<D, false>), C::BYTES);
-    if (e != hipSuccess) return e;
-    e = opted_own.ensure(reinterpret_cast<const void *>(&attn_pairs_kernel<D, true>), C::BYTES);
+    static LdsOptIn opted;  // one per kernel instantiation
+    const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&attn_pairs_kernel<D>), C::BYTES);
     if (e != hipSuccess) return e;
     // Chunks of all lists together: at most one partly filled chunk per list, and no more entries than records fit
     // (or than there are candidate pairs).  Workgroups past the actual number of chunks return at once.
@@ -664,16 +725,13 @@ static hipError_t launch_pairs_d(const Geom &g, const uint16_t *Q, const void *p
     const long long most = (long long)std::min<unsigned long long>((unsigned long long)sc.cap, candidate_pairs(g));
     const long long chunks = most / PAIRS_CHUNK + segs;
     const int own_chunks = (g.G * g.Cmax + PAIRS_CHUNK - 1) / PAIRS_CHUNK;
-    const long long q_chunks = R * (D / 8);
-    hipLaunchKernelGGL(pairs_scale_q_kernel, dim3((unsigned)std::min<long long>((q_chunks + 255) / 256, 256 * 32)), dim3(256), 0, st, g, q_chunks,
-                       1.44269504088896340736f / sqrtf((float)D), flag, Q, sc.qs);
-    hipLaunchKernelGGL((attn_pairs_kernel<D, false>), dim3((unsigned)chunks), dim3(C::THREADS), C::BYTES, st, g, 1, sc.qs, Kp, Vt,
-                       csize, sc.pair_ptr, sc.seg_count, sc.seg_start, sc.seg_chunk, sc.entries, flag, sc.rec, sc.ml);
-    hipLaunchKernelGGL((attn_pairs_kernel<D, true>), dim3((unsigned)(segs * own_chunks)), dim3(C::THREADS), C::BYTES, st, g,
-                       own_chunks, sc.qs, Kp, Vt, csize, sc.pair_ptr, sc.seg_count, sc.seg_start, sc.seg_chunk, sc.entries, flag, sc.rec, sc.ml);
-    const int rows_per_block = 256 / (D / 4);
-    const long long merge_blocks = std::min<long long>((R + rows_per_block - 1) / rows_per_block, 256 * 64);
-    hipLaunchKernelGGL((pairs_merge_kernel<D>), dim3((unsigned)merge_blocks), dim3(256), 0, st, R, sc.pair_ptr, sc.rec,
+    hipLaunchKernelGGL((attn_pairs_kernel<D>), dim3((unsigned)(segs * own_chunks + chunks)), dim3(C::THREADS), C::BYTES, st, g,
+                       own_chunks, sc.qs, Kp, Vt, csize, sc.pair_ptr, sc.seg_count, sc.seg_start, sc.seg_chunk, sc.entries, flag,
+                       sc.rec, sc.ml);
+    constexpr int rows_per_block = 256 / (D / 8);
+    const unsigned merge_blocks = (unsigned)std::min<long long>((g.S + rows_per_block - 1) / rows_per_block,
+                                                                std::max(1, 256 * 64 / g.Hq));
+    hipLaunchKernelGGL((pairs_merge_kernel<D>), dim3(merge_blocks, g.Hq), dim3(256), 0, st, (uint32_t)g.S, sc.pair_ptr, sc.rec,
                        sc.ml, flag, g.Hq, g.G, O, lse);
     return hipGetLastError();
 }
@@ -685,6 +743,13 @@ int *pairs_flags(const Geom &g, void *scratch, size_t scratch_bytes)
     return sc.cap > 0 ? sc.flags : nullptr;
 }
 
+uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int &words)
+{
+    const PairsScratch sc = pairs_layout(g, scratch, scratch_bytes);
+    words = sc.cap > 0 ? (int)(sc.seg_chunk - sc.seg_count) : 0;
+    return sc.seg_count;
+}
+
 // Counts the pairs per KV head, hands heads to this path (flags), numbers their records, and enqueues this path's
 // kernels (they return at once for heads, or altogether, when nothing was handed over).
 hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, void *scratch,
@@ -694,27 +759,23 @@ hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packe
     const PairsScratch sc = pairs_layout(g, scratch, scratch_bytes);
     if (!pairs_supported(g) || sc.cap <= 0) return hipErrorInvalidValue;
     int *flag = sc.flags;
-    const long long R = (long long)g.S * g.Hq;
-    const int segs = g.Hkv * g.N;
-    const long long count_threads = R > segs ? R : segs;
-    const unsigned row_blocks = (unsigned)((R + 255) / 256);
-    const unsigned hist_blocks = (unsigned)((R + PAIRS_HIST_ROWS - 1) / PAIRS_HIST_ROWS);
-    hipLaunchKernelGGL(pair_count_kernel, dim3((unsigned)((count_threads + 255) / 256)), dim3(256), 0, st, g, R, sel_mask,
-                       sc.cnt, sc.seg_count, sc.seg_cursor, segs, sc.kv_sel, flag, force, pairs_below_permille);
-    hipLaunchKernelGGL(pairs_mode_kernel, dim3(1), dim3(PAIRS_MAX_KV_HEADS), 0, st, g, sc.cap,
-                       candidate_pairs(g) / (unsigned long long)g.Hkv, sc.kv_sel, force, pairs_below_permille, flag);
-    hipLaunchKernelGGL(pair_keep_kernel, dim3(row_blocks), dim3(256), 0, st, g, R, flag, sc.cnt);
-    launch_exclusive_scan(sc.cnt, R, sc.tile_sum, sc.pair_ptr, st);
-    hipLaunchKernelGGL((pair_transpose_kernel<false>), dim3(hist_blocks), dim3(PAIRS_HIST_ROWS), (size_t)segs * 4, st, g,
-                       R, sel_mask, sc.pair_ptr, flag, sc.seg_count, sc.seg_start, sc.seg_cursor, sc.entries);
-    hipLaunchKernelGGL(pairs_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, st, segs, sc.seg_count, sc.seg_start,
-                       sc.seg_chunk, flag);
-    hipLaunchKernelGGL((pair_transpose_kernel<true>), dim3(hist_blocks), dim3(PAIRS_HIST_ROWS), (size_t)segs * 8, st, g,
-                       R, sel_mask, sc.pair_ptr, flag, sc.seg_count, sc.seg_start, sc.seg_cursor, sc.entries);
-    const hipError_t e = hipGetLastError();
+    const uint32_t R = (uint32_t)((long long)g.S * g.Hq);  // (below 2^31: the entry points check)
+    const int segs = g.Hkv * g.N, tiles = (int)pairs_tiles(g);
+    static LdsOptIn opted;  // (with the most lists the counters take 64 KB)
+    hipError_t e = opted.ensure(reinterpret_cast<const void *>(&pair_fill_kernel), PAIRS_MAX_SEGMENTS * 8);
     if (e != hipSuccess) return e;
-    return g.D == 64 ? launch_pairs_d<64>(g, Q, packed, sc, flag, O, lse, st)
-                     : launch_pairs_d<128>(g, Q, packed, sc, flag, O, lse, st);
+    hipLaunchKernelGGL(pair_count_kernel, dim3(tiles), dim3(PAIRS_TILE), (size_t)segs * 4, st, g, R, sel_mask, sc.cnt,
+                       sc.seg_count, sc.tile_need, flag, force, pairs_below_permille);
+    hipLaunchKernelGGL(pairs_plan_kernel, dim3(1), dim3(PAIRS_TILE), 0, st, g, sc.cap,
+                       candidate_pairs(g) / (unsigned long long)g.Hkv, tiles, sc.tile_need, sc.seg_count, sc.tile_off,
+                       sc.seg_start, sc.seg_chunk, flag, force, pairs_below_permille);
+    hipLaunchKernelGGL(pair_fill_kernel, dim3(tiles), dim3(PAIRS_TILE), (size_t)segs * 8, st, g, R,
+                       1.44269504088896340736f / sqrtf((float)g.D), Q, sel_mask, sc.cnt, sc.tile_off, flag, sc.seg_start,
+                       sc.seg_cursor, sc.pair_ptr, sc.entries, sc.qs);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return g.D == 64 ? launch_pairs_d<64>(g, packed, sc, flag, O, lse, st)
+                     : launch_pairs_d<128>(g, packed, sc, flag, O, lse, st);
 }
 
 }  // namespace adaspark

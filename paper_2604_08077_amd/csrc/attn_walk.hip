@@ -457,7 +457,8 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 
 // ---- the share of candidate cubes the rows select, per KV head, from a sample of rows.  One workgroup; writes
 // flags[FLAG_MODE] = 1 (compaction) or 2 (masked walk) from the overall share, flags[FLAG_ESTIMATE] = the smallest
-// share of a KV head in permille, and (kv_modes) clears the per-head part.
+// share of a KV head in permille, and (kv_modes) the heads' shares; clears the per-head choices and the key-stationary path's
+// counters.
 constexpr int DENSITY_THREADS = 1024;
 constexpr int DENSITY_MAX_ROWS = 2048;  // two sampled rows per thread: an estimate is all that is needed
 constexpr int DENSITY_GROUPS = 16;          // sampled (cube, query head) pairs for the union estimate
@@ -467,23 +468,28 @@ constexpr int DENSITY_UNION_WORDS = ADASPARK_MAX_CUBES / 32;
 constexpr int MASKED_ABOVE_PERMILLE = 15;
 
 __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, const uint32_t *__restrict__ sel_mask,
-                                                                      int *__restrict__ flags, int kv_modes)
+                                                                      int *__restrict__ flags, int kv_modes,
+                                                                      uint32_t *__restrict__ counters, int counter_words)
 {
-    __shared__ unsigned long long acc[2][PAIRS_MAX_KV_HEADS];  // selected, candidates; heads beyond the array fold
-    for (int x = threadIdx.x; x < 2 * PAIRS_MAX_KV_HEADS; x += DENSITY_THREADS) (&acc[0][0])[x] = 0ull;
+    // selected, candidates (at most DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES); heads beyond the array fold
+    __shared__ uint32_t acc[2][PAIRS_MAX_KV_HEADS];
+    for (int x = threadIdx.x; x < 2 * PAIRS_MAX_KV_HEADS; x += DENSITY_THREADS) (&acc[0][0])[x] = 0u;
+    for (int x = threadIdx.x; x < counter_words; x += DENSITY_THREADS) counters[x] = 0u;
     __syncthreads();
     // sample k: token (k * tstride) mod S, query head k mod Hq -- every head gets its share of the samples
     const int samples = (int)min((long long)DENSITY_MAX_ROWS, (long long)g.S * g.Hq);
     const int tstride = max(1, g.S / samples) | 1;
     for (int k = threadIdx.x; k < samples; k += DENSITY_THREADS) {
-        const int n = (int)(((long long)k * tstride) % g.S), a = k % g.Hq;
+        // (k * tstride < S + DENSITY_MAX_ROWS, or below DENSITY_MAX_ROWS: 32 bits)
+        const int n = (int)((uint32_t)k * (uint32_t)tstride % (uint32_t)g.S), a = k % g.Hq;
         const int i = cube_of_token(g, n);
         const uint32_t *mr = sel_mask + ((size_t)n * g.Hq + a) * g.words;
-        unsigned long long sel = 0;
+        uint32_t sel = 0;
+#pragma unroll 4
         for (int w = 0; 32 * w < i; ++w) sel += __popc(mr[w]);
         const int kv = (a / g.G) % PAIRS_MAX_KV_HEADS;
         atomicAdd(&acc[0][kv], sel);
-        atomicAdd(&acc[1][kv], (unsigned long long)i);
+        atomicAdd(&acc[1][kv], (uint32_t)i);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -491,7 +497,8 @@ __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, co
         for (int kv = 0; kv < min(g.Hkv, PAIRS_MAX_KV_HEADS); ++kv) {
             sel += acc[0][kv];
             cand += acc[1][kv];
-            if (acc[1][kv] > 0ull) least = min(least, acc[0][kv] * 1000ull / acc[1][kv]);
+            if (acc[1][kv] == 0u) continue;
+            least = min(least, acc[0][kv] * 1000ull / acc[1][kv]);
         }
         flags[FLAG_MODE] = (sel * 1000ull > cand * (unsigned long long)MASKED_ABOVE_PERMILLE) ? 2 : 1;
         flags[FLAG_ESTIMATE] = (int)least;
@@ -548,14 +555,11 @@ __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, co
         if (threadIdx.x == 0)
             flags[FLAG_UNION] = ucount[1] > 0ull ? max(1, (int)(ucount[0] * 1000ull / ucount[1])) : 1000;
     }
-    if (kv_modes) {
-        unsigned long long *kv_sel =
-            reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(flags) + FLAG_BLOCK_BYTES);
+    if (kv_modes)
         for (int kv = threadIdx.x; kv < g.Hkv; kv += DENSITY_THREADS) {
             flags[FLAG_KV + kv] = 0;
-            kv_sel[kv] = 0ull;
+            flags[FLAG_SHARE + kv] = acc[1][kv] > 0u ? (int)(acc[0][kv] * 1000ull / acc[1][kv]) : 0;
         }
-    }
 }
 
 template <int D, bool MASKED>
@@ -582,6 +586,20 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
 // Below this many candidate (row, cube) pairs the automatic choice is the masked walk outright (see launch_attn_d).
 constexpr unsigned long long AUTO_MIN_CANDIDATE_PAIRS = 2ull << 20;
 
+// The walks of a launch over the longest one, where every CU takes the same share (1.18: they do not).
+static double walk_rounds(const Geom &g)
+{
+    return 1.18 * (g.causal ? 0.5 : 1.0) * g.Hkv * std::ceil((double)g.S * g.G / 256) / 256;
+}
+
+// Whether the automatic choice is made on the device.  Where the time of the masked walk is that of its longest walk, heads that
+// go to the key-stationary kernel do not shorten it (3,600 tokens of 28/4 heads of 128 in cubes of 32, half the heads selecting nearly
+// nothing: the walk 218 us, with all heads as with half of them, and the others another 140).
+static bool chosen_on_device(const Geom &g)
+{
+    return candidate_pairs(g) >= AUTO_MIN_CANDIDATE_PAIRS && walk_rounds(g) > 1.0;
+}
+
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
 // axis), text cubes in two.
 static long long tiles_of_cubes(const Geom &g, int keys)
@@ -606,23 +624,24 @@ static long long tiles_of_cubes(const Geom &g, int keys)
 //          7 to start and to combine its parts
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
-//   choice  where this kernel would be one of those chosen from on the device, the dozen launches of that choice take 50
-//          (3,366 tokens of 28/4 heads of 128 in cubes of 32, half the heads selecting nearly nothing: 423 split; 538 in all where the
-//          choice was made, of which the walk 267)
+//   choice  where this kernel would be one of those chosen from on the device, the launches of that choice take 40
 bool attn_split_pays(const Geom &g, bool choice)
 {
     if (!attn_split_fits(g)) return false;
-    const double rows = (double)g.S * g.G, share = g.causal ? 0.5 : 1.0;  // of all cubes that the average walk visits
-    const double slots = (double)tiles_of_cubes(g, KEY_TILE), walks = g.Hkv * std::ceil(rows / 256);
-    const double walk = 11 + (choice && candidate_pairs(g) >= AUTO_MIN_CANDIDATE_PAIRS ? 50 : 0) + (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, 1.18 * share * walks / 256);
-    const double steps = (double)tiles_of_cubes(g, 32), blocks = g.Hkv * std::ceil(rows / 32);
+    const double slots = (double)tiles_of_cubes(g, KEY_TILE);
+    const double walk = 11 + (choice && chosen_on_device(g) ? 40 : 0) +
+                        (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, walk_rounds(g));
+    const double share = g.causal ? 0.5 : 1.0;  // of all cubes that the average walk visits
+    const double steps = (double)tiles_of_cubes(g, 32), blocks = g.Hkv * std::ceil((double)g.S * g.G / 32);
     const double split = 5 + 7 * std::max(1.0, blocks / 256) + blocks / 256 * share * steps * (g.D == 64 ? 0.15 : 0.24);
     return split < walk;
 }
 
-// Measured on MI355X (65,536 tokens, 28/4 heads, head_dim 128, rows selecting independently): the key-stationary
-// kernel is the faster one below this share of selected candidate cubes (break-even at 44 %).
-constexpr int PAIRS_BELOW_PERMILLE = 400;
+// The key-stationary kernel is the faster one below this share of selected candidate cubes.  The walk takes time by the
+// tiles of a cube, 0.03 ns a candidate pair and tile at head-dim 128; a selected pair costs the other path 0.22 ns in cubes of one tile and
+// 0.24 in cubes of four, most of it its record.  (Measured: 65,536 tokens of 28/4 heads in cubes of 256, break-even at 44 %;
+// 7,688 tokens in cubes of 32, 33 % selected, 2,250 us against 910.)
+static int pairs_below_permille(const Geom &g) { return 60 + 85 * g.TPC; }  // (TPC at most 4: pairs_supported)
 
 template <int D>
 static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, const uint32_t *sel_mask,
@@ -637,10 +656,10 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
         return launch_attn_compact(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     if (sparse_kernel == ADASPARK_SPARSE_MASKED || !g.causal)  // non-causal mode: the masked walk is the one kernel
         return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
-    // Small problems (8,192 rows of 64 cubes, say) are bound by the latency from one dependent kernel to the next:
-    // the dozen kernels that measure the selection and prepare the other paths would cost more than any choice
+    // Small problems (8,192 rows of 64 cubes, say) are bound by the latency from one dependent kernel to the next, or by the
+    // longest walk: the kernels that measure the selection and prepare the other paths would cost more than any choice
     // among them can win back.  The masked walk is the one kernel then.
-    if (sparse_kernel == ADASPARK_SPARSE_AUTO && candidate_pairs(g) < AUTO_MIN_CANDIDATE_PAIRS)
+    if (sparse_kernel == ADASPARK_SPARSE_AUTO && !chosen_on_device(g))
         return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     // Automatic (or the key-stationary kernel asked for): the choice is made on the device, every candidate kernel
     // is enqueued, and the workgroups of those not chosen return at once.  First the selected share from a sample
@@ -652,12 +671,15 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
         if (sparse_kernel == ADASPARK_SPARSE_PAIRS) return hipErrorInvalidValue;  // the entry point checks this first
         flags = reinterpret_cast<int *>(reinterpret_cast<char *>(packed) + attn_workspace_bytes(g) - 16);
     }
-    hipLaunchKernelGGL(sel_density_kernel, dim3(1), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes);
+    int counter_words = 0;
+    uint32_t *counters = kv_modes ? pairs_counters(g, scratch, scratch_bytes, counter_words) : nullptr;
+    hipLaunchKernelGGL(sel_density_kernel, dim3(1), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes, counters,
+                       counter_words);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (kv_modes) {
         e = launch_attn_pairs(g, Q, packed, sel_mask, scratch, scratch_bytes, sparse_kernel == ADASPARK_SPARSE_PAIRS,
-                              PAIRS_BELOW_PERMILLE, O, lse, st);
+                              pairs_below_permille(g), O, lse, st);
         if (e != hipSuccess) return e;
     }
     e = launch_attn_compact(g, Q, packed, sel_mask, flags, 1, kv_modes, O, lse, st);

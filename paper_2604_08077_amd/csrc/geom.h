@@ -192,12 +192,12 @@ hipError_t launch_kv_pack(const Geom &g, const uint16_t *K, const uint16_t *V, v
 //                    the others), permille, from a sample of workgroups; 1000 where rows select independently
 //   [FLAG_KV + kv]   3: the rows of KV head kv are left to the key-stationary kernel; 0: to the kernel above
 // The per-head part exists only where the caller's workspace has room for the key-stationary kernel's tables
-// (kernels take `kv_modes` = 1); the block is then 512 bytes long and followed by that kernel's per-head pair
-// totals, u64 [Hkv], which the kernel that fills the first two flags also clears.  Otherwise the block is the
-// four ints at the end of the minimum workspace.
+// (kernels take `kv_modes` = 1); the block is then 512 bytes long and followed by the heads' estimated shares,
+// [FLAG_SHARE + kv], permille.  Otherwise the block is the four ints at the end of the minimum workspace.
 constexpr int FLAG_MODE = 0, FLAG_ESTIMATE = 1, FLAG_ACTIVE = 2, FLAG_UNION = 3, FLAG_KV = 4;
 constexpr int PAIRS_MAX_KV_HEADS = 64;
 constexpr int FLAG_BLOCK_BYTES = 512;
+constexpr int FLAG_SHARE = FLAG_BLOCK_BYTES / 4;
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device, before its first launch.
 // One object per kernel: ensure() asks the runtime only the first time a device (or a larger size) comes by, so a
@@ -241,13 +241,15 @@ hipError_t launch_attn_compact(const Geom &g, const uint16_t *Q, const void *pac
 // The key-stationary sparse kernel (attn_pairs.hip).  pairs_scratch_bytes: scratch for max_selected selected (row,
 // cube) pairs.  pairs_flags: the flag block inside the scratch memory (with the per-head part), or null if the
 // scratch memory does not hold the tables or the geometry is not covered.  launch_attn_pairs expects
-// flags[FLAG_MODE], flags[FLAG_ESTIMATE] set and flags[FLAG_KV ...] zero; it enqueues kernels that -- unless the
+// flags[FLAG_MODE], flags[FLAG_ESTIMATE], flags[FLAG_SHARE ...] set, flags[FLAG_KV ...] and the counters zero; it enqueues kernels that -- unless the
 // estimate is well above pairs_below_permille and force is 0 -- count the pairs exactly per KV head, hand the heads
 // whose share is below pairs_below_permille (all heads, if force) to this path as long as their records fit, and run
 // it for those heads.
 bool pairs_supported(const Geom &g);
 size_t pairs_scratch_bytes(const Geom &g, long long max_selected);
 int *pairs_flags(const Geom &g, void *scratch, size_t scratch_bytes);
+// the counters inside the scratch memory that have to be zero when launch_attn_pairs is called (words of them)
+uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int &words);
 hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, void *scratch,
                              size_t scratch_bytes, int force, int pairs_below_permille, uint16_t *O, float *lse,
                              hipStream_t st);
