@@ -308,6 +308,21 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 #pragma unroll
         for (int s = 0; s < NS; ++s) mword_ahead[s] = sel_mask[(size_t)rowid[lr[s]] * g.words];
     }
+    // Wave-uniform: no row of the wavefront is without a reference point any more; no row that takes part in the cube is
+    // (softmax_tile_fast may be tried).  Rows that select a cube or two are without one for most of their walk, and would
+    // keep their wavefront on the long step (144,585 tokens of 14/2 heads of 128, one KV head's rows
+    // selecting nearly nothing: 63.7 ms, with only the first condition 73.1).
+    bool settled = false, short_step = false;
+    auto references = [&]() __attribute__((always_inline)) {
+        bool open = false, here = false;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            open = open || fresh[s];
+            here = here || (fresh[s] && (!MASKED || rsel[s]));
+        }
+        settled = __ballot(open) == 0ull;
+        short_step = __ballot(here) == 0ull;
+    };
     // Per-cube constants of the softmax: key limits of every row, and (MASKED) whether the row attends the cube.  A row
     // attends its own cube up to its rank and no later one.
     auto enter_cube = [&](int j, int size) __attribute__((always_inline)) {
@@ -336,6 +351,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
                 if (g.causal && j >= own) lim[s] = j == own ? min(rrank[lr[s]], size - 1) : -1;
             }
         }
+        if (!settled) references();
     };
     auto advance = [&]() __attribute__((always_inline)) {
         if (cc_t + 1 < cc_nt) ++cc_t;
@@ -352,19 +368,15 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 
     f32x4 sacc[NS][4];
     bf16x8 pf[NS][2];
-    bool settled = false;  // wave-uniform: no row of the wavefront is fresh any more (softmax_tile_fast may be tried)
     auto softmax_step = [&]() __attribute__((always_inline)) {
         const int key0 = KEY_TILE * cc_t;
         // the causal edge (of the sparse entry's rows, a cube behind the own one is just not selected); padding keys
         const bool edge = g.causal && cc_j >= own_lo && (MASKED ? cc_j <= own_hi : true) &&
                           (cc_j > own_lo || key0 + KEY_TILE - 1 > rank_lo);
         const int fill = cc_size - key0;
-        if (edge || !softmax_tile_fast<NS>(sacc, pf, settled, smem + C::OFF_FILL, fill, q4)) {
+        if (edge || !softmax_tile_fast<NS>(sacc, pf, short_step, smem + C::OFF_FILL, fill, q4)) {
             softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, lim, key0, edge || fill < KEY_TILE, q4);
-            bool open = false;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) open = open || fresh[s];
-            settled = __ballot(open) == 0ull;  // every row of the wavefront has a reference point by now
+            references();
         }
         advance();
     };

@@ -373,7 +373,8 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws)
 // past the line, 4,131 of 2048/8448 in 42 cubes, 275, 267.
 static bool finish_small(const Geom &g, int d_model)
 {
-    return g.Cmax >= 128 && (long long)g.N * ((d_model + 511) / 512) <= FINISH_SMALL;
+    const long long blocks = (long long)g.N * ((d_model + 511) / 512);
+    return g.Cmax >= 128 && blocks <= (g.S >= 96LL * g.N ? FINISH_SMALL : FINISH_SMALL / 2);
 }
 
 hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_t *X, const uint16_t *Wg,
