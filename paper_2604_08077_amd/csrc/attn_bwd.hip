@@ -13,14 +13,14 @@
 //                        Q, dO and two floats, so rows are gathered into tiles, and the work follows the selection.
 //                        S = Q.K^T, dP = dO.V^T, dV^T += dO^T.P, dK^T += Q^T.dS.
 // The streamed tiles of the first come from packed, pre-swizzled copies (kvtile.h layouts) straight into LDS: K
-// natural / V natural / K transposed per 64 keys (two runs of the forward's pack kernel).  The second gathers rows of
+// natural / V natural / K transposed per 64 keys (bwd_prep_kernel).  The second gathers rows of
 // Q and dO as the caller holds them, and reads each tile in LDS both ways: rows as they are, and transposed
 // (ds_read_b64_tr_b16).
 // The score products take Q and K as they are (bf16 x bf16 -> fp32: exact products, so the rebuilt probabilities
 // carry nothing but their own rounding, whatever the size of the scores) and their accumulators start from
 // -lse * sqrt(D), -inf for a row that did not select the key cube: the accumulator times the softmax scale in base
 // 2 is then the exponent of the probability, and the selection costs no instruction per score.  The dP accumulators
-// start from minus delta.  bwd_row_values_kernel leaves both start values per row.
+// start from minus delta.  bwd_prep_kernel leaves both start values per row.
 #include <algorithm>
 #include <type_traits>
 
@@ -77,8 +77,8 @@ static size_t bwd_part_bytes(const Geom &g, const BwdParts &p)
 }
 
 struct BwdWorkspace {
-    void *packA;             // launch_kv_pack(K, V): natural K first (its V^T half is not used here)
-    void *packB;             // launch_kv_pack(V, K): natural V, then K transposed
+    uint16_t *Kn, *Vn, *Kt;  // packed copies (kvtile.h): K and V natural, K transposed
+    int32_t *csize;          // [N] sizes of the cubes
     // -lse * sqrt(D) and -delta per row (what the score and dP products start from); entry [rows] belongs to the rows
     // that pad a tile: -inf, 0
     float *lse2, *delta;     // [S * Hq + 1]
@@ -103,8 +103,11 @@ BwdWorkspace bwd_workspace(const Geom &g, void *ws, bool in_place)
     w.cut = bwd_parts(g);
     const size_t rows = (size_t)g.S * g.Hq + 1;
     size_t off = 0;
-    w.packA = p + off; off = up(off + attn_workspace_bytes(g));
-    w.packB = p + off; off = up(off + attn_workspace_bytes(g));
+    const size_t copy_bytes = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * g.D * sizeof(uint16_t);
+    w.Kn = reinterpret_cast<uint16_t *>(p + off); off = up(off + copy_bytes);
+    w.Vn = reinterpret_cast<uint16_t *>(p + off); off = up(off + copy_bytes);
+    w.Kt = reinterpret_cast<uint16_t *>(p + off); off = up(off + copy_bytes);
+    w.csize = reinterpret_cast<int32_t *>(p + off); off = up(off + (size_t)g.N * 4);
     w.lse2 = reinterpret_cast<float *>(p + off); off = up(off + rows * 4);
     w.delta = reinterpret_cast<float *>(p + off); off = up(off + rows * 4);
     w.colmask = reinterpret_cast<unsigned long long *>(p + off); off = up(off + (size_t)g.Hkv * g.N * g.N * w.tpcr * 8);
@@ -176,59 +179,108 @@ __global__ __launch_bounds__(256) void bwd_copy_rows_kernel(long long pieces, co
     dOc[x] = dO[x];
 }
 
-// What a row's products start from: lse2 = -lse * sqrt(D), delta = -dO.O; entry [rows]: what padding rows start from.
+// What the kernels below read, in one launch whose workgroups do one of three things (as four launches, 1,080 tokens of 6/2 heads of
+// 128, a layer's training pass 135 us, and 127):
+//   a tile of 64 keys   its packed copies, K and V natural and K transposed (kvtile.h); padding keys are zero
+//   256 / (D / 8) rows  what their products start from: lse2 = -lse * sqrt(D), delta = -dO.O; entry [rows]: what padding rows
+//                       start from
+//   four row tiles      the selection bits transposed for the key-stationary kernel, a wavefront per (KV head, row cube i, row
+//                       tile t): lane k holds the mask words of row 64 t + k (rank-major: row r of a cube is head r % G of rank
+//                       r / G), a ballot per cube turns 64 rows' bits into one 64-bit word.  sel_mask == nullptr: every row
+//                       selects every cube.  KV head 0 also leaves the row ids of the row tiles (those of KV head kv are
+//                       kv * G higher).
+struct BwdPrep {
+    const uint16_t *K, *V, *O, *dO;
+    const float *lse;
+    const uint32_t *sel_mask;
+    uint16_t *Kn, *Vn, *Kt;
+    int32_t *csize;
+    float *lse2, *delta;
+    unsigned long long *colmask;
+    uint32_t *rowtab;
+    int tpcr;
+    uint32_t mask_blocks, key_blocks;  // the first workgroups are row tiles', the next ones key tiles', the rest rows'
+};
 template <int D>
-__global__ __launch_bounds__(256) void bwd_row_values_kernel(long long rows, const uint16_t *__restrict__ dO,
-                                                             const uint16_t *__restrict__ O, const float *__restrict__ lse,
-                                                             float *__restrict__ lse2, float *__restrict__ delta)
+__global__ __launch_bounds__(256) void bwd_prep_kernel(Geom g, BwdPrep p)
 {
-    constexpr int CPR = D / 8;  // lanes per row, 16 bytes each
-    const long long r = ((long long)blockIdx.x * 256 + threadIdx.x) / CPR;
-    const int col = threadIdx.x % CPR;
-    float part = 0.f;
-    if (r < rows) {
-        const uint4 gg = *reinterpret_cast<const uint4 *>(dO + r * D + col * 8);
-        const uint4 oo = *reinterpret_cast<const uint4 *>(O + r * D + col * 8);
-        const uint32_t gw[4] = {gg.x, gg.y, gg.z, gg.w}, ow[4] = {oo.x, oo.y, oo.z, oo.w};
+    constexpr int CPR = D / 8;  // 16-byte pieces of a row
+    __shared__ __attribute__((aligned(16))) uint16_t ks[KEY_TILE][D + 8];
+    const int lane = threadIdx.x & 63;
+    if (blockIdx.x < p.mask_blocks) {
+        uint32_t x = blockIdx.x * 4 + (threadIdx.x >> 6);
+        if (x >= (uint32_t)p.tpcr * (uint32_t)g.N * (uint32_t)g.Hkv) return;
+        const int t = (int)(x % (uint32_t)p.tpcr);
+        x /= (uint32_t)p.tpcr;
+        const int i = (int)(x % (uint32_t)g.N), kv = (int)(x / (uint32_t)g.N);
+        const CubeBox box = cube_box(g, i);
+        const int r = 64 * t + lane;
+        const bool valid = r < box.size() * g.G;
+        const size_t rowid = valid ? (size_t)token_of(g, box, r / g.G) * g.Hq + kv * g.G + r % g.G : 0;
+        if (kv == 0) p.rowtab[((size_t)i * p.tpcr + t) * 64 + lane] = (uint32_t)rowid;
+        for (int jw = 0; 32 * jw < i; ++jw) {
+            const uint32_t word = valid ? (p.sel_mask != nullptr ? p.sel_mask[rowid * g.words + jw] : ~0u) : 0u;
+            unsigned long long mine = 0ull;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            part = fmaf(__uint_as_float(gw[e] << 16), __uint_as_float(ow[e] << 16), part);
-            part = fmaf(__uint_as_float(gw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), part);
+            for (int b = 0; b < 32; ++b) {
+                const unsigned long long bal = __ballot((word >> b) & 1u);
+                if (lane == b) mine = bal;
+            }
+            const int j = 32 * jw + lane;
+            if (lane < 32 && j < i) p.colmask[(((size_t)kv * g.N + j) * g.N + i) * p.tpcr + t] = mine;
         }
-    }
-#pragma unroll
-    for (int d = CPR / 2; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
-    if (col == 0 && r <= rows) {
-        lse2[r] = r < rows ? -lse[r] * sqrtf((float)D) : -INFINITY;  // = -(lse in base 2) / (softmax scale in base 2)
-        delta[r] = -part;
-    }
-}
-
-// The selection bits transposed for the key-stationary kernel: one wavefront per (KV head, row cube i, row tile t);
-// lane k holds the mask words of row 64 t + k (rank-major: row r of a cube is head r % G of rank r / G), a ballot per
-// cube turns 64 rows' bits into one 64-bit word.  sel_mask == nullptr: every row selects every cube.  KV head 0 also
-// leaves the row ids of the row tiles (those of KV head kv are kv * G higher).
-__global__ __launch_bounds__(64) void bwd_colmask_kernel(Geom g, const uint32_t *__restrict__ sel_mask, int tpcr,
-                                                        unsigned long long *__restrict__ colmask,
-                                                        uint32_t *__restrict__ rowtab)
-{
-    const int t = blockIdx.x, i = blockIdx.y, kv = blockIdx.z;
-    const int lane = threadIdx.x;
-    const CubeBox box = cube_box(g, i);
-    const int r = 64 * t + lane;
-    const bool valid = r < box.size() * g.G;
-    const size_t rowid = valid ? (size_t)token_of(g, box, r / g.G) * g.Hq + kv * g.G + r % g.G : 0;
-    if (kv == 0) rowtab[((size_t)i * tpcr + t) * 64 + lane] = (uint32_t)rowid;
-    for (int jw = 0; 32 * jw < i; ++jw) {
-        const uint32_t word = valid ? (sel_mask != nullptr ? sel_mask[rowid * g.words + jw] : ~0u) : 0u;
-        unsigned long long mine = 0ull;
-#pragma unroll
-        for (int b = 0; b < 32; ++b) {
-            const unsigned long long bal = __ballot((word >> b) & 1u);
-            if (lane == b) mine = bal;
+    } else if (blockIdx.x < p.mask_blocks + p.key_blocks) {
+        uint32_t x = blockIdx.x - p.mask_blocks;
+        const size_t tile_base = (size_t)x * (KEY_TILE * D);
+        const int t = (int)(x % (uint32_t)g.TPC);
+        x /= (uint32_t)g.TPC;
+        const int c = (int)(x % (uint32_t)g.N), kv = (int)(x / (uint32_t)g.N);
+        const CubeBox box = cube_box(g, c);
+        const int size = box.size();
+        if (t == 0 && kv == 0 && threadIdx.x == 0) p.csize[c] = size;
+        for (int y = threadIdx.x; y < KEY_TILE * CPR; y += 256) {
+            const int k = y / CPR, col = y % CPR, rank = KEY_TILE * t + k;
+            uint4 kk = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
+            if (rank < size) {
+                const size_t src = ((size_t)token_of(g, box, rank) * g.Hkv + kv) * D + col * 8;
+                kk = *reinterpret_cast<const uint4 *>(p.K + src);
+                vv = *reinterpret_cast<const uint4 *>(p.V + src);
+            }
+            *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(p.Kn + tile_base) + k_tile_off<D>(k, col)) = kk;
+            *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(p.Vn + tile_base) + k_tile_off<D>(k, col)) = vv;
+            *reinterpret_cast<uint4 *>(&ks[k][col * 8]) = kk;
         }
-        const int j = 32 * jw + lane;
-        if (lane < 32 && j < i) colmask[(((size_t)kv * g.N + j) * g.N + i) * tpcr + t] = mine;
+        __syncthreads();
+        for (int y = threadIdx.x; y < D * (KEY_TILE / 8); y += 256) {
+            const int d = y / (KEY_TILE / 8), kc = y % (KEY_TILE / 8);
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                w[e] = (uint32_t)ks[kc * 8 + 2 * e][d] | ((uint32_t)ks[kc * 8 + 2 * e + 1][d] << 16);
+            *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(p.Kt + tile_base) + vt_tile_off(d, kc)) =
+                make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    } else {
+        const long long rows = (long long)g.S * g.Hq;
+        const long long r = ((long long)(blockIdx.x - p.mask_blocks - p.key_blocks) * 256 + threadIdx.x) / CPR;
+        const int col = threadIdx.x % CPR;
+        float part = 0.f;
+        if (r < rows) {
+            const uint4 gg = *reinterpret_cast<const uint4 *>(p.dO + r * D + col * 8);
+            const uint4 oo = *reinterpret_cast<const uint4 *>(p.O + r * D + col * 8);
+            const uint32_t gw[4] = {gg.x, gg.y, gg.z, gg.w}, ow[4] = {oo.x, oo.y, oo.z, oo.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                part = fmaf(__uint_as_float(gw[e] << 16), __uint_as_float(ow[e] << 16), part);
+                part = fmaf(__uint_as_float(gw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), part);
+            }
+        }
+#pragma unroll
+        for (int d = CPR / 2; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
+        if (col == 0 && r <= rows) {
+            p.lse2[r] = r < rows ? -p.lse[r] * sqrtf((float)D) : -INFINITY;  // = -(lse in base 2) / (softmax scale in base 2)
+            p.delta[r] = -part;
+        }
     }
 }
 
@@ -927,22 +979,14 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
         Q = w.Q;
         dO = w.dO;
     }
-    hipError_t e = launch_kv_pack(g, K, V, w.packA, false, st);  // natural K as it is: exact score products
+    BwdPrep prep{K, V, O, dO, lse, sel_mask, w.Kn, w.Vn, w.Kt, w.csize, w.lse2, w.delta, w.colmask, w.rowtab, w.tpcr, 0, 0};
+    prep.mask_blocks = (uint32_t)(((long long)w.tpcr * g.N * g.Hkv + 3) / 4);
+    prep.key_blocks = (uint32_t)((long long)g.TPC * g.N * g.Hkv);
+    const long long row_blocks = ((long long)g.S * g.Hq + 1 + 256 / (D / 8) - 1) / (256 / (D / 8));
+    hipLaunchKernelGGL((bwd_prep_kernel<D>), dim3((unsigned)(prep.mask_blocks + prep.key_blocks + row_blocks)), dim3(256), 0, st, g,
+                       prep);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_kv_pack(g, V, K, w.packB, false, st);
-    if (e != hipSuccess) return e;
-    const long long rows = (long long)g.S * g.Hq;
-    hipLaunchKernelGGL((bwd_row_values_kernel<D>), dim3((unsigned)((rows + 1 + 256 / (D / 8) - 1) / (256 / (D / 8)))),
-                       dim3(256), 0, st, rows, dO, O, lse, w.lse2, w.delta);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(bwd_colmask_kernel, dim3(w.tpcr, g.N, g.Hkv), dim3(64), 0, st, g, sel_mask, w.tpcr, w.colmask, w.rowtab);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-
-    const size_t half_elems = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * D;
-    const uint16_t *Kn = reinterpret_cast<const uint16_t *>(w.packA);
-    const uint16_t *Vn = reinterpret_cast<const uint16_t *>(w.packB);
-    const uint16_t *Kt = Vn + half_elems;
-    const int32_t *csize = reinterpret_cast<const int32_t *>(Kt + half_elems);
     constexpr int TILE = 64 * D * 2;
 
     const int keys = dq_keys(g), rows_q = BWD_ROWS / keys;
@@ -957,8 +1001,8 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
         static LdsOptIn opted_q;  // one per kernel instantiation
         const hipError_t err = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED, KEYS>), lds_q);
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED, KEYS>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, Kn, Vn,
-                           Kt, csize, w.lse2, w.delta, sel_mask, dQ);
+        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED, KEYS>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, w.Kn, w.Vn,
+                           w.Kt, w.csize, w.lse2, w.delta, sel_mask, dQ);
         return hipGetLastError();
     };
     const std::integral_constant<int, 1> one;

@@ -9,9 +9,9 @@
 
 namespace adaspark {
 
-// F16: the natural copy (the first operand's) is written as fp16 -- the score operand of the attention kernels
-// (attn_tile.h: exact within fp16's range, saturating beyond it); otherwise as the bf16 it is.
-template <int D, bool F16>
+// The natural copy of K is written as fp16 -- the score operand of the attention kernels (attn_tile.h: exact within fp16's
+// range, saturating beyond it).
+template <int D>
 __global__ __launch_bounds__(256) void kv_pack_kernel(Geom g, const uint16_t *__restrict__ K,
                                                       const uint16_t *__restrict__ V, uint16_t *__restrict__ Kp,
                                                       uint16_t *__restrict__ Vt, int32_t *__restrict__ csize)
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(Geom g, const uint16_t *__
             kk = *reinterpret_cast<const uint4 *>(K + src);
             vv = *reinterpret_cast<const uint4 *>(V + src);
         }
-        if (F16) kk = __builtin_bit_cast(uint4, score_operand(__builtin_bit_cast(bf16x8, kk), 1.0f));
+        kk = __builtin_bit_cast(uint4, score_operand(__builtin_bit_cast(bf16x8, kk), 1.0f));
         *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(Kp + tile_base) + k_tile_off<D>(k, col)) = kk;
         *reinterpret_cast<uint4 *>(&vs[k][col * 8]) = vv;
     }
@@ -57,21 +57,20 @@ size_t attn_workspace_bytes(const Geom &g)
     return 2 * (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * g.D * sizeof(uint16_t) + (((size_t)g.N * 4 + 15) / 16) * 16 + 16;
 }
 
-template <int D, bool F16>
+template <int D>
 static hipError_t launch_pack_d(const Geom &g, const uint16_t *K, const uint16_t *V, void *ws, hipStream_t st)
 {
     uint16_t *Kp = reinterpret_cast<uint16_t *>(ws);
     const size_t half_elems = (size_t)g.Hkv * g.N * g.TPC * KEY_TILE * D;
     uint16_t *Vt = Kp + half_elems;
     int32_t *csize = reinterpret_cast<int32_t *>(Vt + half_elems);
-    hipLaunchKernelGGL((kv_pack_kernel<D, F16>), dim3(g.TPC, g.N, g.Hkv), dim3(256), 0, st, g, K, V, Kp, Vt, csize);
+    hipLaunchKernelGGL((kv_pack_kernel<D>), dim3(g.TPC, g.N, g.Hkv), dim3(256), 0, st, g, K, V, Kp, Vt, csize);
     return hipGetLastError();
 }
 
-hipError_t launch_kv_pack(const Geom &g, const uint16_t *K, const uint16_t *V, void *ws, bool natural_f16, hipStream_t st)
+hipError_t launch_kv_pack(const Geom &g, const uint16_t *K, const uint16_t *V, void *ws, hipStream_t st)
 {
-    if (g.D == 64) return natural_f16 ? launch_pack_d<64, true>(g, K, V, ws, st) : launch_pack_d<64, false>(g, K, V, ws, st);
-    return natural_f16 ? launch_pack_d<128, true>(g, K, V, ws, st) : launch_pack_d<128, false>(g, K, V, ws, st);
+    return g.D == 64 ? launch_pack_d<64>(g, K, V, ws, st) : launch_pack_d<128>(g, K, V, ws, st);
 }
 
 }  // namespace adaspark
