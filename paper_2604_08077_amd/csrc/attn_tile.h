@@ -368,6 +368,11 @@ __device__ __forceinline__ void mfma_phase_from(const unsigned char *vt, const u
 {
     constexpr int DT = D / 16, KSTEPS = D / 32;
     constexpr int RV = DO_PV ? 2 * DT : 0, RK = DO_QK ? 4 * KSTEPS : 0, R = RV + RK;
+    // The SIMD's other wavefront is (mostly) in its softmax: its vector instructions go where the MFMAs leave room, and not the
+    // other way round (65,536 tokens of 28/4 heads, masked walk, a forward pass: 23.35 ms at one priority, 23.1 so, 23.7 with the
+    // softmax preferred; key-stationary 10.23, 10.08, 10.13.  The backward's kernels, with a barrier per tile and both
+    // wavefronts in phase, gain nothing either way.)
+    __builtin_amdgcn_s_setprio(1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -392,6 +397,7 @@ __device__ __forceinline__ void mfma_phase_from(const unsigned char *vt, const u
         if (r + PF < R) ring[r % PF] = phase_operand<D, DO_PV, DO_QK>(vt, kt, n16, q4, r + PF);
         __builtin_amdgcn_sched_barrier(0);
     }
+    __builtin_amdgcn_s_setprio(0);
 }
 
 template <int D, int NS, int PF, bool DO_PV, bool DO_QK>
