@@ -54,8 +54,8 @@ hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_
                              const uint16_t *Wu, const uint16_t *Wd, const uint8_t *keep, uint16_t *Y,
                              const FfnWorkspace &w, hipStream_t st);
 
-// H[r][:] = silu(W_gate . x) * (W_up . x) for x = X[active[r]], r < *n_rows (rows up to the next multiple of
-// FFN_ROW_TILE are computed too, from the padding of `active`).  m_tiles: upper bound of row tiles (grid size).
+// H[r][:] = silu(W_gate . x) * (W_up . x) for x = X[active[r]], r < *n_rows (rows up to the next multiple of half a
+// FFN_ROW_TILE, or of a whole one, are computed too, from the padding of `active`; those behind them hold what they held).  m_tiles: upper bound of row tiles (grid size).
 hipError_t launch_ffn_gemm_gated(const uint16_t *X, const int32_t *active, const uint16_t *Wg, const uint16_t *Wu,
                                  int d_model, int d_ff, int m_tiles, const int32_t *n_rows, uint16_t *H, hipStream_t st);
 // F[split][r][:]: over the splits (ffn_down_splits) summing to W_down . H[r][:], in fp32.  blocks: FfnWorkspace::down_blocks.

@@ -35,7 +35,8 @@ constexpr int GEMM_THREADS = 512;
 constexpr int TILE_BYTES = GT * GK * 2;     // 32 KB
 constexpr int HALF_BYTES = TILE_BYTES / 2;
 constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // activations, weights
-constexpr int GEMM_LDS = 2 * STAGE_BYTES;   // 128 KB
+constexpr int HALF_STAGE = HALF_BYTES + TILE_BYTES;  // half the activation rows
+constexpr int GEMM_LDS = 3 * HALF_STAGE;    // 144 KB (two whole stages: 128)
 
 // Ends a slot: everything this wavefront has loaded but the newest KEEP loads (63: whatever is on the way) has landed and
 // its LDS reads are done, then the workgroup barrier.
@@ -57,19 +58,45 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
     const int m_tiles = (*n_rows_ptr + GT - 1) / GT;  // row tiles that hold activated tokens
     if (m_tiles == 0) return;
-    const int splits = GATED ? 1 : ffn_down_splits(m_tiles, n_tiles, K);
-    // Workgroup -> tile.  Consecutive workgroups go to different XCDs (each with its own L2), so the 32 tiles of a
-    // 4 x 8 block -- four row tiles that share their weights with eight weight tiles that share their rows -- are
-    // given to one XCD: block k of 32 goes to XCD k % 8.
-    const int total = (m_tiles + 3) / 4 * 4 * n_tiles;
-    const int idx = blockIdx.x >> 3;
-    const int block = (idx >> 5) * 8 + (blockIdx.x & 7), blocks = (total + 31) >> 5;  // (a split: that many blocks)
-    const int split = block / blocks;
-    const int logical = ((block - split * blocks) << 5) + (idx & 31);
-    if (split >= splits || logical >= total) return;
-    const int tm = logical / (4 * n_tiles) * 4 + (logical & 3);
-    const int tn = (logical >> 2) % n_tiles;
-    if (tm >= m_tiles) return;
+    int tm, tn, split = 0, splits = 1;
+    int half = -1;  // 0, 1: that half of the tile's activation rows only
+    if (GATED) {
+        // The tiles that fill whole rounds of one per CU, then the last ones: as halves, where all of them find a CU (964 rows of
+        // 3584/18944: 592 tiles, the last 80 as 160 halves on 256 CUs: a layer with its selection 383 us, and 405).  A tile is
+        // one of m_tiles x n_tiles, in blocks four row tiles high as below; those of a round that share an XCD follow each other.
+        const int total = m_tiles * n_tiles, whole = total / 256 * 256, rest = total - whole;
+        const int round = blockIdx.x >> 8, xcd = blockIdx.x & 7, idx = (blockIdx.x & 255) >> 3;
+        int tile = round * 256 + xcd * 32 + idx;
+        if (round * 256 >= whole) {
+            if (round * 256 > whole) return;
+            const bool halves = 2 * rest <= 256;
+            const int n = halves ? 2 * rest : rest, per = (n + 7) / 8, x = xcd * per + idx;
+            if (idx >= per || x >= n) return;
+            tile = whole + (halves ? x >> 1 : x);
+            if (halves) half = x & 1;
+        }
+        const int group = tile / (4 * n_tiles), high = min(4, m_tiles - 4 * group), in = tile - group * 4 * n_tiles;
+        tm = 4 * group + in % high;
+        tn = in / high;
+        const bool short_tile = *n_rows_ptr - tm * GT <= GT / 2;  // nothing in its second half
+        if (short_tile && half == 1) return;
+        if (short_tile) half = 0;
+    } else {
+        splits = ffn_down_splits(m_tiles, n_tiles, K);
+        // Workgroup -> tile.  Consecutive workgroups go to different XCDs (each with its own L2), so the 32 tiles of a
+        // 4 x 8 block -- four row tiles that share their weights with eight weight tiles that share their rows -- are
+        // given to one XCD: block k of 32 goes to XCD k % 8.
+        const int total = (m_tiles + 3) / 4 * 4 * n_tiles;
+        const int idx = blockIdx.x >> 3;
+        const int block = (idx >> 5) * 8 + (blockIdx.x & 7), blocks = (total + 31) >> 5;  // (a split: that many blocks)
+        split = block / blocks;
+        const int logical = ((block - split * blocks) << 5) + (idx & 31);
+        if (split >= splits || logical >= total) return;
+        tm = logical / (4 * n_tiles) * 4 + (logical & 3);
+        tn = (logical >> 2) % n_tiles;
+        if (tm >= m_tiles) return;
+    }
+    const int half_row = half == 1 ? GT / 2 : 0;
     // this split's reduction steps (at least one: K / GK >= splits)
     const int k_first = (int)((long long)split * (K / GK) / splits);
     const int nk = (int)((long long)(split + 1) * (K / GK) / splits) - k_first;
@@ -88,7 +115,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
         vt_tile_coords((wave * 2 + i) * 64 + lane, row, chunk);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const long long arow = gather ? (long long)gather[tm * GT + h * 128 + row] : (long long)(h * 128 + row);
+            const long long arow = gather ? (long long)gather[tm * GT + (half < 0 ? h * 128 : half_row) + row] : (long long)(h * 128 + row);
             voffA[h][i] = (uint32_t)(arow * K * 2 + chunk * 16);
         }
         voffW[i] = (uint32_t)(row * K * 2 + chunk * 16);
@@ -136,12 +163,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
         for (int x = 0; x < 8; ++x)
             a[x] = *reinterpret_cast<const bf16x8 *>(smem + st + ra[x >> 2] + h * HALF_BYTES + (x & 3) * 2048);
     };
-    auto read_w = [&](uint32_t st) __attribute__((always_inline)) {
+    auto read_w = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int x = 0; x < 4; ++x)
-                w[h][x] = *reinterpret_cast<const bf16x8 *>(smem + st + rw[x >> 1] + h * HALF_BYTES + (x & 1) * 2048);
+                w[h][x] = *reinterpret_cast<const bf16x8 *>(smem + (st + (int)rw[x >> 1]) + h * HALF_BYTES + (x & 1) * 2048);
     };
     // 32 MFMAs: activation half h times both weight halves
     auto multiply = [&](int h) __attribute__((always_inline)) {
@@ -169,50 +196,103 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
         else open_slot<2>();
     };
 
-    issue_first(0);
-    issue_a(1, 0);
-    if (nk > 1) issue_first(1);
-    open_first(0);
-    if (wave < 4) {
-        for (int k = 0; k < nk; ++k) {
-            const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
-            read_a(0, st);
-            read_w(st);
-            if (k + 1 < nk) issue_a(1, k + 1);
+    if (GATED && half >= 0) {
+        // Half the activation rows: a step is two slots, three stages, loads two steps ahead.  In slots (Q one later), step k is
+        //   P  2k: read, load(k+2)   2k+1: multiply
+        // Q's last read of step k is in slot 2k+1, before the loads of step k+3 (same stage) start in 2k+2; those of step k+1
+        // have to have landed before P's read in slot 2k+2.
+        auto issue_step = [&](int k) __attribute__((always_inline)) {
+            const uint32_t dst = lds0 + (uint32_t)(k % 3 * HALF_STAGE);
+            const void *src_a = uniform_ptr(baseA + (size_t)k * (GK * 2));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) dma_1k_s(dst + (uint32_t)(i * 1024), src_a, voffA[0][i]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const void *src_w = uniform_ptr(baseW[h] + (size_t)k * (GK * 2));
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    dma_1k_s(dst + (uint32_t)(HALF_BYTES + h * HALF_BYTES + i * 1024), src_w, voffW[i]);
+            }
+        };
+        auto open_step = [&](int k) __attribute__((always_inline)) {  // the barrier before P reads step k
+            if (k + 1 < nk) open_slot<6>();
+            else open_slot<0>();
+        };
+        auto read_step = [&](int k) __attribute__((always_inline)) {
+            const int st = k % 3 * HALF_STAGE;
+            read_a(0, (uint32_t)st);
+            read_w(st - (TILE_BYTES - HALF_BYTES));
+        };
+        issue_step(0);
+        if (nk > 1) issue_step(1);
+        open_step(0);
+        if (wave < 4) {
+            for (int k = 0; k < nk; ++k) {
+                read_step(k);
+                if (k + 2 < nk) issue_step(k + 2);
+                open_slot<63>();
+                multiply(0);
+                open_step(k + 1);
+            }
             open_slot<63>();
-            multiply(0);
-            open_second(k);
-            read_a(1, st);
-            if (k + 2 < nk) issue_first(k + 2);
+        } else {
+            if (nk > 2) issue_step(2);
             open_slot<63>();
-            multiply(1);
-            open_first(k + 1);
+            for (int k = 0; k < nk; ++k) {
+                read_step(k);
+                open_step(k + 1);
+                if (k + 3 < nk) issue_step(k + 3);
+                multiply(0);
+                open_slot<63>();
+            }
         }
-        open_slot<63>();
     } else {
-        open_slot<63>();
-        for (int k = 0; k < nk; ++k) {
-            const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
-            read_a(0, st);
-            read_w(st);
-            if (k + 1 < nk) issue_a(1, k + 1);
-            open_second(k);
-            multiply(0);
+        issue_first(0);
+        issue_a(1, 0);
+        if (nk > 1) issue_first(1);
+        open_first(0);
+        if (wave < 4) {
+            for (int k = 0; k < nk; ++k) {
+                const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
+                read_a(0, st);
+                read_w((int)st);
+                if (k + 1 < nk) issue_a(1, k + 1);
+                open_slot<63>();
+                multiply(0);
+                open_second(k);
+                read_a(1, st);
+                if (k + 2 < nk) issue_first(k + 2);
+                open_slot<63>();
+                multiply(1);
+                open_first(k + 1);
+            }
             open_slot<63>();
-            read_a(1, st);
-            if (k + 2 < nk) issue_first(k + 2);
-            open_first(k + 1);
-            multiply(1);
+        } else {
             open_slot<63>();
+            for (int k = 0; k < nk; ++k) {
+                const uint32_t st = (uint32_t)((k & 1) * STAGE_BYTES);
+                read_a(0, st);
+                read_w((int)st);
+                if (k + 1 < nk) issue_a(1, k + 1);
+                open_second(k);
+                multiply(0);
+                open_slot<63>();
+                read_a(1, st);
+                if (k + 2 < nk) issue_first(k + 2);
+                open_first(k + 1);
+                multiply(1);
+                open_slot<63>();
+            }
         }
     }
 
     // Results: a lane holds output features 4*q4 .. 4*q4+3 of weight group g for the token of row n16 of slab s.
-    const size_t row0 = (size_t)tm * GT + wm * 64 + n16;  // slab s: + 128 (s / 4) + 16 (s % 4)
+    const size_t row0 = (size_t)tm * GT + half_row + wm * 64 + n16;  // slab s: + 128 (s / 4) + 16 (s % 4)
     if (GATED) {
         uint16_t *H = static_cast<uint16_t *>(out);
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
+        for (int s = 0; s < 8; ++s) {
+            if (s >= 4 && half >= 0) break;
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 bf16x2 p0, p1;
@@ -228,6 +308,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void ffn_gemm_kernel(const uint16_t *
                 o.y = *reinterpret_cast<uint32_t *>(&p1);
                 *reinterpret_cast<uint2 *>(H + (row0 + (s >> 2) * 128 + (s & 3) * 16) * ldo + tn * 128 + wn * 32 + g * 16 + 4 * q4) = o;
             }
+        }
     } else {
         float *F = static_cast<float *>(out) + (size_t)split * m_tiles * GT * ldo;
 #pragma unroll
@@ -246,7 +327,7 @@ hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, const uint16_t 
     static LdsOptIn opted;  // one per instantiation
     const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&ffn_gemm_kernel<GATED>), GEMM_LDS);
     if (e != hipSuccess) return e;
-    const long long grid = (blocks + 7) / 8 * 8 * 32;  // whole rounds over the eight XCDs
+    const long long grid = (blocks + 7) / 8 * 8 * 32;  // whole rounds over the eight XCDs (and so of 256 CUs)
     hipLaunchKernelGGL((ffn_gemm_kernel<GATED>), dim3((unsigned)grid), dim3(GEMM_THREADS), GEMM_LDS, st, A, gather, W0, W1, K,
                        n_tiles, n_rows, out, ldo);
     return hipGetLastError();
