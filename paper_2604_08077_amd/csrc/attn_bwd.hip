@@ -31,6 +31,7 @@ namespace adaspark {
 constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
 constexpr int DQ_SHARED_BLOCKS = 304;  // dq_keys
+constexpr int SHARED_ROWS = 6000;     // dkv_shared
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
 // How attn_bwd_dkv_kernel's work is cut.  A workgroup takes up to 256 keys (one of nkb key blocks) of one (key cube j, KV
@@ -656,7 +657,10 @@ __device__ __forceinline__ bf16x8 lds_read_tr2(uint32_t addr, int step)
     return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <int D>
+// SHARED: cubes of up to 128 tokens (a workgroup then has at most four wavefronts' worth of keys).  Wavefronts w and w + 4 take the
+// same keys, and the first and the second half of every tile's rows; their sums are added through LDS at the end
+// (dkv_shared).
+template <int D, bool SHARED>
 __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const uint16_t *__restrict__ K,
                                                                    const uint16_t *__restrict__ V,
                                                                    const uint16_t *__restrict__ Q,
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
     const int n16 = lane & 15, q4 = lane >> 4;
 
     // the wavefront's keys (B operands)
-    const int key0 = kb * BWD_ROWS + wave * 32;
+    const int key0 = kb * BWD_ROWS + (SHARED ? wave & 3 : wave) * 32;
     const bool busy = key0 < size_j;  // (a wavefront without keys only helps with the loads)
     bf16x8 kf[NS][KSTEPS], vf[NS][KSTEPS];
 #pragma unroll
@@ -765,7 +769,8 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
     auto tile_work = [&](int stage, auto own_tag, int r0) __attribute__((always_inline)) {
         constexpr bool OWN = decltype(own_tag)::value;
         const uint32_t st = lds0 + (uint32_t)(stage * C::STAGE);
-        const uint32_t nat = st + nat0, tr = st + tr0;
+        const uint32_t first = SHARED ? (uint32_t)((wave >> 2) * 2 * BLK) : 0u;  // the wavefront's half of the rows
+        const uint32_t nat = st + nat0 + first, tr = st + tr0 + first;
         auto rows_at = [&](int blk, int k, bf16x8 (&o)[2]) __attribute__((always_inline)) {  // Q, dO
             uint32_t at;
             asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "n"(k << 6), "v"(nat));
@@ -781,11 +786,11 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
         bf16x8 op[2][2];
         rows_at(0, 0, op[0]);
 #pragma unroll
-        for (int H = 0; H < 2; ++H) {
+        for (int H = 0; H < (SHARED ? 1 : 2); ++H) {
             bf16x8 pp[NS], ds[NS];
 #pragma unroll
             for (int x = 0; x < 2; ++x) {  // 16 rows: scores and dP
-                const uint32_t vec = st + (uint32_t)(C::OFF_LSE + 16 * (2 * H + x) * 4) + (uint32_t)(16 * q4);
+                const uint32_t vec = st + (uint32_t)(C::OFF_LSE + 16 * (2 * H + x) * 4 + (SHARED ? wave >> 2 : 0) * 128) + (uint32_t)(16 * q4);
                 const f32x4 li = lds_read<f32x4>(vec), di = lds_read<f32x4>(vec + 256);
                 f32x4 sa[NS], pa[NS];
 #pragma unroll
@@ -803,7 +808,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
                 if (OWN) {  // causal edge: a row attends keys up to its own rank
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int rank = (r0 + 16 * (2 * H + x) + 4 * q4 + v) / g.G;
+                        const int rank = (r0 + (SHARED ? wave >> 2 : 0) * 32 + 16 * (2 * H + x) + 4 * q4 + v) / g.G;
 #pragma unroll
                         for (int s = 0; s < NS; ++s)
                             if (key0 + 16 * s + n16 > rank) sa[s][v] = -INFINITY;
@@ -823,7 +828,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
 #pragma unroll
             for (int e = 0; e < DT; ++e) {
                 if (e + 1 < DT) cols_at(H, e + 1, op[(e + 1) & 1]);
-                else if (H == 0) rows_at(2, 0, op[(e + 1) & 1]);
+                else if (H == 0 && !SHARED) rows_at(2, 0, op[(e + 1) & 1]);
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     accK[s][e] = mfma16(op[e & 1][0], ds[s], accK[s][e]);
@@ -895,6 +900,25 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
             run_list(n, std::integral_constant<bool, true>{}, f);
         }
     }
+    if (SHARED) {
+        static_assert(4 * NS * DT * 1024 <= C::OFF_ROWS, "one sum of four wavefronts fits the tiles' place");
+        f32x4 *sums = reinterpret_cast<f32x4 *>(smem) + (size_t)(wave & 3) * (NS * DT * 64) + lane;
+        auto add = [&](f32x4 (&acc)[NS][DT]) __attribute__((always_inline)) {
+            __syncthreads();
+            if (wave >= 4) {
+#pragma unroll
+                for (int x = 0; x < NS * DT; ++x) sums[x * 64] = acc[x / DT][x % DT];
+            }
+            __syncthreads();
+            if (wave < 4) {
+#pragma unroll
+                for (int x = 0; x < NS * DT; ++x) acc[x / DT][x % DT] += sums[x * 64];
+            }
+        };
+        add(accV);
+        add(accK);
+        if (wave >= 4) return;
+    }
     if (!busy) return;
 
     // ---- results: element (s, e, v) of lane (n16, q4) is key 16 s + n16, head-dim 16 e + 4 q4 + v
@@ -963,6 +987,12 @@ static int dq_keys(const Geom &g)
     return blocks <= DQ_SHARED_BLOCKS ? 2 : 1;
 }
 
+// Whether two wavefronts share 32 keys in the dK/dV kernel: with cubes of up to 128 tokens half or more of a workgroup's wavefronts
+// have no keys of their own.  Few rows of a KV head do not make up for the sums' exchange.  A layer's training pass, us, shared and not:
+// 7,688 tokens of 28/4 heads of 128 in cubes of 32 4,204, 4,536; 4,938 of 6/2 in cubes of 128 556, 580; 2,079 of 6/2 in cubes of 32 301,
+// 304; 855 of 14/2 (5,985 rows of a KV head) 225, 219; 3,339 of 4/4 heads of 64 196, 190.
+static bool dkv_shared(const Geom &g) { return g.Cmax <= BWD_ROWS / 2 && (long long)g.S * g.G >= SHARED_ROWS; }
+
 template <int D>
 static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t *K, const uint16_t *V,
                                const uint16_t *O, const float *lse, const uint16_t *dO, const uint32_t *sel_mask,
@@ -1012,11 +1042,17 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     else
         e = keys == 2 ? launch_dq(std::false_type{}, two) : launch_dq(std::false_type{}, one);
     if (e != hipSuccess) return e;
-    static LdsOptIn opted_k;
-    e = opted_k.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D>), lds_k);
+    auto launch_dkv = [&](auto shared) -> hipError_t {
+        constexpr bool SHARED = decltype(shared)::value;
+        static LdsOptIn opted_k;  // one per kernel instantiation
+        const hipError_t err = opted_k.ensure(reinterpret_cast<const void *>(&attn_bwd_dkv_kernel<D, SHARED>), lds_k);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, SHARED>), grid_k, dim3(BWD_THREADS), lds_k, st, g, K, V, Q, dO, w.lse2, w.delta,
+                           w.tpcr, w.colmask, w.rowtab, cut, w.part, dK, dV);
+        return hipGetLastError();
+    };
+    e = dkv_shared(g) ? launch_dkv(std::true_type{}) : launch_dkv(std::false_type{});
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<D>), grid_k, dim3(BWD_THREADS), lds_k, st, g, K, V, Q, dO, w.lse2, w.delta, w.tpcr,
-                       w.colmask, w.rowtab, cut, w.part, dK, dV);
     if (cut.nc > 1)
         hipLaunchKernelGGL((bwd_reduce_kernel<D>), dim3(cut.nkb * (cut.keys * D / 4 / 256), g.N, g.Hkv), dim3(256), 0, st, g,
                            cut, w.part, dK, dV);

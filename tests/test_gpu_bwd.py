@@ -113,6 +113,20 @@ def test_backward_gathered_rows(B, oracle, monkeypatch, name, grid, cube, hq, hk
     run_case(B, oracle, name, 1.0, dense=True)
 
 
+# Two wavefronts per 32 keys in the dK/dV kernel: cubes of up to 128 tokens and 6,000 rows of a KV head or more; cubes of 33, 97
+# and 128 keys (one key, one of three and four wavefronts' worth of keys), and one row too few for it
+SHARED = [
+    ("keys33", (26, 3, 11), (1, 3, 11), 7, 64), ("keys97", (9, 1, 97), (1, 1, 97), 7, 128), ("keys128", (7, 8, 16), (1, 8, 16), 7, 128),
+    ("rows5999", (1, 1, 857), (1, 1, 50), 7, 128),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,d", SHARED, ids=[c[0] for c in SHARED])
+def test_backward_shared_keys(B, oracle, monkeypatch, name, grid, cube, hq, d):
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, synth.Workload(name, 43, *grid, *cube, hq, 1, d, (0.6,), (1.0,)))
+    run_case(B, oracle, name, 0.6)
+
+
 # The dQ kernel with two wavefronts per 32 rows, up to 304 workgroups' worth of 256 rows, and with one: both sides of the line;
 # cubes whose keys leave the second half of a tile empty, or with one key; row blocks of 128 and a remainder.
 DQ = [
