@@ -179,9 +179,6 @@ hipError_t launch_cube_select(const Geom &g, const uint16_t *Q, const float *kba
 size_t select_shared_workspace_bytes(const Geom &g);
 hipError_t launch_cube_select_shared(const Geom &g, const uint16_t *Q, const float *kbar, float top_p, uint32_t *sel_mask,
                                      int32_t *sel_count, void *ws, hipStream_t st);
-// out[0..n] = exclusive prefix sums of count[0..n-1]; tile_sum: scan_tile_sum_bytes(n) bytes of scratch (select.hip)
-size_t scan_tile_sum_bytes(long long n);
-void launch_exclusive_scan(const int32_t *count, long long n, long long *tile_sum, int64_t *out, hipStream_t st);
 size_t attn_workspace_bytes(const Geom &g);
 hipError_t launch_kv_pack(const Geom &g, const uint16_t *K, const uint16_t *V, void *ws, hipStream_t st);
 // Kernel-choice flags of the sparse attention entries (ints, written and read on the device only):

@@ -1308,10 +1308,8 @@ static void launch_select_d(const Geom &g, int NG, const uint16_t *Q, const uint
     }
 }
 
-size_t scan_tile_sum_bytes(long long n) { return (size_t)((n + SCAN_TILE - 1) / SCAN_TILE) * sizeof(long long); }
-
-// out[0..n] = exclusive prefix sums of count[0..n-1] (out[n] = total); tile_sum: scan_tile_sum_bytes(n) of scratch.
-void launch_exclusive_scan(const int32_t *count, long long n, long long *tile_sum, int64_t *out, hipStream_t st)
+// out[0..n] = exclusive prefix sums of count[0..n-1] (out[n] = total); tile_sum: scratch, one value per SCAN_TILE of them.
+static void launch_exclusive_scan(const int32_t *count, long long n, long long *tile_sum, int64_t *out, hipStream_t st)
 {
     const int tiles = (int)((n + SCAN_TILE - 1) / SCAN_TILE);
     hipLaunchKernelGGL(scan_tile_sums_kernel, dim3(tiles), dim3(SCAN_THREADS), 0, st, count, n, tile_sum);
