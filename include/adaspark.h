@@ -219,6 +219,8 @@ int adaspark_cube_select_shared(const adaspark_shape *shape, const void *Q, cons
  *                  and with it this value, is accurate to about 2^-12 * sum_d |q_d k_d| / sqrt(head_dim).)
  * The score products q.k take fp16 operands: K converts exactly while |k| <= 65504, the limit of that format; larger
  * magnitudes, in K or in the scaled Q, saturate there.  P.V takes bf16 operands as they are.
+ * With causal != 0 nothing that K or V hold in the cubes behind a row's own reaches the row.  V of the earlier cubes and of
+ * the whole own cube has to be finite: a row that does not attend a key may still multiply its V by a probability of 0.
  *   workspace      adaspark_workspace_bytes(ADASPARK_CALL_SPARSE_ATTN), or more: with
  *                  adaspark_pairs_workspace_bytes(...) the key-stationary kernel becomes a candidate
  */

@@ -309,17 +309,19 @@ __device__ __forceinline__ void nat_half_bias(const unsigned char *kt, int n16, 
 
 // acc^T[d, n] += T[d, k] . B[k, n] over the entities k = 32 H .. 32 H + 31 of a tile, slabs 0..NS-1: T a transposed tile in
 // LDS (rows = head-dim), B in registers in the operand order qk_tile's outputs pack into (bf[s][H] = entities
-// 32 H + 8 q4 + 0..7).
-template <int D, int NS, int H>
+// 32 H + 8 q4 + 0..7).  DONE: slab s's column of this lane keeps its value where done[s].
+template <int D, int NS, int H, bool DONE = false>
 __device__ __forceinline__ void tn_half(const unsigned char *tt, int n16, int q4, const bf16x8 (&bf)[NS][2],
-                                        f32x4 (&acc)[NS][D / 16])
+                                        f32x4 (&acc)[NS][D / 16], const bool *done = nullptr)
 {
 #pragma unroll
     for (int e = 0; e < D / 16; ++e) {
         const bf16x8 af = *reinterpret_cast<const bf16x8 *>(tt + vt_tile_off(16 * e + n16, 4 * H + q4));
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
-            acc[s][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[s][H], acc[s][e], 0, 0, 0);
+        for (int s = 0; s < NS; ++s) {
+            const f32x4 sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[s][H], acc[s][e], 0, 0, 0);
+            acc[s][e] = DONE && done[s] ? acc[s][e] : sum;
+        }
     }
 }
 
@@ -474,7 +476,10 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     int stage = 0;
     uint32_t mw[NS] = {0u, 0u};
     int mw_idx = -1;
-    for (int k = 0; k < nlist; ++k) {
+    // BEHIND: a cube behind some rows' own.  These rows' probabilities are zero there, but K and V need not be finite: they
+    // keep their sums.
+    auto walk_cube = [&](auto behind) __attribute__((always_inline)) {
+        constexpr bool BEHIND = decltype(behind)::value;
         const int j = issued, size_j = csize[j], nt = tiles_of(j);
         const bool late = j >= i_first;  // some rows' own cube, or behind it
         // What the score products start from: minus the row's log-sum-exp; -inf for a row that did not select cube
@@ -486,17 +491,20 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
         }
         float le[NS];
         int lim[NS];
+        bool done[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             le[s] = lse2[s];
             lim[s] = size_j - 1;
+            done[s] = false;
             if (MASKED && !((mw[s] >> (j & 31)) & 1u)) le[s] = -INFINITY;
             if (late) {
                 const int4 at = row_place(s);
                 if (j >= at.x) {
-                    le[s] = j == at.x ? lse2[s] : -INFINITY;
-                    lim[s] = at.y;
+                    le[s] = lse2[s];
+                    lim[s] = j == at.x ? at.y : -1;
                 }
+                done[s] = j > at.x;
             }
         }
         for (int t = 0; t < nt; ++t) {
@@ -537,18 +545,21 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
             if (KEYS == 1) {
                 half(std::integral_constant<int, 0>{});
                 half(std::integral_constant<int, 1>{});
-                tn_half<D, NS, 0>(ktt, n16, q4, ds, acc);
-                tn_half<D, NS, 1>(ktt, n16, q4, ds, acc);
+                tn_half<D, NS, 0, BEHIND>(ktt, n16, q4, ds, acc, done);
+                tn_half<D, NS, 1, BEHIND>(ktt, n16, q4, ds, acc, done);
             } else if (khalf == 0) {
                 half(std::integral_constant<int, 0>{});
-                tn_half<D, NS, 0>(ktt, n16, q4, ds, acc);
+                tn_half<D, NS, 0, BEHIND>(ktt, n16, q4, ds, acc, done);
             } else {
                 half(std::integral_constant<int, 1>{});
-                tn_half<D, NS, 1>(ktt, n16, q4, ds, acc);
+                tn_half<D, NS, 1, BEHIND>(ktt, n16, q4, ds, acc, done);
             }
             stage ^= 1;
         }
-    }
+    };
+    int k = 0;
+    for (; k < nlist && issued <= i_first; ++k) walk_cube(std::false_type{});
+    for (; k < nlist; ++k) walk_cube(std::true_type{});
     if (KEYS == 2) {  // (no load is in flight: the last tile's were waited for)
         static_assert(KEYS == 1 || 4 * 64 * (NS * DT * 16 + NS * 4) <= 2 * STAGE, "the second half's sums fit the tiles' place");
         f32x4 *sums = reinterpret_cast<f32x4 *>(smem);              // [4][NS * DT][64]

@@ -13,6 +13,8 @@
 // for 34 MFMAs: 12 to 15 TB/s over the chip), which is why the walk kernel takes over as soon as it fills the chip
 // (attn_split_pays).  In a kernel trace: 2,048 tokens, 4/4 heads of 64, cubes of 32: 18.5 us, the walk kernel 127 us; 1,080
 // tokens, 6/2 heads of 128, clipped cubes of up to 128: 21.5 against 51 us.
+#include <type_traits>
+
 #include "attn_tile.h"
 
 namespace adaspark {
@@ -161,7 +163,10 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
 #pragma unroll
         for (int e = 0; e < DT; ++e) oacc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    auto work = [&](uint32_t e0, uint32_t e1) __attribute__((always_inline)) {  // the step e0; e1 is the next one
+    // The step e0; e1 is the next one.  BEHIND: of a cube behind some rows' own.  These rows' probabilities are zero there, but V
+    // need not be finite (0 * inf): they keep their O.
+    auto work = [&](uint32_t e0, uint32_t e1, auto behind) __attribute__((always_inline)) {
+        constexpr bool BEHIND = decltype(behind)::value;
         const int j = (int)(e0 >> 16);
         const bool edge = j >= i_first;  // some row's own cube, or (causal) behind it
         const int jsize = g.ragged ? csize[j] : g.Cmax;
@@ -232,17 +237,26 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
 #pragma unroll
         for (int e = 0; e < DT; ++e)
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
-                oacc[s][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[e], pf[s], oacc[s][e], 0, 0, 0);
+            for (int s = 0; s < NS; ++s) {
+                const f32x4 sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[e], pf[s], oacc[s][e], 0, 0, 0);
+                oacc[s][e] = BEHIND && j > own[s] ? oacc[s][e] : sum;
+            }
         load_v(e1);
     };
     if (wave < nsteps) {
         uint32_t e0 = entry(wave);
         load_k(e0);
         load_v(e0);
-        for (int p = wave; p < nsteps; p += C::WAVES) {
+        int p = wave;
+        const uint32_t behind = g.causal ? (uint32_t)(i_first + 1) << 16 : ~0u;  // the first such step
+        for (; p < nsteps && e0 < behind; p += C::WAVES) {
             const uint32_t e1 = entry(p + C::WAVES);
-            work(e0, e1);
+            work(e0, e1, std::false_type{});
+            e0 = e1;
+        }
+        for (; p < nsteps; p += C::WAVES) {
+            const uint32_t e1 = entry(p + C::WAVES);
+            work(e0, e1, std::true_type{});
             e0 = e1;
         }
     }

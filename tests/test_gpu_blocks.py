@@ -46,3 +46,59 @@ def test_blocks_across_cubes(B, oracle, name, grid, cube, hq, hkv, d, text, lead
             if causal:
                 ref, absdot = oracle.bwd.lse_rows(osh, Q.double().numpy(), K.double().numpy(), mask, rows)
                 assert (np.abs(lse.cpu().numpy().astype(np.float64) - ref) <= lse_bound(absdot)).all()
+
+
+BEHIND = SHAPES + [  # the last two: the dense walk at both head-dims, and the dQ kernel with one wavefront per 32 rows
+    ("clipped60_text", (16, 10, 15), (3, 4, 5), 48, 4, 64, 70, 45),
+    ("clipped60", (18, 9, 15), (3, 4, 5), 36, 4, 128, 0, 0),
+]
+
+
+def cube_of_tokens(w):
+    """The cube of every token."""
+    C = w.ct * w.ch * w.cw
+    nt, nh, nw = -(-w.T // w.ct), -(-w.H // w.ch), -(-w.W // w.cw)
+    t, h, x = np.indices((w.T, w.H, w.W)).reshape(3, -1)
+    lead = -(-w.lead // C)
+    return torch.from_numpy(np.concatenate([np.arange(w.lead) // C, lead + ((t // w.ct) * nh + h // w.ch) * nw + x // w.cw,
+                                            lead + nt * nh * nw + np.arange(w.text) // C]))
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead", BEHIND, ids=[s[0] for s in BEHIND])
+def test_what_is_not_finite_does_not_reach_rows_before_it(B, oracle, name, grid, cube, hq, hkv, d, text, lead):  # noqa: F811
+    """K and V of a late cube hold infinities and NaN: what the rows of the cubes before it get is bit for bit what they get with
+    finite ones, though their blocks walk that cube too."""
+    w = synth.Workload(name, 49, *grid, *cube, hq, hkv, d, (0.6,), (1.0,) * hkv, text, lead)
+    sh = B.Shape.of(w)
+    Q, K, V = (x.cuda() for x in synth.generate(w))
+    sel = B.cube_select(sh, Q, B.cube_pool(sh, K), 0.6)[0]
+    g = torch.Generator(device="cpu")
+    g.manual_seed(synth.BASE_SEED + 49)
+    dO = torch.randn((w.S, w.Hq, w.D), generator=g, dtype=torch.float32).to(torch.bfloat16).cuda()
+    cubes = cube_of_tokens(w)
+    N = int(cubes.max()) + 1
+
+    def forward(K, V):
+        packed = B.kv_pack(sh, K, V)
+        lse = [torch.empty(w.S * w.Hq, dtype=torch.float32, device="cuda") for _ in range(3)]
+        O = [B.sparse_attn_packed(sh, Q, packed, sel, lse=lse[0], kernel=B.SPARSE_MASKED),
+             B.sparse_attn_packed(sh, Q, packed, sel, lse=lse[1]), B.dense_attn_packed(sh, Q, packed, lse=lse[2])]
+        return O, [x.view(w.S, w.Hq) for x in lse]
+
+    want_O, want_lse = forward(K, V)
+    grads = [(m, O, lse) for m, O, lse in zip((sel, None), want_O[1:], want_lse[1:])]
+    want_dQ = [B.sparse_attn_bwd(sh, Q, K, V, O, lse.reshape(-1), dO, sel_mask=m)[0] for m, O, lse in grads]
+    for c in sorted({N - 1, N // 2}):
+        before, at = (cubes < c).cuda(), (cubes == c).cuda()
+        for bad in (float("inf"), float("nan")):
+            Kx, Vx = K.clone(), V.clone()
+            Kx[at], Vx[at] = bad, bad
+            print(f"[{name}] cube {c} of {N}: {bad}", flush=True)
+            O, lse = forward(Kx, Vx)
+            dQ = [B.sparse_attn_bwd(sh, Q, Kx, Vx, o, x.reshape(-1), dO, sel_mask=m)[0] for m, o, x in grads]
+            torch.cuda.synchronize()
+            for what, a, b in zip(("O masked", "O auto", "O dense", "lse masked", "lse auto", "lse dense", "dQ", "dQ dense"),
+                                  O + lse + dQ, want_O + want_lse + want_dQ):
+                wrong = int((a[before] != b[before]).sum())
+                print(f"[{name}] {what}: {wrong} of {b[before].numel()}", flush=True)
+                assert wrong == 0, what
