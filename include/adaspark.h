@@ -95,7 +95,8 @@ typedef enum {
  *            memory was sized for, the call runs MASKED instead (decided on the device).
  *   AUTO     the choice is made on the device from the selected share (no host synchronisation).  PAIRS is
  *            among the candidates iff the workspace is large enough for it, and the choice is then made per KV
- *            head: heads whose rows select little go to PAIRS, the others to MASKED (or COMPACT).  On short sequences
+ *            head: heads whose rows select little go to PAIRS, the others to MASKED (or COMPACT); with so few rows
+ *            that MASKED takes them all at once, all heads do or none.  On short sequences
  *            a kernel like MASKED whose wavefronts share the keys of few rows instead of the rows of a block runs,
  *            there and in the dense entries (chosen from the shape). */
 typedef enum {

@@ -270,14 +270,14 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long x, u
 }
 
 // The key-stationary kernel takes a KV head's rows (flags[FLAG_KV + kv] = 3) if its share of selected candidate cubes is
-// below the threshold (or force); if the records of the heads so chosen do not fit, none is taken.
+// below the threshold (or force); if the records of the heads so chosen do not fit, or (together) one is not chosen, none is taken.
 __global__ __launch_bounds__(PAIRS_TILE) void pairs_plan_kernel(Geom g, long long cap, unsigned long long candidates_per_head,
                                                                 int tiles, const uint32_t *__restrict__ tile_need,
                                                                 const uint32_t *__restrict__ seg_count,
                                                                 long long *__restrict__ tile_off,
                                                                 uint32_t *__restrict__ seg_start,
                                                                 uint32_t *__restrict__ seg_chunk, int *__restrict__ flags,
-                                                                int force, int pairs_below_permille)
+                                                                int force, int together, int pairs_below_permille)
 {
     if (pairs_gate_closed(flags, force, pairs_below_permille)) return;
     __shared__ unsigned long long need[PAIRS_MAX_KV_HEADS], scan[PAIRS_TILE / 64];
@@ -294,14 +294,16 @@ __global__ __launch_bounds__(PAIRS_TILE) void pairs_plan_kernel(Geom g, long lon
     __syncthreads();
     if (t == 0) {
         unsigned long long total = 0;
+        bool all = true;
         const unsigned long long rows = (unsigned long long)g.S * g.G;
         for (int kv = 0; kv < g.Hkv; ++kv) {
             take[kv] = force || (pairs_head_open(flags, kv, force, pairs_below_permille) &&
                                  (need[kv] - rows) * 1000ull <
                                      candidates_per_head * (unsigned long long)pairs_threshold(flags, pairs_below_permille));
             if (take[kv]) total += need[kv];
+            else all = false;
         }
-        active = total > 0ull && total <= (unsigned long long)cap;
+        active = total > 0ull && total <= (unsigned long long)cap && (all || !together);
         flags[FLAG_ACTIVE] = active;
     }
     __syncthreads();
@@ -753,8 +755,8 @@ uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int
 // Counts the pairs per KV head, hands heads to this path (flags), numbers their records, and enqueues this path's
 // kernels (they return at once for heads, or altogether, when nothing was handed over).
 hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, void *scratch,
-                             size_t scratch_bytes, int force, int pairs_below_permille, uint16_t *O, float *lse,
-                             hipStream_t st)
+                             size_t scratch_bytes, int force, int together, int pairs_below_permille, uint16_t *O,
+                             float *lse, hipStream_t st)
 {
     const PairsScratch sc = pairs_layout(g, scratch, scratch_bytes);
     if (!pairs_supported(g) || sc.cap <= 0) return hipErrorInvalidValue;
@@ -768,7 +770,7 @@ hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packe
                        sc.seg_count, sc.tile_need, flag, force, pairs_below_permille);
     hipLaunchKernelGGL(pairs_plan_kernel, dim3(1), dim3(PAIRS_TILE), 0, st, g, sc.cap,
                        candidate_pairs(g) / (unsigned long long)g.Hkv, tiles, sc.tile_need, sc.seg_count, sc.tile_off,
-                       sc.seg_start, sc.seg_chunk, flag, force, pairs_below_permille);
+                       sc.seg_start, sc.seg_chunk, flag, force, together, pairs_below_permille);
     hipLaunchKernelGGL(pair_fill_kernel, dim3(tiles), dim3(PAIRS_TILE), (size_t)segs * 8, st, g, R,
                        1.44269504088896340736f / sqrtf((float)g.D), Q, sel_mask, sc.cnt, sc.tile_off, flag, sc.seg_start,
                        sc.seg_cursor, sc.pair_ptr, sc.entries, sc.qs);

@@ -45,9 +45,11 @@ template <int D, bool MASKED>
 __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t *__restrict__ Q,
                                                          const uint16_t *__restrict__ Kp, const uint16_t *__restrict__ Vt,
                                                          const int32_t *__restrict__ csize,
-                                                         const uint32_t *__restrict__ sel_mask, uint16_t *__restrict__ O,
-                                                         float *__restrict__ lse)
+                                                         const uint32_t *__restrict__ sel_mask,
+                                                         const int *__restrict__ mode_flag, int my_mode,
+                                                         uint16_t *__restrict__ O, float *__restrict__ lse)
 {
+    if (MASKED && mode_flag != nullptr && mode_flag[FLAG_MODE] != my_mode) return;
     using C = Split<D>;
     constexpr int NS = C::NS, KSTEPS = D / 32, DT = C::DT;
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
@@ -299,8 +301,8 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
 }
 
 template <int D, bool MASKED>
-static hipError_t launch_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, uint16_t *O,
-                               float *lse, hipStream_t st)
+static hipError_t launch_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask,
+                               const int *mode_flag, int my_mode, uint16_t *O, float *lse, hipStream_t st)
 {
     using C = Split<D>;
     const uint16_t *Kp = reinterpret_cast<const uint16_t *>(packed);
@@ -312,18 +314,18 @@ static hipError_t launch_split(const Geom &g, const uint16_t *Q, const void *pac
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)((g.S * g.G - 1) / C::ROWS + 1) * (unsigned)g.Hkv;
     hipLaunchKernelGGL((attn_split_kernel<D, MASKED>), dim3(blocks), dim3(C::THREADS), C::BYTES, st, g, Q, Kp, Vt, csize,
-                       sel_mask, O, lse);
+                       sel_mask, mode_flag, my_mode, O, lse);
     return hipGetLastError();
 }
 
-hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, uint16_t *O,
-                             float *lse, hipStream_t st)
+hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask,
+                             const int *mode_flag, int my_mode, uint16_t *O, float *lse, hipStream_t st)
 {
     if (g.D == 64)
-        return sel_mask ? launch_split<64, true>(g, Q, packed, sel_mask, O, lse, st)
-                        : launch_split<64, false>(g, Q, packed, sel_mask, O, lse, st);
-    return sel_mask ? launch_split<128, true>(g, Q, packed, sel_mask, O, lse, st)
-                    : launch_split<128, false>(g, Q, packed, sel_mask, O, lse, st);
+        return sel_mask ? launch_split<64, true>(g, Q, packed, sel_mask, mode_flag, my_mode, O, lse, st)
+                        : launch_split<64, false>(g, Q, packed, sel_mask, mode_flag, my_mode, O, lse, st);
+    return sel_mask ? launch_split<128, true>(g, Q, packed, sel_mask, mode_flag, my_mode, O, lse, st)
+                    : launch_split<128, false>(g, Q, packed, sel_mask, mode_flag, my_mode, O, lse, st);
 }
 
 }  // namespace adaspark

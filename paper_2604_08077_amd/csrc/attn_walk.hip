@@ -491,8 +491,8 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 }
 
 // ---- the share of candidate cubes the rows select, per KV head, from a sample of rows.  One workgroup; writes
-// flags[FLAG_MODE] = 1 (compaction) or 2 (masked walk) from the overall share, flags[FLAG_ESTIMATE] = the smallest
-// share of a KV head in permille, and (kv_modes) the heads' shares; clears the per-head choices and the key-stationary path's
+// flags[FLAG_MODE] = 1 (the other row-stationary kernel: an overall share of up to other_permille) or 2 (masked walk),
+// flags[FLAG_ESTIMATE] = the smallest share of a KV head in permille (together: the largest), and (kv_modes) the heads' shares; clears the per-head choices and the key-stationary path's
 // counters.
 constexpr int DENSITY_THREADS = 1024;
 constexpr int DENSITY_MAX_ROWS = 2048;  // two sampled rows per thread: an estimate is all that is needed
@@ -503,8 +503,8 @@ constexpr int DENSITY_UNION_WORDS = ADASPARK_MAX_CUBES / 32;
 constexpr int MASKED_ABOVE_PERMILLE = 15;
 
 __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, const uint32_t *__restrict__ sel_mask,
-                                                                      int *__restrict__ flags, int kv_modes,
-                                                                      uint32_t *__restrict__ counters, int counter_words)
+                                                                      int *__restrict__ flags, int kv_modes, int together,
+                                                                      int other_permille, uint32_t *__restrict__ counters, int counter_words)
 {
     // selected, candidates (at most DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES); heads beyond the array fold
     __shared__ uint32_t acc[2][PAIRS_MAX_KV_HEADS];
@@ -528,15 +528,16 @@ __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, co
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long sel = 0, cand = 0, least = 1000ull;
+        unsigned long long sel = 0, cand = 0, least = 1000ull, most = 0;
         for (int kv = 0; kv < min(g.Hkv, PAIRS_MAX_KV_HEADS); ++kv) {
             sel += acc[0][kv];
             cand += acc[1][kv];
             if (acc[1][kv] == 0u) continue;
             least = min(least, acc[0][kv] * 1000ull / acc[1][kv]);
+            most = max(most, acc[0][kv] * 1000ull / acc[1][kv]);
         }
-        flags[FLAG_MODE] = (sel * 1000ull > cand * (unsigned long long)MASKED_ABOVE_PERMILLE) ? 2 : 1;
-        flags[FLAG_ESTIMATE] = (int)least;
+        flags[FLAG_MODE] = other_permille >= 0 && sel * 1000ull <= cand * (unsigned long long)other_permille ? 1 : 2;
+        flags[FLAG_ESTIMATE] = (int)(together ? most : least);
         flags[FLAG_ACTIVE] = 0;
     }
     // What the masked walk cannot leave out: the share of candidate cubes in the union of the selections of one
@@ -627,13 +628,13 @@ static double walk_rounds(const Geom &g)
     return 1.18 * (g.causal ? 0.5 : 1.0) * g.Hkv * std::ceil((double)g.S * g.G / 256) / 256;
 }
 
-// Whether the automatic choice is made on the device.  Where the time of the masked walk is that of its longest walk, heads that
-// go to the key-stationary kernel do not shorten it (3,600 tokens of 28/4 heads of 128 in cubes of 32, half the heads selecting nearly
-// nothing: the walk 218 us, with all heads as with half of them, and the others another 140).
-static bool chosen_on_device(const Geom &g)
-{
-    return candidate_pairs(g) >= AUTO_MIN_CANDIDATE_PAIRS && walk_rounds(g) > 1.0;
-}
+// Whether the automatic choice is made on the device.
+static bool chosen_on_device(const Geom &g) { return candidate_pairs(g) >= AUTO_MIN_CANDIDATE_PAIRS; }
+
+// Whether it is then made for all KV heads together.  Where the time of the masked walk is that of its longest walk, heads that go to
+// the key-stationary kernel do not shorten it, unless all of them go (3,600 tokens of 28/4 heads of 128 in cubes of 32, half the
+// heads selecting nearly nothing: the walk 218 us, with all heads as with half of them, and the others another 140).
+static bool heads_together(const Geom &g) { return walk_rounds(g) <= 1.0; }
 
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
 // axis), text cubes in two.
@@ -660,16 +661,35 @@ static long long tiles_of_cubes(const Geom &g, int keys)
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
 //   choice  where this kernel would be one of those chosen from on the device, the launches of that choice take 40
-bool attn_split_pays(const Geom &g, bool choice)
+static double walk_time(const Geom &g)
 {
-    if (!attn_split_fits(g)) return false;
-    const double slots = (double)tiles_of_cubes(g, KEY_TILE);
-    const double walk = 11 + (choice && chosen_on_device(g) ? 40 : 0) +
-                        (g.D == 64 ? 1.19 : 1.62) * slots * std::max(1.0, walk_rounds(g));
+    return 11 + (g.D == 64 ? 1.19 : 1.62) * (double)tiles_of_cubes(g, KEY_TILE) * std::max(1.0, walk_rounds(g));
+}
+
+// What the split takes, and of that what grows with the steps it visits.
+static double split_time(const Geom &g, double &of_steps)
+{
     const double share = g.causal ? 0.5 : 1.0;  // of all cubes that the average walk visits
     const double steps = (double)tiles_of_cubes(g, 32), blocks = g.Hkv * std::ceil((double)g.S * g.G / 32);
-    const double split = 5 + 7 * std::max(1.0, blocks / 256) + blocks / 256 * share * steps * (g.D == 64 ? 0.15 : 0.24);
-    return split < walk;
+    of_steps = blocks / 256 * share * steps * (g.D == 64 ? 0.15 : 0.24);
+    return 5 + 7 * std::max(1.0, blocks / 256) + of_steps;
+}
+
+bool attn_split_pays(const Geom &g, bool choice)
+{
+    double of_steps;
+    return attn_split_fits(g) && split_time(g, of_steps) < walk_time(g) + (choice && chosen_on_device(g) ? 40 : 0);
+}
+
+// Up to which share of selected candidate cubes (permille) the split beats the walk where it does not at any share: it leaves
+// out what none of 32 rows selected, rows that select independently (1 - share)^32 of the cubes.  Its time, us, at
+// 61, 3.3 and 0.8 % selected, and the walk's: 7,680 tokens of 14/2 heads of 128 in cubes of 32: 498, 357, 231; 408, 464, 447.
+static int split_below_permille(const Geom &g)
+{
+    if (!attn_split_fits(g)) return -1;
+    double of_steps;
+    const double all = split_time(g, of_steps), visited = 1.0 - (all - walk_time(g)) / of_steps;
+    return visited <= 0.0 ? -1 : (int)(1000.0 * (1.0 - std::pow(std::max(0.0, 1.0 - visited), 1.0 / 32)));
 }
 
 // The key-stationary kernel is the faster one below this share of selected candidate cubes.  The walk takes time by the
@@ -685,15 +705,15 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
 {
     if ((sel_mask == nullptr || sparse_kernel == ADASPARK_SPARSE_AUTO) &&
         attn_split_pays(g, sel_mask != nullptr && g.causal))
-        return launch_attn_split(g, Q, packed, sel_mask, O, lse, st);
+        return launch_attn_split(g, Q, packed, sel_mask, nullptr, 0, O, lse, st);
     if (sel_mask == nullptr) return launch_walk<D, false>(g, Q, packed, nullptr, nullptr, 0, 0, O, lse, st);
     if (sparse_kernel == ADASPARK_SPARSE_COMPACT && g.causal)
         return launch_attn_compact(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     if (sparse_kernel == ADASPARK_SPARSE_MASKED || !g.causal)  // non-causal mode: the masked walk is the one kernel
         return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
-    // Small problems (8,192 rows of 64 cubes, say) are bound by the latency from one dependent kernel to the next, or by the
-    // longest walk: the kernels that measure the selection and prepare the other paths would cost more than any choice
-    // among them can win back.  The masked walk is the one kernel then.
+    // Small problems (8,192 rows of 64 cubes, say) are bound by the latency from one dependent kernel to the next: the
+    // kernels that measure the selection and prepare the other paths would cost more than any choice among them can win
+    // back.  The masked walk is the one kernel then.
     if (sparse_kernel == ADASPARK_SPARSE_AUTO && !chosen_on_device(g))
         return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     // Automatic (or the key-stationary kernel asked for): the choice is made on the device, every candidate kernel
@@ -706,18 +726,26 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
         if (sparse_kernel == ADASPARK_SPARSE_PAIRS) return hipErrorInvalidValue;  // the entry point checks this first
         flags = reinterpret_cast<int *>(reinterpret_cast<char *>(packed) + attn_workspace_bytes(g) - 16);
     }
+    // Heads together: the walk, or all of them by the key-stationary kernel; without room for that one, by the kernel for
+    // short sequences.  (Attention, us, chosen so, by the walk and by the key-stationary kernel: 24,576 tokens of 4/4 heads of 64 in
+    // cubes of 256, 63, 34 and 18 % selected: 474, 319, 220; 439, 441, 445; 489, 320, 221.  Never one of the latter two: a call of
+    // these that selects much is 8 % faster, one that selects little 50 % slower.)
+    const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g);
+    const int other_permille = !together ? MASKED_ABOVE_PERMILLE : kv_modes ? -1 : split_below_permille(g);
+    if (together && !kv_modes && other_permille < 0) return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     int counter_words = 0;
     uint32_t *counters = kv_modes ? pairs_counters(g, scratch, scratch_bytes, counter_words) : nullptr;
-    hipLaunchKernelGGL(sel_density_kernel, dim3(1), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes, counters,
-                       counter_words);
+    hipLaunchKernelGGL(sel_density_kernel, dim3(1), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes, together,
+                       other_permille, counters, counter_words);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (kv_modes) {
-        e = launch_attn_pairs(g, Q, packed, sel_mask, scratch, scratch_bytes, sparse_kernel == ADASPARK_SPARSE_PAIRS,
+        e = launch_attn_pairs(g, Q, packed, sel_mask, scratch, scratch_bytes, sparse_kernel == ADASPARK_SPARSE_PAIRS, together,
                               pairs_below_permille(g), O, lse, st);
         if (e != hipSuccess) return e;
     }
-    e = launch_attn_compact(g, Q, packed, sel_mask, flags, 1, kv_modes, O, lse, st);
+    if (!together) e = launch_attn_compact(g, Q, packed, sel_mask, flags, 1, kv_modes, O, lse, st);
+    else if (!kv_modes) e = launch_attn_split(g, Q, packed, sel_mask, flags, 1, O, lse, st);
     if (e != hipSuccess) return e;
     return launch_walk<D, true>(g, Q, packed, sel_mask, flags, 2, kv_modes, O, lse, st);
 }

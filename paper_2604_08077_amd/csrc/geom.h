@@ -182,8 +182,9 @@ hipError_t launch_cube_select_shared(const Geom &g, const uint16_t *Q, const flo
 size_t attn_workspace_bytes(const Geom &g);
 hipError_t launch_kv_pack(const Geom &g, const uint16_t *K, const uint16_t *V, void *ws, hipStream_t st);
 // Kernel-choice flags of the sparse attention entries (ints, written and read on the device only):
-//   [FLAG_MODE]      the row-stationary kernel that runs: 1 compaction, 2 masked walk
-//   [FLAG_ESTIMATE]  smallest share of selected candidate cubes over the KV heads, permille, from a sample of rows
+//   [FLAG_MODE]      the row-stationary kernel that runs: 1 compaction or the kernel for short sequences, 2 masked walk
+//   [FLAG_ESTIMATE]  smallest share of selected candidate cubes over the KV heads, permille, from a sample of rows (where the
+//                    heads are chosen for together, the largest)
 //   [FLAG_ACTIVE]    1 if some KV head is the key-stationary kernel's
 //   [FLAG_UNION]     share of the candidate cubes that some row of a masked-walk workgroup selected (that kernel skips
 //                    the others), permille, from a sample of workgroups; 1000 where rows select independently
@@ -229,8 +230,9 @@ hipError_t launch_attn(const Geom &g, const uint16_t *Q, void *packed, const uin
 // be made on the device).
 bool attn_split_fits(const Geom &g);
 bool attn_split_pays(const Geom &g, bool choice);
-hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, uint16_t *O,
-                             float *lse, hipStream_t st);
+// mode_flag (device, may be null; selection only): the flag block below; it runs only if mode_flag[FLAG_MODE] == my_mode.
+hipError_t launch_attn_split(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask,
+                             const int *mode_flag, int my_mode, uint16_t *O, float *lse, hipStream_t st);
 // The compacting sparse kernel alone (attn_compact.hip).  flags (device, may be null): the flag block above; a
 // workgroup runs only if flags[FLAG_MODE] == my_mode and (kv_modes) its KV head is not the key-stationary kernel's.
 hipError_t launch_attn_compact(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask,
@@ -240,16 +242,16 @@ hipError_t launch_attn_compact(const Geom &g, const uint16_t *Q, const void *pac
 // scratch memory does not hold the tables or the geometry is not covered.  launch_attn_pairs expects
 // flags[FLAG_MODE], flags[FLAG_ESTIMATE], flags[FLAG_SHARE ...] set, flags[FLAG_KV ...] and the counters zero; it enqueues kernels that -- unless the
 // estimate is well above pairs_below_permille and force is 0 -- count the pairs exactly per KV head, hand the heads
-// whose share is below pairs_below_permille (all heads, if force) to this path as long as their records fit, and run
-// it for those heads.
+// whose share is below pairs_below_permille (all heads, if force; all or none, if together) to this path as long as their
+// records fit, and run it for those heads.
 bool pairs_supported(const Geom &g);
 size_t pairs_scratch_bytes(const Geom &g, long long max_selected);
 int *pairs_flags(const Geom &g, void *scratch, size_t scratch_bytes);
 // the counters inside the scratch memory that have to be zero when launch_attn_pairs is called (words of them)
 uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int &words);
 hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, void *scratch,
-                             size_t scratch_bytes, int force, int pairs_below_permille, uint16_t *O, float *lse,
-                             hipStream_t st);
+                             size_t scratch_bytes, int force, int together, int pairs_below_permille, uint16_t *O,
+                             float *lse, hipStream_t st);
 
 // Backward of the attention entries (attn_bwd.hip): dQ, dK, dV in bf16 from Q, K, V, the forward's O and
 // log-sum-exp, and dO.  sel_mask == nullptr: dense causal attention.  in_place: a gradient overlaps Q or dO.

@@ -80,3 +80,40 @@ def test_dense_walk_of_64(B, oracle, name, grid, cube, hq, hkv, text, lead):  # 
         O = B.dense_attn(sh, Q.cuda(), K.cuda(), V.cuda(), causal=causal)
         torch.cuda.synchronize()
         check_outputs(f"{name} causal={causal}", rows_of(O, rows, w), oracle.dense_attn(osh, Q, K, V, rows=rows, causal=causal))
+
+
+# Few rows, which the masked walk takes in one round, where all KV heads select little, all select much, and one of two little:
+# the kernel that the automatic choice has to take with room for the key-stationary one, and without.  (Grid, cube, query heads, KV
+# heads, key scale of each, what is selected: Top-p or Top-K; kernel with room, kernel without.)
+FEW = [
+    ("cubes256_little", (56, 16, 16), (4, 8, 8), 6, 2, (1.0, 1.0), 0.5, "pairs", "masked"),
+    ("cubes256_much", (56, 16, 16), (4, 8, 8), 6, 2, (1.0, 1.0), 0.9, "masked", "masked"),
+    ("cubes256_one_little", (56, 16, 16), (4, 8, 8), 6, 2, (0.0, 4.0), 0.9, "masked", "masked"),
+    ("cubes32_one", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 1, "pairs", "split"),
+    ("cubes32_much", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 0.8, "masked", "masked"),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,scale,sel,room,no_room", FEW, ids=[s[0] for s in FEW])
+def test_choice_for_few_rows(B, oracle, name, grid, cube, hq, hkv, scale, sel, room, no_room):  # noqa: F811
+    w = synth.Workload(name, 50, *grid, *cube, hq, hkv, 128, (0.5,), scale)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    Qg = Q.cuda()
+    kbar = B.cube_pool(sh, K.cuda())
+    mask, count = (B.cube_select(sh, Qg, kbar, sel) if isinstance(sel, float) else B.cube_select_topk(sh, Qg, kbar, sel))[:2]
+    rows = stratified_rows(oracle, osh, w, 200)
+    ref = oracle.sparse_attn(osh, Q, K, V, mask.cpu().numpy().view(np.uint32)[rows], rows=rows)[0]
+    big = B.kv_pack(sh, K.cuda(), V.cuda(), workspace=B.alloc_workspace(sh, B.CALL_SPARSE_ATTN, pairs_capacity=int(count.sum())))
+    small = B.kv_pack(sh, K.cuda(), V.cuda())
+    forced = {"masked": B.sparse_attn_packed(sh, Qg, big, mask, kernel=B.SPARSE_MASKED).float(),
+              "pairs": B.sparse_attn_packed(sh, Qg, big, mask, kernel=B.SPARSE_PAIRS).float()}
+    for ws, expected in ((big, room), (small, no_room)):
+        O = B.sparse_attn_packed(sh, Qg, ws, mask)
+        torch.cuda.synchronize()
+        check_outputs(f"{name} {expected}", rows_of(O, rows, w), ref)
+        # kernels round at different places (2e-3 of the result), one kernel the same way each time but for a few rows
+        off = {k: float((O.float() - x).norm() / x.norm()) for k, x in forced.items()}
+        print(f"[{name}] expected {expected}: from the forced kernels' results {off}", flush=True)
+        for k, x in off.items():
+            assert (x < 1e-4) == (k == expected), (k, expected)
