@@ -496,7 +496,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 // counters.
 constexpr int DENSITY_THREADS = 1024;
 constexpr int DENSITY_MAX_ROWS = 2048;  // two sampled rows per thread: an estimate is all that is needed
-constexpr int DENSITY_GROUPS = 16;          // sampled (cube, query head) pairs for the union estimate
+constexpr int DENSITY_GROUPS = 16;          // sampled blocks of rows for the union estimate
 constexpr int DENSITY_UNION_WORDS = ADASPARK_MAX_CUBES / 32;
 // Measured on MI355X with rows that select independently of each other: the compacting kernel wins only below
 // about 1.5 % selected cubes.
@@ -528,73 +528,78 @@ __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, co
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long sel = 0, cand = 0, least = 1000ull, most = 0;
+        static_assert((unsigned long long)DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES * 1000 < (1ull << 32), "permille in 32 bits");
+        uint32_t sel = 0, cand = 0, least = 1000, most = 0;
         for (int kv = 0; kv < min(g.Hkv, PAIRS_MAX_KV_HEADS); ++kv) {
             sel += acc[0][kv];
             cand += acc[1][kv];
             if (acc[1][kv] == 0u) continue;
-            least = min(least, acc[0][kv] * 1000ull / acc[1][kv]);
-            most = max(most, acc[0][kv] * 1000ull / acc[1][kv]);
+            const uint32_t share = acc[0][kv] * 1000u / acc[1][kv];
+            least = min(least, share);
+            most = max(most, share);
         }
-        flags[FLAG_MODE] = other_permille >= 0 && sel * 1000ull <= cand * (unsigned long long)other_permille ? 1 : 2;
+        flags[FLAG_MODE] = other_permille >= 0 && sel * 1000u <= cand * (uint32_t)other_permille ? 1 : 2;
         flags[FLAG_ESTIMATE] = (int)(together ? most : least);
         flags[FLAG_ACTIVE] = 0;
     }
-    // What the masked walk cannot leave out: the share of candidate cubes in the union of the selections of one
-    // query head's tokens in a cube (a workgroup's rows), over DENSITY_GROUPS sampled (cube, head) pairs, one per
-    // wavefront, all at once.
+    // What the masked walk cannot leave out: the share of the cubes before a block of its rows that some row of the block selected
+    // or is in, over DENSITY_GROUPS sampled (block, KV head) pairs, one per wavefront, all at once.
     {
-        static_assert(DENSITY_THREADS / 64 == DENSITY_GROUPS, "one sampled (cube, head) pair per wavefront");
+        static_assert(DENSITY_THREADS / 64 == DENSITY_GROUPS, "one sampled block per wavefront");
         __shared__ uint32_t uni[DENSITY_GROUPS][DENSITY_UNION_WORDS];
-        __shared__ unsigned long long ucount[2];  // cubes in the unions, candidate cubes
-        if (threadIdx.x < 2) ucount[threadIdx.x] = 0ull;
+        __shared__ uint32_t ucount[2];  // cubes in the unions, cubes before the blocks
+        if (threadIdx.x < 2) ucount[threadIdx.x] = 0u;
         const int k = threadIdx.x >> 6, t = threadIdx.x & 63;
         const bool measured = g.causal != 0;
-        const int i = g.N - 1 - (int)((long long)k * g.N / DENSITY_GROUPS);  // late cubes weigh most, as in the walk
-        const int a = (k * 5 + 1) % g.Hq;
+        // late blocks weigh most, as in the walk, and the blocks of a whole cube (of its query heads) take turns
+        const int nrows = g.S * g.G, nblk = (nrows - 1) / Walk<64>::MMAX + 1;
+        const int blk = min((int)((long long)k * nblk / DENSITY_GROUPS) + k % walk_group(g), nblk - 1), kv = k % g.Hkv;
+        const int row1 = nrows - blk * Walk<64>::MMAX, row0 = max(0, row1 - Walk<64>::MMAX);
+        // every second row, from the last one: each is a cache line of its own, and one CU fetches them all
+        RowAt at[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) at[q] = row_at(g, kv, max(row1 - 1 - 2 * (64 * q + t), row0));
+        const int i = __builtin_amdgcn_readfirstlane(at[0].cube), i_first = __builtin_amdgcn_readlane(at[1].cube, 63);
         const int wlim = (i + 31) >> 5;
         if (measured)
             for (int w = t; w < wlim; w += 64) uni[k][w] = 0u;
         __syncthreads();
         if (measured) {
-            const CubeBox box = cube_box(g, i);
-            const int size = box.size();
-            // every second token of the cube: each row read is a cache line of its own, and one CU fetches them all
-            for (int r0 = 0; r0 < size; r0 += 512)
-                for (int w0 = 0; w0 < wlim; w0 += 8) {  // 4 tokens x 8 words in flight per lane, then combined
-                    uint32_t m[4][8];
+            const uint32_t *mr[2];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int r = r0 + 2 * (64 * q + t);
-                        const uint32_t *mr =
-                            sel_mask + ((size_t)token_of(g, box, min(r, size - 1)) * g.Hq + a) * g.words;
+            for (int q = 0; q < 2; ++q) mr[q] = sel_mask + (size_t)at[q].id * g.words;
+            for (int w0 = 0; w0 < wlim; w0 += 8) {  // 2 rows x 8 words in flight per lane, then combined
+                uint32_t m[2][8];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) m[q][u] = (r < size && w0 + u < wlim) ? mr[w0 + u] : 0u;
-                    }
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        uint32_t x = m[0][u] | m[1][u] | m[2][u] | m[3][u];
-                        for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
-                        if (t == 0 && x) uni[k][w0 + u] |= x;  // the wavefront owns this row of `uni`
-                    }
+                    for (int u = 0; u < 8; ++u) m[q][u] = w0 + u < wlim ? mr[q][w0 + u] : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    uint32_t x = m[0][u] | m[1][u];
+                    for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
+                    if (t == 0 && x) uni[k][w0 + u] |= x;  // the wavefront owns this row of `uni`
                 }
+            }
         }
         __syncthreads();
         if (measured) {
-            unsigned long long n = 0;
-            for (int w = t; w < wlim; w += 64)
-                n += __popc(uni[k][w] & (w == (i >> 5) ? (1u << (i & 31)) - 1u : ~0u));
+            uint32_t n = 0;
+            for (int w = t; w < wlim; w += 64) {
+                const uint32_t own = w < (i_first >> 5) ? 0u : w > (i_first >> 5) ? ~0u : ~0u << (i_first & 31);
+                n += __popc((uni[k][w] | own) & (w == (i >> 5) ? (1u << (i & 31)) - 1u : ~0u));
+            }
             if (n) atomicAdd(&ucount[0], n);
-            if (t == 0) atomicAdd(&ucount[1], (unsigned long long)i);
+            if (t == 0) atomicAdd(&ucount[1], (uint32_t)i);
         }
         __syncthreads();
         if (threadIdx.x == 0)
-            flags[FLAG_UNION] = ucount[1] > 0ull ? max(1, (int)(ucount[0] * 1000ull / ucount[1])) : 1000;
+            flags[FLAG_UNION] = ucount[1] > 0u ? max(1, (int)(ucount[0] * 1000u / ucount[1])) : 1000;
     }
     if (kv_modes)
         for (int kv = threadIdx.x; kv < g.Hkv; kv += DENSITY_THREADS) {
             flags[FLAG_KV + kv] = 0;
-            flags[FLAG_SHARE + kv] = acc[1][kv] > 0u ? (int)(acc[0][kv] * 1000ull / acc[1][kv]) : 0;
+            flags[FLAG_SHARE + kv] = acc[1][kv] > 0u ? (int)(acc[0][kv] * 1000u / acc[1][kv]) : 0;
         }
 }
 
@@ -695,8 +700,9 @@ static int split_below_permille(const Geom &g)
 // The key-stationary kernel is the faster one below this share of selected candidate cubes.  The walk takes time by the
 // tiles of a cube, 0.03 ns a candidate pair and tile at head-dim 128; a selected pair costs the other path 0.22 ns in cubes of one tile and
 // 0.24 in cubes of four, most of it its record.  (Measured: 65,536 tokens of 28/4 heads in cubes of 256, break-even at 44 %;
-// 7,688 tokens in cubes of 32, 33 % selected, 2,250 us against 910.)
-static int pairs_below_permille(const Geom &g) { return 60 + 85 * g.TPC; }  // (TPC at most 4: pairs_supported)
+// 7,688 tokens in cubes of 32, 33 % selected, 2,250 us against 910; 8,640 on a grid of 9 x 10, where cubes of up to 256 have 1.75 tiles on
+// average, 32 % selected, 897 against 549.)
+static int pairs_below_permille(const Geom &g) { return (int)(60 + 85 * tiles_of_cubes(g, KEY_TILE) / g.N); }
 
 template <int D>
 static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, const uint32_t *sel_mask,

@@ -90,6 +90,8 @@ FEW = [
     ("cubes256_much", (56, 16, 16), (4, 8, 8), 6, 2, (1.0, 1.0), 0.9, "masked", "masked"),
     ("cubes256_one_little", (56, 16, 16), (4, 8, 8), 6, 2, (0.0, 4.0), 0.9, "masked", "masked"),
     ("cubes32_one", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 1, "pairs", "split"),
+    ("cubes32_little", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 4, "pairs", "masked"),
+    ("clipped256_third", (96, 9, 10), (4, 8, 8), 28, 4, (1.0,) * 4, 0.7, "masked", "masked"),  # (more rows: a head at a time)
     ("cubes32_much", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 0.8, "masked", "masked"),
 ]
 
