@@ -168,6 +168,12 @@ int adaspark_internal_short_sequence(const adaspark_shape *shape, int causal)
     return attn_split_pays(g, false) ? 1 : 0;
 }
 
+// Candidate (row, cube) pairs of a shape, 0 for one that is not valid.  Not declared either.
+unsigned long long adaspark_internal_candidate_pairs(const adaspark_shape *shape)
+{
+    return check_shape(shape) == ADASPARK_OK ? candidate_pairs(make_geom(*shape)) : 0;
+}
+
 int adaspark_cube_pool(const adaspark_shape *shape, const void *K, float *kbar, void *stream)
 {
     int rc = check_shape(shape);

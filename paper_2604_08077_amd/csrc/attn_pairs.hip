@@ -701,11 +701,20 @@ __global__ __launch_bounds__(256) void pairs_merge_kernel(uint32_t S, const int6
     }
 }
 
-// Number of candidate (row, cube) pairs: every row of cube i has i preceding cubes.
+// Number of candidate (row, cube) pairs: every row of cube i has i preceding cubes.  In closed form: the entry points ask a few times
+// a call, and over 2,048 cubes one by one it took 15 us each time.
 unsigned long long candidate_pairs(const Geom &g)
 {
-    unsigned long long c = 0;
-    for (int i = 0; i < g.N; ++i) c += (unsigned long long)i * (unsigned long long)cube_box(g, i).size();
+    typedef unsigned long long u64;
+    // sum over the blocks b of `len` things cut by `by` of b * (things of block b)
+    auto weighted = [](int len, int by) -> u64 {
+        const u64 n = ((u64)len + by - 1) / by;
+        return n == 0 ? 0 : (n - 1) * (n - 2) / 2 * by + (n - 1) * (len - (n - 1) * by);
+    };
+    const u64 T = g.T, H = g.H, W = g.W;
+    u64 c = weighted(g.Sp, g.Cmax) + (u64)g.Np * g.Sv;                       // the text before the video, and the video behind it
+    c += weighted(g.T, g.ct) * H * W * g.nHb * g.nWb + T * weighted(g.H, g.ch) * W * g.nWb + T * H * weighted(g.W, g.cw);
+    c += weighted(g.St, g.Cmax) + (u64)(g.Np + g.Nv) * g.St;
     return c * (unsigned long long)g.Hq;
 }
 

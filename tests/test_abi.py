@@ -241,3 +241,24 @@ def test_which_shapes_are_short_sequences(lib):
                      ((8, 16, 16, 4, 8, 8, 14, 2, 128), 1), ((16, 16, 16, 4, 8, 8, 14, 2, 128), 0)):
         cs = binding.Shape(*sh)._c()
         assert lib.adaspark_internal_short_sequence(ctypes.byref(cs), 1) == want, sh
+
+
+@pytest.mark.parametrize("grid,cube,heads,text,lead", [
+    ((1, 1, 1), (1, 1, 1), 1, 0, 0), ((8, 8, 8), (2, 4, 4), 4, 0, 0), ((9, 10, 12), (4, 4, 8), 6, 0, 0), ((7, 5, 13), (4, 5, 13), 3, 63, 0),
+    ((5, 7, 9), (4, 4, 8), 6, 129, 128), ((2, 3, 300), (4, 4, 1), 2, 0, 5), ((32, 16, 16), (1, 2, 2), 28, 0, 0), ((1, 1, 2048), (1, 1, 1), 1, 0, 0),
+])
+def test_candidate_pairs(lib, grid, cube, heads, text, lead):
+    """The number that the automatic choice and the launch sizes go by, summed cube by cube: a row of cube c has c candidates."""
+    sh = binding.Shape(*grid, *cube, heads, 1, 64, text, lead)
+    C = cube[0] * cube[1] * cube[2]
+
+    def cut(n, by):
+        return [min(by, n - k) for k in range(0, n, by)]
+
+    sizes = cut(lead, C) + [t * h * w for t in cut(grid[0], cube[0]) for h in cut(grid[1], cube[1]) for w in cut(grid[2], cube[2])]
+    sizes += cut(text, C)
+    fn = lib.adaspark_internal_candidate_pairs
+    fn.restype = ctypes.c_ulonglong
+    cs = sh._c()
+    assert binding.num_cubes(sh) == len(sizes)
+    assert fn(ctypes.byref(cs)) == heads * sum(c * n for c, n in enumerate(sizes))
