@@ -11,7 +11,7 @@ namespace adaspark {
 
 constexpr int SEL_THREADS = 1024;
 constexpr int TAB_THREADS = 256;
-constexpr int FINISH_SMALL = 150;  // finish_small
+constexpr int FINISH_SMALL_TOKENS = 100;  // finish_small
 
 __device__ __forceinline__ float wave_sum(float x)
 {
@@ -368,13 +368,15 @@ FfnWorkspace ffn_workspace(const Geom &g, int d_model, int d_ff, void *ws)
 }
 
 // Whether a cube's rows are shared out among sixteen wavefronts, 64 columns each, by the residual kernel: where the workgroups
-// of four wavefronts and 512 columns leave CUs idle, and a cube has rows for all.  A layer with its selection, us, so and with
-// four: 910 tokens of 256/1280 in 8 cubes 71, 104; 1,540 of 1536/8064 in 12 cubes 140, 168; 4,664 of 2048/10112 in 35 cubes 310, 316;
-// past the line, 4,131 of 2048/8448 in 42 cubes, 275, 267.
+// of four wavefronts and 512 columns leave CUs idle, and the largest cube, which is then the kernel's time, has rows for all.  A
+// layer with its selection of d_model 512 and d_ff 2,560, us, so and with four wavefronts, by such workgroups: cubes of 36 tokens, 50 74, 73; of 120,
+// 50 90, 97, 85 118, 117; of 128, 48 91, 98, 88 117, 117, 120 148, 141; of 256, 48 122, 142, 120 203, 206, 152 260, 253; of 512, 140 455, 478.
+// The same lines with cubes that the grid clips to a few tokens beside these, and at d_model 1,024 to 3,584.
 static bool finish_small(const Geom &g, int d_model)
 {
+    const int largest = std::max(min(g.ct, g.T) * min(g.ch, g.H) * min(g.cw, g.W), min(g.Cmax, std::max(g.Sp, g.St)));
     const long long blocks = (long long)g.N * ((d_model + 511) / 512);
-    return g.Cmax >= 128 && blocks <= (g.S >= 96LL * g.N ? FINISH_SMALL : FINISH_SMALL / 2);
+    return largest >= FINISH_SMALL_TOKENS && blocks <= 45 + 3LL * largest / 8;
 }
 
 hipError_t launch_ffn_sparse(const Geom &g, int d_model, int d_ff, const uint16_t *X, const uint16_t *Wg,

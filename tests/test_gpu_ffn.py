@@ -117,10 +117,12 @@ def test_ffn_split_reduction(B, oracle, name, d_model, d_ff, p):
     test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, p)
 
 
-# The selection and residual kernels for few cubes, whose sixteen wavefronts take 128 tokens at a time: cubes of 127, 128, 129
-# and 300 tokens (clipped to 43, 86 and less), d_model on both sides of a single piece per lane, text of one token
+# The selection and residual kernels for few cubes, whose sixteen wavefronts take 128 tokens at a time: cubes of 99 (too few), 100, 127,
+# 128, 129 and 300 tokens (clipped to 43, 86 and less) and of 128 that the grid clips to 36; d_model on both sides of a single piece per
+# lane, text of one token
 EDGES = {"tokens127": ((2, 1, 127), (1, 1, 127), 0), "tokens128": ((3, 4, 32), (1, 4, 32), 1), "tokens129": ((2, 3, 86), (1, 3, 43), 0),
-         "tokens300": ((3, 10, 17), (2, 10, 15), 0)}
+         "tokens300": ((3, 10, 17), (2, 10, 15), 0), "tokens99": ((2, 1, 99), (1, 1, 99), 0), "tokens100": ((2, 1, 100), (1, 1, 100), 0),
+         "clipped36": ((3, 3, 6), (2, 8, 8), 0)}
 
 
 @pytest.mark.parametrize("name", EDGES)
