@@ -134,6 +134,25 @@ def test_ffn_few_cubes(B, oracle, monkeypatch, name, d_model, d_ff):
     test_ffn_sparse_matches_oracle(B, oracle, name, d_model, d_ff, 0.6)
 
 
+# The gated product's tiles (256 rows x 128 hidden features): a whole round of 256 and 24, or 4, more, which run as halves of their
+# rows.  The last row tile holds 1, 128, 129 and 256 rows and lies in both parts; in the second shape the halves are of a row tile of
+# the second group of four.
+@pytest.mark.parametrize("frames,d_model,d_ff", [(4, 256, 70 * 128), (5, 1024, 52 * 128)])
+def test_ffn_last_tiles_as_halves(B, oracle, frames, d_model, d_ff):
+    w = synth.Workload("halves", 51, frames, 16, 16, frames, 8, 8, 1, 1, 64, (0.6,), (1.0,))
+    X, Wg, Wu, Wd = synth.generate_ffn(w, d_model, d_ff)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    host, dev = [f64(t) for t in (X, Wg, Wu, Wd)], [t.cuda() for t in (X, Wg, Wu, Wd)]
+    order = torch.randperm(w.S, generator=torch.Generator().manual_seed(51))
+    for count in (w.S - 255, w.S - 128, w.S - 127, w.S):
+        keep = torch.zeros(w.S, dtype=torch.uint8)
+        keep[order[:count]] = 1
+        print(f"[halves] {count} rows, d_model={d_model} d_ff={d_ff}", flush=True)
+        Y = B.ffn_sparse(sh, *dev, keep=keep.cuda())
+        torch.cuda.synchronize()
+        check_outputs(f"halves {count}", f64(Y.cpu()), oracle.ffn.ffn_sparse(osh, *host, keep.numpy()), host[0])
+
+
 def test_ffn_degenerate_masks(B, oracle):
     """No token activated: the input comes back bit for bit.  One activated token per cube: every other token of
     the cube moves by that token's FFN value.  Stale workspace contents must not matter."""
