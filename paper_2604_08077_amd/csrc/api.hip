@@ -168,6 +168,12 @@ int adaspark_internal_short_sequence(const adaspark_shape *shape, int causal)
     return attn_split_pays(g, false) ? 1 : 0;
 }
 
+// Wavefronts that share 32 rows in the backward's dQ kernel (0: not a valid shape).  Not declared either.
+int adaspark_internal_dq_waves(const adaspark_shape *shape)
+{
+    return check_shape(shape) == ADASPARK_OK ? bwd_dq_waves(make_geom(*shape)) : 0;
+}
+
 // Candidate (row, cube) pairs of a shape, 0 for one that is not valid.  Not declared either.
 unsigned long long adaspark_internal_candidate_pairs(const adaspark_shape *shape)
 {

@@ -30,7 +30,7 @@ namespace adaspark {
 
 constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
-constexpr int DQ_SHARED_BLOCKS = 304;  // dq_keys
+constexpr int DQ_SHARED_BLOCKS = 304;  // bwd_dq_waves
 constexpr int SHARED_ROWS = 6000;     // dkv_shared
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
@@ -329,7 +329,7 @@ __device__ __forceinline__ void tn_half(const unsigned char *tt, int n16, int q4
 // dQ: workgroup = 256 / KEYS rows of one KV head; late rows (the long walks) first.
 // KEYS = 1: a wavefront per 32 rows.  KEYS = 2: two, wavefronts w and w + 4, each with half of every tile's keys; their
 // sums are added through LDS at the end.  A tile takes a workgroup 1.5 us at head-dim 128 (its MFMAs and exponentials), and
-// with few workgroups the longest walk is the kernel's time: half as long, over twice as many workgroups (dq_keys).
+// with few workgroups the longest walk is the kernel's time: half as long, over twice as many workgroups (bwd_dq_waves).
 // ---------------------------------------------------------------------------------------------------------------
 template <int D, bool MASKED, int KEYS>
 __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const uint16_t *__restrict__ Q,
@@ -989,19 +989,20 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
 
 // Whether two wavefronts share 32 rows in the dQ kernel.  While the workgroups of 256 rows find a CU each the kernel takes what
 // the longest walk takes; shared, a little over half of that.  With more, every CU is busy most of the time and sharing only adds
-// its own cost.  A backward pass, us, shared and not: 72 workgroups of 256 rows 93, 108; 192 (6/2 heads of 128) 445, 528;
-// 256 (28/4 heads of 128) 197, 212; 256 (4/4 heads of 64) 532, 626; 288 (6/2, 128) 779, 819; 320 (8/2, 64) 479, 476;
-// 336 (6/2, 128) 1,015, 1,002; 336 (28/4, 128) 315, 304; 384 (8/2, 64) 619, 571; 448 (28/4, 128) 487, 439.
-static int dq_keys(const Geom &g)
+// its own cost.  A backward pass, us, shared and not, by workgroups of 256 rows: 28/4 heads of 128, 112 146, 157, 252 226, 233, 308 293, 283;
+// 6/2 of 128, 102 206, 253, 282 749, 791, 330 980, 966; 8/2 of 64, 160 171, 204, 280 379, 396, 328 514, 493; 4/4 of 64, 280 653, 702,
+// 328 860, 839; 32/8 of 128, 256 198, 206, 288 263, 251; 6/2 in cubes of up to 128 clipped to 32, 282 911, 953, 330 1,238, 1,214.
+int bwd_dq_waves(const Geom &g)
 {
     const long long blocks = (long long)g.Hkv * ((g.S * g.G - 1) / BWD_ROWS + 1);
     return blocks <= DQ_SHARED_BLOCKS ? 2 : 1;
 }
 
 // Whether two wavefronts share 32 keys in the dK/dV kernel: with cubes of up to 128 tokens half or more of a workgroup's wavefronts
-// have no keys of their own.  Few rows of a KV head do not make up for the sums' exchange.  A layer's training pass, us, shared and not:
-// 7,688 tokens of 28/4 heads of 128 in cubes of 32 4,204, 4,536; 4,938 of 6/2 in cubes of 128 556, 580; 2,079 of 6/2 in cubes of 32 301,
-// 304; 855 of 14/2 (5,985 rows of a KV head) 225, 219; 3,339 of 4/4 heads of 64 196, 190.
+// have no keys of their own.  Few rows of a KV head do not make up for the sums' exchange.  A backward pass, us, shared and not,
+// by rows of a KV head: 28/4 heads of 128, cubes of 32, 5,040 135, 135, 8,064 176, 181, 16,128 390, 429; of 128, 3,584 57, 59, 16,128 233, 239;
+// 6/2 of 128, cubes of 32, 4,320 175, 167, 6,480 215, 216, 15,984 552, 591; of 64, 5,472 120, 117, 8,064 184, 176, 16,128 303, 319; 8/2 of 64, cubes of
+// 32, 5,760 133, 126, 8,064 149, 149; 4/4 of 64, cubes of 64, 2,976 116, 114, 7,968 294, 312.  Between 3,000 and 8,000 rows either is up to 7 % faster.
 static bool dkv_shared(const Geom &g) { return g.Cmax <= BWD_ROWS / 2 && (long long)g.S * g.G >= SHARED_ROWS; }
 
 template <int D>
@@ -1030,7 +1031,7 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     if (e != hipSuccess) return e;
     constexpr int TILE = 64 * D * 2;
 
-    const int keys = dq_keys(g), rows_q = BWD_ROWS / keys;
+    const int keys = bwd_dq_waves(g), rows_q = BWD_ROWS / keys;
     const dim3 grid_q(bwd_grid(g.Hkv, (g.S * g.G - 1) / rows_q + 1));
     const int lds_q = 2 * 3 * TILE + BWD_ROWS * 16 + ADASPARK_MAX_CUBES / 8 + ADASPARK_MAX_CUBES * 2 + 16;
     const BwdParts &cut = w.cut;

@@ -10,6 +10,8 @@ and the mean error must stay below a fifth of the mean bound.  Terms may cancel 
 large scores), so T, not |g|, is the unit.  delta = dO.O is a function of the O the caller hands over: the oracle is
 given the same bf16 O (the oracle's own pins use the exact one).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -127,8 +129,8 @@ def test_backward_shared_keys(B, oracle, monkeypatch, name, grid, cube, hq, d):
     run_case(B, oracle, name, 0.6)
 
 
-# The dQ kernel with two wavefronts per 32 rows, up to 304 workgroups' worth of 256 rows, and with one: both sides of the line;
-# cubes whose keys leave the second half of a tile empty, or with one key; row blocks of 128 and a remainder.
+# The dQ kernel with two wavefronts per 32 rows (up to 304 workgroups of 256 rows): cubes whose keys leave the second half of a tile empty,
+# or with one key; row blocks of 128 and a remainder.
 DQ = [
     ("blocks304", (38, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
     ("blocks312", (39, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
@@ -144,6 +146,26 @@ def test_backward_shared_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv,
     w = synth.Workload(name, 42, *grid, *cube, hq, hkv, d, (p,), (1.0,) * hkv, text)
     monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
     run_case(B, oracle, name, p)
+    run_case(B, oracle, name, 1.0, dense=True)
+
+
+# The dQ kernel with one wavefront per 32 rows: 305 workgroups of 256 rows and more, many heads of short sequences; both head dims, clipped
+# cubes with text around them, blocks over many cubes of three tokens, a block with a few rows.  And the last shape of the other side.
+ONE = [
+    ("heads154_text", (5, 5, 9), (2, 4, 4), 154, 154, 64, 33, 20, 1),
+    ("heads306_cubes3", (1, 1, 130), (1, 1, 3), 306, 153, 128, 0, 0, 1),
+    ("heads305_ragged", (3, 5, 7), (2, 2, 4), 305, 305, 128, 0, 0, 1),
+    ("heads304_ragged", (3, 5, 7), (2, 2, 4), 304, 304, 128, 0, 0, 2),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead,waves", ONE, ids=[c[0] for c in ONE])
+def test_backward_one_wavefront_per_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, text, lead, waves):
+    w = synth.Workload(name, 52, *grid, *cube, hq, hkv, d, (0.7,), (1.0,) * hkv, text, lead)
+    cs = B.Shape.of(w)._c()
+    assert B.load().adaspark_internal_dq_waves(ctypes.byref(cs)) == waves
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
+    run_case(B, oracle, name, 0.7)
     run_case(B, oracle, name, 1.0, dense=True)
 
 
