@@ -5,7 +5,8 @@
 // p is rebuilt from the forward's log-sum-exp, so nothing of the forward's size is stored.  Two MFMA kernels, neither
 // of which needs a transposition in registers or an atomic:
 //   attn_bwd_dq_kernel   row-stationary (like the forward's masked walk): a wavefront keeps Q and dO of 32 rows as
-//                        MFMA B operands, walks the key tiles of every cube up to its own, and accumulates dQ^T.
+//                        MFMA B operands, walks the key tiles of the cubes that some row of its block selected or is in, and
+//                        accumulates dQ^T.
 //                        S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T.  A row's selection bit for the key cube acts
 //                        as a mask (dense work, like the forward's masked walk).
 //   attn_bwd_dkv_kernel  key-stationary: a wavefront keeps K and V of 32 keys as B operands and accumulates dV^T and
@@ -403,7 +404,7 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
     auto row_place = [&](int s) -> int4 { return place[rgroup * 32 + s * 16 + n16]; };
     const float c2 = BWD_LOG2E / sqrtf((float)D);  // softmax scale in base 2
 
-    // tile stream: cubes 0..i, the tiles of each that hold keys
+    // tile stream: the cubes of the walk (clist), the tiles of each that hold keys
     const size_t head_tiles = (size_t)kv * g.N * g.TPC;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     auto issue = [&](int stage, int j, int t) __attribute__((always_inline)) {

@@ -9,8 +9,8 @@
 // is a partial result -- unnormalised O, running maximum m, sum l -- written to a record in caller-provided
 // scratch memory.  A record holds m, l and s = max |O| in fp32 and O / s in fp16: the merged output is a weighted
 // mean of the records' O / l, so a record's rounding error enters it with at most 2^-11 of that record's largest
-// element, an eighth of the rounding of the bf16 output itself, at half the memory traffic of fp32 records.  The causal part of every row's own cube is one more record, written by a second launch of the
-// same kernel over the rows of each cube.  A last kernel merges each row's records (they are contiguous: a row's
+// element, an eighth of the rounding of the bf16 output itself, at half the memory traffic of fp32 records.  The causal part of every row's own cube is one more record, written by workgroups of
+// their own in the same launch, over the rows of each cube.  A last kernel merges each row's records (they are contiguous: a row's
 // records are numbered in cube order after an exclusive scan of the per-row counts, the own cube last) into the
 // output.
 //

@@ -1,18 +1,17 @@
 // Attention for short sequences (dense, or sparse with the selection as a mask): the wavefronts of a workgroup share
 // the KEYS of one small block of rows instead of the rows of a big one.
 //
-// The walk kernel (attn_walk.hip) gives a workgroup 256 rows of a (query cube, KV head) and one walk over all keys, tile
-// by tile with a barrier each.  On a short sequence that leaves most of the chip idle -- 2,048 tokens of 4 heads in
-// cubes of 32 are 256 workgroups with two wavefronts' worth of rows each, and the time is the latency of the longest
-// walk -- so here a workgroup takes 32 rows, and its eight wavefronts take every eighth 32-key step of their walk,
+// The walk kernel (attn_walk.hip) gives a workgroup 256 rows of a KV head and one walk over all keys, tile by tile with a
+// barrier each.  On a short sequence that leaves most of the chip idle -- 2,048 tokens of 4 heads are 32 workgroups, and the
+// time is the latency of the longest walk -- so here a workgroup takes 32 rows, and its eight wavefronts take every eighth 32-key step of their walk,
 // operands straight from memory (the packed copy is in operand order, and nobody else on the CU wants the same tile).
 // The eight partial results (running reference, sum, unnormalised O, all fp32) are combined through LDS at the end.
 // Cubes in which no row of the block takes part (selection) are left out of the walk.
 //
 // Bound by the latency of a step at the smallest sizes and by L2 above (every wavefront fetches 16 KB at head-dim 128
 // for 34 MFMAs: 12 to 15 TB/s over the chip), which is why the walk kernel takes over as soon as it fills the chip
-// (attn_split_pays).  In a kernel trace: 2,048 tokens, 4/4 heads of 64, cubes of 32: 18.5 us, the walk kernel 127 us; 1,080
-// tokens, 6/2 heads of 128, clipped cubes of up to 128: 21.5 against 51 us.
+// (attn_split_pays).  2,048 tokens, 4/4 heads of 64, cubes of 32: 18.1 us, the walk kernel 98 us; 1,080 tokens, 6/2 heads
+// of 128, clipped cubes of up to 128: 19.1 against 48 us.
 #include <type_traits>
 
 #include "attn_tile.h"

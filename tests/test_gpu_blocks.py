@@ -1,7 +1,8 @@
 """The masked walk on shapes whose blocks of 256 rows lie across cubes, against the fp64 oracle: a KV head with 255, 256, 257
 and 513 rows, blocks over many cubes of one token, over clipped cubes and over the borders of text and video, and last tiles
 with 1, 31, 33 and 63 keys (the padding keys' probabilities are cleared in the short softmax step).  Tolerances are those of
-the other attention tests."""
+the other attention tests.  And values that are not finite in cubes
+behind a row's own, in all attention kernels whose blocks lie across cubes."""
 import numpy as np
 import pytest
 import torch
