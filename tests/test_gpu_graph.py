@@ -32,8 +32,18 @@ def inputs(w, variant):
 
 @pytest.mark.parametrize("name,p", [("T_ragged", 0.9), ("T_text64", 0.6), ("C2", 0.5)])
 def test_forward_step_replays(B, name, p):
-    w = synth.TEST_WORKLOADS.get(name) or synth.WORKLOADS[name]
-    sh = B.Shape.of(w)
+    replay_forward(B, synth.TEST_WORKLOADS.get(name) or synth.WORKLOADS[name], p, True)
+
+
+# Few rows whose heads all select little: the choice for all heads together, with room for the key-stationary kernel and without
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,p,room", [("cubes256", (56, 16, 16), (4, 8, 8), 6, 2, 0.5, True),
+                                                          ("cubes32", (15, 15, 16), (2, 4, 4), 28, 4, 0.05, False)])
+def test_forward_step_of_few_rows_replays(B, name, grid, cube, hq, hkv, p, room):
+    replay_forward(B, synth.Workload(name, 53, *grid, *cube, hq, hkv, 128, (p,), (1.0,) * hkv), p, room)
+
+
+def replay_forward(B, w, p, room):
+    name, sh = w.name, B.Shape.of(w)
     N, R = B.num_cubes(sh), sh.rows
     words = (N + 31) // 32
     dev = "cuda"
@@ -47,7 +57,7 @@ def test_forward_step_replays(B, name, p):
     cap = None
     try:  # room for the key-stationary kernel too, where the geometry is one it covers
         B.pairs_workspace_bytes(sh, R * N)
-        cap = R * N
+        cap = R * N if room else None
     except B.AdasparkError:
         pass
     ws_att = B.alloc_workspace(sh, B.CALL_SPARSE_ATTN, pairs_capacity=cap)
