@@ -23,6 +23,7 @@
 // 2 is then the exponent of the probability, and the selection costs no instruction per score.  The dP accumulators
 // start from minus delta.  bwd_prep_kernel leaves both start values per row.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -600,6 +601,273 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
+// dQ of short sequences: workgroup = 32 rows of one KV head, as in the forward's kernel for short sequences (attn_split.hip); its eight
+// wavefronts take every eighth 32-key step of the walk, operands straight from the packed copies (they are in operand order, and nobody
+// else on the CU wants the same ones), and their sums are added through LDS.
+//
+// Bound by the latency of a step (24 KB from L2, 48 MFMAs at head-dim 128, the next step's operands asked for as soon as this one's
+// are used).  1,080 tokens of 6/2 heads of 128: 20 us, 46 with two wavefronts per 32 rows on 56 workgroups.  The rows' Q and dO are B operands of all steps and of all eight wavefronts: they lie in LDS, which leaves the registers
+// to the operands in flight.
+// ---------------------------------------------------------------------------------------------------------------
+template <int D>
+struct DqSplit {
+    static constexpr int WAVES = BWD_THREADS / 64;
+    static constexpr int NS = 2;
+    static constexpr int ROWS = 16 * NS;
+    static constexpr int STEP = 32;  // keys per step
+    static constexpr int DT = D / 16, KSTEPS = D / 32;
+    static constexpr int OFF_OPS = WAVES * NS * DT * 1024;             // behind the wavefronts' sums: Q and dO as operands
+    static constexpr int OFF_PSUM = OFF_OPS + 2 * NS * KSTEPS * 1024;  // the wavefronts' sums of probabilities
+    static constexpr int OFF_UNION = OFF_PSUM + WAVES * ROWS * 4;
+    static constexpr int OFF_N = OFF_UNION + ADASPARK_MAX_CUBES / 8;
+    static constexpr int BYTES = OFF_N + 16;
+    static constexpr int LIST_MAX = OFF_OPS / 4;  // the list of steps lies where the sums go at the end
+    static_assert(BYTES <= 160 * 1024, "LDS of one CU");
+};
+
+template <int D, bool MASKED>
+__global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_split_kernel(Geom g, const uint16_t *__restrict__ Q,
+                                                                        const uint16_t *__restrict__ dO,
+                                                                        const uint16_t *__restrict__ Kn,
+                                                                        const uint16_t *__restrict__ Vn,
+                                                                        const uint16_t *__restrict__ Kt,
+                                                                        const int32_t *__restrict__ csize,
+                                                                        float *__restrict__ lse2p,
+                                                                        const float *__restrict__ deltap,
+                                                                        const uint32_t *__restrict__ sel_mask,
+                                                                        uint16_t *__restrict__ dQ)
+{
+    using C = DqSplit<D>;
+    constexpr int NS = C::NS, KSTEPS = C::KSTEPS, DT = C::DT;
+    extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+    uint32_t *list = reinterpret_cast<uint32_t *>(smem);  // steps of the walk: cube << 16 | step of the cube
+    bf16x8 *ops = reinterpret_cast<bf16x8 *>(smem + C::OFF_OPS);  // [Q, dO][slab][KSTEPS][lane]
+    float *psums = reinterpret_cast<float *>(smem + C::OFF_PSUM);  // [wave][row]
+    uint32_t *uni = reinterpret_cast<uint32_t *>(smem + C::OFF_UNION);
+    int *nsteps_s = reinterpret_cast<int *>(smem + C::OFF_N);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, q4 = lane >> 4;
+
+    // workgroup -> (KV head, block of 32 rows), late rows (long walks) first, across the cubes' borders
+    const int kv = blockIdx.x % g.Hkv;
+    const int row1 = g.S * g.G - (int)(blockIdx.x / g.Hkv) * C::ROWS, row0 = max(0, row1 - C::ROWS), last = row1 - 1;
+    const RowAt at = row_at(g, kv, min(row0 + (lane & 31), last));  // lane l works out row l % 32 (rows past the last one repeat it)
+    int rank[NS], own[NS];
+    size_t rowid[NS];
+    float lse2[NS], delta[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        rank[s] = __shfl(at.rank, 16 * s + n16, 64);
+        own[s] = __shfl(at.cube, 16 * s + n16, 64);
+        rowid[s] = (size_t)__shfl(at.id, 16 * s + n16, 64);
+        lse2[s] = lse2p[rowid[s]];    // -lse * sqrt(D): what the score products start from
+        delta[s] = deltap[rowid[s]];  // minus delta: what the dP products start from
+    }
+    // the last cube with rows here, and the first
+    const int i = __builtin_amdgcn_readlane(at.cube, 31), i_first = __builtin_amdgcn_readfirstlane(at.cube);
+    const int max_rank = __builtin_amdgcn_readlane(block_max_rank(at, row1 - row0), 31);  // of the block's rows in cube i
+    for (int x = wave; x < 2 * NS * KSTEPS; x += C::WAVES) {
+        const int s = x / KSTEPS % NS, c = x % KSTEPS;
+        ops[x * 64 + lane] = *reinterpret_cast<const bf16x8 *>((x < NS * KSTEPS ? Q : dO) + (s ? rowid[1] : rowid[0]) * D + 32 * c + 8 * q4);
+    }
+
+    // ---- the steps of the walk: the rows' own cubes, the last one up to the block's largest rank, and of those before them the ones
+    // that a row selected
+    if (MASKED) {
+        // wavefront w takes mask words w, w + 8, ...; its lanes are the block's rows, twice over
+        for (int w = wave; 32 * w <= i; w += C::WAVES) {
+            uint32_t m = sel_mask[rowid[(lane >> 4) & 1] * g.words + w];
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) m |= __shfl_xor(m, d, 64);
+            if (lane == 0) uni[w] = m;
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        int n = 0;
+        for (int c0 = 0; c0 <= i; c0 += 64) {
+            const int c = c0 + lane;
+            int steps = 0;
+            if (c <= i && (!MASKED || c >= i_first || ((uni[c >> 5] >> (c & 31)) & 1u))) {
+                const int size = c == i ? max_rank + 1 : g.ragged ? csize[c] : g.Cmax;
+                steps = (size + C::STEP - 1) / C::STEP;
+            }
+            int incl = steps;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int up = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += up;
+            }
+            for (int k = 0; k < steps; ++k) list[n + incl - steps + k] = ((uint32_t)c << 16) | (uint32_t)k;
+            n += __shfl(incl, 63, 64);
+        }
+        if (lane == 0) *nsteps_s = n;
+    }
+    __syncthreads();
+    const int nsteps = __builtin_amdgcn_readfirstlane(*nsteps_s);
+
+    // ---- this wavefront's steps: wave, wave + 8, ...  The next step's operands are loaded as soon as this one's are used.
+    const size_t head = (size_t)kv * g.N * g.TPC * (KEY_TILE * D);
+    bf16x8 kf[KSTEPS][2], vf[KSTEPS][2], tf[DT];
+    uint32_t word[NS], word_next[NS];
+    auto entry = [&](int p) -> uint32_t {  // (past the end the last step's operands are loaded, and not used)
+        return __builtin_amdgcn_readfirstlane(list[min(p, nsteps - 1)]);
+    };
+    auto tile_of = [&](const uint16_t *copy, uint32_t e) __attribute__((always_inline)) {
+        return reinterpret_cast<const unsigned char *>(copy + head + ((size_t)(e >> 16) * g.TPC + ((e & 0xffffu) >> 1)) * (KEY_TILE * D));
+    };
+    auto load_rows = [&](const uint16_t *copy, uint32_t e, bf16x8 (&f)[KSTEPS][2]) __attribute__((always_inline)) {
+        const unsigned char *tile = tile_of(copy, e);
+#pragma unroll
+        for (int c = 0; c < KSTEPS; ++c)
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2) {
+                const int krow = 32 * (int)(e & 1u) + 8 * (n16 >> 2) + 4 * k2 + (n16 & 3);
+                f[c][k2] = *reinterpret_cast<const bf16x8 *>(tile + k_tile_off<D>(krow, 4 * c + q4));
+            }
+    };
+    auto load_cols = [&](uint32_t e) __attribute__((always_inline)) {
+        const unsigned char *tile = tile_of(Kt, e);
+#pragma unroll
+        for (int e2 = 0; e2 < DT; ++e2)
+            tf[e2] = *reinterpret_cast<const bf16x8 *>(tile + vt_tile_off(16 * e2 + n16, 4 * (int)(e & 1u) + q4));
+    };
+    auto load_words = [&](uint32_t e) __attribute__((always_inline)) {
+        if (MASKED) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) word_next[s] = sel_mask[rowid[s] * g.words + (e >> 21)];
+        }
+    };
+    const float c2 = BWD_LOG2E / sqrtf((float)D);  // softmax scale in base 2
+    float psum[NS];
+    f32x4 acc[NS][DT];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        psum[s] = 0.f;
+#pragma unroll
+        for (int e = 0; e < DT; ++e) acc[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // The step e0; e1 is the next one.  BEHIND: of a cube behind some rows' own.  These rows' probabilities are zero there, but K and
+    // V need not be finite: they keep their sums.
+    auto work = [&](uint32_t e0, uint32_t e1, auto behind) __attribute__((always_inline)) {
+        constexpr bool BEHIND = decltype(behind)::value;
+        const int j = (int)(e0 >> 16), key0 = C::STEP * (int)(e0 & 0xffffu);
+        const bool edge = j >= i_first;  // some row's own cube, or behind it
+        const int jsize = g.ragged ? csize[j] : g.Cmax;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) word[s] = MASKED ? word_next[s] : 0u;
+        f32x4 sa[NS][2], pa[NS][2];
+#pragma unroll
+        for (int c = 0; c < KSTEPS; ++c)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const bf16x8 q = ops[(s * KSTEPS + c) * 64 + lane];
+                bool in = !MASKED || ((word[s] >> (j & 31)) & 1u);
+                if (edge) in = j >= own[s] || in;
+                const float b = in ? lse2[s] : -INFINITY;
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2) sa[s][k2] = mfma16(kf[c][k2], q, c == 0 ? f32x4{b, b, b, b} : sa[s][k2]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(Kn, e1, kf);
+        load_words(e1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < KSTEPS; ++c)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const bf16x8 o = ops[((NS + s) * KSTEPS + c) * 64 + lane];
+                const float b = delta[s];
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2) pa[s][k2] = mfma16(vf[c][k2], o, c == 0 ? f32x4{b, b, b, b} : pa[s][k2]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(Vn, e1, vf);
+        __builtin_amdgcn_sched_barrier(0);
+        if (edge || key0 + C::STEP > jsize) {  // the own cubes' causal edge, padding keys
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int lim = j < own[s] ? jsize - 1 : j == own[s] ? rank[s] : -1;
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (key0 + 8 * q4 + 4 * k2 + v > lim) sa[s][k2][v] = -INFINITY;
+            }
+        }
+        bf16x8 ds[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float p = __builtin_amdgcn_exp2f(sa[s][k2][v] * c2);
+                    psum[s] += p;
+                    ds[s][4 * k2 + v] = (__bf16)(p * pa[s][k2][v]);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < DT; ++e)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const f32x4 sum = mfma16(tf[e], ds[s], acc[s][e]);
+                acc[s][e] = BEHIND && j > own[s] ? acc[s][e] : sum;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        load_cols(e1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (wave < nsteps) {
+        uint32_t e0 = entry(wave);
+        load_rows(Kn, e0, kf);
+        load_words(e0);
+        load_rows(Vn, e0, vf);
+        load_cols(e0);
+        int p = wave;
+        const uint32_t behind = (uint32_t)(i_first + 1) << 16;  // the first such step
+        for (; p < nsteps && e0 < behind; p += C::WAVES) {
+            const uint32_t e1 = entry(p + C::WAVES);
+            work(e0, e1, std::false_type{});
+            e0 = e1;
+        }
+        for (; p < nsteps; p += C::WAVES) {
+            const uint32_t e1 = entry(p + C::WAVES);
+            work(e0, e1, std::true_type{});
+            e0 = e1;
+        }
+    }
+    __syncthreads();  // the list is done with
+
+    // ---- the wavefronts' sums, added in their order; then as in the kernel above
+    f32x4 *part = reinterpret_cast<f32x4 *>(smem);  // [wave][s][e][lane]
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+#pragma unroll
+        for (int e = 0; e < DT; ++e) part[((wave * NS + s) * DT + e) * 64 + lane] = acc[s][e];
+        const float total = quad_sum(psum[s]);
+        if (q4 == 0) psums[wave * C::ROWS + 16 * s + n16] = total;
+    }
+    __syncthreads();
+    for (int x = wave; x < NS * DT; x += C::WAVES) {
+        const int s = x / DT, e = x % DT;
+        float total = 0.f;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < C::WAVES; ++w) {
+            total += psums[w * C::ROWS + 16 * s + n16];
+            sum += part[((w * NS + s) * DT + e) * 64 + lane];
+        }
+        if (row0 + 16 * s + n16 > last) continue;
+        const size_t rid = s == 0 ? rowid[0] : rowid[1];
+        if (e == 0 && q4 == 0) lse2p[rid] = (s == 0 ? lse2[0] : lse2[1]) - log2f(total) / c2;
+        *reinterpret_cast<uint2 *>(dQ + rid * D + 16 * e + 4 * q4) = pack_bf16(sum * (1.0f / (sqrtf((float)D) * total)));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
 // dV, dK: workgroup = 256 keys of one (key cube j, KV head) and one range of row cubes (BwdParts).
 //
 // The rows of the range that selected cube j are listed in LDS from the transposed selection bits, BWD_LIST_WORDS
@@ -988,15 +1256,30 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(Geom g, BwdParts cut, c
     *reinterpret_cast<uint2 *>(dK + o) = pack_bf16(k * (1.0f / sqrtf((float)D)));
 }
 
-// Whether two wavefronts share 32 rows in the dQ kernel.  While the workgroups of 256 rows find a CU each the kernel takes what
+// Wavefronts that share 32 rows in the dQ kernel.
+// Two: while the workgroups of 256 rows find a CU each the kernel takes what
 // the longest walk takes; shared, a little over half of that.  With more, every CU is busy most of the time and sharing only adds
 // its own cost.  A backward pass, us, shared and not, by workgroups of 256 rows: 28/4 heads of 128, 112 146, 157, 252 226, 233, 308 293, 283;
 // 6/2 of 128, 102 206, 253, 282 749, 791, 330 980, 966; 8/2 of 64, 160 171, 204, 280 379, 396, 328 514, 493; 4/4 of 64, 280 653, 702,
 // 328 860, 839; 32/8 of 128, 256 198, 206, 288 263, 251; 6/2 in cubes of up to 128 clipped to 32, 282 911, 953, 330 1,238, 1,214.
+// Eight (attn_bwd_dq_split_kernel): from what each of the two takes (us), fitted to the backward passes of 132 shapes of 500 to 6,000 tokens, heads
+// 4/4 .. 32/8 of 64 and 128, cubes of 32 to 256 tokens; but for four the choice is the faster kernel or within 2.5 % of it (10 %: 480 tokens).
+//   two    a tile of 64 keys takes 1.28 at head-dim 64 and 1.85 at 128; the longest walk's tiles, or all of them over the CUs
+//   eight  a step of 32 keys takes a CU 0.29 and 0.42, half the steps on average; a workgroup 4 to start and to combine its sums
+// On both sides of the line: 8/2 heads of 64 in cubes of 256, 2,048 tokens 86 eight, 95 two; 4,096 166, 150.  6/2 of 128 in clipped cubes of
+// up to 128, 1,080 tokens 57, 92.  28/4 of 128 in cubes of 256, 512 tokens 65, 66; 1,024 135, 109.
 int bwd_dq_waves(const Geom &g)
 {
     const long long blocks = (long long)g.Hkv * ((g.S * g.G - 1) / BWD_ROWS + 1);
-    return blocks <= DQ_SHARED_BLOCKS ? 2 : 1;
+    if (blocks > DQ_SHARED_BLOCKS) return 1;
+    const long long list = (long long)g.N * ((g.Cmax + DqSplit<64>::STEP - 1) / DqSplit<64>::STEP);
+    if (list > (g.D == 64 ? DqSplit<64>::LIST_MAX : DqSplit<128>::LIST_MAX) || g.Cmax > 65536 * DqSplit<64>::STEP / 2) return 2;
+    const double x = g.Hkv * std::ceil((double)g.S * g.G / DqSplit<64>::ROWS) / 256;
+    const double two = (g.D == 64 ? 1.28 : 1.85) * (double)tiles_of_cubes(g, KEY_TILE) *
+                       std::max(1.0, 0.64 * g.Hkv * std::ceil((double)g.S * g.G / (BWD_ROWS / 2)) / 256);
+    const double eight = 8 + 4 * std::max(0.0, x - 1) +
+                         (g.D == 64 ? 0.145 : 0.21) * std::max(0.8, x) * (double)tiles_of_cubes(g, DqSplit<64>::STEP);
+    return eight < two ? 8 : 2;
 }
 
 // Whether two wavefronts share 32 keys in the dK/dV kernel: with cubes of up to 128 tokens half or more of a workgroup's wavefronts
@@ -1032,7 +1315,7 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     if (e != hipSuccess) return e;
     constexpr int TILE = 64 * D * 2;
 
-    const int keys = bwd_dq_waves(g), rows_q = BWD_ROWS / keys;
+    const int waves = bwd_dq_waves(g), keys = std::min(2, waves), rows_q = BWD_ROWS / keys;
     const dim3 grid_q(bwd_grid(g.Hkv, (g.S * g.G - 1) / rows_q + 1));
     const int lds_q = 2 * 3 * TILE + BWD_ROWS * 16 + ADASPARK_MAX_CUBES / 8 + ADASPARK_MAX_CUBES * 2 + 16;
     const BwdParts &cut = w.cut;
@@ -1050,7 +1333,19 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     };
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
-    if (sel_mask != nullptr)
+    auto launch_split = [&](auto masked) -> hipError_t {
+        constexpr bool MASKED = decltype(masked)::value;
+        static LdsOptIn opted_s;  // one per kernel instantiation
+        const hipError_t err = opted_s.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_split_kernel<D, MASKED>), DqSplit<D>::BYTES);
+        if (err != hipSuccess) return err;
+        const unsigned blocks = (unsigned)((g.S * g.G - 1) / DqSplit<D>::ROWS + 1) * (unsigned)g.Hkv;
+        hipLaunchKernelGGL((attn_bwd_dq_split_kernel<D, MASKED>), dim3(blocks), dim3(BWD_THREADS), DqSplit<D>::BYTES, st, g, Q, dO, w.Kn,
+                           w.Vn, w.Kt, w.csize, w.lse2, w.delta, sel_mask, dQ);
+        return hipGetLastError();
+    };
+    if (waves == 8)
+        e = sel_mask != nullptr ? launch_split(std::true_type{}) : launch_split(std::false_type{});
+    else if (sel_mask != nullptr)
         e = keys == 2 ? launch_dq(std::true_type{}, two) : launch_dq(std::true_type{}, one);
     else
         e = keys == 2 ? launch_dq(std::false_type{}, two) : launch_dq(std::false_type{}, one);

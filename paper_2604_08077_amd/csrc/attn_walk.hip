@@ -643,7 +643,7 @@ static bool heads_together(const Geom &g) { return walk_rounds(g) <= 1.0; }
 
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
 // axis), text cubes in two.
-static long long tiles_of_cubes(const Geom &g, int keys)
+long long tiles_of_cubes(const Geom &g, int keys)
 {
     auto tiles = [&](int tokens) { return (long long)(tokens + keys - 1) / keys; };
     long long n = (long long)(g.Sp / g.Cmax + g.St / g.Cmax) * tiles(g.Cmax) + tiles(g.Sp % g.Cmax) + tiles(g.St % g.Cmax);

@@ -219,6 +219,8 @@ struct LdsOptIn {
 
 // Number of candidate (row, cube) pairs of a causal selection: every row of cube i has i preceding cubes.
 unsigned long long candidate_pairs(const Geom &g);
+// Tiles of `keys` keys that all cubes together take (attn_walk.hip).
+long long tiles_of_cubes(const Geom &g, int keys);
 
 // sel_mask == nullptr: dense (every preceding cube attended); otherwise sparse_kernel is an adaspark_sparse_kernel.
 // The automatic choice writes a flag into the last 16 bytes of the packed workspace.  scratch (256-byte aligned, may

@@ -149,6 +149,27 @@ def test_backward_shared_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv,
     run_case(B, oracle, name, 1.0, dense=True)
 
 
+# The dQ kernel with eight wavefronts per 32 rows: walks of fewer steps than wavefronts and of many, cubes with one key in their last step,
+# blocks of 32 rows across cubes, a block with one row, more than 64 cubes, text on both sides, clipped cubes
+EIGHT = [
+    ("rows353_keys1", (353, 1, 1), (1, 1, 1), 1, 1, 64, 0, 0),
+    ("keys33", (12, 3, 11), (1, 3, 11), 2, 1, 128, 0, 0),
+    ("keys65_text", (9, 5, 13), (1, 5, 13), 3, 1, 64, 70, 40),
+    ("cubes70", (70, 2, 4), (1, 2, 4), 4, 2, 128, 9, 0),
+    ("clipped", (9, 10, 12), (4, 4, 8), 3, 1, 128, 0, 30),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead", EIGHT, ids=[c[0] for c in EIGHT])
+def test_backward_eight_wavefronts_per_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, text, lead):
+    w = synth.Workload(name, 61, *grid, *cube, hq, hkv, d, (0.7,), (1.0,) * hkv, text, lead)
+    cs = B.Shape.of(w)._c()
+    assert B.load().adaspark_internal_dq_waves(ctypes.byref(cs)) == 8
+    monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
+    run_case(B, oracle, name, 0.7)
+    run_case(B, oracle, name, 1.0, dense=True)
+
+
 # The dQ kernel with one wavefront per 32 rows: 305 workgroups of 256 rows and more, many heads of short sequences; both head dims, clipped
 # cubes with text around them, blocks over many cubes of three tokens, a block with a few rows.  And the last shape of the other side.
 ONE = [
