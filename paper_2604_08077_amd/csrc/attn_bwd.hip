@@ -34,6 +34,7 @@ constexpr int BWD_THREADS = 512;
 constexpr int BWD_ROWS = 256;   // rows (dQ kernel) or keys (dK/dV kernel) per workgroup: 8 wavefronts x 2 x 16
 constexpr int DQ_SHARED_BLOCKS = 304;  // bwd_dq_waves
 constexpr int SHARED_ROWS = 6000;     // dkv_shared
+constexpr int SHARED_CUBE_ROWS = 384;
 constexpr float BWD_LOG2E = 1.44269504088896340736f;
 
 // How attn_bwd_dkv_kernel's work is cut.  A workgroup takes up to 256 keys (one of nkb key blocks) of one (key cube j, KV
@@ -1283,11 +1284,17 @@ int bwd_dq_waves(const Geom &g)
 }
 
 // Whether two wavefronts share 32 keys in the dK/dV kernel: with cubes of up to 128 tokens half or more of a workgroup's wavefronts
-// have no keys of their own.  Few rows of a KV head do not make up for the sums' exchange.  A backward pass, us, shared and not,
+// have no keys of their own.  Few rows do not make up for the sums' exchange: it takes the rows of a KV head, or those of a cube, which a
+// workgroup has all of in one piece.  A backward pass, us, shared and not,
 // by rows of a KV head: 28/4 heads of 128, cubes of 32, 5,040 135, 135, 8,064 176, 181, 16,128 390, 429; of 128, 3,584 57, 59, 16,128 233, 239;
 // 6/2 of 128, cubes of 32, 4,320 175, 167, 6,480 215, 216, 15,984 552, 591; of 64, 5,472 120, 117, 8,064 184, 176, 16,128 303, 319; 8/2 of 64, cubes of
 // 32, 5,760 133, 126, 8,064 149, 149; 4/4 of 64, cubes of 64, 2,976 116, 114, 7,968 294, 312.  Between 3,000 and 8,000 rows either is up to 7 % faster.
-static bool dkv_shared(const Geom &g) { return g.Cmax <= BWD_ROWS / 2 && (long long)g.S * g.G >= SHARED_ROWS; }
+// By rows of a cube, 480 to 2,000 tokens: 896 (28/4, 14/2 heads of 128) 61, 67 and 71, 76; 448 48, 50 and 65, 70; 512 (32/8 of 128, 8/2 of 64) 107, 112 and 56, 59;
+// 384 (6/2 of 128) 67, 71 and 107, 106; 256 69, 67 and 61, 61; 192 73, 71; 128 (4/4 of 64) 92, 82; 96 113, 105.
+static bool dkv_shared(const Geom &g)
+{
+    return g.Cmax <= BWD_ROWS / 2 && ((long long)g.S * g.G >= SHARED_ROWS || g.G * g.Cmax >= SHARED_CUBE_ROWS);
+}
 
 template <int D>
 static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t *K, const uint16_t *V,
