@@ -170,11 +170,15 @@ __device__ __forceinline__ float selm_quad_max(float x)
 // TOPK: fixed Top-K selection (the ablation baseline of "Effect of Top-P Adaptive Selection") instead of Top-p: the
 // top_k most relevant preceding cubes, ties by lower index.  The values ranked are then the logits themselves
 // (as order-preserving integer keys: no softmax, nothing can underflow) and the "mass" is a count.
-template <int D, int MAXG, int SLABS, bool TOPK>
+// SPLIT_HERE: the wavefront splits the mean keys that it needs itself (ksplit is not read, and kbar_split_kernel not run): of up to 64 cubes
+// that is 0.7 us at head-dim 64 on a chip that is not full, where the launch takes 5 (a forward pass of 2,048 tokens of 4/4 heads of 64
+// in 64 cubes 44.5 us with it, 40.9 without; a training pass of 1,080 tokens of 6/2 heads of 128 101, 98).
+template <int D, int MAXG, int SLABS, bool TOPK, bool SPLIT_HERE = false>
 __global__ __launch_bounds__(SELM_THREADS, MAXG == 8 ? 3 : 2) void cube_select_mfma_kernel(
-    Geom g, int NG, int i_end, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ ksplit, float top_p,
-    int top_k, uint32_t *__restrict__ sel_mask, int32_t *__restrict__ sel_count)
+    Geom g, int NG, int i_end, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ ksplit, const float *__restrict__ kbar,
+    float top_p, int top_k, uint32_t *__restrict__ sel_mask, int32_t *__restrict__ sel_count, int32_t *__restrict__ status)
 {
+    if (SPLIT_HERE && blockIdx.x == 0 && threadIdx.x == 0) *status = (int32_t)ADASPARK_OK;  // (as in kbar_split_kernel)
     constexpr int KS = D / 32;
     constexpr int ROWS = SELM_WAVES * SLABS * 16;  // per workgroup
     // the threshold search's short lists (see below): SELM_SHORT entries and a dump slot per lane
@@ -234,34 +238,70 @@ __global__ __launch_bounds__(SELM_THREADS, MAXG == 8 ? 3 : 2) void cube_select_m
     for (int s = 0; s < SLABS; ++s)
 #pragma unroll
         for (int cg = 0; cg < MAXG; ++cg) acc[s][cg] = sel_f32x4{0.f, 0.f, 0.f, 0.f};
-    // The mean-key operands go from global memory (they stay in L2: a few MB per call) straight into registers,
-    // half a cube group ahead of the MFMAs that use them: no staging through LDS, no barriers.
     constexpr int OPS = KS * 3, HALF = OPS / 2, KSH = KS / 2;
     static_assert(KS % 2 == 0, "a cube group's operands are fetched in two halves");
-    const sel_bf16x8 *src = reinterpret_cast<const sel_bf16x8 *>(ksplit) + (size_t)kv * NG * (OPS * 64) + lane;
-    sel_bf16x8 buf0[HALF], buf1[HALF];
+    if (SPLIT_HERE) {
+        typedef float f32x8 __attribute__((ext_vector_type(8)));
+        f32x8 mean[MAXG][KS];  // (all asked for at once)
 #pragma unroll
-    for (int o = 0; o < HALF; ++o) buf0[o] = src[o * 64];  // ng >= 1 here
+        for (int cg = 0; cg < MAXG; ++cg)
+            if (cg < ng) {
+                const int cube = min(16 * cg + n16, g.N - 1);  // (no candidate past the last cube)
 #pragma unroll
-    for (int cg = 0; cg < MAXG; ++cg) {
-        if (cg < ng) {  // uniform for the workgroup
-#pragma unroll
-            for (int o = 0; o < HALF; ++o) buf1[o] = src[((size_t)cg * OPS + HALF + o) * 64];
-#pragma unroll
-            for (int o = 0; o < HALF; ++o)
-#pragma unroll
-                for (int s = 0; s < SLABS; ++s)
-                    acc[s][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf0[o], qf[s][o / 3], acc[s][cg], 0, 0, 0);
-            if (cg + 1 < ng) {
-#pragma unroll
-                for (int o = 0; o < HALF; ++o) buf0[o] = src[((size_t)(cg + 1) * OPS + o) * 64];
+                for (int c = 0; c < KS; ++c)
+                    mean[cg][c] = *reinterpret_cast<const f32x8 *>(kbar + ((size_t)cube * g.Hkv + kv) * D + 32 * c + 8 * q4);
             }
 #pragma unroll
-            for (int o = 0; o < HALF; ++o)
+        for (int cg = 0; cg < MAXG; ++cg)
+            if (cg < ng) {
 #pragma unroll
-                for (int s = 0; s < SLABS; ++s)
-                    acc[s][cg] =
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf1[o], qf[s][KSH + o / 3], acc[s][cg], 0, 0, 0);
+                for (int c = 0; c < KS; ++c) {
+                    sel_bf16x8 term[3];  // hi, mid, lo; the differences are exact
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float v = mean[cg][c][e];
+                        const __bf16 hi = (__bf16)v;
+                        const float r1 = v - (float)hi;
+                        const __bf16 mid = (__bf16)r1;
+                        term[0][e] = hi;
+                        term[1][e] = mid;
+                        term[2][e] = (__bf16)(r1 - (float)mid);
+                    }
+#pragma unroll
+                    for (int o = 0; o < 3; ++o)
+#pragma unroll
+                        for (int s = 0; s < SLABS; ++s)
+                            acc[s][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(term[o], qf[s][c], acc[s][cg], 0, 0, 0);
+                }
+            }
+    } else {
+        // The mean-key operands go from global memory (they stay in L2: a few MB per call) straight into registers,
+        // half a cube group ahead of the MFMAs that use them: no staging through LDS, no barriers.
+        const sel_bf16x8 *src = reinterpret_cast<const sel_bf16x8 *>(ksplit) + (size_t)kv * NG * (OPS * 64) + lane;
+        sel_bf16x8 buf0[HALF], buf1[HALF];
+#pragma unroll
+        for (int o = 0; o < HALF; ++o) buf0[o] = src[o * 64];  // ng >= 1 here
+#pragma unroll
+        for (int cg = 0; cg < MAXG; ++cg) {
+            if (cg < ng) {  // uniform for the workgroup
+#pragma unroll
+                for (int o = 0; o < HALF; ++o) buf1[o] = src[((size_t)cg * OPS + HALF + o) * 64];
+#pragma unroll
+                for (int o = 0; o < HALF; ++o)
+#pragma unroll
+                    for (int s = 0; s < SLABS; ++s)
+                        acc[s][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf0[o], qf[s][o / 3], acc[s][cg], 0, 0, 0);
+                if (cg + 1 < ng) {
+#pragma unroll
+                    for (int o = 0; o < HALF; ++o) buf0[o] = src[((size_t)(cg + 1) * OPS + o) * 64];
+                }
+#pragma unroll
+                for (int o = 0; o < HALF; ++o)
+#pragma unroll
+                    for (int s = 0; s < SLABS; ++s)
+                        acc[s][cg] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(buf1[o], qf[s][KSH + o / 3], acc[s][cg], 0, 0, 0);
+            }
         }
     }
 
@@ -1258,13 +1298,15 @@ size_t select_workspace_bytes(const Geom &g)
 // their own, each with registers for as many candidates as its cubes have.
 template <int D, int SLABS, bool TOPK>
 static void launch_select_narrow(const Geom &g, int NG, int end, bool by_range, const uint16_t *Q, const uint16_t *ksplit,
-                                 float top_p, int top_k, uint32_t *sel_mask, int32_t *sel_count, hipStream_t st)
+                                 const float *kbar, float top_p, int top_k, uint32_t *sel_mask, int32_t *sel_count, int32_t *status,
+                                 hipStream_t st)
 {
     const int rows = SELM_WAVES * SLABS * 16, nblk = (g.G * g.Cmax + rows - 1) / rows;
     auto launch = [&](auto maxg, int lo, int hi) {
         constexpr int MAXG = decltype(maxg)::value;
-        hipLaunchKernelGGL((cube_select_mfma_kernel<D, MAXG, SLABS, TOPK>), dim3((unsigned)((size_t)(hi - lo) * g.Hkv * nblk)),
-                           dim3(SELM_THREADS), 0, st, g, NG, hi, Q, ksplit, top_p, top_k, sel_mask, sel_count);
+        hipLaunchKernelGGL((cube_select_mfma_kernel<D, MAXG, SLABS, TOPK, SLABS == 1 && MAXG == 4>),
+                           dim3((unsigned)((size_t)(hi - lo) * g.Hkv * nblk)), dim3(SELM_THREADS), 0, st, g, NG, hi, Q, ksplit, kbar, top_p,
+                           top_k, sel_mask, sel_count, status);
     };
     // (non-causal: every query cube has all candidates)
     auto split_at = [&](int lo) {
@@ -1283,18 +1325,24 @@ static void launch_select_narrow(const Geom &g, int NG, int end, bool by_range, 
     if (end > 0) launch(std::integral_constant<int, 4>{}, 0, end);
 }
 
+// Whether all query cubes are the one launch's whose wavefronts take a slab each and split the mean keys themselves.
+static bool select_splits(const Geom &g)
+{
+    return g.N <= 64 && (long long)g.N * g.Hkv * ((g.G * g.Cmax + 15) / 16) <= SELM_FEW_SLABS;
+}
+
 template <int D, bool TOPK>
-static void launch_select_d(const Geom &g, int NG, const uint16_t *Q, const uint16_t *ksplit, float top_p, int top_k,
-                            uint32_t *sel_mask, int32_t *sel_count, hipStream_t st)
+static void launch_select_d(const Geom &g, int NG, const uint16_t *Q, const uint16_t *ksplit, const float *kbar, float top_p, int top_k,
+                            uint32_t *sel_mask, int32_t *sel_count, int32_t *status, hipStream_t st)
 {
     // query cubes below SELM_MAX_CUBES have at most that many candidates: one wavefront holds a row's logits
     // (in non-causal mode every query cube has all video cubes as candidates)
     const int i_narrow = g.N <= SELM_MAX_CUBES ? g.N : (g.causal ? SELM_MAX_CUBES : 0);
     if (i_narrow > 0) {
         if ((long long)i_narrow * g.Hkv * ((g.G * g.Cmax + 15) / 16) <= SELM_FEW_SLABS)
-            launch_select_narrow<D, 1, TOPK>(g, NG, i_narrow, false, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
+            launch_select_narrow<D, 1, TOPK>(g, NG, i_narrow, false, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
         else
-            launch_select_narrow<D, 2, TOPK>(g, NG, i_narrow, true, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
+            launch_select_narrow<D, 2, TOPK>(g, NG, i_narrow, true, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
     }
     if (g.N > i_narrow) {  // the later query cubes: a row's candidates are spread over 4 or 8 wavefronts
         const int nblk_max = (g.G * g.Cmax + SELW_ROWS - 1) / SELW_ROWS;
@@ -1329,14 +1377,15 @@ hipError_t launch_cube_select(const Geom &g, const uint16_t *Q, const float *kba
     const int NG = select_groups(g);
     const size_t total = (size_t)g.Hkv * NG * (g.D / 32) * 64;
     int32_t *status = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(ws) + select_status_offset(g));
-    hipLaunchKernelGGL(kbar_split_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g, NG, kbar, ksplit,
-                       status);
+    if (!select_splits(g))
+        hipLaunchKernelGGL(kbar_split_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g, NG, kbar, ksplit,
+                           status);
     if (top_k >= 0) {
-        if (g.D == 64) launch_select_d<64, true>(g, NG, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
-        else launch_select_d<128, true>(g, NG, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
+        if (g.D == 64) launch_select_d<64, true>(g, NG, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
+        else launch_select_d<128, true>(g, NG, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
     } else {
-        if (g.D == 64) launch_select_d<64, false>(g, NG, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
-        else launch_select_d<128, false>(g, NG, Q, ksplit, top_p, top_k, sel_mask, sel_count, st);
+        if (g.D == 64) launch_select_d<64, false>(g, NG, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
+        else launch_select_d<128, false>(g, NG, Q, ksplit, kbar, top_p, top_k, sel_mask, sel_count, status, st);
     }
 
     if (row_ptr != nullptr) {

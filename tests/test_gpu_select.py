@@ -12,6 +12,10 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [  # cubes, tokens of a cube, query heads, KV heads, head_dim
     ("few_64", 64, 5, 3, 1, 64),
+    ("few_2", 2, 33, 2, 1, 128),  # up to 64 cubes: the wavefronts split the mean keys themselves
+    ("few_16", 16, 7, 3, 1, 64),
+    ("few_17", 17, 16, 2, 2, 128),
+    ("few_64_128", 64, 3, 1, 1, 128),
     ("few_65", 65, 16, 1, 1, 128),
     ("few_129", 129, 17, 2, 2, 64),
     ("few_256", 256, 4, 4, 1, 128),
