@@ -754,6 +754,11 @@ int *pairs_flags(const Geom &g, void *scratch, size_t scratch_bytes)
     return sc.cap > 0 ? sc.flags : nullptr;
 }
 
+long long pairs_capacity(const Geom &g, void *scratch, size_t scratch_bytes)
+{
+    return pairs_layout(g, scratch, scratch_bytes).cap;
+}
+
 uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int &words)
 {
     const PairsScratch sc = pairs_layout(g, scratch, scratch_bytes);

@@ -490,10 +490,12 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     write_rows(0x7fffffff);
 }
 
-// ---- the share of candidate cubes the rows select, per KV head, from a sample of rows.  One workgroup; writes
-// flags[FLAG_MODE] = 1 (the other row-stationary kernel: an overall share of up to other_permille) or 2 (masked walk),
-// flags[FLAG_ESTIMATE] = the smallest share of a KV head in permille (together: the largest), and (kv_modes) the heads' shares; clears the per-head choices and the key-stationary path's
-// counters.
+// ---- What the choice of kernel goes by, from samples; two workgroups, which write
+//   0  the share of candidate cubes that the rows select, per KV head: flags[FLAG_MODE] = 1 (the other row-stationary kernel: an overall
+//      share of up to other_permille) or 2 (masked walk), flags[FLAG_ESTIMATE] = the smallest share of a KV head in permille (together:
+//      the largest), and (kv_modes) the heads' shares
+//   1  flags[FLAG_UNION]; it also clears the per-head choices and the key-stationary path's counters
+// (One workgroup that did both: 15 us at 9,000 tokens of 28/4 heads, 28 at 65,536; two 10 and 16.)
 constexpr int DENSITY_THREADS = 1024;
 constexpr int DENSITY_MAX_ROWS = 2048;  // two sampled rows per thread: an estimate is all that is needed
 constexpr int DENSITY_GROUPS = 16;          // sampled blocks of rows for the union estimate
@@ -506,101 +508,102 @@ __global__ __launch_bounds__(DENSITY_THREADS) void sel_density_kernel(Geom g, co
                                                                       int *__restrict__ flags, int kv_modes, int together,
                                                                       int other_permille, uint32_t *__restrict__ counters, int counter_words)
 {
-    // selected, candidates (at most DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES); heads beyond the array fold
-    __shared__ uint32_t acc[2][PAIRS_MAX_KV_HEADS];
-    for (int x = threadIdx.x; x < 2 * PAIRS_MAX_KV_HEADS; x += DENSITY_THREADS) (&acc[0][0])[x] = 0u;
-    for (int x = threadIdx.x; x < counter_words; x += DENSITY_THREADS) counters[x] = 0u;
-    __syncthreads();
-    // sample k: token (k * tstride) mod S, query head k mod Hq -- every head gets its share of the samples
-    const int samples = (int)min((long long)DENSITY_MAX_ROWS, (long long)g.S * g.Hq);
-    const int tstride = max(1, g.S / samples) | 1;
-    for (int k = threadIdx.x; k < samples; k += DENSITY_THREADS) {
-        // (k * tstride < S + DENSITY_MAX_ROWS, or below DENSITY_MAX_ROWS: 32 bits)
-        const int n = (int)((uint32_t)k * (uint32_t)tstride % (uint32_t)g.S), a = k % g.Hq;
-        const int i = cube_of_token(g, n);
-        const uint32_t *mr = sel_mask + ((size_t)n * g.Hq + a) * g.words;
-        uint32_t sel = 0;
+    if (blockIdx.x == 0) {
+        // selected, candidates (at most DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES); heads beyond the array fold
+        __shared__ uint32_t acc[2][PAIRS_MAX_KV_HEADS];
+        for (int x = threadIdx.x; x < 2 * PAIRS_MAX_KV_HEADS; x += DENSITY_THREADS) (&acc[0][0])[x] = 0u;
+        __syncthreads();
+        // sample k: token (k * tstride) mod S, query head k mod Hq -- every head gets its share of the samples
+        const int samples = (int)min((long long)DENSITY_MAX_ROWS, (long long)g.S * g.Hq);
+        const int tstride = max(1, g.S / samples) | 1;
+        for (int k = threadIdx.x; k < samples; k += DENSITY_THREADS) {
+            // (k * tstride < S + DENSITY_MAX_ROWS, or below DENSITY_MAX_ROWS: 32 bits)
+            const int n = (int)((uint32_t)k * (uint32_t)tstride % (uint32_t)g.S), a = k % g.Hq;
+            const int i = cube_of_token(g, n);
+            const uint32_t *mr = sel_mask + ((size_t)n * g.Hq + a) * g.words;
+            uint32_t sel = 0;
 #pragma unroll 4
-        for (int w = 0; 32 * w < i; ++w) sel += __popc(mr[w]);
-        const int kv = (a / g.G) % PAIRS_MAX_KV_HEADS;
-        atomicAdd(&acc[0][kv], sel);
-        atomicAdd(&acc[1][kv], (uint32_t)i);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        static_assert((unsigned long long)DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES * 1000 < (1ull << 32), "permille in 32 bits");
-        uint32_t sel = 0, cand = 0, least = 1000, most = 0;
-        for (int kv = 0; kv < min(g.Hkv, PAIRS_MAX_KV_HEADS); ++kv) {
-            sel += acc[0][kv];
-            cand += acc[1][kv];
-            if (acc[1][kv] == 0u) continue;
-            const uint32_t share = acc[0][kv] * 1000u / acc[1][kv];
-            least = min(least, share);
-            most = max(most, share);
+            for (int w = 0; 32 * w < i; ++w) sel += __popc(mr[w]);
+            const int kv = (a / g.G) % PAIRS_MAX_KV_HEADS;
+            atomicAdd(&acc[0][kv], sel);
+            atomicAdd(&acc[1][kv], (uint32_t)i);
         }
-        flags[FLAG_MODE] = other_permille >= 0 && sel * 1000u <= cand * (uint32_t)other_permille ? 1 : 2;
-        flags[FLAG_ESTIMATE] = (int)(together ? most : least);
-        flags[FLAG_ACTIVE] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            static_assert((unsigned long long)DENSITY_MAX_ROWS * ADASPARK_MAX_CUBES * 1000 < (1ull << 32), "permille in 32 bits");
+            uint32_t sel = 0, cand = 0, least = 1000, most = 0;
+            for (int kv = 0; kv < min(g.Hkv, PAIRS_MAX_KV_HEADS); ++kv) {
+                sel += acc[0][kv];
+                cand += acc[1][kv];
+                if (acc[1][kv] == 0u) continue;
+                const uint32_t share = acc[0][kv] * 1000u / acc[1][kv];
+                least = min(least, share);
+                most = max(most, share);
+            }
+            flags[FLAG_MODE] = other_permille >= 0 && sel * 1000u <= cand * (uint32_t)other_permille ? 1 : 2;
+            flags[FLAG_ESTIMATE] = (int)(together ? most : least);
+        }
+        if (kv_modes)
+            for (int kv = threadIdx.x; kv < g.Hkv; kv += DENSITY_THREADS)
+                flags[FLAG_SHARE + kv] = acc[1][kv] > 0u ? (int)(acc[0][kv] * 1000u / acc[1][kv]) : 0;
+        return;
     }
+    for (int x = threadIdx.x; x < counter_words; x += DENSITY_THREADS) counters[x] = 0u;
+    if (threadIdx.x == 0) flags[FLAG_ACTIVE] = 0;
+    if (kv_modes)
+        for (int kv = threadIdx.x; kv < g.Hkv; kv += DENSITY_THREADS) flags[FLAG_KV + kv] = 0;
     // What the masked walk cannot leave out: the share of the cubes before a block of its rows that some row of the block selected
     // or is in, over DENSITY_GROUPS sampled (block, KV head) pairs, one per wavefront, all at once.
-    {
-        static_assert(DENSITY_THREADS / 64 == DENSITY_GROUPS, "one sampled block per wavefront");
-        __shared__ uint32_t uni[DENSITY_GROUPS][DENSITY_UNION_WORDS];
-        __shared__ uint32_t ucount[2];  // cubes in the unions, cubes before the blocks
-        if (threadIdx.x < 2) ucount[threadIdx.x] = 0u;
-        const int k = threadIdx.x >> 6, t = threadIdx.x & 63;
-        const bool measured = g.causal != 0;
-        // late blocks weigh most, as in the walk, and the blocks of a whole cube (of its query heads) take turns
-        const int nrows = g.S * g.G, nblk = (nrows - 1) / Walk<64>::MMAX + 1;
-        const int blk = min((int)((long long)k * nblk / DENSITY_GROUPS) + k % walk_group(g), nblk - 1), kv = k % g.Hkv;
-        const int row1 = nrows - blk * Walk<64>::MMAX, row0 = max(0, row1 - Walk<64>::MMAX);
-        // every second row, from the last one: each is a cache line of its own, and one CU fetches them all
-        RowAt at[2];
+    static_assert(DENSITY_THREADS / 64 == DENSITY_GROUPS, "one sampled block per wavefront");
+    __shared__ uint32_t uni[DENSITY_GROUPS][DENSITY_UNION_WORDS];
+    __shared__ uint32_t ucount[2];  // cubes in the unions, cubes before the blocks
+    if (threadIdx.x < 2) ucount[threadIdx.x] = 0u;
+    const int k = threadIdx.x >> 6, t = threadIdx.x & 63;
+    const bool measured = g.causal != 0;
+    // late blocks weigh most, as in the walk, and the blocks of a whole cube (of its query heads) take turns
+    const int nrows = g.S * g.G, nblk = (nrows - 1) / Walk<64>::MMAX + 1;
+    const int blk = min((int)((long long)k * nblk / DENSITY_GROUPS) + k % walk_group(g), nblk - 1), kv = k % g.Hkv;
+    const int row1 = nrows - blk * Walk<64>::MMAX, row0 = max(0, row1 - Walk<64>::MMAX);
+    // every second row, from the last one: each is a cache line of its own, and one CU fetches them all
+    RowAt at[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) at[q] = row_at(g, kv, max(row1 - 1 - 2 * (64 * q + t), row0));
-        const int i = __builtin_amdgcn_readfirstlane(at[0].cube), i_first = __builtin_amdgcn_readlane(at[1].cube, 63);
-        const int wlim = (i + 31) >> 5;
-        if (measured)
-            for (int w = t; w < wlim; w += 64) uni[k][w] = 0u;
-        __syncthreads();
-        if (measured) {
-            const uint32_t *mr[2];
+    for (int q = 0; q < 2; ++q) at[q] = row_at(g, kv, max(row1 - 1 - 2 * (64 * q + t), row0));
+    const int i = __builtin_amdgcn_readfirstlane(at[0].cube), i_first = __builtin_amdgcn_readlane(at[1].cube, 63);
+    const int wlim = (i + 31) >> 5;
+    if (measured)
+        for (int w = t; w < wlim; w += 64) uni[k][w] = 0u;
+    __syncthreads();
+    if (measured) {
+        const uint32_t *mr[2];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) mr[q] = sel_mask + (size_t)at[q].id * g.words;
-            for (int w0 = 0; w0 < wlim; w0 += 8) {  // 2 rows x 8 words in flight per lane, then combined
-                uint32_t m[2][8];
+        for (int q = 0; q < 2; ++q) mr[q] = sel_mask + (size_t)at[q].id * g.words;
+        for (int w0 = 0; w0 < wlim; w0 += 8) {  // 2 rows x 8 words in flight per lane, then combined
+            uint32_t m[2][8];
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) m[q][u] = w0 + u < wlim ? mr[q][w0 + u] : 0u;
+                for (int u = 0; u < 8; ++u) m[q][u] = w0 + u < wlim ? mr[q][w0 + u] : 0u;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    uint32_t x = m[0][u] | m[1][u];
-                    for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
-                    if (t == 0 && x) uni[k][w0 + u] |= x;  // the wavefront owns this row of `uni`
-                }
+            for (int u = 0; u < 8; ++u) {
+                uint32_t x = m[0][u] | m[1][u];
+                for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
+                if (t == 0 && x) uni[k][w0 + u] |= x;  // the wavefront owns this row of `uni`
             }
         }
-        __syncthreads();
-        if (measured) {
-            uint32_t n = 0;
-            for (int w = t; w < wlim; w += 64) {
-                const uint32_t own = w < (i_first >> 5) ? 0u : w > (i_first >> 5) ? ~0u : ~0u << (i_first & 31);
-                n += __popc((uni[k][w] | own) & (w == (i >> 5) ? (1u << (i & 31)) - 1u : ~0u));
-            }
-            if (n) atomicAdd(&ucount[0], n);
-            if (t == 0) atomicAdd(&ucount[1], (uint32_t)i);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0)
-            flags[FLAG_UNION] = ucount[1] > 0u ? max(1, (int)(ucount[0] * 1000u / ucount[1])) : 1000;
     }
-    if (kv_modes)
-        for (int kv = threadIdx.x; kv < g.Hkv; kv += DENSITY_THREADS) {
-            flags[FLAG_KV + kv] = 0;
-            flags[FLAG_SHARE + kv] = acc[1][kv] > 0u ? (int)(acc[0][kv] * 1000u / acc[1][kv]) : 0;
+    __syncthreads();
+    if (measured) {
+        uint32_t n = 0;
+        for (int w = t; w < wlim; w += 64) {
+            const uint32_t own = w < (i_first >> 5) ? 0u : w > (i_first >> 5) ? ~0u : ~0u << (i_first & 31);
+            n += __popc((uni[k][w] | own) & (w == (i >> 5) ? (1u << (i & 31)) - 1u : ~0u));
         }
+        if (n) atomicAdd(&ucount[0], n);
+        if (t == 0) atomicAdd(&ucount[1], (uint32_t)i);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        flags[FLAG_UNION] = ucount[1] > 0u ? max(1, (int)(ucount[0] * 1000u / ucount[1])) : 1000;
 }
 
 template <int D, bool MASKED>
@@ -737,11 +740,15 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
     // cubes of 256, 63, 34 and 18 % selected: 474, 319, 220; 439, 441, 445; 489, 320, 221.  Never one of the latter two: a call of
     // these that selects much is 8 % faster, one that selects little 50 % slower.)
     const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g);
-    const int other_permille = !together ? MASKED_ABOVE_PERMILLE : kv_modes ? -1 : split_below_permille(g);
+    // Heads by themselves: the compacting kernel for a selection of up to MASKED_ABOVE_PERMILLE -- which the key-stationary kernel has
+    // already, if there is room for its records (twice as many, and the rows' own: the share is an estimate).
+    const bool compact = !together && !(kv_modes && pairs_capacity(g, scratch, scratch_bytes) >=
+                                                        (long long)(candidate_pairs(g) / 1000 * (2 * MASKED_ABOVE_PERMILLE)) + (long long)g.S * g.Hq);
+    const int other_permille = together ? (kv_modes ? -1 : split_below_permille(g)) : compact ? MASKED_ABOVE_PERMILLE : -1;
     if (together && !kv_modes && other_permille < 0) return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     int counter_words = 0;
     uint32_t *counters = kv_modes ? pairs_counters(g, scratch, scratch_bytes, counter_words) : nullptr;
-    hipLaunchKernelGGL(sel_density_kernel, dim3(1), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes, together,
+    hipLaunchKernelGGL(sel_density_kernel, dim3(2), dim3(DENSITY_THREADS), 0, st, g, sel_mask, flags, kv_modes, together,
                        other_permille, counters, counter_words);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -750,8 +757,8 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
                               pairs_below_permille(g), O, lse, st);
         if (e != hipSuccess) return e;
     }
-    if (!together) e = launch_attn_compact(g, Q, packed, sel_mask, flags, 1, kv_modes, O, lse, st);
-    else if (!kv_modes) e = launch_attn_split(g, Q, packed, sel_mask, flags, 1, O, lse, st);
+    if (compact) e = launch_attn_compact(g, Q, packed, sel_mask, flags, 1, kv_modes, O, lse, st);
+    else if (together && !kv_modes) e = launch_attn_split(g, Q, packed, sel_mask, flags, 1, O, lse, st);
     if (e != hipSuccess) return e;
     return launch_walk<D, true>(g, Q, packed, sel_mask, flags, 2, kv_modes, O, lse, st);
 }

@@ -251,6 +251,7 @@ size_t pairs_scratch_bytes(const Geom &g, long long max_selected);
 int *pairs_flags(const Geom &g, void *scratch, size_t scratch_bytes);
 // the counters inside the scratch memory that have to be zero when launch_attn_pairs is called (words of them)
 uint32_t *pairs_counters(const Geom &g, void *scratch, size_t scratch_bytes, int &words);
+long long pairs_capacity(const Geom &g, void *scratch, size_t scratch_bytes);  // records that fit
 hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packed, const uint32_t *sel_mask, void *scratch,
                              size_t scratch_bytes, int force, int together, int pairs_below_permille, uint16_t *O,
                              float *lse, hipStream_t st);
