@@ -167,12 +167,6 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ uint2 pack_bf16(f32x4 x)
-{
-    const bf16x2 a = {(__bf16)x[0], (__bf16)x[1]}, b = {(__bf16)x[2], (__bf16)x[3]};
-    return make_uint2(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b));
-}
-
 __global__ __launch_bounds__(256) void bwd_copy_rows_kernel(long long pieces, const uint4 *__restrict__ Q,
                                                             const uint4 *__restrict__ dO, uint4 *__restrict__ Qc,
                                                             uint4 *__restrict__ dOc)

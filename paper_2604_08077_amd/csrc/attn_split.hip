@@ -292,9 +292,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(Geom g, const uint16_t 
         if (rho > last) continue;
         const float inv = 1.0f / L;
         const size_t rid = s == 0 ? rowid[0] : rowid[1];
-        const uint32_t w0 = (uint32_t)float_to_bf16_bits(o[0] * inv) | ((uint32_t)float_to_bf16_bits(o[1] * inv) << 16);
-        const uint32_t w1 = (uint32_t)float_to_bf16_bits(o[2] * inv) | ((uint32_t)float_to_bf16_bits(o[3] * inv) << 16);
-        *reinterpret_cast<uint2 *>(O + rid * D + 16 * e + 4 * q4) = make_uint2(w0, w1);
+        *reinterpret_cast<uint2 *>(O + rid * D + 16 * e + 4 * q4) = pack_bf16(o * inv);
         if (lse != nullptr && e == 0 && q4 == 0) lse[rid] = (M + log2f(L)) * 0.69314718055994530942f;
     }
 }

@@ -54,6 +54,12 @@ __device__ __forceinline__ float vmax3(float a, float b, float c)
     return r;
 }
 
+__device__ __forceinline__ uint2 pack_bf16(f32x4 x)
+{
+    const bf16x2 a = {(__bf16)x[0], (__bf16)x[1]}, b = {(__bf16)x[2], (__bf16)x[3]};
+    return make_uint2(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b));
+}
+
 // A-operand of all ones: (ones).P^T has the column sums of P^T, i.e. every query row's sum of probabilities, in each
 // of its 16 rows.
 __device__ __forceinline__ bf16x8 ones_operand()

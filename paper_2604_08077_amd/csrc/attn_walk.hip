@@ -100,21 +100,35 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     const int nrows = g.S * g.G, nblk = (nrows - 1) / MMAX + 1, per_group = walk_group(g);
     const int groups = (nblk + per_group - 1) / per_group;  // of one KV head
     const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int grp = (seq / per_group) * 8 + xcd;
-    if (grp >= groups * g.Hkv) return;
-    // A KV head normally stays on the same XCDs (grp % 8 = xcd: its K/V tiles are the ones that XCD's L2 holds).
-    // When some heads are handed to the key-stationary kernel, the head is rotated with the group instead, so that
-    // the heads that remain still spread over all XCDs.
-    const int rot = (kv_modes && mode_flag[FLAG_ACTIVE]) ? grp / g.Hkv : 0;
-    const int kv = (grp % g.Hkv + rot) % g.Hkv;
-    if (kv_modes && mode_flag[FLAG_KV + kv] == 3) return;  // the key-stationary kernel has this head's rows
-    // Late rows, the long walks, first.  With fewer than eight KV heads a round of eight groups holds several of a head, one
-    // behind the other on the same XCDs; every second round deals them out in the opposite order, or the XCDs that
+    // The KV heads whose rows are this kernel's: all, or those that the key-stationary kernel did not get.
+    int heads = g.Hkv;
+    unsigned long long mine = ~0ull;  // (of up to PAIRS_MAX_KV_HEADS, where some are not)
+    if (kv_modes && mode_flag[FLAG_ACTIVE]) {
+        mine = __ballot((int)(threadIdx.x & 63) < g.Hkv && mode_flag[FLAG_KV + min((int)(threadIdx.x & 63), g.Hkv - 1)] != 3);
+        heads = __popcll(mine);
+        if (heads == 0) return;
+    }
+    // Late rows, the long walks, first, and a round of eight groups (one per XCD) behind the other.  A head normally stays on the same
+    // XCDs (group % 8 = xcd: its K/V tiles are the ones that XCD's L2 holds).  With fewer than eight heads a round holds several groups
+    // of a head, one behind the other; every second round deals them out in the opposite order, or the XCDs that
     // always got the later group would finish last (a forward pass over 16,384 tokens, 28/4 heads of 128: 1.650 ms, without this
-    // 1.667; over 8,736 in 36 cubes 0.591, 0.596; runs of one side differ by 0.2 %).
-    int pos = grp / g.Hkv;
-    const int share = 8 % g.Hkv == 0 ? 8 / g.Hkv : 1, round = pos / share;
-    if ((round & 1) && (round + 1) * share <= groups) pos = (2 * round + 1) * share - 1 - pos;
+    // 1.667; over 8,736 in 36 cubes 0.591, 0.596; runs of one side differ by 0.2 %.  30,000 tokens of 32/8 heads, four of them this
+    // kernel's: 3.16 ms with the heads rotated over the XCDs instead, which ended between 2.89 and 3.16.)  Where neither is a
+    // multiple of the other, the XCDs themselves take turns.
+    const int round = seq / per_group;
+    int grp = round * 8 + xcd;
+    if (8 % heads != 0 && heads % 8 != 0 && (round & 1)) grp = round * 8 + 7 - xcd;
+    if (grp >= groups * heads) return;
+    int kv = grp % heads;
+    int pos = grp / heads;
+    const int share = 8 % heads == 0 ? 8 / heads : 1, turn = pos / share;
+    if (8 % heads == 0 && (turn & 1) && (turn + 1) * share <= groups) pos = (2 * turn + 1) * share - 1 - pos;
+    if (heads < g.Hkv) {  // the kv-th of the heads that remain
+        const int lane = threadIdx.x & 63;
+        const bool it = ((mine >> lane) & 1ull) && __popcll(mine & ((1ull << lane) - 1ull)) == kv;
+        kv = __ffsll(__ballot(it)) - 1;
+    }
+    kv = __builtin_amdgcn_readfirstlane(kv);
     const int blk = pos * per_group + seq % per_group;
     if (blk >= nblk) return;
     const int row1 = nrows - blk * MMAX, row0 = max(0, row1 - MMAX);
@@ -382,11 +396,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
             uint16_t *orow = O + (size_t)rid * D + 4 * q4;
 #pragma unroll
             for (int e = 0; e < DT; ++e) {
-                const uint32_t w0 = (uint32_t)float_to_bf16_bits(oacc[s][e][0] * inv) |
-                                    ((uint32_t)float_to_bf16_bits(oacc[s][e][1] * inv) << 16);
-                const uint32_t w1 = (uint32_t)float_to_bf16_bits(oacc[s][e][2] * inv) |
-                                    ((uint32_t)float_to_bf16_bits(oacc[s][e][3] * inv) << 16);
-                *reinterpret_cast<uint2 *>(orow + 16 * e) = make_uint2(w0, w1);
+                *reinterpret_cast<uint2 *>(orow + 16 * e) = pack_bf16(oacc[s][e] * inv);
             }
             if (lse != nullptr && q4 == 0) lse[rid] = (m_run[s] + log2f(l_run[s][0])) * 0.69314718055994530942f;
         }

@@ -120,3 +120,21 @@ def test_choice_for_few_rows(B, oracle, name, grid, cube, hq, hkv, scale, sel, r
         print(f"[{name}] expected {expected}: from the forced kernels' results {off}", flush=True)
         for k, x in off.items():
             assert (x < 1e-4) == (k == expected), (k, expected)
+
+
+# Some KV heads select next to nothing and go to the key-stationary kernel: the masked walk's workgroups are dealt out over the heads that
+# remain, one, three (eight XCDs are no multiple of them) and five of six, and seven of eight.
+@pytest.mark.parametrize("heads,flat", [(6, 1), (6, 3), (6, 5), (8, 7)])
+def test_walk_of_the_heads_that_remain(B, heads, flat):  # noqa: F811
+    w = synth.Workload(f"heads{heads}_flat{flat}", 62, 560 // heads, 16, 16, 4, 8, 8, heads, heads, 64, (0.9,), (0.0,) * flat + (4.0,) * (heads - flat))
+    sh = B.Shape.of(w)
+    Q, K, V = (x.cuda() for x in synth.generate(w))
+    mask, count = B.cube_select(sh, Q, B.cube_pool(sh, K), 0.9)[:2]
+    packed = B.kv_pack(sh, K, V, workspace=B.alloc_workspace(sh, B.CALL_SPARSE_ATTN, pairs_capacity=int(count.sum())))
+    want = B.sparse_attn_packed(sh, Q, packed, mask, kernel=B.SPARSE_MASKED).float()
+    got = B.sparse_attn_packed(sh, Q, packed, mask, O=torch.full_like(Q, float("nan"))).float()
+    torch.cuda.synchronize()
+    off = [float((got[:, h] - want[:, h]).norm() / want[:, h].norm()) for h in range(heads)]
+    print(f"[{w.name}] heads' results from the masked walk's: {off}", flush=True)
+    # (the same kernel: bit for bit; the other one rounds elsewhere, 2e-3 of the result)
+    assert all(x == 0.0 for x in off[:flat]) and all(0.0 < x < 1e-2 for x in off[flat:])
