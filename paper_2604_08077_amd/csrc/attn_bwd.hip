@@ -878,6 +878,9 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_split_kernel(Geom g, 
 // 128, Top-p 0.9 (61 % selected): 31.0 ms and 0.45 ms of sums, 1.23 PFLOP/s over selected pairs; two kernels that
 // walked every row with the selection as a mask took 40.7 + 29.1 ms (and the transposed copies of Q and dO they
 // streamed 0.4 ms).  At 16,384 tokens, where cube 0's walk used to outlast everything: 2.2 + 0.1 against 8.5 ms.
+// On short sequences a workgroup's chain of memory latencies counts: the selection words and row ids are asked for before the keys, and the
+// own cube's rows lie behind the last list's, one stream of tiles for both.  A backward pass over 1,080 tokens of 6/2 heads of 128: 56.5 us,
+// with each in its turn 59.4.
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int BWD_LIST_WORDS = 64;
 
@@ -972,6 +975,14 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n16 = lane & 15, q4 = lane >> 4;
+
+    // the rows' selection words and, of the wavefront's first one, their ids, for the first list: asked for before the keys
+    const int i0 = max(c * cut.span, j + 1), i1 = min(g.N, (c + 1) * cut.span);
+    const int nwords = max(0, i1 - i0) * tpcr;
+    const unsigned long long *cm = colmask + (((size_t)kv * g.N + j) * g.N + i0) * tpcr;
+    const uint32_t *tab = rowtab + (size_t)i0 * tpcr * 64;
+    unsigned long long bits = lane < nwords ? cm[lane] : 0ull;
+    uint32_t id = wave < nwords ? tab[wave * 64 + lane] : 0u;
 
     // the wavefront's keys (B operands)
     const int key0 = kb * BWD_ROWS + (SHARED ? wave & 3 : wave) * 32;
@@ -1080,13 +1091,14 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (OWN) {  // causal edge: a row attends keys up to its own rank
+                if (OWN) {  // causal edge: a row attends keys up to its own rank, row / G
+                    const int row = r0 + (SHARED ? wave >> 2 : 0) * 32 + 16 * (2 * H + x) + 4 * q4;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int rank = (r0 + (SHARED ? wave >> 2 : 0) * 32 + 16 * (2 * H + x) + 4 * q4 + v) / g.G;
+                    for (int s = 0; s < NS; ++s) {
+                        const int reach = (key0 + 16 * s + n16) * g.G;  // the first row that attends the key
 #pragma unroll
-                        for (int s = 0; s < NS; ++s)
-                            if (key0 + 16 * s + n16 > rank) sa[s][v] = -INFINITY;
+                        for (int v = 0; v < 4; ++v)
+                            if (row + v < reach) sa[s][v] = -INFINITY;
                     }
                 }
 #pragma unroll
@@ -1113,67 +1125,65 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dkv_kernel(Geom g, const
             }
         }
     };
-    // n listed rows through the tiles; OWN: they are rows f .. of cube j itself.
-    auto run_list = [&](int n, auto own_tag, int f) __attribute__((always_inline)) {
-        constexpr bool OWN = decltype(own_tag)::value;
-        const int nt = (n + 63) >> 6;
+    // The list through the tiles: n rows, then, from a tile of their own on, m of cube j itself, its rows f ...
+    auto run_list = [&](int n, int m, int f) __attribute__((always_inline)) {
+        const int nt1 = (n + 63) >> 6, nt = nt1 + ((m + 63) >> 6);
         if (nt == 0) return;
-        issue(0, 0, n);
-        if (nt > 1) issue(1, 64, n);
-        int stage = 0;
-        for (int t = 0; t < nt; ++t) {
+        auto issue_tile = [&](int stage, int t) __attribute__((always_inline)) { issue(stage, 64 * t, t < nt1 ? n : 64 * nt1 + m); };
+        issue_tile(0, 0);
+        if (nt > 1) issue_tile(1, 1);
+        int stage = 0, t = 0;
+        auto tile = [&](auto own_tag) __attribute__((always_inline)) {
+            constexpr bool OWN = decltype(own_tag)::value;
             open_tile(t + 1 < nt);
             const int s2 = stage == 0 ? 2 : stage - 1;  // (stage + 2) % 3: read last at tile t - 1
-            if (t + 2 < nt) issue(s2, 64 * (t + 2), n);
+            if (t + 2 < nt) issue_tile(s2, t + 2);
+            const int r0 = f + 64 * (t - nt1);
             // (own cube: no row of the tile reaches the wavefront's keys if the last one does not)
-            if (busy && (!OWN || (f + 64 * t + 63) / g.G >= key0)) tile_work(stage, own_tag, f + 64 * t);
+            if (busy && (!OWN || (r0 + 63) / g.G >= key0)) tile_work(stage, own_tag, r0);
             stage = stage == 2 ? 0 : stage + 1;
-        }
+        };
+        for (; t < nt1; ++t) tile(std::false_type{});
+        for (; t < nt; ++t) tile(std::true_type{});
     };
 
-    // ---- the rows: 64-row words w of the range's row cubes, BWD_LIST_WORDS at a time
-    const int i0 = max(c * cut.span, j + 1), i1 = min(g.N, (c + 1) * cut.span);
-    const int nwords = max(0, i1 - i0) * tpcr;
-    const unsigned long long *cm = colmask + (((size_t)kv * g.N + j) * g.N + i0) * tpcr;
-    const uint32_t *tab = rowtab + (size_t)i0 * tpcr * 64;
-    for (int w0 = 0; w0 < nwords; w0 += BWD_LIST_WORDS) {
+    // ---- the rows: 64-row words w of the range's row cubes, BWD_LIST_WORDS at a time; behind the last of them cube j's own rows, in
+    // rank order, if the range has it (ranks below the block's first key attend none of its keys)
+    const int own = c == j / cut.span ? size_j * g.G : 0;
+    int f = kb * BWD_ROWS * g.G / 64 * 64;
+    for (int w0 = 0; w0 < nwords || f < own; w0 += BWD_LIST_WORDS) {
         __syncthreads();  // the list before is done with
         const int l = fresh_lane();
-        if (wave == 0) {
-            const unsigned long long bits = w0 + l < nwords ? cm[w0 + l] : 0ull;
-            const int n = __popcll(bits);
-            int incl = n;
+        int n = 0;
+        if (w0 < nwords) {
+            if (wave == 0) {
+                const int mine = __popcll(bits);
+                int incl = mine;
 #pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int up = __shfl_up(incl, d, 64);
-                if (l >= d) incl += up;
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int up = __shfl_up(incl, d, 64);
+                    if (l >= d) incl += up;
+                }
+                words[l] = bits;
+                base[l] = incl - mine;
+                if (l == 63) base[BWD_LIST_WORDS] = incl;
             }
-            words[l] = bits;
-            base[l] = incl - n;
-            if (l == 63) base[BWD_LIST_WORDS] = incl;
-        }
-        __syncthreads();
-        const int n = __builtin_amdgcn_readfirstlane(base[BWD_LIST_WORDS]);
-        for (int x = wave; x < min(BWD_LIST_WORDS, nwords - w0); x += BWD_THREADS / 64) {
-            const unsigned long long bits = words[x];
-            if ((bits >> l) & 1ull)
-                rows[base[x] + __popcll(bits & ((1ull << l) - 1ull))] = tab[(size_t)(w0 + x) * 64 + l] + (uint32_t)(kv * g.G);
-        }
-        __syncthreads();
-        run_list(n, std::integral_constant<bool, false>{}, 0);
-    }
-    // ---- cube j's own rows, in rank order
-    if (c == j / cut.span) {
-        const int own = size_j * g.G;
-        // (ranks below the block's first key attend none of its keys)
-        for (int f = kb * BWD_ROWS * g.G / 64 * 64; f < own; f += 64 * BWD_LIST_WORDS) {
-            const int n = min(own - f, 64 * BWD_LIST_WORDS);
             __syncthreads();
-            for (int x = wave * 64 + fresh_lane(); x < n; x += BWD_THREADS)
-                rows[x] = rowtab[(size_t)j * tpcr * 64 + f + x] + (uint32_t)(kv * g.G);
-            __syncthreads();
-            run_list(n, std::integral_constant<bool, true>{}, f);
+            n = __builtin_amdgcn_readfirstlane(base[BWD_LIST_WORDS]);
+            for (int x = wave; x < min(BWD_LIST_WORDS, nwords - w0); x += BWD_THREADS / 64) {
+                const unsigned long long word = words[x];
+                if (x != wave) id = tab[(size_t)(w0 + x) * 64 + l];
+                if ((word >> l) & 1ull) rows[base[x] + __popcll(word & ((1ull << l) - 1ull))] = id + (uint32_t)(kv * g.G);
+            }
         }
+        const int at = (n + 63) & ~63, m = w0 + BWD_LIST_WORDS >= nwords ? max(0, min(own - f, 64 * BWD_LIST_WORDS - at)) : 0;
+        for (int x = wave * 64 + l; x < m; x += BWD_THREADS) rows[at + x] = rowtab[(size_t)j * tpcr * 64 + f + x] + (uint32_t)(kv * g.G);
+        __syncthreads();
+        run_list(n, m, f);
+        f += m;
+        const int next = w0 + BWD_LIST_WORDS, lane1 = fresh_lane();  // (the next list's, as above)
+        bits = next + lane1 < nwords ? cm[next + lane1] : 0ull;
+        id = next + wave < nwords ? tab[(size_t)(next + wave) * 64 + lane1] : 0u;
     }
     if (SHARED) {
         static_assert(4 * NS * DT * 1024 <= C::OFF_ROWS, "one sum of four wavefronts fits the tiles' place");
