@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(Geom g, BwdPrep p)
         const CubeBox box = cube_box(g, i);
         const int r = 64 * t + lane;
         const bool valid = r < box.size() * g.G;
-        const size_t rowid = valid ? (size_t)token_of(g, box, r / g.G) * g.Hq + kv * g.G + r % g.G : 0;
+        const size_t rowid = valid ? (size_t)token_in_cube(g, box, r / g.G) * g.Hq + kv * g.G + r % g.G : 0;
         if (kv == 0) p.rowtab[((size_t)i * p.tpcr + t) * 64 + lane] = (uint32_t)rowid;
         for (int jw = 0; 32 * jw < i; ++jw) {
             const uint32_t word = valid ? (p.sel_mask != nullptr ? p.sel_mask[rowid * g.words + jw] : ~0u) : 0u;
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(Geom g, BwdPrep p)
             const int k = y / CPR, col = y % CPR, rank = KEY_TILE * t + k;
             uint4 kk = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
             if (rank < size) {
-                const size_t src = ((size_t)token_of(g, box, rank) * g.Hkv + kv) * D + col * 8;
+                const size_t src = ((size_t)token_in_cube(g, box, rank) * g.Hkv + kv) * D + col * 8;
                 kk = *reinterpret_cast<const uint4 *>(p.K + src);
                 vv = *reinterpret_cast<const uint4 *>(p.V + src);
             }

@@ -92,6 +92,24 @@ __host__ __device__ inline int token_of(const Geom &g, const CubeBox &b, int ran
     return g.Sp + ((b.t0 + lt) * g.H + (b.h0 + lh)) * g.W + (b.w0 + lw);
 }
 
+// The same for kernels that look up many tokens of a cube and do little else: divisions in 24 bits, 8 instructions instead of 20 to 30, where
+// the cube's nominal size allows it, and two of them.  (The mean keys of 16,384 tokens in 64 cubes: 11.4 us, so and in parts of a row 6.9.
+// Not in the masked walk, which is fastest as its registers happen to fall with the plain form: 1 % at 65,536 tokens.)
+__host__ __device__ inline int token_in_cube(const Geom &g, const CubeBox &b, int rank)
+{
+    constexpr int SMALL = 1 << 22;
+    if (b.t0 < 0) return b.w0 + rank;
+    int row, lt;
+    if (g.Cmax < SMALL) {  // (the compiler is told the operands' bits)
+        row = (int)(((unsigned)rank & (SMALL - 1u)) / ((unsigned)b.ew & (SMALL - 1u)));
+        lt = (int)(((unsigned)row & (SMALL - 1u)) / ((unsigned)b.eh & (SMALL - 1u)));
+    } else {
+        row = rank / b.ew;
+        lt = row / b.eh;
+    }
+    return g.Sp + ((b.t0 + lt) * g.H + (b.h0 + row - lt * b.eh)) * g.W + (b.w0 + rank - row * b.ew);
+}
+
 // Cube of token n (rank not needed by the callers of this one).
 __host__ __device__ inline int cube_of_token(const Geom &g, int n)
 {

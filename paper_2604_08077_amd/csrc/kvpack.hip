@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(Geom g, const uint16_t *__
         const int rank = KEY_TILE * t + k;
         uint4 kk = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
         if (rank < size) {
-            const int n = token_of(g, box, rank);
+            const int n = token_in_cube(g, box, rank);
             const size_t src = ((size_t)n * g.Hkv + kv) * D + col * 8;
             kk = *reinterpret_cast<const uint4 *>(K + src);
             vv = *reinterpret_cast<const uint4 *>(V + src);

@@ -1,8 +1,8 @@
 // Cube mean keys (Eq. 1: k-bar_j = Mean(k in K_j)).
 //
-// One workgroup per cube.  A token's KV heads are contiguous in memory
-// (Hkv*D bf16), so the workgroup reads whole token rows: thread = (token slot,
-// 16-byte chunk of the row); slots stride over the cube's tokens, the partial
+// A token's KV heads are contiguous in memory (Hkv*D bf16); a workgroup has one cube and
+// all of a token's row, or, with fewer cubes than CUs, a part of it of 128 bytes or more: thread = (token slot,
+// 16-byte chunk); slots stride over the cube's tokens, the partial
 // sums of the slots are combined through LDS in a fixed order (the result does
 // not depend on scheduling).  HBM-bound: K is read exactly once.
 #include "geom.h"
@@ -19,10 +19,11 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
     const CubeBox box = cube_box(g, c);
     const int size = box.size();
     const int row_elems = g.Hkv * g.D;  // elements per token row
-    const int chunks = row_elems / 8;   // 16-byte chunks per row
+    const int chunks = row_elems / 8 / gridDim.y;  // 16-byte chunks of a row that are this workgroup's
+    const int begin = chunks * blockIdx.y, end = begin + chunks;
 
-    for (int chunk0 = 0; chunk0 < chunks; chunk0 += POOL_THREADS) {
-        const int lanes = min(chunks - chunk0, POOL_THREADS);  // chunks handled in this sweep
+    for (int chunk0 = begin; chunk0 < end; chunk0 += POOL_THREADS) {
+        const int lanes = min(end - chunk0, POOL_THREADS);  // chunks handled in this sweep
         const int slots = POOL_THREADS / lanes;                // token slots working in parallel
         const int slot = threadIdx.x / lanes, col = threadIdx.x % lanes;
         float acc[8];
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
                     const int r = r0 + u * slots;
                     v[u] = make_uint4(0, 0, 0, 0);
                     if (r < size) {
-                        const int n = token_of(g, box, r);
+                        const int n = token_in_cube(g, box, r);
                         v[u] = *reinterpret_cast<const uint4 *>(K + (size_t)n * row_elems + (size_t)(chunk0 + col) * 8);
                     }
                 }
@@ -57,16 +58,22 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
 #pragma unroll
         for (int e = 0; e < 8; ++e) part[threadIdx.x * 8 + e] = acc[e];
         __syncthreads();
-        if (threadIdx.x < lanes) {
-            float sum[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum[e] = 0.f;
-            for (int s2 = 0; s2 < slots; ++s2)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sum[e] += part[(s2 * lanes + threadIdx.x) * 8 + e];
-            float *dst = kbar + (size_t)c * row_elems + (size_t)(chunk0 + threadIdx.x) * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dst[e] = sum[e] / (float)size;
+        // the slots' sums: `groups` threads an element, each over every groups-th slot, then these
+        const int elems = lanes * 8, groups = max(1, POOL_THREADS / elems);
+        const int x = threadIdx.x % elems, group = threadIdx.x / elems;
+        float sum = 0.f;
+        if (groups > 1) {
+            if (group < groups)
+                for (int s2 = group; s2 < slots; s2 += groups) sum += part[s2 * elems + x];
+            __syncthreads();
+            if (group < groups) part[threadIdx.x] = sum;
+            __syncthreads();
+        }
+        const int left = groups > 1 ? groups : slots;
+        for (int y = threadIdx.x; y < elems; y += POOL_THREADS) {
+            float total = 0.f;
+            for (int s2 = 0; s2 < left; ++s2) total += part[s2 * elems + y];
+            kbar[(size_t)c * row_elems + (size_t)chunk0 * 8 + y] = total / (float)size;
         }
         __syncthreads();
     }
@@ -74,7 +81,11 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
 
 hipError_t launch_cube_pool(const Geom &g, const uint16_t *K, float *kbar, hipStream_t st)
 {
-    hipLaunchKernelGGL(cube_pool_kernel, dim3(g.N), dim3(POOL_THREADS), 0, st, g, K, kbar);
+    // Parts of a row while the workgroups do not fill the CUs.
+    const int chunks = g.Hkv * g.D / 8;
+    int parts = 1;
+    while (g.N * parts < 256 && chunks % (16 * parts) == 0) parts *= 2;
+    hipLaunchKernelGGL(cube_pool_kernel, dim3(g.N, parts), dim3(POOL_THREADS), 0, st, g, K, kbar);
     return hipGetLastError();
 }
 
