@@ -327,8 +327,10 @@ __device__ __forceinline__ void tn_half(const unsigned char *tt, int n16, int q4
 // KEYS = 1: a wavefront per 32 rows.  KEYS = 2: two, wavefronts w and w + 4, each with half of every tile's keys; their
 // sums are added through LDS at the end.  A tile takes a workgroup 1.5 us at head-dim 128 (its MFMAs and exponentials), and
 // with few workgroups the longest walk is the kernel's time: half as long, over twice as many workgroups (bwd_dq_waves).
+// SMALL (KEYS = 1): no cube has more than 32 tokens, every tile is worked as its first half, the other held no keys (a backward pass, us,
+// whole and half: 5,940 tokens of 28/4 heads of 128 in cubes of 32 2,160, 1,839; 6,048 of 14/2 1,124, 937).
 // ---------------------------------------------------------------------------------------------------------------
-template <int D, bool MASKED, int KEYS>
+template <int D, bool MASKED, int KEYS, bool SMALL = false>
 __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const uint16_t *__restrict__ Q,
                                                                   const uint16_t *__restrict__ dO,
                                                                   const uint16_t *__restrict__ Kn,
@@ -539,7 +541,10 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
                             ds[s][H][4 * k2 + v] = (__bf16)(p * pacc[s][k2][v]);
                         }
             };
-            if (KEYS == 1) {
+            if (SMALL) {
+                half(std::integral_constant<int, 0>{});
+                tn_half<D, NS, 0, BEHIND>(ktt, n16, q4, ds, acc, done);
+            } else if (KEYS == 1) {
                 half(std::integral_constant<int, 0>{});
                 half(std::integral_constant<int, 1>{});
                 tn_half<D, NS, 0, BEHIND>(ktt, n16, q4, ds, acc, done);
@@ -1332,13 +1337,13 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     const BwdParts &cut = w.cut;
     const dim3 grid_k(bwd_grid(g.Hkv, (int)(cut.nkb * cut.parts)));
     constexpr int lds_k = Dkv<D>::BYTES;
-    auto launch_dq = [&](auto masked, auto keys_c) -> hipError_t {
-        constexpr bool MASKED = decltype(masked)::value;
+    auto launch_dq = [&](auto masked, auto keys_c, auto small) -> hipError_t {
+        constexpr bool MASKED = decltype(masked)::value, SMALL = decltype(small)::value;
         constexpr int KEYS = decltype(keys_c)::value;
         static LdsOptIn opted_q;  // one per kernel instantiation
-        const hipError_t err = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED, KEYS>), lds_q);
+        const hipError_t err = opted_q.ensure(reinterpret_cast<const void *>(&attn_bwd_dq_kernel<D, MASKED, KEYS, SMALL>), lds_q);
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED, KEYS>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, w.Kn, w.Vn,
+        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MASKED, KEYS, SMALL>), grid_q, dim3(BWD_THREADS), lds_q, st, g, Q, dO, w.Kn, w.Vn,
                            w.Kt, w.csize, w.lse2, w.delta, sel_mask, dQ);
         return hipGetLastError();
     };
@@ -1356,10 +1361,15 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
     };
     if (waves == 8)
         e = sel_mask != nullptr ? launch_split(std::true_type{}) : launch_split(std::false_type{});
-    else if (sel_mask != nullptr)
-        e = keys == 2 ? launch_dq(std::true_type{}, two) : launch_dq(std::true_type{}, one);
-    else
-        e = keys == 2 ? launch_dq(std::false_type{}, two) : launch_dq(std::false_type{}, one);
+    else {
+        const std::true_type yes;
+        const std::false_type no;
+        auto launch_masked = [&](auto masked) -> hipError_t {
+            if (keys == 2) return launch_dq(masked, two, no);
+            return g.Cmax <= KEY_TILE / 2 ? launch_dq(masked, one, yes) : launch_dq(masked, one, no);
+        };
+        e = sel_mask != nullptr ? launch_masked(yes) : launch_masked(no);
+    }
     if (e != hipSuccess) return e;
     auto launch_dkv = [&](auto shared) -> hipError_t {
         constexpr bool SHARED = decltype(shared)::value;

@@ -215,7 +215,8 @@ constexpr float SOFTMAX_LAZY = 1.0f;
 // SOFTMAX_LAZY + SOFTMAX_HEADROOM before it has to move again; probabilities then lie below 2^-SOFTMAX_HEADROOM
 // most of the time, which the normalisation cancels.
 constexpr float SOFTMAX_HEADROOM = 8.0f;
-template <int D, int NS>
+// KG: of a tile's four groups of 16 keys those that are worked (two where no cube has more than 32 tokens).
+template <int D, int NS, int KG = 4>
 __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8 (&pf)[NS][2], f32x4 (&oacc)[NS][D / 16],
                                                     float (&m_run)[NS], f32x4 (&l_run)[NS], bool (&fresh)[NS],
                                                     const int (&lim)[NS], int key0, bool need_mask, int q4)
@@ -226,7 +227,7 @@ __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int kg = 0; kg < 4; ++kg)
+            for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int kr = kb + 32 * (kg >> 1) + 4 * (kg & 1) + v;
@@ -240,16 +241,21 @@ __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8
     for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][0][3], sacc[s][1][0]);
 #pragma unroll
     for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][1][1], sacc[s][1][2]);
+    if (KG == 4) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][1][3], sacc[s][2][0]);
+        for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][1][3], sacc[s][2][0]);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][2][1], sacc[s][2][2]);
+        for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][2][1], sacc[s][2][2]);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][2][3], sacc[s][3][0]);
+        for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][2][3], sacc[s][3][0]);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][3][1], sacc[s][3][2]);
+        for (int s = 0; s < NS; ++s) mx[s] = vmax3(mx[s], sacc[s][3][1], sacc[s][3][2]);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) mx[s] = vmax(mx[s], sacc[s][3][3]);
+        for (int s = 0; s < NS; ++s) mx[s] = vmax(mx[s], sacc[s][3][3]);
+    } else {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) mx[s] = vmax(mx[s], sacc[s][1][3]);
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) mx[s] = quad_max(mx[s]);
     bool grow[NS];
@@ -267,7 +273,7 @@ __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8
             m_run[s] += d;
             fresh[s] = fresh[s] && !grow[s];
 #pragma unroll
-            for (int kg = 0; kg < 4; ++kg)
+            for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sacc[s][kg][v] -= d;
 #pragma unroll
@@ -276,7 +282,7 @@ __device__ __forceinline__ void softmax_tile_folded(f32x4 (&sacc)[NS][4], bf16x8
         }
     }
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg)
+    for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -303,21 +309,21 @@ __device__ __forceinline__ void fill_masks_init(unsigned char *masks, int tid)
     if (tid < FILL_MASK_BYTES / 2) reinterpret_cast<uint16_t *>(masks)[tid] = tid % 8 < tid / 8 ? 0xffffu : 0u;
 }
 
-template <int NS>
+template <int NS, int KG = 4>
 __device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf16x8 (&pf)[NS][2], bool settled,
                                                   const unsigned char *fill_masks, int fill, int q4)
 {
     if (!settled) return false;
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg)
+    for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
             for (int s = 0; s < NS; ++s)
                 pf[s][kg >> 1][4 * (kg & 1) + v] = (__bf16)__builtin_amdgcn_exp2f(sacc[s][kg][v]);
-    if (fill < KEY_TILE) {
+    if (fill < 16 * KG) {
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
+        for (int sl = 0; sl < KG / 2; ++sl) {
             const u32x4 keep =
                 *reinterpret_cast<const u32x4 *>(fill_masks + 16 * min(max(fill - 32 * sl - 8 * q4, 0), 8));
 #pragma unroll
@@ -328,7 +334,7 @@ __device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
+        for (int sl = 0; sl < KG / 2; ++sl) {
             const u32x4 w = __builtin_bit_cast(u32x4, pf[s][sl]);
             big |= (w[0] | w[1]) | (w[2] | w[3]);
         }
@@ -341,31 +347,31 @@ __device__ __forceinline__ bool softmax_tile_fast(const f32x4 (&sacc)[NS][4], bf
 // here is the order executed (nothing is scheduled across a step).  Step r < RV: V^T operand (sl, e), O^T of every
 // slab; step r >= RV: K operand (c, kg), S^T of every slab.  phase_prefetch starts the first PF loads (it may
 // run before the barrier that opens the phase when the tiles are known to have landed), mfma_phase does the rest.
-template <int D, bool DO_PV, bool DO_QK>
+template <int D, bool DO_PV, bool DO_QK, int KG = 4>
 __device__ __forceinline__ bf16x8 phase_operand(const unsigned char *vt, const unsigned char *kt, int n16, int q4, int r)
 {
     constexpr int DT = D / 16;
-    constexpr int RV = DO_PV ? 2 * DT : 0;
+    constexpr int RV = DO_PV ? KG / 2 * DT : 0;
     if (r < RV) {
         const int sl = r / DT, e = r % DT;
         return *reinterpret_cast<const bf16x8 *>(vt + vt_tile_off(16 * e + n16, 4 * sl + q4));
     }
-    const int c = (r - RV) / 4, kg = (r - RV) % 4;
+    const int c = (r - RV) / KG, kg = (r - RV) % KG;
     const int krow = 32 * (kg >> 1) + 8 * (n16 >> 2) + 4 * (kg & 1) + (n16 & 3);
     return *reinterpret_cast<const bf16x8 *>(kt + k_tile_off<D>(krow, 4 * c + q4));
 }
 
-template <int D, int PF, bool DO_PV, bool DO_QK>
+template <int D, int PF, bool DO_PV, bool DO_QK, int KG = 4>
 __device__ __forceinline__ void phase_prefetch(const unsigned char *vt, const unsigned char *kt, int n16, int q4,
                                                bf16x8 (&ring)[PF])
 {
-    constexpr int R = (DO_PV ? 2 * (D / 16) : 0) + (DO_QK ? 4 * (D / 32) : 0);
+    constexpr int R = (DO_PV ? KG / 2 * (D / 16) : 0) + (DO_QK ? KG * (D / 32) : 0);
 #pragma unroll
-    for (int r = 0; r < PF && r < R; ++r) ring[r] = phase_operand<D, DO_PV, DO_QK>(vt, kt, n16, q4, r);
+    for (int r = 0; r < PF && r < R; ++r) ring[r] = phase_operand<D, DO_PV, DO_QK, KG>(vt, kt, n16, q4, r);
 }
 
 // sinit: what the scores of a slab start from (0, or minus the running maximum: see softmax_tile_folded).
-template <int D, int NS, int PF, bool DO_PV, bool DO_QK>
+template <int D, int NS, int PF, bool DO_PV, bool DO_QK, int KG = 4>
 __device__ __forceinline__ void mfma_phase_from(const unsigned char *vt, const unsigned char *kt, int n16, int q4,
                                                 bf16x8 (&ring)[PF], const bf16x8 (&pf)[NS][2],
                                                 f32x4 (&oacc)[NS][D / 16], f32x4 (&l_run)[NS],
@@ -373,7 +379,7 @@ __device__ __forceinline__ void mfma_phase_from(const unsigned char *vt, const u
                                                 f32x4 (&sacc)[NS][4])
 {
     constexpr int DT = D / 16, KSTEPS = D / 32;
-    constexpr int RV = DO_PV ? 2 * DT : 0, RK = DO_QK ? 4 * KSTEPS : 0, R = RV + RK;
+    constexpr int RV = DO_PV ? KG / 2 * DT : 0, RK = DO_QK ? KG * KSTEPS : 0, R = RV + RK;
     // The SIMD's other wavefront is (mostly) in its softmax: its vector instructions go where the MFMAs leave room, and not the
     // other way round (65,536 tokens of 28/4 heads, masked walk, a forward pass: 23.35 ms at one priority, 23.1 so, 23.7 with the
     // softmax preferred; key-stationary 10.23, 10.08, 10.13.  The backward's kernels, with a barrier per tile and both
@@ -395,12 +401,12 @@ __device__ __forceinline__ void mfma_phase_from(const unsigned char *vt, const u
             for (int s = 0; s < NS; ++s)
                 oacc[s][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, pf[s][sl], oacc[s][e], 0, 0, 0);
         } else {
-            const int c = (r - RV) / 4, kg = (r - RV) % 4;
+            const int c = (r - RV) / KG, kg = (r - RV) % KG;
 #pragma unroll
             for (int s = 0; s < NS; ++s)
                 sacc[s][kg] = score_mfma(af, qf[s][c], c == 0 ? sinit[s] : sacc[s][kg]);
         }
-        if (r + PF < R) ring[r % PF] = phase_operand<D, DO_PV, DO_QK>(vt, kt, n16, q4, r + PF);
+        if (r + PF < R) ring[r % PF] = phase_operand<D, DO_PV, DO_QK, KG>(vt, kt, n16, q4, r + PF);
         __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_setprio(0);

@@ -68,7 +68,10 @@ __device__ __forceinline__ void dma_barrier()
 // Blocks of 256 rows that follow each other on one XCD: as many as a whole cube fills.
 __host__ __device__ inline int walk_group(const Geom &g) { return max(1, g.G * g.Cmax / Walk<64>::MMAX); }
 
-template <int D, bool MASKED>
+// SMALL: no cube has more than 32 tokens, and every tile is worked as its first half; the other half held no keys, and its score
+// products, exponentials and output products were a third of a step.  (This kernel, us, whole tiles and half: cubes of 32, 4,032 tokens
+// of 6/2 heads of 128 222, 157; 8,064 of 28/4 840, 586; 8/2 of 64 367, 266.)
+template <int D, bool MASKED, bool SMALL = false>
 __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     Geom g, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ Kp, const uint16_t *__restrict__ Vt,
     const int32_t *__restrict__ csize, const uint32_t *__restrict__ sel_mask, const int *__restrict__ mode_flag,
@@ -79,6 +82,8 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     constexpr int NS = C::NS, MMAX = C::MMAX, THREADS = C::THREADS, WAVES = C::WAVES, NST = C::NST;
     constexpr int KSTEPS = D / 32, DT = D / 16;
     constexpr int PF = C::PF;
+    constexpr int KG = SMALL ? 2 : 4;                             // groups of 16 keys of a tile that are worked
+    constexpr int DMA_K = SMALL && C::DMA == 2 ? 1 : C::DMA;      // loads of a K tile (SMALL: of its first half), per wavefront
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
     int *rowid = reinterpret_cast<int *>(smem + C::OFF_ROWID);
     int *rrank = reinterpret_cast<int *>(smem + C::OFF_RANK);
@@ -244,6 +249,15 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
         for (int u = 0; u < C::DMA; ++u)
             dma_1k_s(lds_piece + (uint32_t)(off_bytes + u * 1024), tile, src_piece + (uint32_t)(u * 1024));
     };
+    auto issue_k = [&](uint32_t off, int off_bytes) __attribute__((always_inline)) {
+        if constexpr (DMA_K == C::DMA) {
+            issue(khead, off, off_bytes);
+        } else {
+            const uint32_t piece = (uint32_t)(wave * DMA_K * 1024);  // of the tile's first half
+            dma_1k_s(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + piece) + (uint32_t)off_bytes,
+                     uniform_ptr(khead + off), piece + (uint32_t)(lane * 16));
+        }
+    };
     auto next_stage = [](int st) -> int { return st + 1 == NST ? 0 : st + 1; };
 
     // rows of this wavefront: slab k of the block belongs to wavefront k % WAVES as its slot k / WAVES
@@ -274,12 +288,12 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     // prologue: K(0), K(1), V(0)
     Stream sk = stream_begin();
     uint32_t klast = sk.off;  // offset of the K tile issued last
-    issue(khead, sk.off, C::OFF_K);  // (ntiles >= 1: the own cube has a tile)
+    issue_k(sk.off, C::OFF_K);  // (ntiles >= 1: the own cube has a tile)
     issue(vhead, sk.off, C::OFF_V);
     stream_next(sk);
     if (ntiles > 1) {
         klast = sk.off;
-        issue(khead, sk.off, C::OFF_K + C::CHUNK);
+        issue_k(sk.off, C::OFF_K + C::CHUNK);
         stream_next(sk);
     }
 
@@ -410,8 +424,8 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
         const bool edge = g.causal && cc_j >= own_lo && (MASKED ? cc_j <= own_hi : true) &&
                           (cc_j > own_lo || key0 + KEY_TILE - 1 > rank_lo);
         const int fill = cc_size - key0;
-        if (edge || !softmax_tile_fast<NS>(sacc, pf, short_step, smem + C::OFF_FILL, fill, q4)) {
-            softmax_tile_folded<D, NS>(sacc, pf, oacc, m_run, l_run, fresh, lim, key0, edge || fill < KEY_TILE, q4);
+        if (edge || !softmax_tile_fast<NS, KG>(sacc, pf, short_step, smem + C::OFF_FILL, fill, q4)) {
+            softmax_tile_folded<D, NS, KG>(sacc, pf, oacc, m_run, l_run, fresh, lim, key0, edge || fill < 16 * KG, q4);
             references();
         }
         if (LATE && g.causal && cc_j > own_lo) {  // (the product with this tile comes next)
@@ -437,7 +451,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     // Opens slot t.  The loads started after the previous barrier, K(t+1) and V(t), may stay in flight; everything
     // older has landed: K(t) and V(t-1).  Then K(t+2) and V(t+1) are started into the stages that fell free.
     auto open_slot = [&](int t) __attribute__((always_inline)) {
-        if (t > 0 && t + 1 < ntiles) dma_barrier<2 * C::DMA>();
+        if (t > 0 && t + 1 < ntiles) dma_barrier<C::DMA + DMA_K>();
         else dma_barrier<0>();
         const int st_v = kst == 0 ? 2 : kst - 1;  // (kst + 2) % 3: stage of V(t-1), and of K(t+2)
         const int st_n = kst == 2 ? 0 : kst + 1;  // (kst + 1) % 3: stage of V(t+1)
@@ -445,7 +459,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
             issue(vhead, klast, C::OFF_V + st_n * C::CHUNK);
         if (t + 2 < ntiles) {
             klast = sk.off;
-            issue(khead, sk.off, C::OFF_K + st_v * C::CHUNK);
+            issue_k(sk.off, C::OFF_K + st_v * C::CHUNK);
             stream_next(sk);
         }
     };
@@ -454,9 +468,9 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     // The first and the last slot are peeled off the loops: a loop body with a conditional MFMA phase would merge
     // two versions of every accumulator at its end, at the price of a register copy each.
     open_slot(0);
-    phase_prefetch<D, PF, false, true>(nullptr, k_tile(), n16, q4, ring);
+    phase_prefetch<D, PF, false, true, KG>(nullptr, k_tile(), n16, q4, ring);
     set_sinit();
-    mfma_phase_from<D, NS, PF, false, true>(nullptr, k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
+    mfma_phase_from<D, NS, PF, false, true, KG>(nullptr, k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
     // Each set's loop twice: up to the own cube of the wavefront's first row, and behind it (few tiles, and none where a block's
     // rows are of one cube).  As one loop that may write rows out in any step, 65,536 tokens of 28/4 heads took 1.2 % longer; so, 0.3 %
     // longer than without the early writes.
@@ -467,9 +481,9 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
         auto slot = [&](auto when) __attribute__((always_inline)) {
             kst = next_stage(kst);
             open_slot(t);
-            phase_prefetch<D, PF, true, true>(v_tile(), k_tile(), n16, q4, ring);
+            phase_prefetch<D, PF, true, true, KG>(v_tile(), k_tile(), n16, q4, ring);
             set_sinit();
-            mfma_phase_from<D, NS, PF, true, true>(v_tile(), k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
+            mfma_phase_from<D, NS, PF, true, true, KG>(v_tile(), k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
             softmax_step(when);
         };
         softmax_step(early);
@@ -482,9 +496,9 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
             kst = next_stage(kst);
             open_slot(t);
             softmax_step(when);  // of tile t-1
-            phase_prefetch<D, PF, true, true>(v_tile(), k_tile(), n16, q4, ring);
+            phase_prefetch<D, PF, true, true, KG>(v_tile(), k_tile(), n16, q4, ring);
             set_sinit();
-            mfma_phase_from<D, NS, PF, true, true>(v_tile(), k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
+            mfma_phase_from<D, NS, PF, true, true, KG>(v_tile(), k_tile(), n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
         };
         for (; t < ntiles && cc_j <= main_to; ++t) slot(early);
         for (; t < ntiles; ++t) slot(late);
@@ -492,8 +506,8 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
         open_slot(ntiles);
         softmax_step(late);
     }
-    phase_prefetch<D, PF, true, false>(v_tile(), nullptr, n16, q4, ring);
-    mfma_phase_from<D, NS, PF, true, false>(v_tile(), nullptr, n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
+    phase_prefetch<D, PF, true, false, KG>(v_tile(), nullptr, n16, q4, ring);
+    mfma_phase_from<D, NS, PF, true, false, KG>(v_tile(), nullptr, n16, q4, ring, pf, oacc, l_run, qf, sinit, sacc);
 
     // ---- the rest of the rows (no direct-to-LDS load may outlive the workgroup's LDS allocation)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -629,12 +643,16 @@ static hipError_t launch_walk(const Geom &g, const uint16_t *Q, const void *pack
     const int per_group = walk_group(g), nblk = (g.S * g.G - 1) / C::MMAX + 1;
     const int groups = (nblk + per_group - 1) / per_group;
     const dim3 grid((unsigned)((size_t)(((long long)groups * g.Hkv + 7) / 8) * per_group * 8));
-    static LdsOptIn opted;  // one per kernel instantiation
-    const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&attn_walk_kernel<D, MASKED>), C::BYTES);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_walk_kernel<D, MASKED>), grid, dim3(C::THREADS), C::BYTES, st, g, Q, Kp, Vt, csize,
-                       sel_mask, mode_flag, my_mode, kv_modes, O, lse);
-    return hipGetLastError();
+    auto launch = [&](auto small) -> hipError_t {
+        constexpr bool SMALL = decltype(small)::value;
+        static LdsOptIn opted;  // one per kernel instantiation
+        const hipError_t e = opted.ensure(reinterpret_cast<const void *>(&attn_walk_kernel<D, MASKED, SMALL>), C::BYTES);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((attn_walk_kernel<D, MASKED, SMALL>), grid, dim3(C::THREADS), C::BYTES, st, g, Q, Kp, Vt, csize,
+                           sel_mask, mode_flag, my_mode, kv_modes, O, lse);
+        return hipGetLastError();
+    };
+    return g.Cmax <= KEY_TILE / 2 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 // Below this many candidate (row, cube) pairs the automatic choice is the masked walk outright (see launch_attn_d).
@@ -673,15 +691,19 @@ long long tiles_of_cubes(const Geom &g, int keys)
 // with and without text; the figures below are 5 % (walk) and 6 % (split) off on average and pick the faster kernel but for
 // two shapes, 4 and 6 % slower.
 //   walk   a slot (64 keys past 256 rows) takes 1.19 at head-dim 64 and 1.62 at 128; the time is the longest walk's slots,
-//          or all slots over 256 CUs where that is more
+//          or all slots over 256 CUs where that is more.  In cubes of up to 32 tokens a slot is half the keys: 1.16 with most cubes
+//          selected and 1.4 with few at head-dim 128, taken as 1.3 where selections of few cubes have another kernel to go to; where
+//          they do not, and at head-dim 64, the line above stays (2,016 tokens of 28/4 heads, 62, 18 and 5 % selected, a forward
+//          pass: 126, 136, 147 walk, 143, 144, 131 split)
 //   split  a step (32 keys past 32 rows) takes a CU 0.15 and 0.24 -- what its operands take from L2 -- and a workgroup
 //          7 to start and to combine its parts
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
 //   choice  where this kernel would be one of those chosen from on the device, the launches of that choice take 40
-static double walk_time(const Geom &g)
+static double walk_time(const Geom &g, bool choice)
 {
-    return 11 + (g.D == 64 ? 1.19 : 1.62) * (double)tiles_of_cubes(g, KEY_TILE) * std::max(1.0, walk_rounds(g));
+    const double slot = g.D == 64 ? 1.19 : choice && g.Cmax <= KEY_TILE / 2 ? 1.3 : 1.62;
+    return 11 + slot * (double)tiles_of_cubes(g, KEY_TILE) * std::max(1.0, walk_rounds(g));
 }
 
 // What the split takes, and of that what grows with the steps it visits.
@@ -696,7 +718,8 @@ static double split_time(const Geom &g, double &of_steps)
 bool attn_split_pays(const Geom &g, bool choice)
 {
     double of_steps;
-    return attn_split_fits(g) && split_time(g, of_steps) < walk_time(g) + (choice && chosen_on_device(g) ? 40 : 0);
+    choice = choice && chosen_on_device(g);
+    return attn_split_fits(g) && split_time(g, of_steps) < walk_time(g, choice) + (choice ? 40 : 0);
 }
 
 // Up to which share of selected candidate cubes (permille) the split beats the walk where it does not at any share: it leaves
@@ -706,7 +729,7 @@ static int split_below_permille(const Geom &g)
 {
     if (!attn_split_fits(g)) return -1;
     double of_steps;
-    const double all = split_time(g, of_steps), visited = 1.0 - (all - walk_time(g)) / of_steps;
+    const double all = split_time(g, of_steps), visited = 1.0 - (all - walk_time(g, false)) / of_steps;
     return visited <= 0.0 ? -1 : (int)(1000.0 * (1.0 - std::pow(std::max(0.0, 1.0 - visited), 1.0 / 32)));
 }
 
@@ -714,8 +737,16 @@ static int split_below_permille(const Geom &g)
 // tiles of a cube, 0.03 ns a candidate pair and tile at head-dim 128; a selected pair costs the other path 0.22 ns in cubes of one tile and
 // 0.24 in cubes of four, most of it its record.  (Measured: 65,536 tokens of 28/4 heads in cubes of 256, break-even at 44 %;
 // 7,688 tokens in cubes of 32, 33 % selected, 2,250 us against 910; 8,640 on a grid of 9 x 10, where cubes of up to 256 have 1.75 tiles on
-// average, 32 % selected, 897 against 549.)
-static int pairs_below_permille(const Geom &g) { return (int)(60 + 85 * tiles_of_cubes(g, KEY_TILE) / g.N); }
+// average, 32 % selected, 897 against 549.)  With half a tile's keys to a step (no cube above 32 tokens) the walk takes 0.72 of that; at
+// head-dim 64 the other path's records are half as long, and the line stays.  (At head-dim 128, the walk and the key-stationary kernel by
+// the share selected: 8,064 tokens, 28/4 heads, 13.6 % 624, 858, 10.6 % 628, 691, 9.3 % 645, 640; 14/2, 13.6 % 324, 469, 10.6 % 327, 387;
+// 12,000, 14/2, 10.2 % 717, 707; 32/8, 13.1 % 1,460, 2,109, 8.7 % 1,501, 1,530.  KV heads on both sides of the line take both kernels, and that
+// costs more than either near it: at 90, 7 % over 24 such shapes of 10 %, none slower at 110.  At 64: 8,064, 8/2, 16.5 % 265, 216.)
+static int pairs_below_permille(const Geom &g)
+{
+    if (g.Cmax <= KEY_TILE / 2 && g.D == 128) return 110;
+    return (int)(60 + 85 * tiles_of_cubes(g, KEY_TILE) / g.N);
+}
 
 template <int D>
 static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, const uint32_t *sel_mask,

@@ -49,6 +49,20 @@ def test_blocks_across_cubes(B, oracle, name, grid, cube, hq, hkv, d, text, lead
                 assert (np.abs(lse.cpu().numpy().astype(np.float64) - ref) <= lse_bound(absdot)).all()
 
 
+# No cube above 32 tokens, every tile worked as its first half: cubes of 32 and 31 with text, and of 33 on the other side.
+HALF = [
+    ("keys32_text", (6, 4, 12), (2, 4, 4), 6, 2, 64, 33, 31),
+    ("keys32_128", (7, 5, 9), (2, 4, 4), 2, 1, 128, 1, 0),
+    ("keys31_text", (9, 1, 31), (1, 1, 31), 4, 1, 128, 31, 5),
+    ("keys33", (9, 3, 11), (1, 3, 11), 4, 1, 128, 0, 0),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead", HALF, ids=[s[0] for s in HALF])
+def test_half_tiles(B, oracle, name, grid, cube, hq, hkv, d, text, lead):  # noqa: F811
+    test_blocks_across_cubes(B, oracle, name, grid, cube, hq, hkv, d, text, lead)
+
+
 BEHIND = SHAPES + [  # the last two: the dense walk at both head-dims, and the dQ kernel with one wavefront per 32 rows
     ("clipped60_text", (16, 10, 15), (3, 4, 5), 48, 4, 64, 70, 45),
     ("clipped60", (18, 9, 15), (3, 4, 5), 36, 4, 128, 0, 0),

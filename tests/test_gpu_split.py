@@ -82,6 +82,19 @@ def test_dense_walk_of_64(B, oracle, name, grid, cube, hq, hkv, text, lead):  # 
         check_outputs(f"{name} causal={causal}", rows_of(O, rows, w), oracle.dense_attn(osh, Q, K, V, rows=rows, causal=causal))
 
 
+# The dense walk where no cube has more than 32 tokens, and more rows than the kernel for short sequences takes
+@pytest.mark.parametrize("d", [64, 128])
+def test_dense_walk_of_small_cubes(B, oracle, d):  # noqa: F811
+    w = synth.Workload(f"cubes32_{d}", 63, 27, 12, 13, 2, 4, 4, 32, 8, d, (0.5,), (1.0,) * 8, 20, 0)
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    rows = stratified_rows(oracle, osh, w, 200)
+    for causal in (True, False):
+        O = B.dense_attn(sh, Q.cuda(), K.cuda(), V.cuda(), causal=causal)
+        torch.cuda.synchronize()
+        check_outputs(f"{w.name} causal={causal}", rows_of(O, rows, w), oracle.dense_attn(osh, Q, K, V, rows=rows, causal=causal))
+
+
 # Few rows, which the masked walk takes in one round, where all KV heads select little, all select much, and one of two little:
 # the kernel that the automatic choice has to take with room for the key-stationary one, and without.  (Grid, cube, query heads, KV
 # heads, key scale of each, what is selected: Top-p or Top-K; kernel with room, kernel without.)
