@@ -669,8 +669,12 @@ static bool chosen_on_device(const Geom &g) { return candidate_pairs(g) >= AUTO_
 
 // Whether it is then made for all KV heads together.  Where the time of the masked walk is that of its longest walk, heads that go to
 // the key-stationary kernel do not shorten it, unless all of them go (3,600 tokens of 28/4 heads of 128 in cubes of 32, half the
-// heads selecting nearly nothing: the walk 218 us, with all heads as with half of them, and the others another 140).
-static bool heads_together(const Geom &g) { return walk_rounds(g) <= 1.0; }
+// heads selecting nearly nothing: the walk 218 us, with all heads as with half of them, and the others another 140).  With room for the
+// key-stationary kernel, up to 1.2: a fifth of the walk is less than that kernel's share takes.  (A forward pass of as many heads that
+// select nearly nothing as of others, us, one by one and together, by rounds of the walk: 14/2 heads of 128 in cubes of 256, 7,680 tokens,
+// 1.05, 426, 369; 8/2 of 64, 14,336, 1.03, 427, 346; 28/4 in cubes of 32, 4,032, 1.02, 372, 287; 4,752, 1.20, 461, 401; 6/2 in cubes of 128,
+// 19,008, 1.03, 671, 601; 22,464, 1.22, 743, 781.)
+static bool heads_together(const Geom &g, bool room) { return walk_rounds(g) <= (room ? 1.2 : 1.0); }
 
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
 // axis), text cubes in two.
@@ -780,7 +784,7 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
     // short sequences.  (Attention, us, chosen so, by the walk and by the key-stationary kernel: 24,576 tokens of 4/4 heads of 64 in
     // cubes of 256, 63, 34 and 18 % selected: 474, 319, 220; 439, 441, 445; 489, 320, 221.  Never one of the latter two: a call of
     // these that selects much is 8 % faster, one that selects little 50 % slower.)
-    const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g);
+    const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g, kv_modes);
     // Heads by themselves: the compacting kernel for a selection of up to MASKED_ABOVE_PERMILLE -- which the key-stationary kernel has
     // already, if there is room for its records (twice as many, and the rows' own: the share is an estimate).
     const bool compact = !together && !(kv_modes && pairs_capacity(g, scratch, scratch_bytes) >=

@@ -106,6 +106,7 @@ FEW = [
     ("cubes32_little", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 4, "pairs", "masked"),
     ("clipped256_third", (96, 9, 10), (4, 8, 8), 28, 4, (1.0,) * 4, 0.7, "masked", "masked"),  # (more rows: a head at a time)
     ("clipped256_none", (96, 9, 10), (4, 8, 8), 28, 4, (1.0,) * 4, 0.0, "pairs", "compact"),  # (room: not asked whether to compact)
+    ("cubes32_two_little", (28, 12, 12), (2, 4, 4), 28, 4, (0.0, 0.0, 4.0, 4.0), 0.9, "masked", "masked"),  # (a little more than one round)
     ("cubes32_much", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 0.8, "masked", "masked"),
 ]
 
