@@ -703,7 +703,9 @@ long long tiles_of_cubes(const Geom &g, int keys)
 //          7 to start and to combine its parts
 // Measured on both sides of the line: 8,192 tokens of 4/4 heads of 64 in cubes of 128: 113 split, 155 walk; 16,384: 396, 303.
 // 2,048 tokens of 14/2 heads of 128 in cubes of 256: 62, 59; 4,096: 156, 105.
-//   choice  where this kernel would be one of those chosen from on the device, the launches of that choice take 40
+//   choice  where this kernel would be one of those chosen from on the device, the launches of that choice count as 40 (20 to 25 with two of
+//          them gone; the line was
+//          fitted with 40 and is left where selections of few cubes, which the split takes in less time, lie near it)
 static double walk_time(const Geom &g, bool choice)
 {
     const double slot = g.D == 64 ? 1.19 : choice && g.Cmax <= KEY_TILE / 2 ? 1.3 : 1.62;
