@@ -1,30 +1,39 @@
 // Cube mean keys (Eq. 1: k-bar_j = Mean(k in K_j)).
 //
 // A token's KV heads are contiguous in memory (Hkv*D bf16); a workgroup has one cube and
-// all of a token's row, or, with fewer cubes than CUs, a part of it of 128 bytes or more: thread = (token slot,
+// all of a token's row, or a part of it of 128 bytes or more: thread = (token slot,
 // 16-byte chunk); slots stride over the cube's tokens, the partial
-// sums of the slots are combined through LDS in a fixed order (the result does
-// not depend on scheduling).  HBM-bound: K is read exactly once.
+// sums of the slots are combined through LDS in the slots' order.
+// The order of the additions is a function of the shape alone: as many slots as fit POOL_THREADS beside the whole row (or
+// POOL_THREADS chunks of it), whatever part of it a workgroup has.  A selection at the edge of its nucleus hangs on the last bits of a
+// mean key: another order selects other cubes in a few rows of a million.
+// HBM-bound: K is read exactly once.
 #include "geom.h"
 
 namespace adaspark {
 
-constexpr int POOL_THREADS = 1024;  // 16 wavefronts: one workgroup (one cube) per CU has to keep that CU's share of HBM busy
+constexpr int POOL_THREADS = 1024;  // of a whole row: 16 wavefronts
+// Rows are cut while there are fewer workgroups than this, each part with its share of the threads, so that a CU holds several: cubes by
+// themselves leave CUs empty, and a little above 256 of them, the second half of the time.  (Mean keys, us, parts up to 256 workgroups and up to
+// this many: 16,384 tokens of 4 KV heads of 128 in cubes of 256 6.2, 6.4; 65,536 15.9, 12.9; 262,144 47.5, 41.5; 30,000 of 8, 14.9, 13.0;
+// 69,630 of 2 in 318 cubes 11.0, 7.5; uncut rows took 11.1, 16.5, 47.2, 19.3 and 11.9.)  A row of many heads leaves few slots, whose chain of
+// additions is then the time: 256 tokens of 64 heads of 128, 56 us (121 uncut).
+constexpr int POOL_WORKGROUPS = 2048;
 
 __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const uint16_t *__restrict__ K,
                                                                  float *__restrict__ kbar)
 {
-    __shared__ float part[POOL_THREADS * 8];
+    extern __shared__ float part[];  // [slot][chunk][8]: as many as threads
     const int c = blockIdx.x;
     const CubeBox box = cube_box(g, c);
     const int size = box.size();
     const int row_elems = g.Hkv * g.D;  // elements per token row
-    const int chunks = row_elems / 8 / gridDim.y;  // 16-byte chunks of a row that are this workgroup's
-    const int begin = chunks * blockIdx.y, end = begin + chunks;
+    const int chunks = row_elems / 8;   // 16-byte chunks per row
+    const int begin = chunks / gridDim.y * blockIdx.y, end = begin + chunks / gridDim.y;  // this workgroup's
 
-    for (int chunk0 = begin; chunk0 < end; chunk0 += POOL_THREADS) {
-        const int lanes = min(end - chunk0, POOL_THREADS);  // chunks handled in this sweep
-        const int slots = POOL_THREADS / lanes;                // token slots working in parallel
+    for (int sweep = begin / POOL_THREADS * POOL_THREADS; sweep < end; sweep += POOL_THREADS) {  // of as many chunks as threads
+        const int chunk0 = max(sweep, begin), lanes = min(end, sweep + POOL_THREADS) - chunk0;  // handled here
+        const int slots = POOL_THREADS / min(chunks - sweep, POOL_THREADS);                     // token slots working in parallel
         const int slot = threadIdx.x / lanes, col = threadIdx.x % lanes;
         float acc[8];
 #pragma unroll
@@ -58,22 +67,11 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
 #pragma unroll
         for (int e = 0; e < 8; ++e) part[threadIdx.x * 8 + e] = acc[e];
         __syncthreads();
-        // the slots' sums: `groups` threads an element, each over every groups-th slot, then these
-        const int elems = lanes * 8, groups = max(1, POOL_THREADS / elems);
-        const int x = threadIdx.x % elems, group = threadIdx.x / elems;
-        float sum = 0.f;
-        if (groups > 1) {
-            if (group < groups)
-                for (int s2 = group; s2 < slots; s2 += groups) sum += part[s2 * elems + x];
-            __syncthreads();
-            if (group < groups) part[threadIdx.x] = sum;
-            __syncthreads();
-        }
-        const int left = groups > 1 ? groups : slots;
-        for (int y = threadIdx.x; y < elems; y += POOL_THREADS) {
-            float total = 0.f;
-            for (int s2 = 0; s2 < left; ++s2) total += part[s2 * elems + y];
-            kbar[(size_t)c * row_elems + (size_t)chunk0 * 8 + y] = total / (float)size;
+        for (int x = threadIdx.x; x < lanes * 8; x += blockDim.x) {
+            float sum = 0.f;
+#pragma unroll 8
+            for (int s2 = 0; s2 < slots; ++s2) sum += part[s2 * (lanes * 8) + x];
+            kbar[(size_t)c * row_elems + (size_t)chunk0 * 8 + x] = sum / (float)size;
         }
         __syncthreads();
     }
@@ -81,11 +79,11 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
 
 hipError_t launch_cube_pool(const Geom &g, const uint16_t *K, float *kbar, hipStream_t st)
 {
-    // Parts of a row while the workgroups do not fill the CUs.
     const int chunks = g.Hkv * g.D / 8;
     int parts = 1;
-    while (g.N * parts < 256 && chunks % (16 * parts) == 0) parts *= 2;
-    hipLaunchKernelGGL(cube_pool_kernel, dim3(g.N, parts), dim3(POOL_THREADS), 0, st, g, K, kbar);
+    while (g.N * parts < POOL_WORKGROUPS && chunks % (16 * parts) == 0) parts *= 2;
+    const int threads = chunks <= POOL_THREADS ? max(64, POOL_THREADS / parts) : POOL_THREADS;
+    hipLaunchKernelGGL(cube_pool_kernel, dim3(g.N, parts), dim3(threads), threads * 32, st, g, K, kbar);
     return hipGetLastError();
 }
 
