@@ -786,11 +786,14 @@ static hipError_t launch_attn_d(const Geom &g, const uint16_t *Q, void *packed, 
     // short sequences.  (Attention, us, chosen so, by the walk and by the key-stationary kernel: 24,576 tokens of 4/4 heads of 64 in
     // cubes of 256, 63, 34 and 18 % selected: 474, 319, 220; 439, 441, 445; 489, 320, 221.  Never one of the latter two: a call of
     // these that selects much is 8 % faster, one that selects little 50 % slower.)
-    const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g, kv_modes);
+    // Room: for twice the records of a selection of MASKED_ABOVE_PERMILLE (the share is an estimate), and the rows' own.  With less, heads are
+    // by themselves where heads_together says so without the key-stationary kernel.
+    const bool room = kv_modes && pairs_capacity(g, scratch, scratch_bytes) >=
+                                      (long long)(candidate_pairs(g) / 1000 * (2 * MASKED_ABOVE_PERMILLE)) + (long long)g.S * g.Hq;
+    const bool together = sparse_kernel == ADASPARK_SPARSE_AUTO && heads_together(g, room);
     // Heads by themselves: the compacting kernel for a selection of up to MASKED_ABOVE_PERMILLE -- which the key-stationary kernel has
-    // already, if there is room for its records (twice as many, and the rows' own: the share is an estimate).
-    const bool compact = !together && !(kv_modes && pairs_capacity(g, scratch, scratch_bytes) >=
-                                                        (long long)(candidate_pairs(g) / 1000 * (2 * MASKED_ABOVE_PERMILLE)) + (long long)g.S * g.Hq);
+    // already, if there is room.
+    const bool compact = !together && !room;
     const int other_permille = together ? (kv_modes ? -1 : split_below_permille(g)) : compact ? MASKED_ABOVE_PERMILLE : -1;
     if (together && !kv_modes && other_permille < 0) return launch_walk<D, true>(g, Q, packed, sel_mask, nullptr, 0, 0, O, lse, st);
     int counter_words = 0;

@@ -136,6 +136,33 @@ def test_choice_for_few_rows(B, oracle, name, grid, cube, hq, hkv, scale, sel, r
             assert (x < 1e-4) == (k == expected), (k, expected)
 
 
+# Scratch for not quite the rows' own records, and nothing selected: with a little more than one round of the walk the compacting kernel has
+# such a selection, as it has without scratch.
+LITTLE_ROOM = [
+    ("cubes32", (28, 12, 12), (2, 4, 4), 28, 4, 128),
+    ("cubes256", (36, 16, 16), (4, 8, 8), 14, 2, 128),
+    ("cubes256_64", (56, 16, 16), (4, 8, 8), 8, 2, 64),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d", LITTLE_ROOM, ids=[s[0] for s in LITTLE_ROOM])
+def test_choice_with_too_little_scratch(B, name, grid, cube, hq, hkv, d):  # noqa: F811
+    w = synth.Workload(name, 66, *grid, *cube, hq, hkv, d, (0.5,), (1.0,) * hkv)
+    sh = B.Shape.of(w)
+    Q, K, V = (x.cuda() for x in synth.generate(w))
+    mask = B.cube_select(sh, Q, B.cube_pool(sh, K), 0.0)[0]
+    n = B.pairs_workspace_bytes(sh, 0)
+    O = {}
+    for what, size, kernel in (("compact", n, B.SPARSE_COMPACT), ("masked", n, B.SPARSE_MASKED), ("little room", n - 4096, None),
+                               ("none", B.workspace_bytes(sh, B.CALL_SPARSE_ATTN), None)):
+        packed = B.kv_pack(sh, K, V, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        O[what] = B.sparse_attn_packed(sh, Q, packed, mask, kernel=kernel).float()
+    torch.cuda.synchronize()
+    off = {k: float((O["compact"] - x).norm() / x.norm()) for k, x in O.items()}
+    print(f"[{name}] from the compacting kernel's results {off}", flush=True)
+    assert off["masked"] > 1e-4 and off["none"] < 1e-4 and off["little room"] < 1e-4
+
+
 # Some KV heads select next to nothing and go to the key-stationary kernel: the masked walk's workgroups are dealt out over the heads that
 # remain, one, three (eight XCDs are no multiple of them) and five of six, and seven of eight.
 @pytest.mark.parametrize("heads,flat", [(6, 1), (6, 3), (6, 5), (8, 7)])
