@@ -241,15 +241,16 @@ __global__ __launch_bounds__(SELM_THREADS, MAXG == 8 ? 3 : 2) void cube_select_m
     constexpr int OPS = KS * 3, HALF = OPS / 2, KSH = KS / 2;
     static_assert(KS % 2 == 0, "a cube group's operands are fetched in two halves");
     if (SPLIT_HERE) {
-        typedef float f32x8 __attribute__((ext_vector_type(8)));
-        f32x8 mean[MAXG][KS];  // (all asked for at once)
+        sel_f32x4 mean[MAXG][KS][2];  // (all asked for at once; the entry asks for 16-byte alignment, no more)
 #pragma unroll
         for (int cg = 0; cg < MAXG; ++cg)
             if (cg < ng) {
                 const int cube = min(16 * cg + n16, g.N - 1);  // (no candidate past the last cube)
 #pragma unroll
                 for (int c = 0; c < KS; ++c)
-                    mean[cg][c] = *reinterpret_cast<const f32x8 *>(kbar + ((size_t)cube * g.Hkv + kv) * D + 32 * c + 8 * q4);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        mean[cg][c][h] = *reinterpret_cast<const sel_f32x4 *>(kbar + ((size_t)cube * g.Hkv + kv) * D + 32 * c + 8 * q4 + 4 * h);
             }
 #pragma unroll
         for (int cg = 0; cg < MAXG; ++cg)
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(SELM_THREADS, MAXG == 8 ? 3 : 2) void cube_select_m
                     sel_bf16x8 term[3];  // hi, mid, lo; the differences are exact
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        const float v = mean[cg][c][e];
+                        const float v = mean[cg][c][e >> 2][e & 3];
                         const __bf16 hi = (__bf16)v;
                         const float r1 = v - (float)hi;
                         const __bf16 mid = (__bf16)r1;

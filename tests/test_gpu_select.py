@@ -38,3 +38,18 @@ def test_selection_launches(B, oracle, name, cubes, tokens, hq, hkv, d):  # noqa
     torch.cuda.synchronize()
     ref_mask, ref_count, near = oracle.cube_select(osh, Q, kbar, 0.8)
     check_selection(name, to_u32(mask), count.cpu().numpy(), ref_mask, ref_count, near)
+
+
+@pytest.mark.parametrize("cubes,hq,hkv,d", [(17, 2, 2, 128), (64, 3, 1, 64)])
+def test_mean_keys_at_16_bytes(B, cubes, hq, hkv, d):  # noqa: F811
+    """Mean keys 16 bytes behind a 32-byte border, which the entry takes: the sets are those of the aligned ones."""
+    w = synth.Workload("at16", 44, cubes, 1, 5, 1, 1, 5, hq, hkv, d, (0.8,), (1.0,) * hkv)
+    sh = B.Shape.of(w)
+    Q, K, _ = (x.cuda() for x in synth.generate(w))
+    kbar = B.cube_pool(sh, K)
+    buf = torch.empty(kbar.numel() + 4, device="cuda")
+    moved = buf[4:].view_as(kbar).copy_(kbar)
+    assert kbar.data_ptr() % 32 == 0 and moved.data_ptr() % 32 == 16
+    got, want = B.cube_select(sh, Q, moved, 0.8)[:2], B.cube_select(sh, Q, kbar, 0.8)[:2]
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
