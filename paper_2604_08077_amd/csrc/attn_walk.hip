@@ -729,13 +729,19 @@ bool attn_split_pays(const Geom &g, bool choice)
 }
 
 // Up to which share of selected candidate cubes (permille) the split beats the walk where it does not at any share: it leaves
-// out what none of 32 rows selected, rows that select independently (1 - share)^32 of the cubes.  Its time, us, at
-// 61, 3.3 and 0.8 % selected, and the walk's: 7,680 tokens of 14/2 heads of 128 in cubes of 32: 498, 357, 231; 408, 464, 447.
+// out what none of 32 rows selected, rows that select independently (1 - share)^32 of the cubes.  The walk, in cubes of up to 32 tokens at
+// head-dim 128 and with few of them selected, takes 57 and 1.155 a tile, the launches of the choice included (within 4 % over eight shapes of
+// 2,816 to 15,360 tokens, 96 to 480 tiles); 65 because the share is one of rows from the first 60 to 100 % of the tokens, and few cubes are a larger share
+// of the candidates there.  Chosen so, us, split and walk on either side of the line: 7,680 tokens of 14/2 heads of 128 in cubes of 32, 2.5 % selected
+// 314, 334, 3.3 % 348, 339; 3,600 of 28/4, 1.7 % 181, 191, 3.3 % 218, 210; 2,816, 4.5 % 161, 167, 6.7 % 174, 163; 15,360 of 6/2, 4.9 % 588,
+// 616, 6.6 % 640, 613, 61 % 763, 585.
 static int split_below_permille(const Geom &g)
 {
     if (!attn_split_fits(g)) return -1;
     double of_steps;
-    const double all = split_time(g, of_steps), visited = 1.0 - (all - walk_time(g, false)) / of_steps;
+    const double walk = g.D == 128 && g.Cmax <= KEY_TILE / 2 ? 65 + 1.155 * (double)tiles_of_cubes(g, KEY_TILE) * std::max(1.0, walk_rounds(g))
+                                                             : walk_time(g, false);
+    const double all = split_time(g, of_steps), visited = 1.0 - (all - walk) / of_steps;
     return visited <= 0.0 ? -1 : (int)(1000.0 * (1.0 - std::pow(std::max(0.0, 1.0 - visited), 1.0 / 32)));
 }
 

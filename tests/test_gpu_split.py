@@ -107,6 +107,8 @@ FEW = [
     ("clipped256_third", (96, 9, 10), (4, 8, 8), 28, 4, (1.0,) * 4, 0.7, "masked", "masked"),  # (more rows: a head at a time)
     ("clipped256_none", (96, 9, 10), (4, 8, 8), 28, 4, (1.0,) * 4, 0.0, "pairs", "compact"),  # (room: not asked whether to compact)
     ("cubes32_two_little", (28, 12, 12), (2, 4, 4), 28, 4, (0.0, 0.0, 4.0, 4.0), 0.9, "masked", "masked"),  # (a little more than one round)
+    ("cubes32_wide_much", (60, 16, 16), (2, 4, 4), 6, 2, (1.0, 1.0), 0.9, "masked", "masked"),
+    ("cubes32_wide_few", (60, 16, 16), (2, 4, 4), 6, 2, (1.0, 1.0), 4, "pairs", "split"),
     ("cubes32_much", (15, 15, 16), (2, 4, 4), 28, 4, (1.0,) * 4, 0.8, "masked", "masked"),
 ]
 
