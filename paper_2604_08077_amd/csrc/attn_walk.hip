@@ -119,10 +119,12 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
     // always got the later group would finish last (a forward pass over 16,384 tokens, 28/4 heads of 128: 1.650 ms, without this
     // 1.667; over 8,736 in 36 cubes 0.591, 0.596; runs of one side differ by 0.2 %.  30,000 tokens of 32/8 heads, four of them this
     // kernel's: 3.16 ms with the heads rotated over the XCDs instead, which ended between 2.89 and 3.16.)  Where neither is a
-    // multiple of the other, the XCDs themselves take turns.
+    // multiple of the other, the XCDs themselves take turns at head-dim 128.  (This kernel, us, with turns and without: 16,384 tokens of 12/3 heads 653,
+    // 667; 30,720 of 20/5 3,536, 3,565; 20,480 of 28/7 2,251, 2,275; 12,288 of 21/3 655, 651.  24,576 of 28/4, three of them its, the same; five and three
+    // of 32/8 0.3 and 0.6 % slower with turns.  Head-dim 64: 20,480 of 12/12 769, 754; 16,384 of 10/5 460, 452.)
     const int round = seq / per_group;
     int grp = round * 8 + xcd;
-    if (8 % heads != 0 && heads % 8 != 0 && (round & 1)) grp = round * 8 + 7 - xcd;
+    if (D == 128 && 8 % heads != 0 && heads % 8 != 0 && (round & 1)) grp = round * 8 + 7 - xcd;
     if (grp >= groups * heads) return;
     int kv = grp % heads;
     int pos = grp / heads;

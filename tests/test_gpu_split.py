@@ -167,9 +167,9 @@ def test_choice_with_too_little_scratch(B, name, grid, cube, hq, hkv, d):  # noq
 
 # Some KV heads select next to nothing and go to the key-stationary kernel: the masked walk's workgroups are dealt out over the heads that
 # remain, one, three (eight XCDs are no multiple of them) and five of six, and seven of eight.
-@pytest.mark.parametrize("heads,flat", [(6, 1), (6, 3), (6, 5), (8, 7)])
-def test_walk_of_the_heads_that_remain(B, heads, flat):  # noqa: F811
-    w = synth.Workload(f"heads{heads}_flat{flat}", 62, 560 // heads, 16, 16, 4, 8, 8, heads, heads, 64, (0.9,), (0.0,) * flat + (4.0,) * (heads - flat))
+@pytest.mark.parametrize("heads,flat,d", [(6, 1, 64), (6, 3, 64), (6, 5, 64), (8, 7, 64), (6, 3, 128), (6, 5, 128)])
+def test_walk_of_the_heads_that_remain(B, heads, flat, d):  # noqa: F811
+    w = synth.Workload(f"heads{heads}_flat{flat}", 62, 560 // heads, 16, 16, 4, 8, 8, heads, heads, d, (0.9,), (0.0,) * flat + (4.0,) * (heads - flat))
     sh = B.Shape.of(w)
     Q, K, V = (x.cuda() for x in synth.generate(w))
     mask, count = B.cube_select(sh, Q, B.cube_pool(sh, K), 0.9)[:2]
