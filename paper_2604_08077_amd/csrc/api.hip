@@ -174,6 +174,12 @@ int adaspark_internal_dq_waves(const adaspark_shape *shape)
     return check_shape(shape) == ADASPARK_OK ? bwd_dq_waves(make_geom(*shape)) : 0;
 }
 
+// Whether that kernel works every tile as its first half.  Not declared either.
+int adaspark_internal_dq_half_tiles(const adaspark_shape *shape)
+{
+    return check_shape(shape) == ADASPARK_OK && bwd_dq_half_tiles(make_geom(*shape)) ? 1 : 0;
+}
+
 // Candidate (row, cube) pairs of a shape, 0 for one that is not valid.  Not declared either.
 unsigned long long adaspark_internal_candidate_pairs(const adaspark_shape *shape)
 {

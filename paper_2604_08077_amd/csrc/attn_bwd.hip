@@ -1292,6 +1292,8 @@ int bwd_dq_waves(const Geom &g)
     return eight < two ? 8 : 2;
 }
 
+bool bwd_dq_half_tiles(const Geom &g) { return g.Cmax <= KEY_TILE / 2 && bwd_dq_waves(g) == 1; }
+
 // Whether two wavefronts share 32 keys in the dK/dV kernel: with cubes of up to 128 tokens half or more of a workgroup's wavefronts
 // have no keys of their own.  Few rows do not make up for the sums' exchange: it takes the rows of a KV head, or those of a cube, which a
 // workgroup has all of in one piece.  A backward pass, us, shared and not,
@@ -1366,7 +1368,7 @@ static hipError_t launch_bwd_d(const Geom &g, const uint16_t *Q, const uint16_t 
         const std::false_type no;
         auto launch_masked = [&](auto masked) -> hipError_t {
             if (keys == 2) return launch_dq(masked, two, no);
-            return g.Cmax <= KEY_TILE / 2 ? launch_dq(masked, one, yes) : launch_dq(masked, one, no);
+            return bwd_dq_half_tiles(g) ? launch_dq(masked, one, yes) : launch_dq(masked, one, no);
         };
         e = sel_mask != nullptr ? launch_masked(yes) : launch_masked(no);
     }

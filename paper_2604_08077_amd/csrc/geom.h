@@ -278,7 +278,8 @@ hipError_t launch_attn_pairs(const Geom &g, const uint16_t *Q, const void *packe
 // log-sum-exp, and dO.  sel_mask == nullptr: dense causal attention.  in_place: a gradient overlaps Q or dO.
 // ws: attn_bwd_workspace_bytes(g).
 size_t attn_bwd_workspace_bytes(const Geom &g);
-int bwd_dq_waves(const Geom &g);  // wavefronts that share 32 rows in the dQ kernel
+int bwd_dq_waves(const Geom &g);         // wavefronts that share 32 rows in the dQ kernel
+bool bwd_dq_half_tiles(const Geom &g);  // whether it works every tile as its first half
 hipError_t launch_attn_bwd(const Geom &g, const uint16_t *Q, const uint16_t *K, const uint16_t *V, const uint16_t *O,
                            const float *lse, const uint16_t *dO, const uint32_t *sel_mask, uint16_t *dQ, uint16_t *dK,
                            uint16_t *dV, bool in_place, void *ws, hipStream_t st);

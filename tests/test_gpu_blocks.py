@@ -3,6 +3,8 @@ and 513 rows, blocks over many cubes of one token, over clipped cubes and over t
 with 1, 31, 33 and 63 keys (the padding keys' probabilities are cleared in the short softmax step).  Tolerances are those of
 the other attention tests.  And values that are not finite in cubes
 behind a row's own, in all attention kernels whose blocks lie across cubes."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -63,10 +65,22 @@ def test_half_tiles(B, oracle, name, grid, cube, hq, hkv, d, text, lead):  # noq
     test_blocks_across_cubes(B, oracle, name, grid, cube, hq, hkv, d, text, lead)
 
 
-BEHIND = SHAPES + [  # the last two: the dense walk at both head-dims, and the dQ kernel with one wavefront per 32 rows
+BEHIND = SHAPES + [  # the first two: the dense walk at both head-dims, and the dQ kernel with one wavefront per 32 rows; then with two; on half tiles
     ("clipped60_text", (16, 10, 15), (3, 4, 5), 48, 4, 64, 70, 45),
     ("clipped60", (18, 9, 15), (3, 4, 5), 36, 4, 128, 0, 0),
+    ("clipped256_text", (5, 13, 17), (4, 8, 8), 20, 4, 64, 33, 65),
+    ("clipped128_text", (9, 10, 12), (4, 4, 8), 28, 4, 128, 33, 20),
+    ("cubes32_text", (13, 9, 12), (2, 4, 4), 64, 16, 128, 33, 20),
 ]
+
+
+def test_every_dq_kernel_is_reached(B):  # noqa: F811
+    """By the shapes of the test below."""
+    kernels = set()
+    for name, grid, cube, hq, hkv, d, text, lead in BEHIND:
+        cs = B.Shape.of(synth.Workload(name, 49, *grid, *cube, hq, hkv, d, (0.6,), (1.0,) * hkv, text, lead))._c()
+        kernels.add((d, B.load().adaspark_internal_dq_waves(ctypes.byref(cs)), B.load().adaspark_internal_dq_half_tiles(ctypes.byref(cs))))
+    assert kernels >= {(64, 8, 0), (128, 8, 0), (64, 2, 0), (128, 2, 0), (64, 1, 0), (128, 1, 0), (128, 1, 1)}
 
 
 def cube_of_tokens(w):

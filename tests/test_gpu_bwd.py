@@ -50,6 +50,22 @@ def check_grad(name, got, want, terms):
     assert err.mean() <= 0.2 * bound.mean()
 
 
+def check_sums(name, dK, dV, dO, w):
+    """Every row's probabilities sum to one and its dS to zero: sum over tokens of dV = sum over the group's rows of dO, of dK = 0.
+    Every element of dV, dK carries its own bf16 rounding (relative 2^-9) and the noise of its rounded terms, which
+    cancel in part (measured: about 7 x 2^-9 of the column's root-sum-square); over many tokens these add up like
+    a random walk."""
+    dVs, dKs = (x.to(torch.float64).sum(dim=0).cpu().numpy() for x in (dV, dK))  # [Hkv, D]
+    dOs = dO.cuda().view(w.S, w.Hkv, w.Hq // w.Hkv, w.D).to(torch.float64).sum(dim=(0, 2)).cpu().numpy()
+    tol_v = 16.0 * 2.0 ** -9 * torch.sqrt((dV.to(torch.float64) ** 2).sum(dim=0)).cpu().numpy() + 1e-3 * np.abs(dOs)
+    tol_k = 16.0 * 2.0 ** -9 * torch.sqrt((dK.to(torch.float64) ** 2).sum(dim=0)).cpu().numpy()
+    print(f"[{name}] sum dV - sum dO: max {np.abs(dVs - dOs).max():.3e} (tolerance {tol_v.min():.3e}..{tol_v.max():.3e}); "
+          f"sum dK: max {np.abs(dKs).max():.3e} (tolerance {tol_k.min():.3e}..{tol_k.max():.3e})", flush=True)
+    assert np.isfinite(dVs).all() and np.isfinite(dKs).all()
+    assert (np.abs(dVs - dOs) <= tol_v).all()
+    assert (np.abs(dKs) <= tol_k).all()
+
+
 def workload(name):
     return synth.TEST_WORKLOADS.get(name) or synth.SAMPLED_WORKLOADS.get(name) or synth.WORKLOADS[name]
 
@@ -129,24 +145,78 @@ def test_backward_shared_keys(B, oracle, monkeypatch, name, grid, cube, hq, d):
     run_case(B, oracle, name, 0.6)
 
 
-# The dQ kernel with two wavefronts per 32 rows (up to 304 workgroups of 256 rows): cubes whose keys leave the second half of a tile empty,
-# or with one key; row blocks of 128 and a remainder.
+def dq_kernel(B, w):
+    """Which dQ kernel a shape gets: wavefronts that share 32 rows, and whether every tile is worked as its first half."""
+    cs = B.Shape.of(w)._c()
+    return B.load().adaspark_internal_dq_waves(ctypes.byref(cs)), B.load().adaspark_internal_dq_half_tiles(ctypes.byref(cs))
+
+
+# The dQ kernel with two wavefronts per 32 rows, on walks short enough for the oracle to take every row: cubes whose keys leave the second half
+# of a tile empty, or with one key; row blocks of 128 and a remainder.
 DQ = [
-    ("blocks304", (38, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
-    ("blocks312", (39, 2, 4), (1, 2, 4), 8, 8, 64, 0.7, 0),
     ("keys31_rows124", (4, 1, 31), (1, 1, 31), 4, 1, 128, 0.7, 0),
     ("keys33_rows132", (4, 3, 11), (1, 3, 11), 4, 1, 128, 0.7, 5),
     ("keys97_rows291", (3, 1, 97), (1, 1, 97), 3, 1, 64, 0.7, 0),
-    ("keys33_blocks390", (130, 3, 11), (1, 3, 11), 3, 3, 128, 0.6, 0),
 ]
 
 
 @pytest.mark.parametrize("name,grid,cube,hq,hkv,d,p,text", DQ, ids=[c[0] for c in DQ])
 def test_backward_shared_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, p, text):
     w = synth.Workload(name, 42, *grid, *cube, hq, hkv, d, (p,), (1.0,) * hkv, text)
+    assert dq_kernel(B, w) == (2, 0)
     monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
     run_case(B, oracle, name, p)
     run_case(B, oracle, name, 1.0, dense=True)
+
+
+# Longer walks of the dQ kernels that only larger shapes get, against the oracle on a sample of rows.  Two wavefronts per 32 rows: more than 64
+# cubes, text on both sides, clipped cubes, cubes of 256 and of 1,024 tokens with a text cube of one, row blocks with a remainder.  One, on
+# whole tiles: last tiles of 1, 33 and 63 keys, clipped cubes and whole ones; on half tiles.  Both head dims.
+LONG = [
+    ("two_cubes82_text", (80, 3, 11), (1, 3, 11), 16, 16, 64, 9, 5, (2, 0)),
+    ("two_clipped_text", (9, 10, 12), (4, 4, 8), 28, 4, 128, 33, 20, (2, 0)),
+    ("two_cubes256", (6, 16, 16), (4, 8, 8), 28, 4, 128, 0, 0, (2, 0)),
+    ("two_clipped256_text", (5, 13, 17), (4, 8, 8), 20, 4, 64, 33, 65, (2, 0)),
+    ("two_cubes1024", (8, 16, 16), (4, 16, 16), 28, 7, 64, 1, 0, (2, 0)),
+    ("one_last1_33_63", (18, 5, 13), (1, 5, 13), 64, 16, 64, 63, 33, (1, 0)),
+    ("one_last33", (15, 1, 97), (1, 1, 97), 56, 8, 128, 0, 0, (1, 0)),
+    ("one_clipped_text", (9, 10, 12), (4, 4, 8), 72, 18, 128, 40, 43, (1, 0)),
+    ("one_cubes256", (6, 16, 16), (4, 8, 8), 56, 8, 64, 0, 0, (1, 0)),
+    ("one_half_tiles", (13, 9, 12), (2, 4, 4), 64, 16, 128, 33, 20, (1, 1)),
+]
+
+
+@pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead,kernel", LONG, ids=[c[0] for c in LONG])
+def test_backward_long_walks_sampled(B, oracle, name, grid, cube, hq, hkv, d, text, lead, kernel):
+    """dQ of sampled rows, masked and dense; of dK and dV the identities of the full-size tests below (the dK/dV kernel reads what
+    the dQ kernel found of the rows' sums)."""
+    w = synth.Workload(name, 65, *grid, *cube, hq, hkv, d, (0.7,), (1.0,) * hkv, text, lead)
+    assert dq_kernel(B, w) == kernel
+    sh, osh = B.Shape.of(w), oshape(oracle, w)
+    Q, K, V = synth.generate(w)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(synth.BASE_SEED + 65)
+    dO = torch.randn((w.S, w.Hq, w.D), generator=g, dtype=torch.float32).to(torch.bfloat16)
+    Qg, Kg, Vg, dOg = Q.cuda(), K.cuda(), V.cuda(), dO.cuda()
+    q, k, v, do = f64(Q), f64(K), f64(V), f64(dO).reshape(-1, w.D)
+    tables = oracle.bwd.cube_tables(osh)
+    G, c = w.Hq // w.Hkv, 1.0 / np.sqrt(w.D)
+    rows = synth.sample_rows(w, 400)
+    for dense in (False, True):
+        mask = oracle.cube_select(osh, Q, oracle.cube_pool(osh, K), 1.0 if dense else 0.7)[0]
+        mg = None if dense else torch.from_numpy(mask.view(np.int32)).cuda()
+        print(f"[{name}] dense={dense}: {len(rows)} rows", flush=True)
+        O, lse = B.dense_attn(sh, Qg, Kg, Vg, return_lse=True) if dense else B.sparse_attn(sh, Qg, Kg, Vg, mg, return_lse=True)
+        dQ, dK, dV = B.sparse_attn_bwd(sh, Qg, Kg, Vg, O, lse, dOg, sel_mask=mg)
+        torch.cuda.synchronize()
+        o = f64(O.cpu()).reshape(-1, w.D)
+        want, terms = [], []
+        for r in rows:
+            att, dq, _, _, _, ds, _ = oracle.bwd.row_backward(osh, q, k, v, mask[r], r, do[r], o[r], tables)
+            want.append(dq)
+            terms.append(c * np.sqrt((ds * ds) @ (k[att, (r % w.Hq) // G] ** 2)))
+        check_grad(f"{name} dQ", f64(dQ.cpu()).reshape(-1, w.D)[rows], np.array(want), np.array(terms))
+        check_sums(name, dK, dV, dO, w)
 
 
 # The dQ kernel with eight wavefronts per 32 rows: walks of fewer steps than wavefronts and of many, cubes with one key in their last step,
@@ -157,21 +227,23 @@ EIGHT = [
     ("keys65_text", (9, 5, 13), (1, 5, 13), 3, 1, 64, 70, 40),
     ("cubes70", (70, 2, 4), (1, 2, 4), 4, 2, 128, 9, 0),
     ("clipped", (9, 10, 12), (4, 4, 8), 3, 1, 128, 0, 30),
+    ("blocks304", (38, 2, 4), (1, 2, 4), 8, 8, 64, 0, 0),
+    ("blocks312", (39, 2, 4), (1, 2, 4), 8, 8, 64, 0, 0),
+    ("keys33_blocks390", (130, 3, 11), (1, 3, 11), 3, 3, 128, 0, 0),
 ]
 
 
 @pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead", EIGHT, ids=[c[0] for c in EIGHT])
 def test_backward_eight_wavefronts_per_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, text, lead):
     w = synth.Workload(name, 61, *grid, *cube, hq, hkv, d, (0.7,), (1.0,) * hkv, text, lead)
-    cs = B.Shape.of(w)._c()
-    assert B.load().adaspark_internal_dq_waves(ctypes.byref(cs)) == 8
+    assert dq_kernel(B, w) == (8, 0)
     monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
     run_case(B, oracle, name, 0.7)
     run_case(B, oracle, name, 1.0, dense=True)
 
 
-# The dQ kernel with one wavefront per 32 rows: 305 workgroups of 256 rows and more, many heads of short sequences; both head dims, clipped
-# cubes with text around them, blocks over many cubes of three tokens, a block with a few rows.  And the last shape of the other side.
+# The dQ kernel with one wavefront per 32 rows on half tiles: 305 workgroups of 256 rows and more, many heads of short sequences; both head dims,
+# clipped cubes with text around them, blocks over many cubes of three tokens, a block with a few rows.  And the last shape of the other side.
 ONE = [
     ("heads154_text", (5, 5, 9), (2, 4, 4), 154, 154, 64, 33, 20, 1),
     ("heads306_cubes3", (1, 1, 130), (1, 1, 3), 306, 153, 128, 0, 0, 1),
@@ -183,8 +255,7 @@ ONE = [
 @pytest.mark.parametrize("name,grid,cube,hq,hkv,d,text,lead,waves", ONE, ids=[c[0] for c in ONE])
 def test_backward_one_wavefront_per_rows(B, oracle, monkeypatch, name, grid, cube, hq, hkv, d, text, lead, waves):
     w = synth.Workload(name, 52, *grid, *cube, hq, hkv, d, (0.7,), (1.0,) * hkv, text, lead)
-    cs = B.Shape.of(w)._c()
-    assert B.load().adaspark_internal_dq_waves(ctypes.byref(cs)) == waves
+    assert dq_kernel(B, w) == (waves, int(waves == 1))
     monkeypatch.setitem(synth.TEST_WORKLOADS, name, w)
     run_case(B, oracle, name, 0.7)
     run_case(B, oracle, name, 1.0, dense=True)
@@ -348,18 +419,7 @@ def test_backward_full_size_sampled(B, oracle):
     check_grad("C3 dK last tokens", f64(dK[idx, gk].cpu()), wk, np.sqrt(tk))
     check_grad("C3 dV last tokens", f64(dV[idx, gk].cpu()), wv, np.sqrt(tv))
 
-    dVs = dV.to(torch.float64).sum(dim=0).cpu().numpy()                      # [Hkv, D]
-    dKs = dK.to(torch.float64).sum(dim=0).cpu().numpy()
-    dOs = f64(dO).reshape(w.S, w.Hkv, G, w.D).sum(axis=(0, 2))
-    # every element of dV, dK carries its own bf16 rounding (relative 2^-9) and the noise of its rounded terms, which
-    # cancel in part (measured: about 7 x 2^-9 of the column's root-sum-square); over 65,536 tokens these add up like
-    # a random walk
-    tol_v = 16.0 * 2.0 ** -9 * np.sqrt((f64(dV.cpu()) ** 2).sum(axis=0)) + 1e-3 * np.abs(dOs)
-    tol_k = 16.0 * 2.0 ** -9 * np.sqrt((f64(dK.cpu()) ** 2).sum(axis=0))
-    print(f"[C3] sum dV - sum dO: max {np.abs(dVs - dOs).max():.3e} (tolerance {tol_v.min():.3e}..{tol_v.max():.3e}); "
-          f"sum dK: max {np.abs(dKs).max():.3e} (tolerance {tol_k.min():.3e}..{tol_k.max():.3e})", flush=True)
-    assert (np.abs(dVs - dOs) <= tol_v).all()
-    assert (np.abs(dKs) <= tol_k).all()
+    check_sums("C3", dK, dV, dO, w)
 
 
 def test_backward_quarter_million_tokens(B, oracle):
@@ -394,13 +454,4 @@ def test_backward_quarter_million_tokens(B, oracle):
         want.append(dq)
         terms.append(c * np.sqrt((ds * ds) @ (k[att, (r % w.Hq) // G] ** 2)))
     check_grad("C4 dQ sampled rows", f64(dQ.reshape(-1, w.D)[idx].cpu()), np.array(want), np.array(terms))
-    dVs = dV.to(torch.float64).sum(dim=0).cpu().numpy()
-    dKs = dK.to(torch.float64).sum(dim=0).cpu().numpy()
-    dOs = dOg.view(w.S, w.Hkv, G, w.D).to(torch.float64).sum(dim=(0, 2)).cpu().numpy()
-    tol_v = 16.0 * 2.0 ** -9 * torch.sqrt((dV.to(torch.float64) ** 2).sum(dim=0)).cpu().numpy() + 1e-3 * np.abs(dOs)
-    tol_k = 16.0 * 2.0 ** -9 * torch.sqrt((dK.to(torch.float64) ** 2).sum(dim=0)).cpu().numpy()
-    print(f"[C4] sum dV - sum dO: max {np.abs(dVs - dOs).max():.3e} (tolerance {tol_v.min():.3e}..{tol_v.max():.3e}); "
-          f"sum dK: max {np.abs(dKs).max():.3e} (tolerance {tol_k.min():.3e}..{tol_k.max():.3e})", flush=True)
-    assert np.isfinite(dVs).all() and np.isfinite(dKs).all()
-    assert (np.abs(dVs - dOs) <= tol_v).all()
-    assert (np.abs(dKs) <= tol_k).all()
+    check_sums("C4", dK, dV, dO, w)
