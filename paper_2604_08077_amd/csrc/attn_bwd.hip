@@ -606,7 +606,8 @@ __global__ __launch_bounds__(BWD_THREADS) void attn_bwd_dq_kernel(Geom g, const 
 // else on the CU wants the same ones), and their sums are added through LDS.
 //
 // Bound by the latency of a step (24 KB from L2, 48 MFMAs at head-dim 128, the next step's operands asked for as soon as this one's
-// are used).  1,080 tokens of 6/2 heads of 128: 20 us, 46 with two wavefronts per 32 rows on 56 workgroups.  The rows' Q and dO are B operands of all steps and of all eight wavefronts: they lie in LDS, which leaves the registers
+// are used): its wavefronts wait for data 44 % of their time and for their turn another 36 %, the matrix pipes are busy 5 %, and it reads
+// 138 MB from L2, 6.6 TB/s.  1,080 tokens of 6/2 heads of 128: 20 us, 46 with two wavefronts per 32 rows on 56 workgroups.  The rows' Q and dO are B operands of all steps and of all eight wavefronts: they lie in LDS, which leaves the registers
 // to the operands in flight.
 // ---------------------------------------------------------------------------------------------------------------
 template <int D>
@@ -1301,7 +1302,9 @@ bool bwd_dq_half_tiles(const Geom &g) { return g.Cmax <= KEY_TILE / 2 && bwd_dq_
 // 6/2 of 128, cubes of 32, 4,320 175, 167, 6,480 215, 216, 15,984 552, 591; of 64, 5,472 120, 117, 8,064 184, 176, 16,128 303, 319; 8/2 of 64, cubes of
 // 32, 5,760 133, 126, 8,064 149, 149; 4/4 of 64, cubes of 64, 2,976 116, 114, 7,968 294, 312.  Between 3,000 and 8,000 rows either is up to 7 % faster.
 // By rows of a cube, 480 to 2,000 tokens: 896 (28/4, 14/2 heads of 128) 61, 67 and 71, 76; 448 48, 50 and 65, 70; 512 (32/8 of 128, 8/2 of 64) 107, 112 and 56, 59;
-// 384 (6/2 of 128) 67, 71 and 107, 106; 256 69, 67 and 61, 61; 192 73, 71; 128 (4/4 of 64) 92, 82; 96 113, 105.
+// 384 (6/2 of 128) 67, 71 and 107, 106; 256 69, 67 and 61, 61; 192 73, 71; 128 (4/4 of 64) 92, 82; 96 113, 105.  Between 224 and 384 rows either is
+// faster by up to 6 %: 8/2 of 64, 960 tokens, 256 37.7, 39.7, 320 42.3, 45.1, 384 38.6, 39.7, but 1,440, 256 59.2, 58.6; 6/2 of 128, 336, 1,080 tokens 59.9, 62.0,
+// 1,920 93.7, 90.8; 384, 1,080 56.6, 58.0, 1,920 88.6, 86.5; 32/8 of 128, 320 113, 107; 28/4 of 128, 224 97.5, 93.5, 336 130, 129.
 static bool dkv_shared(const Geom &g)
 {
     return g.Cmax <= BWD_ROWS / 2 && ((long long)g.S * g.G >= SHARED_ROWS || g.G * g.Cmax >= SHARED_CUBE_ROWS);

@@ -521,7 +521,7 @@ __global__ __launch_bounds__(FWD_MAX_THREADS) void attn_walk_kernel(
 //      share of up to other_permille) or 2 (masked walk), flags[FLAG_ESTIMATE] = the smallest share of a KV head in permille (together:
 //      the largest), and (kv_modes) the heads' shares
 //   1  flags[FLAG_UNION]; it also clears the per-head choices and the key-stationary path's counters
-// (One workgroup that did both: 15 us at 9,000 tokens of 28/4 heads, 28 at 65,536; two 10 and 16.)
+// (One workgroup that did both: 15 us at 9,000 tokens of 28/4 heads, 28 at 65,536; two 11 and 19, and 31 at 262,144.)
 constexpr int DENSITY_THREADS = 1024;
 constexpr int DENSITY_MAX_ROWS = 2048;  // two sampled rows per thread: an estimate is all that is needed
 constexpr int DENSITY_GROUPS = 16;          // sampled blocks of rows for the union estimate
@@ -671,11 +671,11 @@ static bool chosen_on_device(const Geom &g) { return candidate_pairs(g) >= AUTO_
 
 // Whether it is then made for all KV heads together.  Where the time of the masked walk is that of its longest walk, heads that go to
 // the key-stationary kernel do not shorten it, unless all of them go (3,600 tokens of 28/4 heads of 128 in cubes of 32, half the
-// heads selecting nearly nothing: the walk 218 us, with all heads as with half of them, and the others another 140).  With room for the
-// key-stationary kernel, up to 1.2: a fifth of the walk is less than that kernel's share takes.  (A forward pass of as many heads that
-// select nearly nothing as of others, us, one by one and together, by rounds of the walk: 14/2 heads of 128 in cubes of 256, 7,680 tokens,
-// 1.05, 426, 369; 8/2 of 64, 14,336, 1.03, 427, 346; 28/4 in cubes of 32, 4,032, 1.02, 372, 287; 4,752, 1.20, 461, 401; 6/2 in cubes of 128,
-// 19,008, 1.03, 671, 601; 22,464, 1.22, 743, 781.)
+// heads selecting nearly nothing: the walk 202 us with all heads; with half of them, and the others by that kernel, 295).  With room for the
+// key-stationary kernel, up to 1.2: a fifth of the walk is less than that kernel's share takes.  (Attention of as many heads that
+// select nearly nothing as of others, us, one by one and together, by rounds of the walk: 14/2 heads of 128 in cubes of 256, 9,216 tokens,
+// 1.16, 367, 293; 8/2 of 64, 14,336, 1.03, 384, 299; 28/4 in cubes of 32, 4,032, 1.02, 303, 218; 4,752, 1.20, 343, 283; 6/2 in cubes of 128,
+// 19,008, 1.03, 589, 507; 22,464, 1.22, 684, 680.)
 static bool heads_together(const Geom &g, bool room) { return walk_rounds(g) <= (room ? 1.2 : 1.0); }
 
 // Tiles of `keys` keys that all cubes together take.  The cubes of a grid come in eight sizes (clipped or not along each
@@ -750,8 +750,8 @@ static int split_below_permille(const Geom &g)
 // The key-stationary kernel is the faster one below this share of selected candidate cubes.  The walk takes time by the
 // tiles of a cube, 0.03 ns a candidate pair and tile at head-dim 128; a selected pair costs the other path 0.22 ns in cubes of one tile and
 // 0.24 in cubes of four, most of it its record.  (Measured: 65,536 tokens of 28/4 heads in cubes of 256, break-even at 44 %;
-// 7,688 tokens in cubes of 32, 33 % selected, 2,250 us against 910; 8,640 on a grid of 9 x 10, where cubes of up to 256 have 1.75 tiles on
-// average, 32 % selected, 897 against 549.)  With half a tile's keys to a step (no cube above 32 tokens) the walk takes 0.72 of that; at
+// 7,688 tokens in cubes of 32, 32 % selected, 1,665 us against 583; 8,640 on a grid of 9 x 10, where cubes of up to 256 have 1.75 tiles on
+// average, 33 % selected, 874 against 575, 18 % 587, 598.)  With half a tile's keys to a step (no cube above 32 tokens) the walk takes 0.72 of that; at
 // head-dim 64 the other path's records are half as long, and the line stays.  (At head-dim 128, the walk and the key-stationary kernel by
 // the share selected: 8,064 tokens, 28/4 heads, 13.6 % 624, 858, 10.6 % 628, 691, 9.3 % 645, 640; 14/2, 13.6 % 324, 469, 10.6 % 327, 387;
 // 12,000, 14/2, 10.2 % 717, 707; 32/8, 13.1 % 1,460, 2,109, 8.7 % 1,501, 1,530.  KV heads on both sides of the line take both kernels, and that
