@@ -39,8 +39,8 @@ PEAK_HBM_GBS = 8000.0
 
 # HBM traffic of one sparse-attention launch (bytes), from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
 # scaled by a copy of known size; HBM traffic under profiles/, "forward 64k" and "top-p 0.5"; keyed by (workload, top_p).
-# (C3, 0.9): attn_walk_kernel<128, true>; (C3, 0.5): the key-stationary kernels together (pairs, own cubes, merge).
-MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 5.238e9, ("C3", 0.5): 3.815e10}
+# (C3, 0.9): attn_walk_kernel<128, true, false>; (C3, 0.5): the key-stationary kernels together (pairs, own cubes, merge).
+MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 5.354e9, ("C3", 0.5): 3.830e10}
 
 
 def cube_tables(w):
@@ -145,7 +145,7 @@ FFN_D_MODEL, FFN_D_FF, FFN_TOP_P = 3584, 18944, 0.7
 # Bytes the two matrix-product kernels of one adaspark_ffn_sparse call move between the L2 caches and the fabric
 # (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a copy of known size; HBM traffic under profiles/, "ffn 64k"), keyed
 # by workload.
-FFN_MEASURED_TRAFFIC_BYTES = {"C3": 2.343e10}
+FFN_MEASURED_TRAFFIC_BYTES = {"C3": 2.310e10}
 
 
 def ffn_leg(B, w, steps, dense=True):
@@ -181,7 +181,7 @@ def ffn_leg(B, w, steps, dense=True):
 # Bytes all kernels of one backward call move between the L2 caches and the fabric (rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE, scaled by a copy of known size; HBM traffic under profiles/, "train 64k": preparation, dQ,
 # dK/dV and the sums), keyed by (workload, top_p).
-BWD_MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 4.66e10}
+BWD_MEASURED_TRAFFIC_BYTES = {("C3", 0.9): 4.637e10}
 
 
 def bwd_leg(B, w, sh, Qg, Kg, Vg, ws_att, mask, eff_flops, dense_flops, steps, top_p):
