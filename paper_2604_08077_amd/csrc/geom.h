@@ -93,7 +93,7 @@ __host__ __device__ inline int token_of(const Geom &g, const CubeBox &b, int ran
 }
 
 // The same for kernels that look up many tokens of a cube and do little else: divisions in 24 bits, 8 instructions instead of 20 to 30, where
-// the cube's nominal size allows it, and two of them.  (The mean keys of 16,384 tokens in 64 cubes: 11.4 us, so and in parts of a row 6.9.
+// the cube's nominal size allows it, and two of them.  (The mean keys of 16,384 tokens in 64 cubes, when every thread worked out its own tokens' places: 11.4 us, so and in parts of a row 6.9.
 // Not in the masked walk, which is fastest as its registers happen to fall with the plain form: 1 % at 65,536 tokens.)
 __host__ __device__ inline int token_in_cube(const Geom &g, const CubeBox &b, int rank)
 {

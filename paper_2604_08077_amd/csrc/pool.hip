@@ -16,14 +16,18 @@ constexpr int POOL_THREADS = 1024;  // of a whole row: 16 wavefronts
 // Rows are cut while there are fewer workgroups than this, each part with its share of the threads, so that a CU holds several: cubes by
 // themselves leave CUs empty, and a little above 256 of them, the second half of the time.  (Mean keys, us, parts up to 256 workgroups and up to
 // this many: 16,384 tokens of 4 KV heads of 128 in cubes of 256 6.2, 6.4; 65,536 15.9, 12.9; 262,144 47.5, 41.5; 30,000 of 8, 14.9, 13.0;
-// 69,630 of 2 in 318 cubes 11.0, 7.5; uncut rows took 11.1, 16.5, 47.2, 19.3 and 11.9.)  A row of many heads leaves few slots, whose chain of
-// additions is then the time: 256 tokens of 64 heads of 128, 56 us (121 uncut).
+// 69,630 of 2 in 318 cubes 11.0, 7.5; uncut rows took 11.1, 16.5, 47.2, 19.3 and 11.9.)
 constexpr int POOL_WORKGROUPS = 2048;
+// Places of a cube's tokens that a workgroup works out at a time, each once.  A row of many heads leaves few slots, and their chains are then the
+// time: 8,192 tokens of 32 heads of 128 20.7 us, one cube of 64 heads 31.5, and 31.4 and 56.5 with every thread working out its own; 16,384 of 4
+// heads 5.3, 6.4.
+constexpr int POOL_TOKENS = 2048;
 
 __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const uint16_t *__restrict__ K,
                                                                  float *__restrict__ kbar)
 {
     extern __shared__ float part[];  // [slot][chunk][8]: as many as threads
+    __shared__ int token[POOL_TOKENS];
     const int c = blockIdx.x;
     const CubeBox box = cube_box(g, c);
     const int size = box.size();
@@ -38,20 +42,24 @@ __global__ __launch_bounds__(POOL_THREADS) void cube_pool_kernel(Geom g, const u
         float acc[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-        if (slot < slots) {
-            // eight independent 16-byte loads in flight per thread: a cube is read by one workgroup, so the
-            // memory-level parallelism has to come from inside it
+        const int span = POOL_TOKENS / slots * slots;
+        for (int base = 0; base < size; base += span) {
+            const int n = min(span, size - base);
+            __syncthreads();  // (the tokens before are done with)
+            for (int r = threadIdx.x; r < n; r += blockDim.x) token[r] = token_in_cube(g, box, base + r);
+            __syncthreads();
+            if (slot >= slots) continue;
+            // eight independent 16-byte loads in flight per thread: a cube is read by few workgroups, so the
+            // memory-level parallelism has to come from inside them
             constexpr int UNROLL = 8;
-            for (int r0 = slot; r0 < size; r0 += slots * UNROLL) {
+            for (int r0 = slot; r0 < n; r0 += slots * UNROLL) {
                 uint4 v[UNROLL];
 #pragma unroll
                 for (int u = 0; u < UNROLL; ++u) {
                     const int r = r0 + u * slots;
                     v[u] = make_uint4(0, 0, 0, 0);
-                    if (r < size) {
-                        const int n = token_in_cube(g, box, r);
-                        v[u] = *reinterpret_cast<const uint4 *>(K + (size_t)n * row_elems + (size_t)(chunk0 + col) * 8);
-                    }
+                    if (r < n)
+                        v[u] = *reinterpret_cast<const uint4 *>(K + (size_t)token[r] * row_elems + (size_t)(chunk0 + col) * 8);
                 }
 #pragma unroll
                 for (int u = 0; u < UNROLL; ++u) {

@@ -19,6 +19,7 @@ SHAPES = [  # grid, cube, KV heads, head_dim, text after and before
     ("sweeps3", (256, 1, 1), (1, 1, 1), 160, 128, 0, 0),  # as many cubes as CUs: whole rows, three sweeps
     ("piece320", (256, 1, 5), (1, 1, 5), 20, 128, 0, 0),  # more elements than threads, three slots
     ("cubes256", (256, 2, 2), (1, 2, 2), 4, 64, 0, 0),
+    ("tokens2820", (1, 47, 60), (1, 47, 60), 3, 64, 0, 0),  # more tokens than are looked up at a time: 2,016 of 42 slots, and the rest
     ("one_token", (3, 3, 3), (1, 1, 1), 1, 64, 2, 1),
     ("cubes_over_22_bits", (3, 5, 7), (4096, 32, 33), 2, 64, 0, 0),  # nominal size 4.3 M tokens
 ]
